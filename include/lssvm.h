@@ -18,9 +18,10 @@
  *   comes from the caller's `workspace` (device, 256-byte aligned, at least
  *   the size reported by the matching *_workspace_bytes call).
  * - dtype is LSSVM_F64 or LSSVM_F32 and applies to every floating-point
- *   device array of the call. In LSSVM_F32 the point data, the matrix-core
- *   contraction and the kernel epilogue are fp32; CG vectors, dot products,
- *   CG scalars and b are fp64.
+ *   device array of the call. In LSSVM_F32 the point data, the inner products
+ *   and the kernel epilogue are fp32 (the matrix cores multiply three bf16
+ *   slices that add up to each value exactly, and sum in fp32); CG vectors,
+ *   dot products, CG scalars and b are fp64.
  * - Points are n x d, row-major (point i's d features contiguous).
  * - All work is enqueued on `stream` (a hipStream_t; NULL = default stream)
  *   and the call returns only after it has finished.
@@ -255,12 +256,13 @@ int64_t lssvm_host_contexts(void);
 size_t lssvm_mfma_peak_workspace_bytes(void);
 
 /*
- * Sustained matrix-core rate in TFLOP/s of the instruction the tile kernel
- * uses for dtype (fp32: v_mfma_f32_32x32x2_f32, fp64: v_mfma_f64_16x16x4_f64),
- * measured by a kernel that issues only that instruction on every SIMD, with
+ * Sustained matrix-core rate in TFLOP/s of dtype's own instruction (fp32:
+ * v_mfma_f32_32x32x2_f32, fp64: v_mfma_f64_16x16x4_f64, which the fp64 tile
+ * kernel uses), measured by a kernel that issues only that instruction on every SIMD, with
  * HIP events on `stream` (one warm-up launch, median of three). A measurement
- * aid: it sets the tile kernel's rate against what the chip sustains, beside
- * the published peak. workspace: device, lssvm_mfma_peak_workspace_bytes()
+ * aid: it sets the fp64 tile kernel's rate against what the chip sustains,
+ * beside the published peak, and the fp32 one's against what it would be on
+ * the fp32 instruction. workspace: device, lssvm_mfma_peak_workspace_bytes()
  * bytes, 256-byte aligned (overwritten). Synchronizes `stream`.
  * Returns LSSVM_OK, LSSVM_EINVAL or LSSVM_EHIP.
  */

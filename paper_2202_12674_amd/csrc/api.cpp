@@ -225,7 +225,7 @@ struct Carver {
 
 template <typename T>
 struct TrainWs {
-  T* Xt;
+  store_t<T>* Xt;
   T* norms;
   double* q64;
   int64_t* acc; // fixed-point row sums of a product (two words per row)
@@ -239,6 +239,7 @@ struct TrainWs {
   uint32_t* order;
   double* hist;
   unsigned* ticket;   // workgroups done in a fused iteration's launch
+  T gscale = T(1);    // what the stored points' inner products are multiplied by
   size_t bytes;
 };
 
@@ -247,7 +248,7 @@ template <typename T>
 TrainWs<T> carve_train(const Geometry& g, void* base) {
   Carver c(base);
   TrainWs<T> w{};
-  w.Xt = c.take<T>(g.d_pad * g.ld);
+  w.Xt = c.take<store_t<T>>(TileShape<T>::SLICES * g.d_pad * g.ld);
   w.norms = c.take<T>(g.ld);
   w.q64 = c.take<double>(g.ld);
   // Row sums: two 64-bit words per row, however many tiles add to them; the
@@ -275,8 +276,8 @@ TrainWs<T> carve_train(const Geometry& g, void* base) {
 
 template <typename T>
 struct PredictWs {
-  T *Xtr, *ntr, *alpha;
-  T *Xte, *nte;
+  store_t<T> *Xtr, *Xte;
+  T *ntr, *nte, *alpha;
   double* part;
   int* flags;
   double* lin_part;  // linear kernel: partial sums of w over point chunks
@@ -293,10 +294,10 @@ PredictWs<T> carve_predict(const Geometry& g, int64_t n_test, void* base) {
   w.ld_te = round_up(n_test, g.tile);
   w.nTc = g.ld / g.tile;
   w.nTr = w.ld_te / g.tile;
-  w.Xtr = c.take<T>(g.d_pad * g.ld);
+  w.Xtr = c.take<store_t<T>>(TileShape<T>::SLICES * g.d_pad * g.ld);
   w.ntr = c.take<T>(g.ld);
   w.alpha = c.take<T>(g.ld);
-  w.Xte = c.take<T>(g.d_pad * w.ld_te);
+  w.Xte = c.take<store_t<T>>(TileShape<T>::SLICES * g.d_pad * w.ld_te);
   w.nte = c.take<T>(w.ld_te);
   w.part = c.take<double>(w.nTc * w.ld_te);
   w.flags = c.take<int>(F_COUNT);
@@ -488,14 +489,13 @@ TileArgs<T> sym_args(const Geometry& g, const TrainWs<T>& w, const lssvm_params&
   TileArgs<T> a{};
   a.A = w.Xt;
   a.B = w.Xt;
-  a.lda = g.ld;
-  a.ldb = g.ld;
-  a.nkb = g.d_pad / g.bk;
+  a.nkb = g.d_pad / TileShape<T>::SB;
   a.nA = w.norms;
   a.nB = w.norms;
   a.pv = p;
   a.q64 = w.q64;
   a.pq = w.pq;
+  a.gscale = w.gscale;
   a.gamma = (T)kp.gamma;
   a.coef0 = (T)kp.coef0;
   a.rbf_scale = rbf_scale<T>(kp.gamma);
@@ -528,14 +528,49 @@ int clear_and_order(const Geometry& g, const TrainWs<T>& w, int32_t kernel, hipS
   return LSSVM_OK;
 }
 
+// fp32 points with values below kSplitMin (F_TINY, raised by the layout kernel)
+// are laid out again, scaled up by 2^s so that no slice of any value is
+// subnormal: s = 46 lifts the smallest float's 24 bits, less where the largest
+// value leaves no room for the products (its 2^104 times 2^21 features; values
+// 2^155 below the largest then keep fewer bits). *gscale is multiplied by 2^-s.
+// Rare, so it may wait for the device.
+int relayout_tiny(const float* X, int64_t n, int64_t d, uint16_t* Xt, int64_t ld, int64_t d_pad,
+                  int* flags, float* gscale, hipStream_t s) {
+  int* word = flags + F_TINY;
+  LSSVM_HIP(hipMemsetAsync(word, 0, sizeof(int), s));
+  LSSVM_HIP(launch_abs_max(X, n * d, word, s));
+  LSSVM_HIP(hipMemcpyAsync(g_ctx->flags, word, sizeof(int), hipMemcpyDeviceToHost, s));
+  LSSVM_HIP(hipStreamSynchronize(s));
+  float top;
+  std::memcpy(&top, g_ctx->flags, sizeof top);
+  const int up = std::min(46, std::max(0, 52 - (top > 0.f ? std::ilogb(top) : 0)));
+  LSSVM_HIP(launch_layout<float>(X, n, d, Xt, ld, d_pad, std::ldexp(1.f, up), flags, s));
+  *gscale = std::ldexp(*gscale, -up);
+  return LSSVM_OK;
+}
+int relayout_tiny(const double*, int64_t, int64_t, double*, int64_t, int64_t, int*, double*,
+                  hipStream_t) {
+  return LSSVM_OK;   // fp64 points are stored as they are
+}
+
+// The training points: rows and columns of every product.
+template <typename T>
+int rescale_points(const Geometry& g, TrainWs<T>& w, const T* X, hipStream_t s) {
+  T one_side = T(1);
+  LSSVM_TRY(relayout_tiny(X, g.n, g.d, w.Xt, g.ld, g.d_pad, w.flags, &one_side, s));
+  w.gscale = one_side * one_side;
+  return LSSVM_OK;
+}
+
 // a1 + a2: layout, norms, q and k_mm (left on the device). With check set,
-// reads back the input flags and reports a non-finite X; otherwise the
+// reads back the input flags, reports a non-finite X and relays out tiny
+// values (the norms stand: the slices add up to every value); otherwise the
 // caller reads them back with its next result.
 template <typename T>
-int setup_points(const Geometry& g, const TrainWs<T>& w, const T* X, int32_t kernel,
+int setup_points(const Geometry& g, TrainWs<T>& w, const T* X, int32_t kernel,
                  const lssvm_params& kp, hipStream_t s, bool check = true) {
   LSSVM_TRY(clear_and_order<T>(g, w, kernel, s));
-  LSSVM_HIP(launch_layout<T>(X, g.n, g.d, w.Xt, g.ld, g.d_pad, w.flags, s));
+  LSSVM_HIP(launch_layout<T>(X, g.n, g.d, w.Xt, g.ld, g.d_pad, 1.f, w.flags, s));
   LSSVM_HIP(launch_norms_q<T>(w.Xt, g.ld, g.d_pad, g.N, g.N, kernel, kp.gamma, kp.coef0,
                               kp.degree, w.norms, w.q64, w.scal, s));
   if (!check) return LSSVM_OK;
@@ -543,7 +578,7 @@ int setup_points(const Geometry& g, const TrainWs<T>& w, const T* X, int32_t ker
                            s));
   LSSVM_HIP(hipStreamSynchronize(s));
   if (g_ctx->flags[F_NONFINITE]) return fail(LSSVM_ENONFINITE, "X holds a NaN or an infinity");
-  return LSSVM_OK;
+  return g_ctx->flags[F_TINY] ? rescale_points<T>(g, w, X, s) : LSSVM_OK;
 }
 
 // A finished product's row sums and the terms of Q~ p the tiles leave out.
@@ -633,7 +668,7 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
 
   if (n == 1) {  // alpha = [0], b = y_0
     LSSVM_HIP(hipMemsetAsync(w.flags, 0, F_COUNT * sizeof(int), s));
-    LSSVM_HIP(launch_layout<T>(X, g.n, g.d, w.Xt, g.ld, g.d_pad, w.flags, s));
+    LSSVM_HIP(launch_layout<T>(X, g.n, g.d, w.Xt, g.ld, g.d_pad, 1.f, w.flags, s));
     LSSVM_HIP(launch_single_point<T>(y, alpha_out, w.scal, w.flags, s));
     LSSVM_HIP(hipMemcpyAsync(g_ctx->flags, w.flags, F_COUNT * sizeof(int),
                              hipMemcpyDeviceToHost, s));
@@ -659,10 +694,11 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
   LSSVM_HIP(hipMemcpyAsync(g_ctx->p, w.scal + S_DELTA0, (S_INFLAGS - S_DELTA0 + 1) * sizeof(double),
                            hipMemcpyDeviceToHost, s));
   LSSVM_HIP(hipStreamSynchronize(s));
-  const double inflags = g_ctx->p[S_INFLAGS - S_DELTA0];
-  if (inflags == 1.0 || inflags == 3.0) return fail(LSSVM_ENONFINITE, "X holds a NaN or an infinity");
-  if (inflags == 2.0) return fail(LSSVM_EBADLABEL, "labels must be +1 or -1");
+  const int inflags = (int)g_ctx->p[S_INFLAGS - S_DELTA0];
+  if (inflags & 1) return fail(LSSVM_ENONFINITE, "X holds a NaN or an infinity");
+  if (inflags & 2) return fail(LSSVM_EBADLABEL, "labels must be +1 or -1");
   const double delta0 = g_ctx->p[0];
+  if (inflags & 4) LSSVM_TRY(rescale_points<T>(g, w, X, s));
   const double t_setup = ms_since(t0);
   MatvecTimer tm;
   LSSVM_HIP(tm.init(info && info->time_matvec, info ? info->matvec_times : nullptr,
@@ -910,8 +946,8 @@ int predict_impl(const T* Xtr, const T* alpha, double b, int64_t n, int64_t d, i
       return fail(LSSVM_ENONFINITE, "X_train or X_test holds a NaN or an infinity");
     return LSSVM_OK;
   }
-  LSSVM_HIP(launch_layout<T>(Xtr, n, d, w.Xtr, g.ld, g.d_pad, w.flags, s));
-  LSSVM_HIP(launch_layout<T>(Xte, n_test, d, w.Xte, w.ld_te, g.d_pad, w.flags, s));
+  LSSVM_HIP(launch_layout<T>(Xtr, n, d, w.Xtr, g.ld, g.d_pad, 1.f, w.flags, s));
+  LSSVM_HIP(launch_layout<T>(Xte, n_test, d, w.Xte, w.ld_te, g.d_pad, 1.f, w.flags, s));
   if (kernel == LSSVM_RBF) {  // squared norms are only read by the radial kernel
     LSSVM_HIP(launch_norms_q<T>(w.Xtr, g.ld, g.d_pad, -1, 0, kernel, kp.gamma, kp.coef0,
                                 kp.degree, w.ntr, nullptr, nullptr, s));
@@ -922,12 +958,11 @@ int predict_impl(const T* Xtr, const T* alpha, double b, int64_t n, int64_t d, i
   TileArgs<T> a{};
   a.A = w.Xte;
   a.B = w.Xtr;
-  a.lda = w.ld_te;
-  a.ldb = g.ld;
-  a.nkb = g.d_pad / g.bk;
+  a.nkb = g.d_pad / TileShape<T>::SB;
   a.nA = w.nte;
   a.nB = w.ntr;
   a.wB = w.alpha;
+  a.gscale = T(1);
   a.gamma = (T)kp.gamma;
   a.coef0 = (T)kp.coef0;
   a.rbf_scale = rbf_scale<T>(kp.gamma);
@@ -936,15 +971,22 @@ int predict_impl(const T* Xtr, const T* alpha, double b, int64_t n, int64_t d, i
   a.ksplit = 1;
   a.part = w.part;
   a.part_ld = w.ld_te;
-  LSSVM_HIP(launch_tiles_gen<T>(a, kernel, w.nTr, s));
-  LSSVM_HIP(launch_predict_finish<T>(w.part, w.nTc, w.ld_te, n_test, b, scores, labels, w.flags,
-                                     s));
-  LSSVM_HIP(hipMemcpyAsync(g_ctx->flags, w.flags, F_COUNT * sizeof(int), hipMemcpyDeviceToHost,
-                           s));
-  LSSVM_HIP(hipStreamSynchronize(s));
-  if (g_ctx->flags[F_NONFINITE])
-    return fail(LSSVM_ENONFINITE, "X_train or X_test holds a NaN or an infinity");
-  return LSSVM_OK;
+  bool relaid = false;
+  for (;;) {
+    LSSVM_HIP(launch_tiles_gen<T>(a, kernel, w.nTr, s));
+    LSSVM_HIP(launch_predict_finish<T>(w.part, w.nTc, w.ld_te, n_test, b, scores, labels, w.flags,
+                                       s));
+    LSSVM_HIP(hipMemcpyAsync(g_ctx->flags, w.flags, F_COUNT * sizeof(int), hipMemcpyDeviceToHost,
+                             s));
+    LSSVM_HIP(hipStreamSynchronize(s));
+    if (g_ctx->flags[F_NONFINITE])
+      return fail(LSSVM_ENONFINITE, "X_train or X_test holds a NaN or an infinity");
+    if (!g_ctx->flags[F_TINY] || relaid) return LSSVM_OK;
+    // tiny values on either side: once more on points stored scaled up
+    LSSVM_TRY(relayout_tiny(Xtr, n, d, w.Xtr, g.ld, g.d_pad, w.flags, &a.gscale, s));
+    LSSVM_TRY(relayout_tiny(Xte, n_test, d, w.Xte, w.ld_te, g.d_pad, w.flags, &a.gscale, s));
+    relaid = true;
+  }
 }
 
 template <typename T>

@@ -159,132 +159,243 @@ __device__ inline double product_row(const RankOne& c, int64_t i, double inv_sca
 
 // ------------------------------------------------------------- a1 layout ----
 // Panel-major, feature-blocked layout. Points are grouped in panels of TP
-// (the tile edge) and features in blocks of BK; panel pb holds its nkb blocks
-// one after the other, and inside a block each point's BK features are
-// contiguous:
-//   Xb[((pb * nkb + kb) * TP + (i % TP)) * BK + kk] = x_i[kb * BK + kk],  pb = i / TP.
+// (the tile edge) and features in blocks of SB; panel pb holds its nkb blocks
+// one after the other, each a slab of kSlabElems elements:
+//   fp64: each point's SB features contiguous,
+//     Xb[((pb * nkb + kb) * TP + (i % TP)) * SB + kk] = x_i[kb * SB + kk],  pb = i / TP;
+//   fp32: the three bf16 slices of the values, in chunks of 8 features of one
+//     point and slice, in split_chunk order.
 // A tile therefore streams one contiguous run of memory per panel (few pages,
-// coalesced), and each point's features in a block are contiguous (wide LDS
-// reads). Zero fill beyond n points and d features.
+// coalesced). Zero fill beyond n points and d features.
 //
-// One workgroup moves one slab b = pb * nkb + kb (TP points x BK features,
-// 16 KiB) as 16-byte chunks, PER per thread, all loads issued before the
-// stores: chunk c of the slab is point c / CPR's features (c % CPR) VEC ..,
-// a 16-byte piece of one input row, so the lanes of a load instruction read
-// whole 128-byte row segments and the stores are one contiguous run. With
-// vec_ok (d a multiple of VEC and X 16-byte aligned) a chunk is one vector
-// load; otherwise each element is loaded on its own.
-template <typename T, int BK, int TP>
-__global__ __launch_bounds__(256) void k_layout(const T* __restrict__ X, int64_t n, int64_t d,
-                                                T* __restrict__ Xb, int64_t nslab, int64_t nkb,
-                                                int vec_ok, int* __restrict__ flags) {
-  constexpr int VEC = 16 / (int)sizeof(T), CPR = BK / VEC, PER = TP * CPR / 256;
-  static_assert(TP * CPR % 256 == 0, "a slab splits evenly over 256 threads");
+// One workgroup moves one block of BK features of a panel (BK bytes x TP x
+// the type's size = 16 KiB of points) as 16-byte chunks, PER per thread, all
+// loads issued before the stores: chunk c is point c / CPR's features
+// (c % CPR) VEC .., a piece of one input row, so the lanes of a load
+// instruction read whole 128-byte row segments. With vec_ok (d a multiple of
+// VEC and X 16-byte aligned) a chunk is one vector load; otherwise each
+// element is loaded on its own.
+template <typename T, int VEC>
+__device__ inline bool load_chunk(const T* __restrict__ X, int64_t n, int64_t d, int64_t i,
+                                  int64_t k, int vec_ok, T* v) {
   typedef T vec_t __attribute__((ext_vector_type(VEC)));
+  vec_t x;
+  if (vec_ok) {
+    if (i < n && k < d) {
+      x = *reinterpret_cast<const vec_t*>(X + i * d + k);
+    } else {
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) x[e] = T(0);
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) x[e] = (i < n && k + e < d) ? X[i * d + k + e] : T(0);
+  }
+  bool bad = false;
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) {
+    bad |= !__builtin_isfinite(x[e]);
+    v[e] = x[e];
+  }
+  return bad;
+}
+
+__global__ __launch_bounds__(256) void k_layout(const double* __restrict__ X, int64_t n, int64_t d,
+                                                double* __restrict__ Xb, int64_t nslab, int64_t nkb,
+                                                int vec_ok, int* __restrict__ flags) {
+  constexpr int TP = TileShape<double>::T, BK = TileShape<double>::BK;
+  constexpr int VEC = 2, CPR = BK / VEC, PER = TP * CPR / 256;
+  static_assert(BK == TileShape<double>::SB && TP * CPR % 256 == 0, "one slab per workgroup");
   for (int64_t b = blockIdx.x; b < nslab; b += gridDim.x) {
     const int64_t pb = b / nkb, kb = b - pb * nkb;
-    vec_t v[PER];
+    double v[PER][VEC];
     bool bad = false;
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
       const int c = u * 256 + (int)threadIdx.x;
-      const int64_t i = pb * TP + c / CPR, k = kb * BK + (c % CPR) * VEC;
-      if (vec_ok) {
-        if (i < n && k < d) {
-          v[u] = *reinterpret_cast<const vec_t*>(X + i * d + k);
-        } else {
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) v[u][e] = T(0);
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) v[u][e] = (i < n && k + e < d) ? X[i * d + k + e] : T(0);
-      }
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) bad |= !__builtin_isfinite(v[u][e]);
+      bad |= load_chunk<double, VEC>(X, n, d, pb * TP + c / CPR, kb * BK + (c % CPR) * VEC, vec_ok,
+                                     v[u]);
     }
-    T* dst = Xb + b * TP * BK;
+    double2* dst = reinterpret_cast<double2*>(Xb + b * TP * BK);
 #pragma unroll
     for (int u = 0; u < PER; ++u)
-      *reinterpret_cast<vec_t*>(dst + (u * 256 + (int)threadIdx.x) * VEC) = v[u];
+      dst[u * 256 + (int)threadIdx.x] = make_double2(v[u][0], v[u][1]);
     if (bad) flags[F_NONFINITE] = 1;
   }
 }
 
-// ----------------------------------------------------------- a2 norms, q ----
-// Threads per point of k_norms_q: two lane groups (even and odd feature
-// blocks) of one thread per 16-byte chunk of a point's block row.
-template <typename T>
-constexpr int norms_threads_per_point() {
-  return 2 * (TileShape<T>::BK * (int)sizeof(T) / 16);
+// fp32: block b of BK = 32 features is two slabs of 16; a thread takes 8
+// features of a point (two vector loads) and stores them as one chunk of each
+// slice (the 16 points of a quarter wave give 256 contiguous bytes).
+__global__ __launch_bounds__(256) void k_layout_split(const float* __restrict__ X, int64_t n,
+                                                      int64_t d, uint16_t* __restrict__ Xb,
+                                                      int64_t nblk, int64_t nkb32, int vec_ok,
+                                                      float scale, int* __restrict__ flags) {
+  using TS = TileShape<float>;
+  constexpr int TP = TS::T, CPR = TS::BK / 8, PER = TP * CPR / 256, SLAB = kSlabElems<float>;
+  static_assert(TS::SB == 16 && TS::BK == 32 && TP * CPR % 256 == 0, "two slabs per block");
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  for (int64_t b = blockIdx.x; b < nblk; b += gridDim.x) {
+    const int64_t pb = b / nkb32, kb = b - pb * nkb32;
+    float v[PER][8];
+    bool bad = false, tiny = false;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int c = u * 256 + (int)threadIdx.x;
+      const int64_t i = pb * TP + c / CPR, k = kb * TS::BK + (c % CPR) * 8;
+      bad |= load_chunk<float, 4>(X, n, d, i, k, vec_ok, v[u]);
+      bad |= load_chunk<float, 4>(X, n, d, i, k + 4, vec_ok, v[u] + 4);
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int c = u * 256 + (int)threadIdx.x, p = c / CPR, q = c % CPR;
+      u32x4 w[3];
+#pragma unroll
+      for (int e = 0; e < 8; e += 2) {
+        uint16_t s0[3], s1[3];
+        tiny |= fabsf(v[u][e]) < kSplitMin && v[u][e] != 0.f;
+        tiny |= fabsf(v[u][e + 1]) < kSplitMin && v[u][e + 1] != 0.f;
+        bf16_split(v[u][e] * scale, s0);
+        bf16_split(v[u][e + 1] * scale, s1);
+#pragma unroll
+        for (int t = 0; t < 3; ++t) w[t][e / 2] = (uint32_t)s0[t] | ((uint32_t)s1[t] << 16);
+      }
+      uint16_t* slab = Xb + (2 * b + (q >> 1)) * SLAB;
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+        *reinterpret_cast<u32x4*>(slab + 8 * split_chunk(t, p, q & 1)) = w[t];
+    }
+    if (bad) flags[F_NONFINITE] = 1;
+    if (tiny) flags[F_TINY] = 1;
+  }
 }
+
+__global__ __launch_bounds__(256) void k_abs_max(const float* __restrict__ X, int64_t count,
+                                                 int* __restrict__ out) {
+  __shared__ double sh[NT / 64];
+  float m = 0.f;
+  for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < count; i += (int64_t)gridDim.x * NT)
+    m = fmaxf(m, fabsf(X[i]));
+  const float mx = (float)block_max((double)m, sh);
+  if (threadIdx.x == 0) atomicMax(out, __float_as_int(mx));   // ordered like the values
+}
+
+// ----------------------------------------------------------- a2 norms, q ----
+// VEC consecutive features of a point, from chunk c (VEC features each) of
+// its row in the layout: 8 for fp32 (the three slices of a chunk summed, which
+// gives the value back exactly), 2 for fp64.
+template <typename T> struct PointRow;
+template <> struct PointRow<double> {
+  static constexpr int VEC = 2, CPS = TileShape<double>::SB / VEC;   // chunks per slab row
+  const double* p;
+  __device__ PointRow(const double* Xb, int64_t nkb, int64_t i)
+      : p(Xb + (i / TileShape<double>::T) * nkb * kSlabElems<double> +
+          (i % TileShape<double>::T) * TileShape<double>::SB) {}
+  __device__ void load(int64_t c, double (&v)[VEC]) const {
+    const double2 x =
+        *reinterpret_cast<const double2*>(p + (c / CPS) * kSlabElems<double> + (c % CPS) * VEC);
+    v[0] = x.x;
+    v[1] = x.y;
+  }
+};
+template <> struct PointRow<float> {
+  static constexpr int VEC = 8, CPS = TileShape<float>::SB / VEC;
+  const uint16_t* p;
+  int point;
+  __device__ PointRow(const uint16_t* Xb, int64_t nkb, int64_t i)
+      : p(Xb + (i / TileShape<float>::T) * nkb * kSlabElems<float>),
+        point((int)(i % TileShape<float>::T)) {}
+  __device__ void load(int64_t c, double (&v)[VEC]) const {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const uint16_t* s = p + (c / CPS) * kSlabElems<float>;
+    u32x4 w[3];
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+      w[t] = *reinterpret_cast<const u32x4*>(s + 8 * split_chunk(t, point, (int)(c % CPS)));
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      float x = 0.f;
+#pragma unroll
+      for (int t = 2; t >= 0; --t)
+        x += bf16_value(e & 1 ? w[t][e / 2] >> 16 : w[t][e / 2] & 0xffffu);
+      v[e] = (double)x;
+    }
+  }
+};
 
 // ||x_i||^2 and, if a pivot m is given, the cached q_i = k(x_i, x_m) for
 // i < N (zero beyond) and k(x_m, x_m). fp64 sums. A workgroup takes PPB
-// points, KSPL x CPR threads per point: each thread sums one 16-byte chunk of
-// the point's row in every KSPL-th feature block (a wave reads whole 128-byte
-// rows), and the point's partial sums are then combined over its lanes (xor
-// 1, 2, 4, 8: a fixed order).
-template <typename T, int BK, int TP, int KER>
-__global__ __launch_bounds__(256) void k_norms_q(const T* __restrict__ Xb, int64_t ld,
-                                                 int64_t nkb, int64_t m, int64_t N, double gamma,
-                                                 double coef0, int degree, T* __restrict__ norms,
+// points, 256 / PPB threads per point, each summing every (256 / PPB)-th
+// chunk of the point's row; the point's partial sums are then added in a fixed
+// order. The points of a wave's load instruction are neighbours in the layout:
+// fp64 8 chunks (a whole 128-byte row) of 8 points, fp32 one chunk of 32
+// points (512 contiguous bytes per slice).
+template <typename T> constexpr int kNormPoints = sizeof(T) == 8 ? 16 : 32;
+template <typename T, int KER>
+__global__ __launch_bounds__(256) void k_norms_q(const store_t<T>* __restrict__ Xb, int64_t nkb,
+                                                 int64_t m, int64_t N, double gamma, double coef0,
+                                                 int degree, T* __restrict__ norms,
                                                  double* __restrict__ q64,
                                                  double* __restrict__ scal) {
-  constexpr int VEC = 16 / (int)sizeof(T), CPR = BK / VEC, KSPL = 2, TPP = KSPL * CPR;
-  static_assert(TPP == norms_threads_per_point<T>() && BK == TileShape<T>::BK, "launch shape");
-  constexpr int PPB = 256 / TPP;
-  static_assert(TP % PPB == 0, "a workgroup's points lie in one panel");
-  typedef T vec_t __attribute__((ext_vector_type(VEC)));
+  constexpr int PPB = kNormPoints<T>, TPP = 256 / PPB;
+  static_assert(TileShape<T>::T % PPB == 0, "a workgroup's points lie in one panel");
+  constexpr int VEC = PointRow<T>::VEC;
   __shared__ double sh[NT / 64];
-  const int q = (int)threadIdx.x % CPR, h = ((int)threadIdx.x / CPR) % KSPL;
-  const int64_t i = (int64_t)blockIdx.x * PPB + (int64_t)threadIdx.x / TPP;   // < ld
-  const int64_t bstride = (int64_t)TP * BK;   // elements between a point's feature blocks
-  const T* pi = Xb + ((i / TP) * nkb * TP + i % TP) * BK + q * VEC;
+  __shared__ double part[3][TPP][PPB];
+  const int tid = (int)threadIdx.x;
+  const int q = sizeof(T) == 8 ? tid % TPP : tid / PPB;    // this thread's share of the chunks
+  const int pl = sizeof(T) == 8 ? tid / TPP : tid % PPB;   // its point
+  const int64_t i = (int64_t)blockIdx.x * PPB + pl;        // below the padded point count
+  const int64_t nchunks = nkb * PointRow<T>::CPS;
+  const PointRow<T> ri(Xb, nkb, i);
   double nrm = 0.0, dot = 0.0, dist = 0.0;
   if (m >= 0) {
-    const T* pm = Xb + ((m / TP) * nkb * TP + m % TP) * BK + q * VEC;
+    const PointRow<T> rm(Xb, nkb, m);
 #pragma unroll 4
-    for (int64_t kb = h; kb < nkb; kb += KSPL) {
-      const vec_t xi = *reinterpret_cast<const vec_t*>(pi + kb * bstride);
-      const vec_t xm = *reinterpret_cast<const vec_t*>(pm + kb * bstride);
+    for (int64_t c = q; c < nchunks; c += TPP) {
+      double xi[VEC], xm[VEC];
+      ri.load(c, xi);
+      rm.load(c, xm);
 #pragma unroll
       for (int e = 0; e < VEC; ++e) {
-        const double xv = (double)xi[e], xw = (double)xm[e];
-        nrm += xv * xv;
-        dot += xv * xw;
-        const double df = xv - xw;
+        nrm += xi[e] * xi[e];
+        dot += xi[e] * xm[e];
+        const double df = xi[e] - xm[e];
         dist += df * df;
       }
     }
   } else {
 #pragma unroll 4
-    for (int64_t kb = h; kb < nkb; kb += KSPL) {
-      const vec_t xi = *reinterpret_cast<const vec_t*>(pi + kb * bstride);
+    for (int64_t c = q; c < nchunks; c += TPP) {
+      double xi[VEC];
+      ri.load(c, xi);
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) {
-        const double xv = (double)xi[e];
-        nrm += xv * xv;
-      }
+      for (int e = 0; e < VEC; ++e) nrm += xi[e] * xi[e];
     }
   }
-#pragma unroll
-  for (int off = 1; off < TPP; off <<= 1) {
-    nrm += __shfl_xor(nrm, off);
-    dot += __shfl_xor(dot, off);
-    dist += __shfl_xor(dist, off);
-  }
-  if (q == 0 && h == 0) {
-    norms[i] = (T)nrm;
+  part[0][q][pl] = nrm;
+  part[1][q][pl] = dot;
+  part[2][q][pl] = dist;
+  __syncthreads();
+  nrm = 0.0;
+  if (tid < PPB) {
+    dot = dist = 0.0;
+    for (int t = 0; t < TPP; ++t) {
+      nrm += part[0][t][tid];
+      dot += part[1][t][tid];
+      dist += part[2][t][tid];
+    }
+    const int64_t r = (int64_t)blockIdx.x * PPB + tid;
+    norms[r] = (T)nrm;
     if (m >= 0) {
       const double kv = kernel_value64<KER>(dot, dist, gamma, coef0, degree);
-      q64[i] = i < N ? kv : 0.0;
-      if (i == m) scal[S_KMM] = kv;
+      q64[r] = r < N ? kv : 0.0;
+      if (r == m) scal[S_KMM] = kv;
     }
   }
   if (m >= 0) {   // the largest squared norm bounds the kernel values (fixed-point scale)
     const double mx = block_max(nrm, sh);
-    if (threadIdx.x == 0)
+    if (tid == 0)
       atomicMax(reinterpret_cast<unsigned long long*>(scal + S_NMAX),
                 (unsigned long long)__double_as_longlong(mx));
   }
@@ -329,7 +440,8 @@ __global__ __launch_bounds__(256) void k_finish_delta0(const double* bpart, int6
   __shared__ double sh[NT / 64];
   const double s = sum_partials(bpart, nb, sh);
   if (threadIdx.x == 0) {
-    scal[S_INFLAGS] = (flags[F_NONFINITE] ? 1.0 : 0.0) + (flags[F_BADLABEL] ? 2.0 : 0.0);
+    scal[S_INFLAGS] = (flags[F_NONFINITE] ? 1.0 : 0.0) + (flags[F_BADLABEL] ? 2.0 : 0.0) +
+                      (flags[F_TINY] ? 4.0 : 0.0);
     scal[S_DELTA0] = s;
     scal[S_DHIST + 0] = s;
     double* st = scal + S_STATUS;
@@ -991,39 +1103,51 @@ hipError_t launch_setup_clear(int64_t nT, int64_t group, int64_t diag_last, uint
   return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_layout(const T* X, int64_t n, int64_t d, T* Xt, int64_t ld, int64_t d_pad,
-                         int* flags, hipStream_t s) {
-  constexpr int BK = TileShape<T>::BK, TP = TileShape<T>::T, VEC = 16 / (int)sizeof(T);
-  const int64_t nkb = d_pad / BK, nslab = (ld / TP) * nkb;
-  const int vec_ok = d % VEC == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
-  // slab-stride: the slab count can exceed what one dispatch should hold
-  const int64_t blocks = std::min<int64_t>(nslab, int64_t(1) << 20);
-  hipLaunchKernelGGL((k_layout<T, BK, TP>), dim3((unsigned)blocks), dim3(256), 0, s, X, n, d, Xt,
-                     nslab, nkb, vec_ok, flags);
+// Blocks of BK features per workgroup step (slab-stride: their count can exceed
+// what one dispatch should hold).
+template <>
+hipError_t launch_layout<double>(const double* X, int64_t n, int64_t d, double* Xt, int64_t ld,
+                                 int64_t d_pad, float, int* flags, hipStream_t s) {
+  const int64_t nkb = d_pad / TileShape<double>::BK, nblk = (ld / TileShape<double>::T) * nkb;
+  const int vec_ok = d % 2 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
+  const int64_t blocks = std::min<int64_t>(nblk, int64_t(1) << 20);
+  hipLaunchKernelGGL(k_layout, dim3((unsigned)blocks), dim3(256), 0, s, X, n, d, Xt, nblk, nkb,
+                     vec_ok, flags);
+  return hipGetLastError();
+}
+template <>
+hipError_t launch_layout<float>(const float* X, int64_t n, int64_t d, uint16_t* Xt, int64_t ld,
+                                int64_t d_pad, float scale, int* flags, hipStream_t s) {
+  const int64_t nkb = d_pad / TileShape<float>::BK, nblk = (ld / TileShape<float>::T) * nkb;
+  const int vec_ok = d % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
+  const int64_t blocks = std::min<int64_t>(nblk, int64_t(1) << 20);
+  hipLaunchKernelGGL(k_layout_split, dim3((unsigned)blocks), dim3(256), 0, s, X, n, d, Xt, nblk,
+                     nkb, vec_ok, scale, flags);
+  return hipGetLastError();
+}
+hipError_t launch_abs_max(const float* X, int64_t count, int* out, hipStream_t s) {
+  hipLaunchKernelGGL(k_abs_max, dim3((unsigned)vec_blocks(count)), dim3(NT), 0, s, X, count, out);
   return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_norms_q(const T* Xt, int64_t ld, int64_t d_pad, int64_t m, int64_t N,
+hipError_t launch_norms_q(const store_t<T>* Xt, int64_t ld, int64_t d_pad, int64_t m, int64_t N,
                           int kernel, double gamma, double coef0, int degree, T* norms,
                           double* q64, double* scal, hipStream_t s) {
-  constexpr int BK = TileShape<T>::BK, TP = TileShape<T>::T;
-  const int64_t nkb = d_pad / BK;
-  constexpr int PPB = 256 / norms_threads_per_point<T>();   // points per workgroup
-  const unsigned g = (unsigned)(ld / PPB);                   // ld is a multiple of TP
+  const int64_t nkb = d_pad / TileShape<T>::SB;
+  const unsigned g = (unsigned)(ld / kNormPoints<T>);   // ld is a multiple of the tile edge
   switch (kernel) {
     case KLIN:
-      hipLaunchKernelGGL((k_norms_q<T, BK, TP, KLIN>), dim3(g), dim3(NT), 0, s, Xt, ld, nkb, m, N,
-                         gamma, coef0, degree, norms, q64, scal);
+      hipLaunchKernelGGL((k_norms_q<T, KLIN>), dim3(g), dim3(NT), 0, s, Xt, nkb, m, N, gamma,
+                         coef0, degree, norms, q64, scal);
       break;
     case KPOLY:
-      hipLaunchKernelGGL((k_norms_q<T, BK, TP, KPOLY>), dim3(g), dim3(NT), 0, s, Xt, ld, nkb, m, N,
-                         gamma, coef0, degree, norms, q64, scal);
+      hipLaunchKernelGGL((k_norms_q<T, KPOLY>), dim3(g), dim3(NT), 0, s, Xt, nkb, m, N, gamma,
+                         coef0, degree, norms, q64, scal);
       break;
     default:
-      hipLaunchKernelGGL((k_norms_q<T, BK, TP, KRBF>), dim3(g), dim3(NT), 0, s, Xt, ld, nkb, m, N,
-                         gamma, coef0, degree, norms, q64, scal);
+      hipLaunchKernelGGL((k_norms_q<T, KRBF>), dim3(g), dim3(NT), 0, s, Xt, nkb, m, N, gamma,
+                         coef0, degree, norms, q64, scal);
       break;
   }
   return hipGetLastError();
@@ -1303,10 +1427,8 @@ int64_t linear_predict_part_elems(int64_t n, int64_t d) {
 }
 
 #define LSSVM_INSTANTIATE(T)                                                                      \
-  template hipError_t launch_layout<T>(const T*, int64_t, int64_t, T*, int64_t, int64_t, int*,    \
-                                       hipStream_t);                                              \
-  template hipError_t launch_norms_q<T>(const T*, int64_t, int64_t, int64_t, int64_t, int,        \
-                                        double, double, int, T*, double*, double*,                \
+  template hipError_t launch_norms_q<T>(const store_t<T>*, int64_t, int64_t, int64_t, int64_t,    \
+                                        int, double, double, int, T*, double*, double*,           \
                                         hipStream_t);                                             \
   template hipError_t launch_tiles_sym<T>(const TileArgs<T>&, int, int, int64_t, hipStream_t);    \
   template hipError_t launch_tiles_gen<T>(const TileArgs<T>&, int, int64_t, hipStream_t);         \

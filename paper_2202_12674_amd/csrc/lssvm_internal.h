@@ -46,7 +46,7 @@ enum Scalar : int {
   S_NMAX = 21,
   S_FIXSC = 22,
   S_INFLAGS = 23,   // the input flags as read after the right-hand side: 1 non-finite
-                    // X, 2 a label other than +-1 (one read-back with S_DELTA0)
+                    // X, 2 a label other than +-1, 4 F_TINY (one read-back with S_DELTA0)
   S_COUNT = 24
 };
 enum StatusField : int { ST_DELTA = 0, ST_CURV = 1, ST_STEP = 2, ST_ITER = 3, ST_DONE = 4,
@@ -69,7 +69,8 @@ inline int64_t cg_blocks(int64_t NP) { return vec_blocks(NP); }
 // Flags raised by kernels (int32 each).
 // F_PRODUCT: a symmetric product had a row sum that is not finite (its
 // entries then come out as NaN, so CG reports a breakdown).
-enum Flag : int { F_NONFINITE = 0, F_BADLABEL = 1, F_PRODUCT = 2, F_COUNT = 4 };
+// F_TINY: an fp32 point holds a nonzero value below kSplitMin.
+enum Flag : int { F_NONFINITE = 0, F_BADLABEL = 1, F_PRODUCT = 2, F_TINY = 3, F_COUNT = 4 };
 
 
 // One symmetric product as its readers see it: (K p)_i in the fixed-point
@@ -113,11 +114,15 @@ hipError_t launch_setup_clear(int64_t nT, int64_t group, int64_t diag_last, uint
                               int* flags, double* scal, int64_t* acc, int64_t nacc,
                               unsigned* ticket, hipStream_t s);
 
+// scale: what fp32 values are multiplied by as they are stored (a power of two).
 template <typename T>
-hipError_t launch_layout(const T* X, int64_t n, int64_t d, T* Xt, int64_t ld, int64_t d_pad,
-                         int* flags, hipStream_t s);
+hipError_t launch_layout(const T* X, int64_t n, int64_t d, store_t<T>* Xt, int64_t ld, int64_t d_pad,
+                         float scale, int* flags, hipStream_t s);
+// Raises *out (an int32 set to 0 before) to the bits of the largest |X[k]| of
+// `count` values.
+hipError_t launch_abs_max(const float* X, int64_t count, int* out, hipStream_t s);
 template <typename T>
-hipError_t launch_norms_q(const T* Xt, int64_t ld, int64_t d_pad, int64_t m, int64_t N,
+hipError_t launch_norms_q(const store_t<T>* Xt, int64_t ld, int64_t d_pad, int64_t m, int64_t N,
                           int kernel, double gamma, double coef0, int degree, T* norms,
                           double* q64, double* scal, hipStream_t s);
 template <typename T>

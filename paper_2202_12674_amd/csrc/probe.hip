@@ -1,5 +1,5 @@
-// Measured matrix-core peak of gfx950 for the instructions the tile kernel
-// issues (v_mfma_f32_32x32x2_f32, v_mfma_f64_16x16x4_f64), so that the tile
+// Measured matrix-core peak of gfx950 for v_mfma_f32_32x32x2_f32 and
+// v_mfma_f64_16x16x4_f64 (which the fp64 tile kernel issues), so that the tile
 // kernel's rate can be set against a sustained rather than only a published
 // peak. No memory traffic: every wave runs four independent accumulation
 // chains (enough to cover the instruction's dependency latency) and stores

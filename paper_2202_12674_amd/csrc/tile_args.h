@@ -13,17 +13,28 @@ enum Kern : int { KLIN = 0, KPOLY = 1, KRBF = 2 };
 // Points per tile edge and features per staged block, per element type
 // (compile-time, like the block sizes of Sec. III-C4). The symmetric schedule
 // needs square tiles.
-#ifndef LSSVM_F32_BK
-#define LSSVM_F32_BK 32
-#endif
-#ifndef LSSVM_F64_BK
-#define LSSVM_F64_BK 16
-#endif
+//
+// Plans and padding count blocks of BK features; the kernel stages SB features
+// at a time. fp64 stages its blocks whole. fp32 points are stored as three
+// bf16 slices h + m + l (bf16_split in tiles.h), which hold every bit of the
+// value, and the kernel multiplies the slices on the bf16 matrix cores: a
+// staged block is SLICES x T x SB slice elements, 12 KiB for 16 features, so
+// that two stages of two panels leave room for two workgroups on a CU.
 constexpr int kNumXcd = 8;
 
 template <typename T> struct TileShape;
-template <> struct TileShape<float> { static constexpr int T = 128, BK = LSSVM_F32_BK; };
-template <> struct TileShape<double> { static constexpr int T = 128, BK = LSSVM_F64_BK; };
+template <> struct TileShape<float> {
+  static constexpr int T = 128, BK = 32, SB = 16, SLICES = 3;
+  using store_t = uint16_t;   // bf16 bits
+};
+template <> struct TileShape<double> {
+  static constexpr int T = 128, BK = 16, SB = 16, SLICES = 1;
+  using store_t = double;
+};
+// Elements of one staged block of a panel of T points.
+template <typename T>
+constexpr int kSlabElems = TileShape<T>::SLICES * TileShape<T>::T * TileShape<T>::SB;
+template <typename T> using store_t = typename TileShape<T>::store_t;
 
 // What a symmetric tile launch computes: whole tiles, parked feature splits
 // of tiles (their raw inner products), or the fixup that sums a tile's parked
@@ -32,16 +43,17 @@ enum TilePart : int { kWhole = 0, kPartial = 1, kFixup = 2 };
 
 template <typename T>
 struct TileArgs {
-  const T* A;    // panel-major feature-blocked row points (see k_layout)
-  const T* B;    // panel-major feature-blocked column points
-  int64_t lda, ldb;
-  int64_t nkb;   // feature blocks of BK (even)
+  const store_t<T>* A;   // panel-major feature-blocked row points (see k_layout)
+  const store_t<T>* B;   // panel-major feature-blocked column points
+  int64_t nkb;   // staged feature blocks of SB (even)
   const T* nA;   // squared norms of row points (RBF)
   const T* nB;   // squared norms of column points (RBF)
   const double* pv;   // symmetric mode: the vector multiplied (fp64), zero beyond N
   const double* q64;  // symmetric mode: q_i = k(x_i, x_m), zero beyond N
   double* pq;         // symmetric mode: per panel I, sum p_j at [I], sum q_j p_j at [nTc + I]
   const T* wB;        // general mode: per-column weights (alpha)
+  T gscale;   // fp32: what the stored points' inner products are multiplied by, a power
+              // of two: 1 unless they were stored scaled up (k_layout_split)
   T gamma, coef0;
   T rbf_scale;   // RBF exponent scale: gamma (fp64, exp) or gamma log2(e) (fp32, exp2)
   int degree;

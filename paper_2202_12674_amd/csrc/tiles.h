@@ -18,15 +18,17 @@ namespace {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef double doublex4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // ---------------------------------------------------------------- MFMA ------
 // One matrix-core instruction computes an M x M block D += A B with a
-// contraction depth K. Lane l supplies A[l % M][l / M] and B[l / M][l % M];
-// accumulator element v of lane l is D[row(v, l)][l % M].
+// contraction depth K. Lane l supplies A[l % M][(l / M) KL + e] and
+// B[(l / M) KL + e][l % M], e < KL = K M / 64; accumulator element v of lane l
+// is D[row(v, l)][l % M].
 template <typename T> struct Mfma;
 
-template <> struct Mfma<float> {  // v_mfma_f32_32x32x2_f32
-  static constexpr int M = 32, K = 2, NACC = 16;
+template <> struct Mfma<float> {  // v_mfma_f32_32x32x16_bf16
+  static constexpr int M = 32, K = 16, NACC = 16;
   using acc_t = floatx16;
   __device__ static inline acc_t zero() {
     acc_t z;
@@ -34,8 +36,8 @@ template <> struct Mfma<float> {  // v_mfma_f32_32x32x2_f32
     for (int i = 0; i < NACC; ++i) z[i] = 0.f;
     return z;
   }
-  __device__ static inline acc_t mma(float a, float b, acc_t c) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+  __device__ static inline acc_t mma(bf16x8 a, bf16x8 b, acc_t c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
   }
   __device__ static inline int row(int v, int lane) {
     return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
@@ -61,7 +63,6 @@ template <> struct Mfma<double> {  // v_mfma_f64_16x16x4_f64
 // grid, each wave owning a (T/2) x (T/2) block of MFMA accumulators.
 template <typename T> struct TileCfg {
   static constexpr int BM = TileShape<T>::T;
-  static constexpr int BK = TileShape<T>::BK;
   static constexpr int WM = BM / 2, WN = BM / 2;
 };
 
@@ -213,23 +214,56 @@ __device__ inline void fixed_add(int64_t* acc, int* bad, int64_t row, double v, 
   atomicAdd(reinterpret_cast<unsigned long long*>(acc + 2 * row + 1), hi);
 }
 
-// XOR swizzle of the 16-byte chunk index inside a point's 128-byte LDS row.
-// LDS has 64 four-byte banks, and a 16-byte read serves 16 lanes per cycle,
-// so the 16 lanes served together must cover the 16 chunk positions of a
-// 256-byte bank line. Those 16 lanes are not 16 consecutive lanes: measured
+// fp32 points as bf16 slices. x = h + m + l exactly: h is x rounded to bf16
+// (8 significant bits), m the rest rounded, l what is left, which has at most
+// 8 bits. (x near the largest float, where rounding would reach infinity, is
+// cut instead; the rest still fits.) A product x y is formed as the six
+// partial products h h, h m, m h, m m, h l and l h, each exact in fp32, summed
+// by the matrix cores in fp32; the three left out (m l, l m, l l) are below
+// 2^-23 |x y|, and 2^-26 |x y| in the root mean square over random values.
+// The bf16 instructions take subnormal operands as zero, so points holding
+// values below kSplitMin, whose lowest slice may be subnormal, are stored
+// scaled up by a power of two.
+constexpr float kSplitMin = 0x1p-103f;   // 24 bits down from here: 2^-126
+__device__ inline uint32_t bf16_round(float x) {   // bf16 bits of finite x
+  const uint32_t u = __builtin_bit_cast(uint32_t, x);
+  const uint32_t r = (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
+  return (r & 0x7f80u) == 0x7f80u ? u >> 16 : r;
+}
+__device__ inline float bf16_value(uint32_t bits) {
+  return __builtin_bit_cast(float, bits << 16);
+}
+__device__ inline void bf16_split(float x, uint16_t (&s)[3]) {
+  const uint32_t h = bf16_round(x);
+  const float r1 = x - bf16_value(h);
+  const uint32_t m = bf16_round(r1);
+  const float r2 = r1 - bf16_value(m);
+  s[0] = (uint16_t)h;
+  s[1] = (uint16_t)m;
+  s[2] = (uint16_t)bf16_round(r2);
+}
+
+// Order of the 16-byte chunks of a staged fp32 block, in memory and in LDS
+// alike: slice, group of 32 points, half (8 features), point. A wave's operand
+// read takes the chunk of its lane's point and half, so 64 lanes read 64
+// consecutive chunks: no bank conflict under any grouping of the lanes.
+__device__ inline int split_chunk(int slice, int point, int half) {
+  return ((slice * (TileShape<float>::T / 32) + (point >> 5)) * 2 + half) * 32 + (point & 31);
+}
+
+// fp64: XOR swizzle of the 16-byte chunk index inside a point's 128-byte LDS
+// row. LDS has 64 four-byte banks, and a 16-byte read serves 16 lanes per
+// cycle, so the 16 lanes served together must cover the 16 chunk positions of
+// a 256-byte bank line. Those 16 lanes are not 16 consecutive lanes: measured
 // with the bank-conflict counter, patterns that keep lanes 16 apart on one
 // position run conflict-free, and the grouping that fits every pattern tried
 // sets lane bit 5 and a parity of lane bits 2..4 apart. A point's row fixes
-// the half-line (p & 1); the swizzle must spread the rest.
-// fp32 (32 x 32 x 2 blocks): lanes l and l + 32 read chunks 4 apart of the
-// same 32 points; (p >> 1) & 7 is conflict-free. fp64 (16 x 16 x 4 blocks):
-// the four 16-lane groups read chunks 2 apart of the same 16 points, where
-// (p >> 1) & 7 doubles every read (8 cycles instead of 4: half the fp64
+// the half-line (p & 1); the swizzle must spread the rest. The four 16-lane
+// groups of a 16 x 16 x 4 block read chunks 2 apart of the same 16 points,
+// where (p >> 1) & 7 doubles every read (8 cycles instead of 4: half the
 // kernel's LDS time was conflict); ((p >> 1) & 1) | (p & 4) is conflict-free
 // (measured, both chunk parities).
-template <typename T> __device__ inline int chunk_swizzle(int p);
-template <> __device__ inline int chunk_swizzle<float>(int p) { return (p >> 1) & 7; }
-template <> __device__ inline int chunk_swizzle<double>(int p) { return ((p >> 1) & 1) | (p & 4); }
+__device__ inline int chunk_swizzle(int p) { return ((p >> 1) & 1) | (p & 4); }
 
 // Tile rows per band of the general-mode visit order.
 constexpr int64_t kBandRows = 8;
@@ -273,41 +307,36 @@ __device__ __forceinline__ bool tile_body(const TileArgs<T>& a) {
                 "single-block workgroups: split linear tiles only");
   using MF = Mfma<T>;
   using C = TileCfg<T>;
-  constexpr int BM = C::BM, BK = C::BK;
+  using ST = store_t<T>;
+  constexpr int BM = C::BM;
+  constexpr bool SPLIT = sizeof(T) == 4;    // fp32: bf16 slices
+  constexpr int SLAB = kSlabElems<T>;       // elements of a staged block of a panel
   constexpr int VEC = 16 / sizeof(T);
-  constexpr int CPR = BK / VEC;             // 16-byte chunks per point row of a block
-  static_assert(CPR == 8, "rows of 128 bytes: the XOR swizzle below spans 8 chunks");
-  constexpr int CHUNKS = BM * CPR;          // chunks per panel slice
+  constexpr int CHUNKS = SLAB * (int)sizeof(ST) / 16;
   constexpr int LOADS = CHUNKS / 256;       // direct loads per thread per panel
   static_assert(CHUNKS % 256 == 0, "panel must split evenly over 256 threads");
   constexpr int RB = C::WM / MF::M, CB = C::WN / MF::M;
   constexpr int WAVES_N = BM / C::WN, WAVES_M = BM / C::WM;
   static_assert(WAVES_M * WAVES_N == 4, "four waves per workgroup");
-  // Lane group g = lane / M contracts the features [g * FPG, (g + 1) * FPG) of
-  // each block, one per MFMA step; A and B use the same feature order.
-  constexpr int FPG = BK / MF::K;           // features per lane group and block
-  constexpr int CPG = FPG / VEC;            // chunks per lane group
-  static_assert(FPG % VEC == 0, "lane operands are read in 16-byte chunks");
-  typedef T vec_t __attribute__((ext_vector_type(VEC)));
   typedef __attribute__((address_space(1))) const void* gptr_t;
   typedef __attribute__((address_space(3))) void* lptr_t;
 
-  // LDS: per stage and panel, BM rows of 128 bytes; chunk c of point p sits at
-  // physical chunk p * 8 + (c ^ chunk_swizzle<T>(p)) (see there: the swizzle
-  // makes the operand reads conflict-free); the lane-linear direct loads are
-  // conflict-free by construction.
-  // one array per stage and panel: with fixed names the compiler can tell the
-  // stage being filled from the stage being read and need not wait in between
-  __shared__ __attribute__((aligned(16))) T As0[CHUNKS * VEC];
-  __shared__ __attribute__((aligned(16))) T As1[CHUNKS * VEC];
-  __shared__ __attribute__((aligned(16))) T Bs0[CHUNKS * VEC];
-  __shared__ __attribute__((aligned(16))) T Bs1[CHUNKS * VEC];
+  // LDS: one array per stage and panel: with fixed names the compiler can tell
+  // the stage being filled from the stage being read and need not wait in
+  // between. fp64: BM rows of 128 bytes; chunk c of point p sits at physical
+  // chunk p * 8 + (c ^ chunk_swizzle(p)) (see there: the swizzle makes the
+  // operand reads conflict-free). fp32: in split_chunk order, as in memory.
+  // The lane-linear direct loads are conflict-free by construction.
+  __shared__ __attribute__((aligned(16))) ST As0[SLAB];
+  __shared__ __attribute__((aligned(16))) ST As1[SLAB];
+  __shared__ __attribute__((aligned(16))) ST Bs0[SLAB];
+  __shared__ __attribute__((aligned(16))) ST Bs1[SLAB];
   __shared__ double red_r[WAVES_N][BM];
   __shared__ double red_c[WAVES_M][BM];
   // The tile's panel vectors are staged with its first feature block, so the
   // epilogue reads no global memory (its loads of p and the norms otherwise
-  // cost several L2 round trips per tile: up to 10% of the product at 64
-  // features, 0.5% at 4096 in fp32; in fp64 ~1% at 1024 and 2048 features).
+  // cost several L2 round trips per tile: ~1% of an fp64 product at 1024 and
+  // 2048 features, more at fewer).
   // p over rows I and over columns J (symmetric mode) go to vp, q over panel
   // I to vq (diagonal tiles); the squared norms of both panels (radial
   // kernel) and the column weights (general mode) to vt[0], vt[1], vt[2].
@@ -391,12 +420,12 @@ __device__ __forceinline__ bool tile_body(const TileArgs<T>& a) {
     fx_nmax = a.fx[1];
   }
 
-  // panel I is a.nkb consecutive blocks of BM * BK elements; this workgroup
+  // panel I is a.nkb consecutive staged blocks of SLAB elements; this workgroup
   // contracts blocks [ks nkb, (ks + 1) nkb) of it
   const int64_t nkb = a.nkb / KS;
-  const T* __restrict__ Ap = a.A + (I * a.nkb + ks * nkb) * BM * BK;
-  const T* __restrict__ Bp = a.B + (J * a.nkb + ks * nkb) * BM * BK;
-  constexpr int64_t astride = (int64_t)BM * BK;   // elements per block of a panel
+  const ST* __restrict__ Ap = a.A + (I * a.nkb + ks * nkb) * SLAB;
+  const ST* __restrict__ Bp = a.B + (J * a.nkb + ks * nkb) * SLAB;
+  constexpr int64_t block_bytes = (int64_t)SLAB * sizeof(ST);
 
   // Direct loads of block kb into a stage, memory -> LDS with no registers in
   // between: instruction u of wave w fills physical chunks [(4u + w) * 64, +64)
@@ -406,27 +435,26 @@ __device__ __forceinline__ bool tile_body(const TileArgs<T>& a) {
   // in range), the lane's chunk offset as the 32-bit vector offset and the
   // block's offset as the scalar offset, so a block's loads need no vector
   // instruction for their addresses. (Global loads into LDS took two 64-bit
-  // vector adds and a readfirstlane per load; at 32768 x 4096 fp32 the tile
-  // kernel ran at 88% of the matrix-core peak with them and 94.5% without,
-  // bit-identical.) The spans stay below 4 GiB (at most 2^21 features: 1 GiB
+  // vector adds and a readfirstlane per load; at 16384 x 4096 fp64 the tile
+  // kernel ran at 88.3% of the matrix-core peak with them and 90.9% without,
+  // bit-identical.) The spans stay below 4 GiB (at most 2^21 features: 1.5 GiB
   // fp32, 2 GiB fp64 per panel).
   uint32_t goff[LOADS];
 #pragma unroll
   for (int u = 0; u < LOADS; ++u) {
     const int P = (u * 4 + wave) * 64 + lane;
-    const int p = P / CPR, c = (P % CPR) ^ chunk_swizzle<T>(p);
-    goff[u] = (uint32_t)((p * CPR + c) * VEC * (int)sizeof(T));
+    goff[u] = SPLIT ? 16u * P : 16u * (uint32_t)((P & ~7) + ((P & 7) ^ chunk_swizzle(P >> 3)));
   }
-  const int span = (int)(uint32_t)((uint64_t)nkb * astride * sizeof(T));
+  const int span = (int)(uint32_t)((uint64_t)nkb * block_bytes);
   const __amdgpu_buffer_rsrc_t ra =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(Ap), (short)0, span, kBufferWord3);
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<ST*>(Ap), (short)0, span, kBufferWord3);
   const __amdgpu_buffer_rsrc_t rb =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(Bp), (short)0, span, kBufferWord3);
-  auto dload = [&](int64_t kb, T (&sa)[CHUNKS * VEC], T (&sb)[CHUNKS * VEC]) {
-    const int so = (int)(uint32_t)((uint64_t)kb * astride * sizeof(T));   // uniform
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<ST*>(Bp), (short)0, span, kBufferWord3);
+  auto dload = [&](int64_t kb, ST (&sa)[SLAB], ST (&sb)[SLAB]) {
+    const int so = (int)(uint32_t)((uint64_t)kb * block_bytes);   // uniform
 #pragma unroll
     for (int u = 0; u < LOADS; ++u) {
-      const int base = (u * 4 + wave) * 64 * VEC;   // wave-uniform LDS element offset
+      const int base = (u * 4 + wave) * 64 * 16 / (int)sizeof(ST);   // wave-uniform
       __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lptr_t)(&sa[base]), 16, (int)goff[u], so,
                                                0, 0);
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lptr_t)(&sb[base]), 16, (int)goff[u], so,
@@ -470,40 +498,75 @@ __device__ __forceinline__ bool tile_body(const TileArgs<T>& a) {
   for (int i = 0; i < RB; ++i)
 #pragma unroll
     for (int j = 0; j < CB; ++j) acc[i][j] = MF::zero();
+  // fp32: the five partial products with a lower slice are summed apart from
+  // h h and added once at the end, so the large sum is rounded once per 16
+  // features instead of six times.
+  typename MF::acc_t low[SPLIT ? RB : 1][SPLIT ? CB : 1];
+  if constexpr (SPLIT) {
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int j = 0; j < CB; ++j) low[i][j] = MF::zero();
+  }
 
   const int cl = lane % MF::M;   // point of this lane inside an MFMA block
   const int kl = lane / MF::M;   // lane group: which features of the block it contracts
 
-  // A block's operands are CPG groups of 16-byte LDS reads (chunk q of every
-  // row and column block). fp64 reads group q + 1 into registers of its own
-  // before group q's MFMAs issue, so a group's LDS latency hides behind the
-  // MFMAs of the one before it (A/B: 4096 x 1024 linear 83.7% -> 85.3% of the
-  // fp64 peak, 16384 x 2048 RBF 93.3% -> 93.6%). fp32, where the compiler
-  // reuses one group's registers and the two workgroups of a CU cover each
-  // other's waits, measured the same either way and keeps the plain loop.
-  // Both issue the MFMAs in the order of a plain loop over the features.
-  auto read_group = [&](const T (&sa)[CHUNKS * VEC], const T (&sb)[CHUNKS * VEC], int q,
-                        vec_t (&a)[RB], vec_t (&b)[CB]) {
+  // fp32: the slices of a staged block's rows and columns (12 reads of 16
+  // bytes per lane) and the six partial products of every accumulator block
+  // (24 MFMAs of 16 features), those that share a row operand in a row: the
+  // matrix cores then run cooler and clock higher (32768 x 4096 cubic, bound by
+  // the board's power: 20.9-21.2 ms with the products outermost, 20.5 ms).
+  // fp64: lane group kl contracts the features [kl FPG, (kl + 1) FPG) of the
+  // block, one per MFMA step. A block's operands are CPG groups of 16-byte LDS
+  // reads (chunk q of every row and column block); group q + 1 is read into
+  // registers of its own before group q's MFMAs issue, so a group's LDS
+  // latency hides behind the MFMAs of the one before it (A/B: 4096 x 1024
+  // linear 83.7% -> 85.3% of the fp64 peak, 16384 x 2048 RBF 93.3% -> 93.6%).
+  auto compute = [&](const ST (&sa)[SLAB], const ST (&sb)[SLAB]) {
+    if constexpr (SPLIT) {
+      bf16x8 av[3][RB], bv[3][CB];
 #pragma unroll
-    for (int i = 0; i < RB; ++i) {
-      const int p = wm * C::WM + i * MF::M + cl;
-      a[i] = *reinterpret_cast<const vec_t*>(
-          &sa[(p * CPR + ((kl * CPG + q) ^ chunk_swizzle<T>(p))) * VEC]);
-    }
+      for (int t = 0; t < 3; ++t) {
 #pragma unroll
-    for (int j = 0; j < CB; ++j) {
-      const int p = wn * C::WN + j * MF::M + cl;
-      b[j] = *reinterpret_cast<const vec_t*>(
-          &sb[(p * CPR + ((kl * CPG + q) ^ chunk_swizzle<T>(p))) * VEC]);
-    }
-  };
-  auto compute = [&](const T (&sa)[CHUNKS * VEC], const T (&sb)[CHUNKS * VEC]) {
-    if constexpr (sizeof(T) == 8) {
+        for (int i = 0; i < RB; ++i)
+          av[t][i] = *reinterpret_cast<const bf16x8*>(
+              &sa[8 * split_chunk(t, wm * C::WM + i * MF::M + cl, kl)]);
+#pragma unroll
+        for (int j = 0; j < CB; ++j)
+          bv[t][j] = *reinterpret_cast<const bf16x8*>(
+              &sb[8 * split_chunk(t, wn * C::WN + j * MF::M + cl, kl)]);
+      }
+      constexpr int PA[6] = {2, 1, 1, 0, 0, 0}, PB[6] = {0, 1, 0, 0, 1, 2};
+#pragma unroll
+      for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int t = 0; t < 6; ++t)
+#pragma unroll
+          for (int j = 0; j < CB; ++j) {
+            typename MF::acc_t& c = PA[t] + PB[t] == 0 ? acc[i][j] : low[i][j];
+            c = MF::mma(av[PA[t]][i], bv[PB[t]][j], c);
+          }
+    } else {
+      typedef T vec_t __attribute__((ext_vector_type(VEC)));
+      constexpr int FPG = TileShape<T>::SB / MF::K;   // features per lane group and block
+      constexpr int CPG = FPG / VEC;                  // chunks per lane group
+      static_assert(TileShape<T>::SB * sizeof(T) == 128, "rows of 8 chunks (chunk_swizzle)");
+      auto operand = [&](const ST (&sm)[SLAB], int p, int q) {
+        return *reinterpret_cast<const vec_t*>(
+            &sm[(p * 8 + ((kl * CPG + q) ^ chunk_swizzle(p))) * VEC]);
+      };
       vec_t av[2][RB], bv[2][CB];
-      read_group(sa, sb, 0, av[0], bv[0]);
+      auto read_group = [&](int q, vec_t (&va)[RB], vec_t (&vb)[CB]) {
+#pragma unroll
+        for (int i = 0; i < RB; ++i) va[i] = operand(sa, wm * C::WM + i * MF::M + cl, q);
+#pragma unroll
+        for (int j = 0; j < CB; ++j) vb[j] = operand(sb, wn * C::WN + j * MF::M + cl, q);
+      };
+      read_group(0, av[0], bv[0]);
 #pragma unroll
       for (int q = 0; q < CPG; ++q) {
-        if (q + 1 < CPG) read_group(sa, sb, q + 1, av[(q + 1) & 1], bv[(q + 1) & 1]);
+        if (q + 1 < CPG) read_group(q + 1, av[(q + 1) & 1], bv[(q + 1) & 1]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int e = 0; e < VEC; ++e)
@@ -513,31 +576,6 @@ __device__ __forceinline__ bool tile_body(const TileArgs<T>& a) {
             for (int j = 0; j < CB; ++j)
               acc[i][j] = MF::mma(av[q & 1][i][e], bv[q & 1][j][e], acc[i][j]);
       }
-    } else {
-      vec_t av[RB][CPG], bv[CB][CPG];
-#pragma unroll
-      for (int i = 0; i < RB; ++i) {
-        const int p = wm * C::WM + i * MF::M + cl;
-#pragma unroll
-        for (int q = 0; q < CPG; ++q)
-          av[i][q] = *reinterpret_cast<const vec_t*>(
-              &sa[(p * CPR + ((kl * CPG + q) ^ chunk_swizzle<T>(p))) * VEC]);
-      }
-#pragma unroll
-      for (int j = 0; j < CB; ++j) {
-        const int p = wn * C::WN + j * MF::M + cl;
-#pragma unroll
-        for (int q = 0; q < CPG; ++q)
-          bv[j][q] = *reinterpret_cast<const vec_t*>(
-              &sb[(p * CPR + ((kl * CPG + q) ^ chunk_swizzle<T>(p))) * VEC]);
-      }
-#pragma unroll
-      for (int kk = 0; kk < FPG; ++kk)
-#pragma unroll
-        for (int i = 0; i < RB; ++i)
-#pragma unroll
-          for (int j = 0; j < CB; ++j)
-            acc[i][j] = MF::mma(av[i][kk / VEC][kk % VEC], bv[j][kk / VEC][kk % VEC], acc[i][j]);
     }
   };
 
@@ -547,14 +585,20 @@ __device__ __forceinline__ bool tile_body(const TileArgs<T>& a) {
   // even number of blocks, so both halves of the loop body always run.
   //
   // Scheduling fence, chosen by measurement: left alone, the compiler sinks
-  // the block loads into the compute (fp32: into its last quarter; fp64: it
-  // waits for them, and holds the barrier, after the first four MFMAs, so the
-  // load latency is hidden only by the other workgroup's waves). Pinned above
-  // the compute, a wave's own 64 MFMAs cover it: fp32 +0.5%; fp64, with its
-  // conflict-free LDS reads (chunk_swizzle), 16384 x 2048 RBF 90.9% -> 93.2%
-  // of the fp64 peak, 16384 x 4096 linear 90.9% -> 95.5%, 16384 x 1024 cubic
-  // 90.8% -> 92.3%, 4096 x 1024 linear 82.7% -> 84.0% (with the conflicting
-  // reads pinning had cost fp64 ~1%).
+  // the block loads into the compute (fp64: it waits for them, and holds the
+  // barrier, after the first four MFMAs, so the load latency is hidden only by
+  // the other workgroup's waves). Pinned above
+  // the compute, a wave's own MFMAs cover it: with conflict-free LDS reads
+  // (chunk_swizzle) 16384 x 2048 RBF 90.9% -> 93.2% of the fp64 peak, 16384 x
+  // 1024 cubic 90.8% -> 92.3%.
+  //
+  // What bounds fp32: six bf16 products per fp32 one, and the board's power.
+  // 32768 x 4096 cubic takes 20.4 ms (29.1 ms on v_mfma_f32_32x32x2_f32), 216
+  // TFLOP/s of fp32 products or 1.3 PFLOP/s of bf16 ones, with the matrix cores
+  // 78% busy at a clock that the power limit has brought down to 1.5 GHz; with
+  // all points equal, which toggles few bits, the same launch takes 15.4 ms. A
+  // third stage (loads two blocks ahead) changed neither (20.5 and 15.2 ms);
+  // super-tiles of 4, 8 and 16 tiles are within 3%.
   if constexpr (PART != kFixup) {
   dload(0, As0, Bs0);
   if constexpr (PART == kWhole) dvec();
@@ -581,6 +625,19 @@ __device__ __forceinline__ bool tile_body(const TileArgs<T>& a) {
     __syncthreads();
   }
   }
+  }
+
+  if constexpr (SPLIT && PART != kFixup) {
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int j = 0; j < CB; ++j) acc[i][j] += low[i][j];
+    if (PART == kWhole && a.gscale != T(1)) {   // uniform
+#pragma unroll
+      for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int j = 0; j < CB; ++j) acc[i][j] *= a.gscale;
+    }
   }
 
   // Split tiles: park this split's inner products, or sum all splits of the
@@ -624,6 +681,12 @@ __device__ __forceinline__ bool tile_body(const TileArgs<T>& a) {
               for (int e = 0; e < PER; ++e) acc[i][j][w * PER + e] += x[e];
             }
       }
+      if (SPLIT && a.gscale != T(1)) {   // uniform
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+          for (int j = 0; j < CB; ++j) acc[i][j] *= a.gscale;
+      }
     }
   }
 
@@ -634,6 +697,13 @@ __device__ __forceinline__ bool tile_body(const TileArgs<T>& a) {
   // their products with the vector and all sums in fp64, so an fp32 product
   // uses the fp64 CG direction as it is instead of a rounded copy.
   const bool diag = SYM && (I == J);
+  // A diagonal tile holds both G_ij and G_ji. In fp64 they are the same bits;
+  // the slice products of fp32 enter the sum in another order, and an operator
+  // that is not exactly symmetric costs CG iterations (32768 x 4096 cubic: 27
+  // against 25, 3001 x 123 RBF: 50-55 against 47-52). So fp32 takes the values
+  // above the diagonal for both triangles, as off-diagonal tiles do, and half
+  // of each diagonal value (exact) for either.
+  constexpr bool HALF = SYM && SPLIT;
   double fxs = 1.0;   // fixed-point scale of the row sums (symmetric mode)
   if constexpr (SYM) {
     fxs = fixed_scale<KER>(a, fx_pmax, fx_nmax);
@@ -676,6 +746,17 @@ __device__ __forceinline__ bool tile_body(const TileArgs<T>& a) {
                                          a.rbf_scale);
     }
     if constexpr (KER == KPOLY) poly_power(kv, a.degree);
+    if (HALF && diag) {   // uniform
+#pragma unroll
+      for (int vv = 0; vv < VH; ++vv) {
+        const int li = wm * C::WM + i * MF::M + MF::row(v0 + vv, lane);
+#pragma unroll
+        for (int j = 0; j < CB; ++j) {
+          const int lj = wn * C::WN + j * MF::M + cl;
+          kv[vv][j] *= li < lj ? T(1) : (li == lj ? T(0.5) : T(0));
+        }
+      }
+    }
     double rs[VH];
 #pragma unroll
     for (int vv = 0; vv < VH; ++vv) {
@@ -741,7 +822,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs<T>& a) {
     for (int w = 0; w < WAVES_N; ++w) s += red_r[w][tid];
     if constexpr (SYM) fixed_add(a.acc, a.fx_bad, I * BM + tid, s, fxs);
     else a.part[J * a.part_ld + I * BM + tid] = s;
-  } else if (SYM && !diag && tid < 2 * BM) {
+  } else if (SYM && (HALF || !diag) && tid < 2 * BM) {
     const int c = tid - BM;
     double s = 0.0;
 #pragma unroll
