@@ -69,6 +69,12 @@ bool log_enabled() {
   return on;
 }
 constexpr int64_t kReplaceEvery = 50;  // residual recomputed every 50th iteration
+// The products of the linear passes are so nearly exact that the CG recurrence
+// goes on falling below the residual that fp64 iterates can have (4096 x 1024,
+// eps 1e-13: 7.7e-14 at iteration 161 against a true 1.3e-12). So for an eps
+// below this, a linear training of such products converges on recomputed
+// residuals only (every 50th iteration, and the last one allowed).
+constexpr double kTrustedEps = 1e-12;
 
 inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
@@ -83,7 +89,8 @@ struct Geometry {
   int64_t n, d, N;  // N = n - 1 unknowns of the reduced system
   int64_t tile, bk;
   int64_t ld;       // points per feature row of the layout (>= n, multiple of tile)
-  int64_t d_pad;    // features, multiple of 2 bk
+  int64_t d_pad;    // features, an even number of staged blocks
+  int64_t plan_nkb; // feature blocks of bk the tile plans count (even)
   int64_t nT;       // tiles per edge of the reduced system
   int64_t NP;       // nT * tile: padded length of every CG vector
   int64_t nb;       // blocks of the CG vector kernels over NP (block partials per reduction)
@@ -106,6 +113,17 @@ struct Geometry {
 inline bool fused_iteration(const Geometry& g, int32_t kernel) {
   const bool one_launch = kernel == LSSVM_LINEAR ? g.lin_tail_q == 0 : g.tail_q == 0;
   return LSSVM_FUSED_SMALL && g.NP <= kFusedMaxNP && one_launch;
+}
+
+// Linear products run in two passes over the points, w = X^T p and X w (k_lin_w,
+// k_lin_rows): O(n d) in place of the tiles' O(n^2 d). Measured per CG iteration,
+// fp64: 4096 x 1024 258 us with tiles and 30 us so, 20011 x 301 1840 and 38,
+// 600 x 3000 196 and 24. Below about 10^5 values the four launches of an
+// iteration (21 us) lose to a fused one: 1000 x 100 22.6 us against 20.6, 256 x
+// 64 21 against 11; at 300 x 732 they win, 23 against 101.
+inline bool linear_passes(const Geometry& g, int32_t kernel) {
+  constexpr int64_t kFusedValues = int64_t(1) << 17;
+  return kernel == LSSVM_LINEAR && !(fused_iteration(g, kernel) && g.n * g.d <= kFusedValues);
 }
 
 inline int64_t tri_count(int64_t nT) { return nT * (nT + 1) / 2; }
@@ -201,12 +219,17 @@ Geometry geometry(int64_t n, int64_t d) {
   g.tile = TileShape<T>::T;
   g.bk = TileShape<T>::BK;
   g.ld = round_up(n, g.tile);
-  g.d_pad = round_up(d, 2 * g.bk);   // an even number of feature blocks (two LDS stages)
   g.nT = (g.N + g.tile - 1) / g.tile;
   g.NP = g.nT * g.tile;
   g.nb = cg_blocks(g.NP);
-  linear_plan(g.nT, g.d_pad / g.bk, &g.ksplit, &g.lin_tail_q, &g.lin_tail_split);
-  tail_plan(g.nT, g.d_pad / g.bk, &g.tail_q, &g.tail_split);
+  g.plan_nkb = round_up(d, 2 * g.bk) / g.bk;
+  linear_plan(g.nT, g.plan_nkb, &g.ksplit, &g.lin_tail_q, &g.lin_tail_split);
+  tail_plan(g.nT, g.plan_nkb, &g.tail_q, &g.tail_split);
+  // An even number of staged blocks (two LDS stages), as many as planned where
+  // a plan shares them out: in fp32, whose staged blocks are half a planned
+  // one, that can be 32 features of padding more.
+  const bool shared = g.tail_q > 0 || g.NP <= kFusedMaxNP;
+  g.d_pad = shared ? g.plan_nkb * g.bk : round_up(d, 2 * TileShape<T>::SB);
   return g;
 }
 
@@ -232,6 +255,8 @@ struct TrainWs {
   T* gpart;     // parked inner products of split tail tiles
   double* pq;   // per tile panel: sum p_j, then sum q_j p_j (2 nT)
   double *rhs, *x, *r, *dir, *qv;
+  double* dir2;    // linear passes: the other buffer of the direction
+  double *lin_part, *lin_w;   // linear passes: partial and whole w = X^T p
   double* xbest;   // iterate of the smallest recomputed residual (returned on a stall)
   double *bp0, *bp1, *bp2;
   double* scal;
@@ -255,16 +280,20 @@ TrainWs<T> carve_train(const Geometry& g, void* base) {
   // split tail's parked inner products (at most a quarter round of tiles).
   w.acc = c.take<int64_t>(2 * g.NP);
   w.gpart = c.take<T>(g.tail_q * g.tail_split * g.tile * g.tile);
-  w.pq = c.take<double>(2 * g.nT);
+  const int64_t chunks = lin_max_chunks(g.n, g.d);
+  w.pq = c.take<double>(2 * std::max(g.nT, chunks));
   w.rhs = c.take<double>(g.NP);
   w.x = c.take<double>(g.NP);
   w.r = c.take<double>(g.NP);
   w.dir = c.take<double>(g.NP);
   w.qv = c.take<double>(g.NP);
+  w.dir2 = c.take<double>(g.NP);
+  w.lin_part = c.take<double>(2 * chunks * g.d);
+  w.lin_w = c.take<double>(2 * g.d);
   w.xbest = c.take<double>(g.NP);
-  w.bp0 = c.take<double>(g.nb + 1);
-  w.bp1 = c.take<double>(g.nb + 1);
-  w.bp2 = c.take<double>(g.nb + 1);   // energy partials at residual recomputations
+  w.bp0 = c.take<double>(kVecBlocks + 1);
+  w.bp1 = c.take<double>(kVecBlocks + 1);
+  w.bp2 = c.take<double>(kVecBlocks + 1);   // energy partials at residual recomputations
   w.scal = c.take<double>(S_COUNT);
   w.flags = c.take<int>(F_COUNT);
   w.order = c.take<uint32_t>(LSSVM_TILE_GROUP > 0 ? tri_count(g.nT) : 0);
@@ -301,8 +330,8 @@ PredictWs<T> carve_predict(const Geometry& g, int64_t n_test, void* base) {
   w.nte = c.take<T>(w.ld_te);
   w.part = c.take<double>(w.nTc * w.ld_te);
   w.flags = c.take<int>(F_COUNT);
-  w.lin_part = c.take<double>(linear_predict_part_elems(g.n, g.d));
-  w.lin_w = c.take<double>(g.d);
+  w.lin_part = c.take<double>(2 * lin_max_chunks(g.n, g.d) * g.d);
+  w.lin_w = c.take<double>(2 * g.d);
   w.lin_f = c.take<double>(n_test);
   w.bytes = c.off;
   return w;
@@ -474,7 +503,7 @@ inline int64_t product_split(const Geometry& g, int32_t kernel) {
   if (kernel != LSSVM_LINEAR) return 1;
   int64_t S = g.ksplit;
   if (!fused_iteration(g, kernel)) return S;
-  const int64_t nkb = g.d_pad / g.bk, W = tri_count(g.nT);
+  const int64_t nkb = g.plan_nkb, W = tri_count(g.nT);
   // double while every workgroup keeps an even block count (the two-stage
   // loop) or gets exactly one (the single-block variant)
   while (S < LSSVM_LINEAR_SPLIT_MAX && W * 2 * S <= kResidentTiles &&
@@ -586,8 +615,42 @@ template <typename T>
 RankOne rank_one(const Geometry& g, const TrainWs<T>& w, int32_t kernel, double C,
                  const double* p) {
   (void)kernel;
-  return RankOne{w.pq, g.nT, w.acc, w.q64, p, w.scal, w.flags, 1.0 / C};
+  return RankOne{w.pq, g.nT, w.acc, w.q64, p, w.scal, w.flags, 1.0 / C, nullptr};
 }
+
+// The linear kernel's two passes over the caller's points.
+template <typename T>
+struct LinearPasses {
+  const Geometry& g;
+  const TrainWs<T>& w;
+  const T* X;
+  double C;
+  hipStream_t s;
+  int64_t nch, nbg;   // chunks of w; block partials of a gather
+  LinearPasses(const Geometry& g_, const TrainWs<T>& w_, const T* X_, double C_, hipStream_t s_)
+      : g(g_), w(w_), X(X_), C(C_), s(s_), nch(lin_shape(g_.N, g_.d, lin_vec(X_, g_.d)).nch),
+        nbg(lin_gather_blocks(X_, g_.N, g_.d)) {}
+  RankOne rank_one(const double* p, const double* kp) const {
+    return RankOne{w.pq, nch, nullptr, w.q64, p, w.scal, w.flags, 1.0 / C, kp};
+  }
+  // w = X^T p, with S and T of p
+  hipError_t weights(const LinVec& v) const {
+    return launch_lin_w<T>(X, g.N, g.d, v, w.q64, w.lin_part, w.lin_w, w.pq, s);
+  }
+  LinVec vec(const double* p, bool stop) const {
+    LinVec v{};
+    v.p = p;
+    v.scal = w.scal;
+    v.stop = stop;
+    return v;
+  }
+  // K p into qv, for the readers of rank_one(p, qv)
+  int product(const double* p, bool stop) const {
+    LSSVM_HIP(weights(vec(p, stop)));
+    LSSVM_HIP(launch_lin_kp<T>(X, g.N, g.d, w.lin_w, w.qv, s));
+    return LSSVM_OK;
+  }
+};
 
 // The tile launches of one product: all tiles whole (the linear kernel's
 // split tiles included), or the full rounds whole and the tail split, parked
@@ -686,10 +749,20 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
   }
 
   // ---- setup: a1, a2, a3 (one read-back for the input flags and r0^T r0)
-  LSSVM_TRY(setup_points<T>(g, w, X, kernel, kp, s, /*check=*/false));
-  LSSVM_HIP(launch_rhs_init<T>(y, g.N, g.NP, w.rhs, w.x, w.xbest, w.r, w.dir, w.bp0, w.flags,
+  // Linear passes keep the points as they are and their vectors unpadded.
+  const bool passes = linear_passes(g, kernel);
+  const int64_t NP = passes ? g.N : g.NP, nb = cg_blocks(NP);
+  const LinearPasses<T> lin(g, w, X, C, s);
+  if (passes) {
+    LSSVM_HIP(launch_setup_clear(0, LSSVM_TILE_GROUP, 0, nullptr, w.flags, w.scal, nullptr, 0,
+                                 nullptr, s));
+    LSSVM_HIP(launch_lin_q<T>(X, g.n, g.d, w.q64, w.scal, w.flags, s));
+  } else {
+    LSSVM_TRY(setup_points<T>(g, w, X, kernel, kp, s, /*check=*/false));
+  }
+  LSSVM_HIP(launch_rhs_init<T>(y, g.N, NP, w.rhs, w.x, w.xbest, w.r, w.dir, w.bp0, w.flags,
                                w.scal, s));
-  LSSVM_HIP(launch_finish_delta0(w.bp0, g.nb, w.scal, eps * eps, w.flags, s));
+  LSSVM_HIP(launch_finish_delta0(w.bp0, nb, w.scal, eps * eps, w.flags, s));
   // one read-back: r0^T r0 and the input flags
   LSSVM_HIP(hipMemcpyAsync(g_ctx->p, w.scal + S_DELTA0, (S_INFLAGS - S_DELTA0 + 1) * sizeof(double),
                            hipMemcpyDeviceToHost, s));
@@ -721,14 +794,17 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
   int64_t batch = 1;   // fused (small) problems start at 8, below
   double* st = g_ctx->p;
   int64_t warm_products = 0;
+  auto product_of = [&](const double* p) {   // a finished product, for its readers
+    return passes ? lin.rank_one(p, w.qv) : rank_one(g, w, kernel, C, p);
+  };
   if (info && info->warm_start && !done) {
     // x0 = the caller's alpha~, r0 = rhs - Q~ x0, dir = r0; the stop threshold
     // set from rhs^T rhs above is kept
-    LSSVM_HIP(launch_pad_to_f64<T>(alpha_out, g.N, w.x, g.NP, w.scal, s));
-    LSSVM_TRY(matvec_partials<T>(g, w, kp, kernel, w.x, s));
-    LSSVM_HIP(launch_cg_residual(rank_one(g, w, kernel, C, w.x), g.NP, g.N, w.rhs,
-                                 w.r, w.bp1, w.bp2, s));
-    LSSVM_HIP(launch_warm_start(w.bp1, w.bp2, g.nb, w.scal, w.r, w.dir, w.x, w.xbest, g.NP, s));
+    LSSVM_HIP(launch_pad_to_f64<T>(alpha_out, g.N, w.x, NP, w.scal, s));
+    if (passes) LSSVM_TRY(lin.product(w.x, false));
+    else LSSVM_TRY(matvec_partials<T>(g, w, kp, kernel, w.x, s));
+    LSSVM_HIP(launch_cg_residual(product_of(w.x), NP, g.N, w.rhs, w.r, w.bp1, w.bp2, s));
+    LSSVM_HIP(launch_warm_start(w.bp1, w.bp2, nb, w.scal, w.r, w.dir, w.x, w.xbest, NP, s));
     LSSVM_HIP(hipMemcpyAsync(st, w.scal + S_STATUS, ST_COUNT * sizeof(double),
                              hipMemcpyDeviceToHost, s));
     LSSVM_HIP(hipStreamSynchronize(s));
@@ -744,11 +820,17 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
   // threshold (with a quarter to spare).
   int64_t it_prev = 0, need = max_iter;
   double delta_prev = delta;
-  const bool fused = fused_iteration(g, kernel);
+  const bool fused = !passes && fused_iteration(g, kernel);
   // A fused iteration takes ~15 us and a status read-back ~30 us: small
   // problems start with 8 iterations queued (those run past the stop return at
   // once, a few microseconds each)
   if (fused) batch = 8;
+  // Linear passes form the direction of the next iteration with its product
+  // (from one buffer into the other); `pending` until then. The last one of a
+  // batch is formed on its own, so that the status is complete when read.
+  double *dir = w.dir, *dir_other = w.dir2;
+  bool pending = false;
+  const bool trusted = eps >= kTrustedEps;
   while (!done && queued < max_iter) {
     const int64_t nq = std::min<int64_t>(std::min(batch, need), max_iter - queued);
     for (int64_t b = 0; b < nq; ++b) {
@@ -766,6 +848,43 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
         LSSVM_HIP(tm.stop(s));
         continue;
       }
+      if (passes) {
+        LSSVM_HIP(tm.start(s, k));
+        LinVec v = lin.vec(dir, true);
+        if (pending) {
+          v.r = w.r;
+          v.dir_out = dir_other;
+          v.bp = w.bp1;
+          v.nb = nb;
+          v.par = par ^ 1;
+          v.iter = k - 1;
+          v.test = trusted;
+          v.hist = w.hist;
+          v.hist_cap = g.NP + 1;
+          std::swap(dir, dir_other);
+        }
+        LSSVM_HIP(lin.weights(v));
+        LSSVM_HIP(launch_lin_gather<T>(X, g.N, g.d, w.lin_w, lin.rank_one(dir, nullptr), w.qv,
+                                       w.bp0, s));
+        LSSVM_HIP(tm.stop(s));
+        LSSVM_HIP(launch_cg_update(refresh, w.bp0, lin.nbg, w.scal, par, dir, w.qv, w.x, w.r,
+                                   w.bp1, NP, s));
+        pending = true;
+        if (refresh) {
+          LSSVM_HIP(tm.start(s, k));
+          LSSVM_TRY(lin.product(w.x, true));
+          LSSVM_HIP(tm.stop(s));
+          LSSVM_HIP(launch_cg_residual(product_of(w.x), NP, g.N, w.rhs, w.r, w.bp1, w.bp2, s));
+        }
+        if (refresh || b + 1 == nq) {
+          LSSVM_HIP(launch_cg_direction(w.bp1, nb, w.scal, par, k, w.r, dir, NP, w.hist, g.NP + 1,
+                                        refresh ? k / kReplaceEvery : 0,
+                                        trusted || refresh || k == max_iter, w.bp2, w.x, w.xbest,
+                                        s));
+          pending = false;
+        }
+        continue;
+      }
       LSSVM_TRY(timed_matvec<T>(g, w, kp, kernel, w.dir, s, tm, k));
       LSSVM_HIP(launch_cg_gather(rank_one(g, w, kernel, C, w.dir), g.NP, g.N, w.qv, w.bp0, s));
       if (refresh) {
@@ -779,7 +898,7 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
                                    g.NP, s));
       }
       LSSVM_HIP(launch_cg_direction(w.bp1, g.nb, w.scal, par, k, w.r, w.dir, g.NP, w.hist,
-                                    g.NP + 1, refresh ? k / kReplaceEvery : 0, w.bp2, w.x,
+                                    g.NP + 1, refresh ? k / kReplaceEvery : 0, 1, w.bp2, w.x,
                                     w.xbest, s));
     }
     LSSVM_HIP(hipMemcpyAsync(st, w.scal + S_STATUS, ST_COUNT * sizeof(double),
@@ -837,7 +956,7 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
   }
   if (stalled) {
     // the iterate of the smallest recomputed residual, whose r^T r the status reported
-    LSSVM_HIP(hipMemcpyAsync(w.x, w.xbest, g.NP * sizeof(double), hipMemcpyDeviceToDevice, s));
+    LSSVM_HIP(hipMemcpyAsync(w.x, w.xbest, NP * sizeof(double), hipMemcpyDeviceToDevice, s));
     status = LSSVM_NOT_CONVERGED;
     fail(LSSVM_NOT_CONVERGED,
          "CG stalled after %lld iterations: no new minimum of the true residual or the energy "
@@ -874,9 +993,10 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
   if (info && info->compute_true_residual) {
     double tr = 0.0;
     if (delta0 > 0.0) {
-      LSSVM_TRY(matvec_partials<T>(g, w, kp, kernel, w.x, s));
-      LSSVM_HIP(launch_true_residual(rank_one(g, w, kernel, C, w.x), g.NP, g.N, w.rhs, w.bp1, s));
-      LSSVM_HIP(launch_finish_sum(w.bp1, g.nb, w.scal, S_TRUE, s));
+      if (passes) LSSVM_TRY(lin.product(w.x, false));
+      else LSSVM_TRY(matvec_partials<T>(g, w, kp, kernel, w.x, s));
+      LSSVM_HIP(launch_true_residual(product_of(w.x), NP, g.N, w.rhs, w.bp1, s));
+      LSSVM_HIP(launch_finish_sum(w.bp1, nb, w.scal, S_TRUE, s));
       LSSVM_HIP(hipMemcpyAsync(g_ctx->p, w.scal + S_TRUE, sizeof(double), hipMemcpyDeviceToHost,
                                s));
       LSSVM_HIP(hipStreamSynchronize(s));
@@ -918,6 +1038,21 @@ int matvec_impl(const T* X, int64_t n, int64_t d, int32_t kernel, const lssvm_pa
   LSSVM_TRY(check_workspace(workspace, ws_bytes, w.bytes));
   w = carve_train<T>(g, workspace);
   LSSVM_HIP(g_ctx->ensure());
+  if (linear_passes(g, kernel)) {   // out stays untouched if X is not finite: one wait, at the end
+    const LinearPasses<T> lin(g, w, X, C, s);
+    LSSVM_HIP(launch_setup_clear(0, LSSVM_TILE_GROUP, 0, nullptr, w.flags, w.scal, nullptr, 0,
+                                 nullptr, s));
+    LSSVM_HIP(launch_lin_q<T>(X, g.n, g.d, w.q64, w.scal, w.flags, s));
+    LSSVM_HIP(launch_pad_to_f64<T>(p, g.N, w.dir, g.N, nullptr, s));
+    LSSVM_HIP(lin.weights(lin.vec(w.dir, false)));
+    LSSVM_HIP(launch_lin_out<T>(X, g.N, g.d, w.lin_w, lin.rank_one(w.dir, nullptr), out, w.flags,
+                                s));
+    LSSVM_HIP(hipMemcpyAsync(g_ctx->flags, w.flags, F_COUNT * sizeof(int), hipMemcpyDeviceToHost,
+                             s));
+    LSSVM_HIP(hipStreamSynchronize(s));
+    if (g_ctx->flags[F_NONFINITE]) return fail(LSSVM_ENONFINITE, "X holds a NaN or an infinity");
+    return LSSVM_OK;
+  }
   LSSVM_TRY(setup_points<T>(g, w, X, kernel, kp, s));
   LSSVM_HIP(launch_pad_to_f64<T>(p, g.N, w.dir, g.NP, w.scal, s));
   LSSVM_TRY(matvec_partials<T>(g, w, kp, kernel, w.dir, s));

@@ -21,6 +21,7 @@
 #include <algorithm>
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 namespace lssvm {
 
@@ -151,8 +152,10 @@ __device__ inline double fixed_take(int64_t* acc, int64_t i, double inv_scale) {
   return ((double)H2 * 4294967296.0 + (double)L2) * inv_scale;
 }
 
-// (K p)_i of a finished product, or NaN once any of its row sums was not finite.
+// (K p)_i of a finished product: as k_lin_rows left it, or from the tiles'
+// row sums, NaN once any of its row sums was not finite.
 __device__ inline double product_row(const RankOne& c, int64_t i, double inv_scale, bool bad) {
+  if (c.kp) return c.kp[i];
   const double t = fixed_take(c.acc, i, inv_scale);
   return bad ? __builtin_nan("") : t;
 }
@@ -577,7 +580,8 @@ __global__ __launch_bounds__(256) void k_true_residual(RankOne c, int64_t NP, in
 
 // beta = r^T r (new) / r^T r (old); d = r + beta d (beta = 0 if the old
 // r^T r is 0, an exact solution). Block 0 records the iteration in the
-// status (and the history) and raises done once r^T r <= eps^2 r0^T r0.
+// status (and the history) and raises done once r^T r <= eps^2 r0^T r0 (with
+// `test` clear only on r = 0).
 //
 // At the refresh-th residual recomputation (refresh > 0) r is a true
 // residual. Unless it met eps, CG has progressed if r^T r or the energy
@@ -591,7 +595,7 @@ __global__ __launch_bounds__(256) void k_cg_direction(const double* __restrict__
                                                       double* scal, int par, int64_t iter,
                                                       const double* __restrict__ r, double* dir,
                                                       int64_t NP, double* hist, int64_t hist_cap,
-                                                      int64_t refresh,
+                                                      int64_t refresh, int test,
                                                       const double* __restrict__ bp_phi,
                                                       const double* __restrict__ x,
                                                       double* __restrict__ xbest) {
@@ -600,7 +604,7 @@ __global__ __launch_bounds__(256) void k_cg_direction(const double* __restrict__
   if (st[ST_DONE] != 0.0) return;
   const double dnew = sum_partials(bp_in, nb, sh);
   const double dold = scal[S_DHIST + par];
-  const bool conv = dnew <= st[ST_STOP];
+  const bool conv = dnew <= (test ? st[ST_STOP] : 0.0);
   bool stall = false;
   double dbest = dnew;
   if (refresh > 0 && !conv) {   // uniform over the grid: every block sums the same partials
@@ -751,70 +755,350 @@ __global__ void k_single_point(const T* __restrict__ y, T* __restrict__ alpha_ou
   }
 }
 
-// --------------------------------------------- a7 linear-kernel shortcut ----
-// For the linear kernel Phi is the identity, so w = sum_i alpha_i x_i (Eq. (15))
-// and f(x) = <w, x> + b: O((n + n_test) d) instead of a tile contraction.
-// Partial sums of w over chunks of kLinRows points (coalesced over features),
-// then a fixed-order sum of the chunks.
-constexpr int kLinRows = 64;
-constexpr int64_t kLinMaxChunks = 32768;   // stays inside the 65535 grid limit in y
-inline int64_t lin_rows(int64_t n) {
-  const int64_t r = (n + kLinMaxChunks - 1) / kLinMaxChunks;
-  return r > kLinRows ? r : kLinRows;
-}
+// ----------------------------------------- linear kernel: through w = X^T p ----
+// For the linear kernel Phi is the identity, so K p = X (X^T p) and a decision
+// value is <X^T alpha, x> + b (Eq. (15)): two passes over the points, O(n d),
+// in place of the O(n^2 d) contraction, on the rows as the caller stores them.
+// fp64 throughout (fp32 products and sums are not rounded before the result).
+//
+// k_lin_w: w = X^T p by chunks of rows. A workgroup takes 64 VEC columns of
+// `rows` rows; a wave reads one row's 64 VEC values per load, its four waves
+// every fourth row, and a thread sums its VEC columns. The four waves' sums
+// are added in order and written as the chunk's partial w; k_lin_w_sum adds the
+// chunks in order. Bound by the read of X (from the Infinity Cache where it
+// fits). P says what p is:
+//   P_VEC    a vector (fp64), S and T of the rank-one terms left per chunk;
+//   P_DIR    the new CG direction r + beta d, formed here (what
+//            k_cg_direction does, which saves its launch), written to dir_out;
+//   P_ALPHA  model coefficients (T); X is checked for non-finite values.
+enum LinP : int { P_VEC = 0, P_DIR = 1, P_ALPHA = 2 };
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_linear_w_part(const T* __restrict__ X,
-                                                       const T* __restrict__ alpha, int64_t n,
-                                                       int64_t d, int64_t rows,
-                                                       double* __restrict__ part,
-                                                       int* __restrict__ flags) {
-  const int64_t k = (int64_t)blockIdx.x * NT + threadIdx.x;
-  const int64_t i0 = (int64_t)blockIdx.y * rows;
-  if (k >= d) return;
-  double acc = 0.0;
-  bool bad = false;
-  const int64_t i1 = i0 + rows < n ? i0 + rows : n;
-  for (int64_t i = i0; i < i1; ++i) {
-    const T xv = X[i * d + k];
-    bad |= !__builtin_isfinite(xv);
-    acc += (double)alpha[i] * (double)xv;
+// Sums of the linear passes carry their rounding errors along (an unevaluated
+// pair hi + lo: the exact error of a product by fma, of an addition by Knuth's
+// two-sum), so K p is rounded once, at the end. Memory-bound either way.
+struct Pair {
+  double hi, lo;
+};
+__device__ inline void pair_add(Pair& s, double v) {
+  const double t = s.hi + v, z = t - s.hi;
+  s.lo += (s.hi - (t - z)) + (v - z);
+  s.hi = t;
+}
+__device__ inline void pair_fma(Pair& s, double a, double b) {   // s += a b
+  const double p = a * b;
+  s.lo += __builtin_fma(a, b, -p);
+  pair_add(s, p);
+}
+__device__ inline void pair_join(Pair& s, const Pair& v) {
+  pair_add(s, v.hi);
+  s.lo += v.lo;
+}
+// Sums of four pairs over a wave, reduce-scattered: the lanes of 16-lane row r
+// end with the total of a[r]. Lane bits 5 and 4 halve the pairs a lane carries
+// (permlane swaps), DPP moves sum the 16 lanes that are left.
+__device__ inline Pair pair_swap_join(const Pair& a, const Pair& b, bool by32) {
+  const uint64_t ah = as_u64(a.hi), al = as_u64(a.lo), bh = as_u64(b.hi), bl = as_u64(b.lo);
+  auto swap = [&](uint64_t x, uint64_t y, double& first, double& second) {
+    const auto lo = by32 ? __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false)
+                         : __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+    const auto hi = by32 ? __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32),
+                                                            (uint32_t)(y >> 32), false, false)
+                         : __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32),
+                                                            (uint32_t)(y >> 32), false, false);
+    first = as_f64(lo[0], hi[0]);
+    second = as_f64(lo[1], hi[1]);
+  };
+  Pair s, o;
+  swap(ah, bh, s.hi, o.hi);
+  swap(al, bl, s.lo, o.lo);
+  pair_join(s, o);
+  return s;
+}
+template <int CTRL>
+__device__ inline void pair_dpp_join(Pair& s) {
+  const Pair o{dpp_move<CTRL>(s.hi), dpp_move<CTRL>(s.lo)};
+  pair_join(s, o);
+}
+__device__ inline Pair pair_wave_sum4(const Pair (&a)[4]) {
+  Pair s = pair_swap_join(pair_swap_join(a[0], a[2], true), pair_swap_join(a[1], a[3], true), false);
+  pair_dpp_join<kDppRowHalfMirror>(s);
+  pair_dpp_join<kDppQuadXor1>(s);
+  pair_dpp_join<kDppQuadXor2>(s);
+  pair_dpp_join<kDppRowRor8>(s);
+  return s;
+}
+constexpr int kLinTile = 256;   // rows of p staged at a time
+
+template <typename T, int VEC>
+__device__ inline void load_vec(const T* __restrict__ x, int64_t k, int64_t d, T (&v)[VEC]) {
+  if constexpr (VEC == 1) {
+    v[0] = k < d ? x[k] : T(0);
+  } else {
+    typedef T vec_t __attribute__((ext_vector_type(VEC)));
+    vec_t t;
+    if (k < d) {   // d is a multiple of VEC
+      t = *reinterpret_cast<const vec_t*>(x + k);
+    } else {
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) t[e] = T(0);
+    }
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) v[e] = t[e];
   }
-  part[(int64_t)blockIdx.y * d + k] = acc;
-  if (bad) flags[F_NONFINITE] = 1;
 }
 
-__global__ __launch_bounds__(256) void k_linear_w_sum(const double* __restrict__ part,
-                                                      int64_t nchunks, int64_t d,
-                                                      double* __restrict__ w) {
-  const int64_t k = (int64_t)blockIdx.x * NT + threadIdx.x;
-  if (k >= d) return;
-  double s = 0.0;
-  for (int64_t c = 0; c < nchunks; ++c) s += part[c * d + k];
-  w[k] = s;
-}
-
-// One block per test point: f = <w, x> (fp64) into a workspace vector; the
-// bias, the scores and the labels follow in k_predict_finish once every
-// point has been checked.
-template <typename T>
-__global__ __launch_bounds__(256) void k_linear_scores(const T* __restrict__ Xte, int64_t d,
-                                                       const double* __restrict__ w,
-                                                       double* __restrict__ f,
-                                                       int* __restrict__ flags) {
+template <typename T, int VEC, int P>
+__global__ __launch_bounds__(256) void k_lin_w(const T* __restrict__ X, int64_t N, int64_t d,
+                                               int64_t rows, LinVec v, const T* __restrict__ alpha,
+                                               const double* __restrict__ q64,
+                                               Pair* __restrict__ part, double* __restrict__ pq,
+                                               int* __restrict__ flags) {
   __shared__ double sh[NT / 64];
-  const int64_t t = blockIdx.x;
-  const T* x = Xte + t * d;
-  double acc = 0.0;
-  bool bad = false;
-  for (int64_t k = threadIdx.x; k < d; k += NT) {
-    const T xv = x[k];
-    bad |= !__builtin_isfinite(xv);
-    acc += (double)xv * w[k];
+  __shared__ double ps[kLinTile];
+  __shared__ Pair red[NT / 64][64 * VEC];
+  const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t k = ((int64_t)blockIdx.x * 64 + lane) * VEC;
+  const int64_t i0 = (int64_t)blockIdx.y * rows, i1 = i0 + rows < N ? i0 + rows : N;
+  // the first rows are on their way while beta is summed
+  constexpr int U = 8;   // rows in flight per wave
+  T x[U][VEC];
+  auto load_rows = [&](int64_t r0, int cnt, int r) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (r + u * (NT / 64) < cnt)   // uniform over the wave
+        load_vec<T, VEC>(X + (r0 + r + u * (NT / 64)) * d, k, d, x[u]);
+  };
+  auto tile_rows = [&](int64_t r0) { return (int)(i1 - r0 < kLinTile ? i1 - r0 : kLinTile); };
+  load_rows(i0, tile_rows(i0), wave);
+  double beta = 0.0;
+  if constexpr (P != P_ALPHA) {
+    if (v.stop && v.scal[S_STATUS + ST_DONE] != 0.0) return;
   }
-  if (bad) flags[F_NONFINITE] = 1;
-  const double v = block_sum(acc, sh);
-  if (threadIdx.x == 0) f[t] = v;
+  if constexpr (P == P_DIR) {
+    double* st = v.scal + S_STATUS;
+    const double dnew = sum_partials(v.bp, v.nb, sh);
+    const double dold = v.scal[S_DHIST + v.par];
+    const bool conv = dnew <= (v.test ? st[ST_STOP] : 0.0);   // uniform over the grid
+    if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) {
+      v.scal[S_DHIST + (v.par ^ 1)] = dnew;
+      st[ST_DELTA] = dnew;
+      st[ST_CURV] = v.scal[S_GAMMA];
+      st[ST_STEP] = v.scal[S_ALPHA];
+      st[ST_ITER] = (double)v.iter;
+      if (v.iter <= v.hist_cap) v.hist[v.iter - 1] = dnew;
+      if (conv) st[ST_DONE] = 1.0;
+    }
+    if (conv) return;
+    beta = dold != 0.0 ? dnew / dold : 0.0;
+  }
+  Pair acc[VEC];
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) acc[e] = Pair{0.0, 0.0};
+  double sp = 0.0, sq = 0.0;
+  bool bad = false;
+  for (int64_t r0 = i0; r0 < i1; r0 += kLinTile) {
+    const int cnt = tile_rows(r0);
+    double pi = 0.0;
+    if (tid < cnt) {
+      const int64_t i = r0 + tid;
+      if constexpr (P == P_ALPHA) {
+        pi = (double)alpha[i];
+      } else if constexpr (P == P_DIR) {
+        pi = v.r[i] + beta * v.p[i];
+        if (blockIdx.x == 0) v.dir_out[i] = pi;
+      } else {
+        pi = v.p[i];
+      }
+      if (P != P_ALPHA && blockIdx.x == 0) {
+        sp += pi;
+        sq += q64[i] * pi;
+      }
+    }
+    if (r0 != i0) __syncthreads();   // the previous tile's readers are done
+    ps[tid] = pi;
+    __syncthreads();
+    for (int r = wave; r < cnt; r += U * (NT / 64)) {
+      if (r0 != i0 || r != wave) load_rows(r0, cnt, r);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (r + u * (NT / 64) >= cnt) continue;   // uniform over the wave
+        const double pr = ps[r + u * (NT / 64)];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+          pair_fma(acc[e], pr, (double)x[u][e]);
+          if (P == P_ALPHA) bad |= !__builtin_isfinite(x[u][e]);
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) red[wave][lane * VEC + e] = acc[e];
+  __syncthreads();
+  for (int c = tid; c < 64 * VEC; c += NT) {
+    const int64_t col = (int64_t)blockIdx.x * 64 * VEC + c;
+    Pair s = red[0][c];
+#pragma unroll
+    for (int w = 1; w < NT / 64; ++w) pair_join(s, red[w][c]);
+    if (col < d) part[(int64_t)blockIdx.y * d + col] = s;
+  }
+  if (P == P_ALPHA) {
+    if (bad) flags[F_NONFINITE] = 1;
+  } else if (blockIdx.x == 0) {
+    sp = block_sum(sp, sh);
+    sq = block_sum(sq, sh);
+    if (tid == 0) {
+      pq[blockIdx.y] = sp;
+      pq[gridDim.y + blockIdx.y] = sq;
+    }
+  }
+}
+
+// 64 columns per workgroup; wave v adds chunks v, v + 4, ... (eight loads in
+// flight), then the four sums are added in order.
+__global__ __launch_bounds__(256) void k_lin_w_sum(const Pair* __restrict__ part,
+                                                   int64_t nchunks, int64_t d,
+                                                   double* __restrict__ w) {
+  __shared__ Pair sh[NT / 64][64];
+  const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+  const int64_t k = (int64_t)blockIdx.x * 64 + lane;
+  Pair s{0.0, 0.0};
+  if (k < d) {
+#pragma unroll 8
+    for (int64_t c = wave; c < nchunks; c += NT / 64) pair_join(s, part[c * d + k]);
+  }
+  sh[wave][lane] = s;
+  __syncthreads();
+  if (wave == 0 && k < d) {
+#pragma unroll
+    for (int v = 1; v < NT / 64; ++v) pair_join(s, sh[v][lane]);
+    w[k] = s.hi;
+    w[d + k] = s.lo;
+  }
+}
+
+// k_lin_rows: f_i = <x_i, w> for the rows of X, four rows at a time so that a
+// piece of w serves four rows: a wave takes them alone (CS = 1), or the
+// workgroup's four waves take a quarter of the columns each (CS = 4: long rows
+// of few points). M says where f goes:
+//   R_Q       w is the pivot's row (T): q_i, k(x_m, x_m); checks X for
+//             non-finite values
+//   R_KP      (K p)_i into out
+//   R_GATHER  (Q~ p)_i into out and the block partials of p^T Q~ p
+//             (k_cg_gather on the spot)
+//   R_OUT     (Q~ p)_i as T, nothing if the flags report a non-finite point
+//   R_SCORE   f_i into out; checks X for non-finite values
+enum LinM : int { R_Q = 0, R_KP = 1, R_GATHER = 2, R_OUT = 3, R_SCORE = 4 };
+constexpr int kLinRows = 4;
+
+template <typename T, int VEC, int CS, int M>
+__global__ __launch_bounds__(256) void k_lin_rows(const T* __restrict__ X, int64_t nrows, int64_t d,
+                                                  const double* __restrict__ w, int64_t m,
+                                                  RankOne c, double* __restrict__ out,
+                                                  T* __restrict__ outT, double* __restrict__ bp,
+                                                  int* __restrict__ flags) {
+  using W = typename std::conditional<M == R_Q, T, double>::type;
+  __shared__ double sh[NT / 64];
+  __shared__ Pair red[CS][kLinRows];
+  // What the end needs from memory is read first and waited for after the rows.
+  double stop = 0.0, pS = 0.0, pT = 0.0, qmm = 0.0;
+  if (M == R_GATHER) stop = c.scal[S_STATUS + ST_DONE];
+  if (M == R_OUT) stop = (double)flags[F_NONFINITE];
+  if constexpr (M == R_GATHER || M == R_OUT) {
+    for (int64_t t = threadIdx.x; t < c.nT; t += NT) {
+      pS += c.pq[t];
+      pT += c.pq[c.nT + t];
+    }
+    qmm = c.scal[S_KMM] + c.invC;
+  }
+  const W* wv;
+  if constexpr (M == R_Q) wv = X + m * d;
+  else wv = w;
+  RankOneSums ro{};
+  bool summed = false;
+  const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int GROUPS = CS == 1 ? NT / 64 : 1;   // row groups per workgroup and step
+  const int64_t ngroups = (nrows + kLinRows - 1) / kLinRows;
+  double prod = 0.0;
+  bool bad = false;
+  for (int64_t g0 = (int64_t)blockIdx.x * GROUPS; g0 < ngroups; g0 += (int64_t)gridDim.x * GROUPS) {
+    const int64_t g = g0 + (CS == 1 ? wave : 0), i0 = g * kLinRows;
+    Pair acc[kLinRows];
+    const T* x[kLinRows];
+#pragma unroll
+    for (int r = 0; r < kLinRows; ++r) {
+      acc[r] = Pair{0.0, 0.0};
+      const int64_t i = i0 + r;
+      x[r] = X + (i < nrows ? i : nrows - 1) * d;   // a repeated last row is not written
+    }
+    if (CS > 1 || g < ngroups) {
+#pragma unroll 2
+      for (int64_t k = (int64_t)((CS == 1 ? 0 : wave * 64) + lane) * VEC; k < d;
+           k += 64 * VEC * CS) {
+        W wk[VEC], wl[VEC];
+        load_vec<W, VEC>(wv, k, d, wk);
+        if constexpr (M != R_Q) load_vec<W, VEC>(wv + d, k, d, wl);
+        T xv[kLinRows][VEC];
+#pragma unroll
+        for (int r = 0; r < kLinRows; ++r) load_vec<T, VEC>(x[r], k, d, xv[r]);
+#pragma unroll
+        for (int r = 0; r < kLinRows; ++r)
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) {
+            pair_fma(acc[r], (double)xv[r][e], (double)wk[e]);
+            if constexpr (M != R_Q) acc[r].lo += (double)xv[r][e] * wl[e];
+            if (M == R_Q || M == R_SCORE) bad |= !__builtin_isfinite(xv[r][e]);
+          }
+      }
+    }
+    Pair own = pair_wave_sum4(acc);   // row i0 + lane / 16
+    const int orow = lane >> 4;
+    const bool finish = (lane & 15) == 0;
+    if constexpr (CS > 1) {
+      __syncthreads();   // the previous step's readers are done
+      if (finish) red[wave][orow] = own;
+      __syncthreads();
+    }
+    if constexpr (M == R_GATHER || M == R_OUT) {
+      if (!summed) {   // uniform
+        if (stop != 0.0) return;
+        ro.S = block_sum(pS, sh);
+        ro.Tq = block_sum(pT, sh);
+        ro.qmm = qmm;
+        summed = true;
+      }
+    }
+    // one lane per row, of the group's (first) wave, finishes it
+    if (finish && (CS == 1 || wave == 0)) {
+      const int64_t i = i0 + orow;
+      if constexpr (CS > 1) {
+        own = red[0][orow];
+#pragma unroll
+        for (int v = 1; v < CS; ++v) pair_join(own, red[v][orow]);
+      }
+      const double f = own.hi + own.lo;
+      if (i < nrows) {
+        if constexpr (M == R_Q) {
+          if (i == m) c.scal[S_KMM] = f;
+          else out[i] = f;
+        } else if constexpr (M == R_KP || M == R_SCORE) {
+          out[i] = f;
+        } else {
+          const double q = qtilde_row(c, ro, i, f);
+          if constexpr (M == R_GATHER) {
+            out[i] = q;
+            prod += c.p[i] * q;
+          } else {
+            outT[i] = (T)q;
+          }
+        }
+      }
+    }
+  }
+  if ((M == R_Q || M == R_SCORE) && bad) flags[F_NONFINITE] = 1;
+  if constexpr (M == R_GATHER) {
+    const double t = block_sum(prod, sh);
+    if (tid == 0) bp[blockIdx.x] = t;
+  }
 }
 
 // ------------------------------------------------------------ tile order ----
@@ -1281,11 +1565,12 @@ hipError_t launch_true_residual(const RankOne& c, int64_t NP, int64_t N, const d
 
 hipError_t launch_cg_direction(const double* bp_in, int64_t nb, double* scal, int par,
                                int64_t iter, const double* r, double* dir, int64_t NP,
-                               double* hist, int64_t hist_cap, int64_t refresh,
+                               double* hist, int64_t hist_cap, int64_t refresh, int test,
                                const double* bp_phi, const double* x, double* xbest,
                                hipStream_t s) {
   hipLaunchKernelGGL(k_cg_direction, dim3((unsigned)cg_blocks(NP)), dim3(NT), 0, s, bp_in, nb,
-                     scal, par, iter, r, dir, NP, hist, hist_cap, refresh, bp_phi, x, xbest);
+                     scal, par, iter, r, dir, NP, hist, hist_cap, refresh, test, bp_phi, x,
+                     xbest);
   return hipGetLastError();
 }
 
@@ -1306,7 +1591,7 @@ hipError_t launch_cg_step(int64_t N, double* x, double* r, double* d, const doub
   hipLaunchKernelGGL(k_cg_update, dim3((unsigned)nb), dim3(NT), 0, s, 0, bp0, nb, scal, 0, d, q,
                      x, r, bp1, N);
   hipLaunchKernelGGL(k_cg_direction, dim3((unsigned)nb), dim3(NT), 0, s, bp1, nb, scal, 0,
-                     (int64_t)1, r, d, N, (double*)nullptr, (int64_t)0, (int64_t)0,
+                     (int64_t)1, r, d, N, (double*)nullptr, (int64_t)0, (int64_t)0, 1,
                      (const double*)nullptr, (const double*)nullptr, (double*)nullptr);
   hipLaunchKernelGGL(k_step_end, dim3(1), dim3(64), 0, s, scal, scalars);
   return hipGetLastError();
@@ -1362,23 +1647,139 @@ hipError_t launch_finish_sum(const double* bpart, int64_t nb, double* scal, int 
   return hipGetLastError();
 }
 
+// Launch shape of k_lin_w for N rows of d columns: about 512 workgroups (two
+// per CU) of at least 32 rows each.
+static int64_t lin_chunks_wanted(int64_t N, int64_t d, int vec) {
+  const int64_t ncb = (d + 64 * vec - 1) / (64 * vec);
+  return std::max<int64_t>(1, std::min<int64_t>((512 + ncb - 1) / ncb, N / 32));
+}
+LinShape lin_shape(int64_t N, int64_t d, int vec) {
+  LinShape s;
+  s.ncb = (d + 64 * vec - 1) / (64 * vec);
+  const int64_t want = lin_chunks_wanted(N, d, vec);
+  s.rows = (N + want - 1) / want;
+  s.nch = (N + s.rows - 1) / s.rows;
+  return s;
+}
+template <typename T>
+int lin_vec(const T* X, int64_t d) {
+  constexpr int V = 16 / (int)sizeof(T);
+  return d % V == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0 ? V : 1;
+}
+// At least nch of lin_shape for N and any fewer rows: wider columns mean fewer
+// column blocks, so more chunks.
+int64_t lin_max_chunks(int64_t N, int64_t d) { return lin_chunks_wanted(N, d, 4); }
+
+template <typename T, int VEC>
+static hipError_t lin_w(LinP P, const T* X, int64_t N, int64_t d, const LinVec& v, const T* alpha,
+                        const double* q64, double* part2, double* w, double* pq, int* flags,
+                        hipStream_t s) {
+  const LinShape g = lin_shape(N, d, VEC);
+  Pair* part = reinterpret_cast<Pair*>(part2);
+  // grid.y holds the chunks (at most 512), grid.x the column blocks
+  const dim3 grid((unsigned)g.ncb, (unsigned)g.nch);
+  switch (P) {
+    case P_VEC:
+      hipLaunchKernelGGL((k_lin_w<T, VEC, P_VEC>), grid, dim3(NT), 0, s, X, N, d, g.rows, v, alpha,
+                         q64, part, pq, flags);
+      break;
+    case P_DIR:
+      hipLaunchKernelGGL((k_lin_w<T, VEC, P_DIR>), grid, dim3(NT), 0, s, X, N, d, g.rows, v, alpha,
+                         q64, part, pq, flags);
+      break;
+    default:
+      hipLaunchKernelGGL((k_lin_w<T, VEC, P_ALPHA>), grid, dim3(NT), 0, s, X, N, d, g.rows, v,
+                         alpha, q64, part, pq, flags);
+      break;
+  }
+  hipLaunchKernelGGL(k_lin_w_sum, dim3((unsigned)((d + 63) / 64)), dim3(NT), 0, s, part, g.nch, d,
+                     w);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_lin_w(const T* X, int64_t N, int64_t d, const LinVec& v, const double* q64,
+                        double* part, double* w, double* pq, hipStream_t s) {
+  const LinP P = v.dir_out ? P_DIR : P_VEC;
+  constexpr int V = 16 / (int)sizeof(T);
+  if (lin_vec(X, d) == V)
+    return lin_w<T, V>(P, X, N, d, v, nullptr, q64, part, w, pq, nullptr, s);
+  return lin_w<T, 1>(P, X, N, d, v, nullptr, q64, part, w, pq, nullptr, s);
+}
+
+// Workgroups of k_lin_rows: a wave per four rows, or, where that leaves fewer
+// than two workgroups per CU and a row keeps four waves busy, a workgroup per
+// four rows.
+constexpr int64_t kLinLongRow = 512;
+static bool lin_col_split(int64_t nrows, int64_t d, int vec) {
+  return nrows < 16 * 512 && d >= kLinLongRow * vec;
+}
+static int64_t lin_row_blocks(int64_t nrows, bool split) {
+  const int64_t groups = (nrows + kLinRows - 1) / kLinRows;
+  return std::min<int64_t>(kVecBlocks, split ? groups : (groups + NT / 64 - 1) / (NT / 64));
+}
+template <typename T>
+int64_t lin_gather_blocks(const T* X, int64_t N, int64_t d) {
+  return lin_row_blocks(N, lin_col_split(N, d, lin_vec(X, d)));
+}
+
+template <typename T, int M>
+static hipError_t lin_rows(const T* X, int64_t nrows, int64_t d, const double* w, int64_t m,
+                           const RankOne& c, double* out, T* outT, double* bp, int* flags,
+                           hipStream_t s) {
+  constexpr int V = 16 / (int)sizeof(T);
+  const int vec = lin_vec(X, d);
+  const bool split = lin_col_split(nrows, d, vec);
+  const dim3 grid((unsigned)lin_row_blocks(nrows, split));
+  if (vec == V && split)
+    hipLaunchKernelGGL((k_lin_rows<T, V, 4, M>), grid, dim3(NT), 0, s, X, nrows, d, w, m, c, out,
+                       outT, bp, flags);
+  else if (vec == V)
+    hipLaunchKernelGGL((k_lin_rows<T, V, 1, M>), grid, dim3(NT), 0, s, X, nrows, d, w, m, c, out,
+                       outT, bp, flags);
+  else if (split)
+    hipLaunchKernelGGL((k_lin_rows<T, 1, 4, M>), grid, dim3(NT), 0, s, X, nrows, d, w, m, c, out,
+                       outT, bp, flags);
+  else
+    hipLaunchKernelGGL((k_lin_rows<T, 1, 1, M>), grid, dim3(NT), 0, s, X, nrows, d, w, m, c, out,
+                       outT, bp, flags);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_lin_q(const T* X, int64_t n, int64_t d, double* q64, double* scal, int* flags,
+                        hipStream_t s) {
+  RankOne c{};
+  c.scal = scal;
+  return lin_rows<T, R_Q>(X, n, d, nullptr, n - 1, c, q64, nullptr, nullptr, flags, s);
+}
+template <typename T>
+hipError_t launch_lin_kp(const T* X, int64_t N, int64_t d, const double* w, double* kp,
+                         hipStream_t s) {
+  return lin_rows<T, R_KP>(X, N, d, w, 0, RankOne{}, kp, nullptr, nullptr, nullptr, s);
+}
+template <typename T>
+hipError_t launch_lin_gather(const T* X, int64_t N, int64_t d, const double* w, const RankOne& c,
+                             double* qv, double* bp, hipStream_t s) {
+  return lin_rows<T, R_GATHER>(X, N, d, w, 0, c, qv, nullptr, bp, nullptr, s);
+}
+template <typename T>
+hipError_t launch_lin_out(const T* X, int64_t N, int64_t d, const double* w, const RankOne& c,
+                          T* out, int* flags, hipStream_t s) {
+  return lin_rows<T, R_OUT>(X, N, d, w, 0, c, nullptr, out, nullptr, flags, s);
+}
+
 template <typename T>
 hipError_t launch_linear_predict(const T* Xtr, const T* alpha, int64_t n, int64_t d, const T* Xte,
                                  int64_t n_test, double b, double* part, double* w, double* f,
                                  T* scores, int32_t* labels, int* flags, hipStream_t s) {
-  const int64_t rows = lin_rows(n);
-  const int64_t nchunks = (n + rows - 1) / rows;
-  const unsigned gx = (unsigned)((d + NT - 1) / NT);
-  hipLaunchKernelGGL(k_linear_w_part<T>, dim3(gx, (unsigned)nchunks), dim3(NT), 0, s, Xtr, alpha,
-                     n, d, rows, part, flags);
-  hipError_t e = hipGetLastError();
+  constexpr int V = 16 / (int)sizeof(T);
+  hipError_t e =
+      lin_vec(Xtr, d) == V
+          ? lin_w<T, V>(P_ALPHA, Xtr, n, d, LinVec{}, alpha, nullptr, part, w, nullptr, flags, s)
+          : lin_w<T, 1>(P_ALPHA, Xtr, n, d, LinVec{}, alpha, nullptr, part, w, nullptr, flags, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_linear_w_sum, dim3(gx), dim3(NT), 0, s, part, nchunks, d, w);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_linear_scores<T>, dim3((unsigned)n_test), dim3(NT), 0, s, Xte, d, w, f,
-                     flags);
-  e = hipGetLastError();
+  e = lin_rows<T, R_SCORE>(Xte, n_test, d, w, -1, RankOne{}, f, nullptr, nullptr, flags, s);
   if (e != hipSuccess) return e;
   return launch_predict_finish<T>(f, 1, n_test, n_test, b, scores, labels, flags, s);
 }
@@ -1421,11 +1822,6 @@ hipError_t static_scratch(double** ptr, int64_t* capacity) {
   return hipSuccess;
 }
 
-int64_t linear_predict_part_elems(int64_t n, int64_t d) {
-  const int64_t rows = lin_rows(n);
-  return (n + rows - 1) / rows * d;
-}
-
 #define LSSVM_INSTANTIATE(T)                                                                      \
   template hipError_t launch_norms_q<T>(const store_t<T>*, int64_t, int64_t, int64_t, int64_t,    \
                                         int, double, double, int, T*, double*, double*,           \
@@ -1445,6 +1841,18 @@ int64_t linear_predict_part_elems(int64_t n, int64_t d) {
                                                T*, int32_t*, const int*, hipStream_t);            \
   template hipError_t launch_pad_to_f64<T>(const T*, int64_t, double*, int64_t, double*,          \
                                            hipStream_t);                                          \
+  template hipError_t launch_lin_w<T>(const T*, int64_t, int64_t, const LinVec&, const double*,   \
+                                      double*, double*, double*, hipStream_t);                    \
+  template hipError_t launch_lin_q<T>(const T*, int64_t, int64_t, double*, double*, int*,         \
+                                      hipStream_t);                                               \
+  template hipError_t launch_lin_kp<T>(const T*, int64_t, int64_t, const double*, double*,        \
+                                       hipStream_t);                                              \
+  template hipError_t launch_lin_gather<T>(const T*, int64_t, int64_t, const double*,             \
+                                           const RankOne&, double*, double*, hipStream_t);        \
+  template hipError_t launch_lin_out<T>(const T*, int64_t, int64_t, const double*,                \
+                                        const RankOne&, T*, int*, hipStream_t);                   \
+  template int lin_vec<T>(const T*, int64_t);                                                     \
+  template int64_t lin_gather_blocks<T>(const T*, int64_t, int64_t);                              \
   template hipError_t launch_linear_predict<T>(const T*, const T*, int64_t, int64_t, const T*,    \
                                                int64_t, double, double*, double*, double*, T*,    \
                                                int32_t*, int*, hipStream_t);

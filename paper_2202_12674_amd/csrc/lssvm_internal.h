@@ -88,6 +88,29 @@ struct RankOne {
   double* scal;        // k(x_m, x_m) at S_KMM, the product's scale at S_FIXSC
   const int* flags;    // F_PRODUCT
   double invC;
+  const double* kp;    // (K p)_i itself (linear products), or null: from acc
+};
+
+// The vector a linear product multiplies: p, or, with dir_out, the new CG
+// direction r + beta p, which is written to dir_out. beta and the status come
+// from the last update's block partials (bp, nb) as in k_cg_direction, whose
+// iteration `iter` (r^T r before it in S_DHIST + par) this ends.
+struct LinVec {
+  const double* p;
+  const double* r;
+  double* dir_out;
+  const double* bp;
+  int64_t nb;
+  double* scal;
+  int par, stop;      // stop: return at once when CG has stopped
+  int test;           // test r^T r against the stop threshold
+  int64_t iter;
+  double* hist;
+  int64_t hist_cap;
+};
+// Launch shape of w = X^T p: column blocks, row chunks, rows per chunk.
+struct LinShape {
+  int64_t ncb, nch, rows;
 };
 
 // One fused CG iteration for small problems (see launch_tiles_cg): the
@@ -180,7 +203,7 @@ hipError_t launch_cg_step(int64_t N, double* x, double* r, double* d, const doub
 // minimum).
 hipError_t launch_cg_direction(const double* bp_in, int64_t nb, double* scal, int par,
                                int64_t iter, const double* r, double* dir, int64_t NP,
-                               double* hist, int64_t hist_cap, int64_t refresh,
+                               double* hist, int64_t hist_cap, int64_t refresh, int test,
                                const double* bp_phi, const double* x, double* xbest,
                                hipStream_t s);
 template <typename T>
@@ -210,13 +233,35 @@ hipError_t launch_true_residual(const RankOne& c, int64_t NP, int64_t N, const d
                                 double* bp_out, hipStream_t s);
 
 // Linear-kernel decision values through w = sum_i alpha_i x_i (Eq. (15)).
-// part: linear_predict_part_elems(n, d) doubles; w: d doubles; f: n_test
+// part: lin_max_chunks(n, d) d doubles; w: d doubles; f: n_test
 // doubles (the inner products before the bias).
 template <typename T>
 hipError_t launch_linear_predict(const T* Xtr, const T* alpha, int64_t n, int64_t d, const T* Xte,
                                  int64_t n_test, double b, double* part, double* w, double* f,
                                  T* scores, int32_t* labels, int* flags, hipStream_t s);
-int64_t linear_predict_part_elems(int64_t n, int64_t d);
+// Linear products (two passes over the caller's rows): q_i and k(x_m, x_m) with
+// the finite check; w = X^T p (part: lin_max_chunks(N, d) d doubles, pq: S and T
+// per chunk); then (K p)_i, (Q~ p)_i with the partials of p^T Q~ p
+// (lin_gather_blocks of them), or (Q~ p)_i as T.
+int64_t lin_max_chunks(int64_t N, int64_t d);
+LinShape lin_shape(int64_t N, int64_t d, int vec);
+template <typename T> int lin_vec(const T* X, int64_t d);
+template <typename T> int64_t lin_gather_blocks(const T* X, int64_t N, int64_t d);
+template <typename T>
+hipError_t launch_lin_q(const T* X, int64_t n, int64_t d, double* q64, double* scal, int* flags,
+                        hipStream_t s);
+template <typename T>
+hipError_t launch_lin_w(const T* X, int64_t N, int64_t d, const LinVec& v, const double* q64,
+                        double* part, double* w, double* pq, hipStream_t s);
+template <typename T>
+hipError_t launch_lin_kp(const T* X, int64_t N, int64_t d, const double* w, double* kp,
+                         hipStream_t s);
+template <typename T>
+hipError_t launch_lin_gather(const T* X, int64_t N, int64_t d, const double* w, const RankOne& c,
+                             double* qv, double* bp, hipStream_t s);
+template <typename T>
+hipError_t launch_lin_out(const T* X, int64_t N, int64_t d, const double* w, const RankOne& c,
+                          T* out, int* flags, hipStream_t s);
 
 // The device array that lssvm_cg_step_noalloc works in, for the current
 // device: its address (resolved once per device) and its size in doubles.
