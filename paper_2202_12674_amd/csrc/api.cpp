@@ -69,11 +69,11 @@ bool log_enabled() {
   return on;
 }
 constexpr int64_t kReplaceEvery = 50;  // residual recomputed every 50th iteration
-// The products of the linear passes are so nearly exact that the CG recurrence
+// The products of linear trainings are so nearly exact that the CG recurrence
 // goes on falling below the residual that fp64 iterates can have (4096 x 1024,
 // eps 1e-13: 7.7e-14 at iteration 161 against a true 1.3e-12). So for an eps
-// below this, a linear training of such products converges on recomputed
-// residuals only (every 50th iteration, and the last one allowed).
+// below this, a linear training of passes (or whole, in one workgroup)
+// converges on recomputed residuals only (every 50th iteration, and the last one allowed).
 constexpr double kTrustedEps = 1e-12;
 
 inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
@@ -707,6 +707,142 @@ int timed_matvec(const Geometry& g, const TrainWs<T>& w, const lssvm_params& kp,
 }
 
 
+// How CG ended, for the report.
+struct CgEnd {
+  int64_t it = 0, extra_products = 0, n_timed = 0;
+  bool converged = false, broke = false, stalled = false;
+  double delta0 = 0.0, delta = 0.0, t_setup = 0.0, t_cg = 0.0, t_matvec = 0.0;
+  int status = LSSVM_OK;
+  double rel() const { return delta0 > 0.0 ? std::sqrt(delta / delta0) : 0.0; }
+};
+
+void fill_info(const CgEnd& e, lssvm_info* info, double t_total) {
+  if (!info) return;
+  info->iterations = e.it;
+  info->stop_reason = e.broke     ? LSSVM_STOP_BREAKDOWN
+                      : e.stalled ? LSSVM_STOP_STALL
+                      : e.converged ? LSSVM_STOP_EPS
+                                    : LSSVM_STOP_MAX_ITER;
+  info->rel_residual = e.rel();
+  // products: one per iteration plus each completed residual recomputation
+  // (a breakdown stops before its iteration's recomputation)
+  info->n_matvec = e.it + (e.broke ? e.it - 1 : e.it) / kReplaceEvery + e.extra_products;
+  info->t_matvec_ms = e.t_matvec;
+  info->n_matvec_timed = e.n_timed;
+  info->t_setup_ms = e.t_setup;
+  info->t_cg_ms = e.t_cg;
+  info->t_total_ms = t_total;
+}
+
+// The end of CG: its message and status, the residual history. A breakdown
+// leaves the outputs untouched, and the report says how far CG got.
+template <typename T>
+int end_cg(const Geometry& g, const TrainWs<T>& w, CgEnd& e, int status, lssvm_info* info,
+           clock_t_::time_point t0, hipStream_t s) {
+  if (status < 0) {
+    fill_info(e, info, ms_since(t0));
+    return status;
+  }
+  if (e.stalled)
+    e.status = fail(LSSVM_NOT_CONVERGED,
+                    "CG stalled after %lld iterations: no new minimum of the true residual or the "
+                    "energy (best relative residual %g)", (long long)e.it, e.rel());
+  else if (!e.converged)
+    e.status = fail(LSSVM_NOT_CONVERGED, "CG stopped after %lld iterations at relative residual %g",
+                    (long long)e.it, e.rel());
+  if (info && info->residual_history && e.it > 0) {
+    const int64_t nh = std::min(std::min(e.it, info->history_capacity), g.NP + 1);
+    if (nh > 0) {
+      LSSVM_HIP(hipMemcpyAsync(info->residual_history, w.hist, nh * sizeof(double),
+                               hipMemcpyDeviceToHost, s));
+      LSSVM_HIP(hipStreamSynchronize(s));
+      for (int64_t k = 0; k < nh; ++k) info->residual_history[k] /= e.delta0;
+    }
+  }
+  return LSSVM_OK;
+}
+
+// The report of a finished training (the optional true-residual product, which
+// follows, is not training).
+void end_report(const Geometry& g, const CgEnd& e, lssvm_info* info, clock_t_::time_point t0) {
+  const double t_total = ms_since(t0);
+  if (log_enabled())
+    std::fprintf(stderr,
+                 "[lssvm] train n=%lld d=%lld: %lld iterations, relative residual %.3e, "
+                 "setup %.2f ms, cg %.2f ms, total %.2f ms\n",
+                 (long long)g.n, (long long)g.d, (long long)e.it, e.rel(), e.t_setup, e.t_cg,
+                 t_total);
+  fill_info(e, info, t_total);
+}
+
+// info->true_rel_residual from a finished product of x.
+template <typename T>
+int true_residual(const Geometry& g, const TrainWs<T>& w, const RankOne& c, int64_t NP,
+                  double delta0, lssvm_info* info, hipStream_t s) {
+  double tr = 0.0;
+  if (delta0 > 0.0) {
+    LSSVM_HIP(launch_true_residual(c, NP, g.N, w.rhs, w.bp1, s));
+    LSSVM_HIP(launch_finish_sum(w.bp1, cg_blocks(NP), w.scal, S_TRUE, s));
+    LSSVM_HIP(hipMemcpyAsync(g_ctx->p, w.scal + S_TRUE, sizeof(double), hipMemcpyDeviceToHost, s));
+    LSSVM_HIP(hipStreamSynchronize(s));
+    tr = std::sqrt(g_ctx->p[0] / delta0);
+  }
+  info->true_rel_residual = tr;
+  return LSSVM_OK;
+}
+
+// A whole linear training in one launch and one read-back (k_lin_train).
+template <typename T>
+int train_small_linear(const Geometry& g, const TrainWs<T>& w, const T* X, const T* y, double C,
+                       double eps, int64_t max_iter, T* alpha_out, double* b_out, lssvm_info* info,
+                       clock_t_::time_point t0, hipStream_t s) {
+  LinTrain a{};
+  a.invC = 1.0 / C;
+  a.eps2 = eps * eps;
+  a.max_iter = max_iter > 0 ? max_iter : g.N;
+  a.replace_every = kReplaceEvery;
+  a.trusted = eps >= kTrustedEps;
+  a.x = w.x;
+  a.rhs = w.rhs;
+  a.q64 = w.q64;
+  a.scal = w.scal;
+  a.hist = w.hist;
+  a.hist_cap = g.NP + 1;
+  a.flags = w.flags;
+  LSSVM_HIP(launch_lin_train<T>(X, y, g.n, g.d, a, alpha_out, s));
+  LSSVM_HIP(hipMemcpyAsync(g_ctx->p, w.scal, S_COUNT * sizeof(double), hipMemcpyDeviceToHost, s));
+  LSSVM_HIP(hipStreamSynchronize(s));
+  const double* p = g_ctx->p;
+  const double* st = p + S_STATUS;
+  const int inflags = (int)p[S_INFLAGS];
+  if (inflags & 1) return fail(LSSVM_ENONFINITE, "X holds a NaN or an infinity");
+  if (inflags & 2) return fail(LSSVM_EBADLABEL, "labels must be +1 or -1");
+  constexpr double kTicksPerMs = 1e5;   // the device's wall clock runs at 100 MHz
+  CgEnd e;
+  e.broke = st[ST_BREAK] != 0.0;
+  e.stalled = st[ST_STALL] != 0.0;
+  e.converged = st[ST_DONE] != 0.0 && !e.broke && !e.stalled;
+  e.it = (int64_t)st[ST_ITER] + (e.broke ? 1 : 0);   // the update of the next found the curvature
+  e.delta0 = p[S_DELTA0];
+  e.delta = st[ST_DELTA];
+  e.t_setup = p[S_TIMES] / kTicksPerMs;
+  e.t_cg = p[S_TIMES + 1] / kTicksPerMs;
+  const double b = p[S_B];
+  int status = LSSVM_OK;
+  if (e.broke)
+    status = fail(LSSVM_EBREAKDOWN, "CG breakdown at iteration %lld (d^T Q d = %g)",
+                  (long long)e.it, st[ST_CURV]);
+  LSSVM_TRY(end_cg<T>(g, w, e, status, info, t0, s));
+  *b_out = b;
+  end_report(g, e, info, t0);
+  if (info && info->compute_true_residual) {
+    const LinearPasses<T> lin(g, w, X, C, s);
+    if (e.delta0 > 0.0) LSSVM_TRY(lin.product(w.x, false));
+    LSSVM_TRY(true_residual<T>(g, w, lin.rank_one(w.x, w.qv), g.N, e.delta0, info, s));
+  }
+  return e.status;
+}
+
 template <typename T>
 int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
                const lssvm_params& kp, double C, double eps, int64_t max_iter, void* workspace,
@@ -747,6 +883,12 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
     }
     return LSSVM_OK;
   }
+
+  // A linear problem that fits one workgroup's LDS, from a zero start and with no
+  // product timed on its own.
+  if (kernel == LSSVM_LINEAR && lin_train_fits(n, d, sizeof(T)) &&
+      !(info && (info->warm_start || info->time_matvec)))
+    return train_small_linear<T>(g, w, X, y, C, eps, max_iter, alpha_out, b_out, info, t0, s);
 
   // ---- setup: a1, a2, a3 (one read-back for the input flags and r0^T r0)
   // Linear passes keep the points as they are and their vectors unpadded.
@@ -930,81 +1072,36 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
     it_prev = it;
     delta_prev = delta;
   }
-  const bool converged = done && !broke && !stalled;
-  // products: one per iteration plus each completed residual recomputation
-  // (a breakdown stops before its iteration's recomputation)
-  const int64_t nmv = it + (broke ? it - 1 : it) / kReplaceEvery + warm_products;
-  const double t_cg = ms_since(t1);
-  auto report = [&](double t_total) {
-    if (!info) return;
-    info->iterations = it;
-    info->stop_reason = broke     ? LSSVM_STOP_BREAKDOWN
-                        : stalled ? LSSVM_STOP_STALL
-                        : converged ? LSSVM_STOP_EPS
-                                    : LSSVM_STOP_MAX_ITER;
-    info->rel_residual = delta0 > 0.0 ? std::sqrt(delta / delta0) : 0.0;
-    info->n_matvec = nmv;
-    info->t_matvec_ms = tm.total_ms;
-    info->n_matvec_timed = tm.count;
-    info->t_setup_ms = t_setup;
-    info->t_cg_ms = t_cg;
-    info->t_total_ms = t_total;
-  };
-  if (status < 0) {   // breakdown: outputs untouched, the report says how far CG got
-    report(ms_since(t0));
-    return status;
-  }
-  if (stalled) {
-    // the iterate of the smallest recomputed residual, whose r^T r the status reported
+  CgEnd e;
+  e.it = it;
+  e.extra_products = warm_products;
+  e.converged = done && !broke && !stalled;
+  e.broke = broke;
+  e.stalled = stalled;
+  e.delta0 = delta0;
+  e.delta = delta;
+  e.t_setup = t_setup;
+  e.t_cg = ms_since(t1);
+  e.t_matvec = tm.total_ms;
+  e.n_timed = tm.count;
+  LSSVM_TRY(end_cg<T>(g, w, e, status, info, t0, s));
+  if (stalled)   // the iterate of the smallest recomputed residual, whose r^T r was reported
     LSSVM_HIP(hipMemcpyAsync(w.x, w.xbest, NP * sizeof(double), hipMemcpyDeviceToDevice, s));
-    status = LSSVM_NOT_CONVERGED;
-    fail(LSSVM_NOT_CONVERGED,
-         "CG stalled after %lld iterations: no new minimum of the true residual or the energy "
-         "(best relative residual %g)", (long long)it, std::sqrt(delta / delta0));
-  } else if (!converged) {
-    status = LSSVM_NOT_CONVERGED;
-    fail(LSSVM_NOT_CONVERGED, "CG stopped after %lld iterations at relative residual %g",
-         (long long)it, std::sqrt(delta / delta0));
-  }
-  if (info && info->residual_history && it > 0) {
-    const int64_t nh = std::min(std::min(it, info->history_capacity), g.NP + 1);
-    if (nh > 0) {
-      LSSVM_HIP(hipMemcpyAsync(info->residual_history, w.hist, nh * sizeof(double),
-                               hipMemcpyDeviceToHost, s));
-      LSSVM_HIP(hipStreamSynchronize(s));
-      for (int64_t k = 0; k < nh; ++k) info->residual_history[k] /= delta0;
-    }
-  }
 
   // ---- a6: alpha_m and b
   LSSVM_HIP(launch_bias<T>(w.x, w.q64, g.N, y, w.scal, 1.0 / C, alpha_out, s));
   LSSVM_HIP(hipMemcpyAsync(g_ctx->p, w.scal + S_B, sizeof(double), hipMemcpyDeviceToHost, s));
   LSSVM_HIP(hipStreamSynchronize(s));
   *b_out = g_ctx->p[0];
-
-  const double t_total = ms_since(t0);   // the optional true-residual product is not training
-  if (log_enabled())
-    std::fprintf(stderr,
-                 "[lssvm] train n=%lld d=%lld: %lld iterations, relative residual %.3e, "
-                 "setup %.2f ms, cg %.2f ms, total %.2f ms\n",
-                 (long long)n, (long long)d, (long long)it,
-                 delta0 > 0.0 ? std::sqrt(delta / delta0) : 0.0, t_setup, t_cg, t_total);
-  report(t_total);
+  end_report(g, e, info, t0);
   if (info && info->compute_true_residual) {
-    double tr = 0.0;
     if (delta0 > 0.0) {
       if (passes) LSSVM_TRY(lin.product(w.x, false));
       else LSSVM_TRY(matvec_partials<T>(g, w, kp, kernel, w.x, s));
-      LSSVM_HIP(launch_true_residual(product_of(w.x), NP, g.N, w.rhs, w.bp1, s));
-      LSSVM_HIP(launch_finish_sum(w.bp1, nb, w.scal, S_TRUE, s));
-      LSSVM_HIP(hipMemcpyAsync(g_ctx->p, w.scal + S_TRUE, sizeof(double), hipMemcpyDeviceToHost,
-                               s));
-      LSSVM_HIP(hipStreamSynchronize(s));
-      tr = std::sqrt(g_ctx->p[0] / delta0);
     }
-    info->true_rel_residual = tr;
+    LSSVM_TRY(true_residual<T>(g, w, product_of(w.x), NP, delta0, info, s));
   }
-  return status;
+  return e.status;
 }
 
 // Workspace of lssvm_cg_step: the scalar area and two block-partial arrays.

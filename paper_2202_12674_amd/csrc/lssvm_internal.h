@@ -47,7 +47,8 @@ enum Scalar : int {
   S_FIXSC = 22,
   S_INFLAGS = 23,   // the input flags as read after the right-hand side: 1 non-finite
                     // X, 2 a label other than +-1, 4 F_TINY (one read-back with S_DELTA0)
-  S_COUNT = 24
+  S_TIMES = 24,     // k_lin_train: wall clock ticks of its setup, and of the rest
+  S_COUNT = 26
 };
 enum StatusField : int { ST_DELTA = 0, ST_CURV = 1, ST_STEP = 2, ST_ITER = 3, ST_DONE = 4,
                          ST_BREAK = 5, ST_STOP = 6, ST_STALL = 7, ST_COUNT = 8 };
@@ -239,6 +240,23 @@ template <typename T>
 hipError_t launch_linear_predict(const T* Xtr, const T* alpha, int64_t n, int64_t d, const T* Xte,
                                  int64_t n_test, double b, double* part, double* w, double* f,
                                  T* scores, int32_t* labels, int* flags, hipStream_t s);
+// A whole linear training in one workgroup (k_lin_train): what it needs beside
+// the points, and where it leaves x, rhs, q and the scalars (the status fields,
+// S_KMM, S_DELTA0, S_B, S_INFLAGS, S_TIMES). alpha is written only if the inputs
+// passed and CG did not break down.
+struct LinTrain {
+  double invC, eps2;
+  int64_t max_iter, replace_every;
+  int trusted;   // converge on the recurrence too, not only at recomputations
+  double *x, *rhs, *q64, *scal, *hist;
+  int64_t hist_cap;
+  int* flags;
+};
+bool lin_train_fits(int64_t n, int64_t d, int64_t elem);
+template <typename T>
+hipError_t launch_lin_train(const T* X, const T* y, int64_t n, int64_t d, const LinTrain& a,
+                            T* alpha_out, hipStream_t s);
+
 // Linear products (two passes over the caller's rows): q_i and k(x_m, x_m) with
 // the finite check; w = X^T p (part: lin_max_chunks(N, d) d doubles, pq: S and T
 // per chunk); then (K p)_i, (Q~ p)_i with the partials of p^T Q~ p
