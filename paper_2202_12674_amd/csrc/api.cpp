@@ -118,12 +118,13 @@ inline bool fused_iteration(const Geometry& g, int32_t kernel) {
 // Linear products run in two passes over the points, w = X^T p and X w (k_lin_w,
 // k_lin_rows): O(n d) in place of the tiles' O(n^2 d). Measured per CG iteration,
 // fp64: 4096 x 1024 258 us with tiles and 30 us so, 20011 x 301 1840 and 38,
-// 600 x 3000 196 and 24. Below about 10^5 values the four launches of an
-// iteration (21 us) lose to a fused one: 1000 x 100 22.6 us against 20.6, 256 x
-// 64 21 against 11; at 300 x 732 they win, 23 against 101.
+// 600 x 3000 196 and 24. Only up to 1025 points of few features, where an
+// iteration on tiles is one launch of a block or two per workgroup, do the four
+// launches lose: 1000 x 100 22.4 us against 21.3, 1000 x 30 23.6 against 15.7;
+// at 600 x 200 they win, 20 against 38, at 300 x 400 20 against 61.
 inline bool linear_passes(const Geometry& g, int32_t kernel) {
-  constexpr int64_t kFusedValues = int64_t(1) << 17;
-  return kernel == LSSVM_LINEAR && !(fused_iteration(g, kernel) && g.n * g.d <= kFusedValues);
+  constexpr int64_t kFusedFeatures = 128;
+  return kernel == LSSVM_LINEAR && !(fused_iteration(g, kernel) && g.d <= kFusedFeatures);
 }
 
 inline int64_t tri_count(int64_t nT) { return nT * (nT + 1) / 2; }
@@ -309,6 +310,8 @@ struct PredictWs {
   T *ntr, *nte, *alpha;
   double* part;
   int* flags;
+  double* few_part;  // few test points: partial scores, and whether a workgroup met
+  int* few_bad;      // a value that is not finite
   double* lin_part;  // linear kernel: partial sums of w over point chunks
   double* lin_w;     // linear kernel: w = sum_i alpha_i x_i
   double* lin_f;     // linear kernel: <w, x> per test point
@@ -333,6 +336,11 @@ PredictWs<T> carve_predict(const Geometry& g, int64_t n_test, void* base) {
   w.lin_part = c.take<double>(2 * lin_max_chunks(g.n, g.d) * g.d);
   w.lin_w = c.take<double>(2 * g.d);
   w.lin_f = c.take<double>(n_test);
+  if (n_test <= kFewTests) {
+    const int64_t slots = predict_few_slots(g.n, n_test);
+    w.few_part = c.take<double>(slots * n_test);
+    w.few_bad = c.take<int>(slots);
+  }
   w.bytes = c.off;
   return w;
 }
@@ -1167,6 +1175,28 @@ int predict_impl(const T* Xtr, const T* alpha, double b, int64_t n, int64_t d, i
   LSSVM_TRY(check_workspace(workspace, ws_bytes, w.bytes));
   w = carve_predict<T>(g, n_test, workspace);
   LSSVM_HIP(g_ctx->ensure());
+  if (kernel != LSSVM_LINEAR && n_test <= kFewTests) {
+    PredictFew<T> a{};
+    a.Xtr = Xtr;
+    a.Xte = Xte;
+    a.alpha = alpha;
+    a.n = n;
+    a.n_test = n_test;
+    a.d = d;
+    a.gamma = (T)kp.gamma;
+    a.coef0 = (T)kp.coef0;
+    a.rbf_scale = rbf_scale<T>(kp.gamma);
+    a.degree = kp.degree;
+    a.part = w.few_part;
+    a.bad = w.few_bad;
+    LSSVM_HIP(launch_predict_few<T>(a, kernel, b, scores, labels, w.flags, s));
+    LSSVM_HIP(hipMemcpyAsync(g_ctx->flags, w.flags, F_COUNT * sizeof(int), hipMemcpyDeviceToHost,
+                             s));
+    LSSVM_HIP(hipStreamSynchronize(s));
+    if (g_ctx->flags[F_NONFINITE])
+      return fail(LSSVM_ENONFINITE, "X_train or X_test holds a NaN or an infinity");
+    return LSSVM_OK;
+  }
   LSSVM_HIP(hipMemsetAsync(w.flags, 0, F_COUNT * sizeof(int), s));
   if (kernel == LSSVM_LINEAR) {  // Eq. (15): w = sum_i alpha_i x_i, f(x) = <w, x> + b
     LSSVM_HIP(launch_linear_predict<T>(Xtr, alpha, n, d, Xte, n_test, b, w.lin_part, w.lin_w,

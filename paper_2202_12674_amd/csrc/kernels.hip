@@ -755,6 +755,214 @@ __global__ void k_single_point(const T* __restrict__ y, T* __restrict__ alpha_ou
   }
 }
 
+// ------------------------------------------ a7 for few points: k_predict_few ----
+// Decision values of up to 128 points (16 NB) on a polynomial or RBF model, from
+// the caller's rows: with one tile row of test points the tile path reads the
+// model once to lay it out, writes it, and reads it for the norms and for the
+// tiles. Here it is read once, straight into matrix-core operands (16 x 16 x 4,
+// in T: fp32 products and sums as fp32). Bound by that read up to about 64 points
+// (fp64) or 32 (fp32), by the matrix cores beyond. Measured, the whole call, tile
+// path before: 8192 x 512 fp64 cubic, 16 points 113 -> 41 us; 50000 x 2800 fp64
+// RBF, 5 points 1310 -> 269 us (4.2 TB/s); 11490 x 3521 fp64 RBF, 89 points 733
+// -> 693 us; 31219 x 2028 fp32 cubic, 76 points 281 -> 227 us; 25583 x 3000 fp32
+// cubic, 128 points 356 -> 338 us.
+//
+// A workgroup takes blocks of 16 RB model points; its four waves share the
+// features in chunks of 16 (wave v the chunks v, v + 4, ...), so that even a
+// small model keeps every CU loading. Lane l holds features 4 (l / 16) .. + 3 of
+// a chunk, of model point l % 16 and, from the cache, of test point l % 16 of
+// each block of 16. Squared norms (RBF) are summed on the way in fp64. The
+// waves' products are added in LDS in order, then 16 NB threads groups apply the
+// kernel function and sum alpha_i k over the block's points in fp64; a
+// workgroup's sums over its blocks are one partial per test point.
+template <typename T> struct Mfma16;
+template <> struct Mfma16<double> {
+  using acc_t = doublex4;
+  __device__ static inline acc_t mma(double a, double b, acc_t c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  __device__ static inline int row(int v, int lane) { return (lane >> 4) + 4 * v; }
+};
+template <> struct Mfma16<float> {
+  typedef float acc_t __attribute__((ext_vector_type(4)));
+  __device__ static inline acc_t mma(float a, float b, acc_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  __device__ static inline int row(int v, int lane) { return 4 * (lane >> 4) + v; }
+};
+
+// Features k .. k + 3 of a row, zero from d on; vec: 16-byte loads (d a multiple
+// of the loads' width, rows aligned).
+template <typename T>
+__device__ inline void load4(const T* __restrict__ x, int64_t k, int64_t d, int vec, T (&v)[4]) {
+  constexpr int W = 16 / (int)sizeof(T);
+  typedef T vec_t __attribute__((ext_vector_type(W)));
+  if (vec) {
+#pragma unroll
+    for (int h = 0; h < 4; h += W) {
+      vec_t t;
+      if (k + h < d) {
+        t = *reinterpret_cast<const vec_t*>(x + k + h);
+      } else {
+#pragma unroll
+        for (int e = 0; e < W; ++e) t[e] = T(0);
+      }
+#pragma unroll
+      for (int e = 0; e < W; ++e) v[h + e] = t[e];
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = k + e < d ? x[k + e] : T(0);
+  }
+}
+
+template <typename T, int KER, int RB, int NB>
+__global__ __launch_bounds__(256) void k_predict_few(PredictFew<T> a) {
+  using MF = Mfma16<T>;
+  constexpr int ROWS = 16 * RB, COLS = 16 * NB, GRP = NT / COLS;
+  constexpr int LDG = COLS + 1;
+  __shared__ T g[ROWS * LDG];
+  __shared__ double nrm[2][NT / 64][ROWS > COLS ? ROWS : COLS];
+  __shared__ double sums[GRP][COLS];
+  const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int cl = lane & 15, kl = lane >> 4;
+  const int64_t nblk = (a.n + ROWS - 1) / ROWS, nchk = (a.d + 15) / 16;
+  double total = 0.0;   // of this thread's test point and share of the rows
+  T finite = T(0);      // NaN once a value is not finite
+  for (int64_t b = blockIdx.x; b < nblk; b += gridDim.x) {
+    const T* xa[RB];
+    const T* xb[NB];
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+      const int64_t i = b * ROWS + r * 16 + cl;
+      xa[r] = a.Xtr + (i < a.n ? i : a.n - 1) * a.d;   // repeated rows get weight 0
+    }
+#pragma unroll
+    for (int c = 0; c < NB; ++c) {
+      const int64_t t = c * 16 + cl;
+      xb[c] = a.Xte + (t < a.n_test ? t : a.n_test - 1) * a.d;   // repeated: not written
+    }
+    typename MF::acc_t acc[RB][NB];
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+#pragma unroll
+      for (int c = 0; c < NB; ++c) acc[r][c] = typename MF::acc_t{};
+    double na[RB] = {}, nb[NB] = {};
+    for (int64_t ch = wave; ch < nchk; ch += NT / 64) {
+      const int64_t k = ch * 16 + 4 * kl;
+      T va[RB][4], vb[NB][4];
+#pragma unroll
+      for (int r = 0; r < RB; ++r) load4<T>(xa[r], k, a.d, a.vec, va[r]);
+#pragma unroll
+      for (int c = 0; c < NB; ++c) load4<T>(xb[c], k, a.d, a.vec, vb[c]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+          for (int c = 0; c < NB; ++c) acc[r][c] = MF::mma(va[r][e], vb[c][e], acc[r][c]);
+#pragma unroll
+      for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          finite += T(0) * va[r][e];
+          if constexpr (KER == KRBF) na[r] += (double)va[r][e] * (double)va[r][e];
+        }
+#pragma unroll
+      for (int c = 0; c < NB; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          finite += T(0) * vb[c][e];
+          if constexpr (KER == KRBF) nb[c] += (double)vb[c][e] * (double)vb[c][e];
+        }
+    }
+    if constexpr (KER == KRBF) {   // a point's four lanes, then the waves below
+      auto lanes = [&](double v) {
+        v += __shfl_xor(v, 16);
+        return v + __shfl_xor(v, 32);
+      };
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        const double v = lanes(na[r]);
+        if (kl == 0) nrm[0][wave][r * 16 + cl] = v;
+      }
+#pragma unroll
+      for (int c = 0; c < NB; ++c) {
+        const double v = lanes(nb[c]);
+        if (kl == 0) nrm[1][wave][c * 16 + cl] = v;
+      }
+    }
+    for (int w = 0; w < NT / 64; ++w) {
+      if (wave == w) {
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+          for (int c = 0; c < NB; ++c)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              T& s = g[(r * 16 + MF::row(v, lane)) * LDG + c * 16 + cl];
+              s = w == 0 ? acc[r][c][v] : s + acc[r][c][v];
+            }
+      }
+      __syncthreads();
+    }
+    const int c = tid % COLS, part = tid / COLS;
+    double nt = 0.0;
+    if constexpr (KER == KRBF)
+      nt = ((nrm[1][0][c] + nrm[1][1][c]) + nrm[1][2][c]) + nrm[1][3][c];
+#pragma unroll 4
+    for (int r = part; r < ROWS; r += GRP) {
+      const int64_t i = b * ROWS + r;
+      if (i >= a.n) continue;
+      double nr = 0.0;
+      if constexpr (KER == KRBF)
+        nr = ((nrm[0][0][r] + nrm[0][1][r]) + nrm[0][2][r]) + nrm[0][3][r];
+      T kv = kernel_value<KER, T>(g[r * LDG + c], (T)nt, (T)nr, a.gamma, a.coef0, a.rbf_scale);
+      if constexpr (KER == KPOLY) {
+        const T base = kv;
+        for (int e = 1; e < a.degree; ++e) kv *= base;
+      }
+      total += (double)kv * (double)a.alpha[i];
+    }
+    __syncthreads();   // g and nrm are free
+  }
+  sums[tid / COLS][tid % COLS] = total;
+  const int bad = __syncthreads_or(!(finite == T(0)));
+  if (tid < COLS && tid < a.n_test) {
+    double s = 0.0;
+#pragma unroll
+    for (int p = 0; p < GRP; ++p) s += sums[p][tid];
+    a.part[(int64_t)tid * gridDim.x + blockIdx.x] = s;
+  }
+  if (tid == 0) a.bad[blockIdx.x] = bad;
+}
+
+// One workgroup per test point: b + the sum of its nslots partials, and the
+// label, unless a workgroup met a value that is not finite (then only the flag).
+template <typename T>
+__global__ __launch_bounds__(256) void k_predict_few_end(const double* __restrict__ part,
+                                                         const int* __restrict__ bad,
+                                                         int64_t nslots, double b,
+                                                         T* __restrict__ scores,
+                                                         int32_t* __restrict__ labels,
+                                                         int* __restrict__ flags) {
+  __shared__ double sh[NT / 64];
+  double s = 0.0;
+  int any = 0;
+  for (int64_t k = threadIdx.x; k < nslots; k += NT) {
+    s += part[(int64_t)blockIdx.x * nslots + k];
+    any |= bad[k];
+  }
+  any = __syncthreads_or(any);
+  s = block_sum(s, sh);
+  if (threadIdx.x != 0) return;
+  if (blockIdx.x == 0) flags[F_NONFINITE] = any;
+  if (any) return;
+  const double f = b + s;
+  scores[blockIdx.x] = (T)f;
+  if (labels) labels[blockIdx.x] = f > 0.0 ? 1 : -1;
+}
+
 // ----------------------------------------- linear kernel: through w = X^T p ----
 // For the linear kernel Phi is the identity, so K p = X (X^T p) and a decision
 // value is <X^T alpha, x> + b (Eq. (15)): two passes over the points, O(n d),
@@ -1990,6 +2198,38 @@ hipError_t launch_lin_train(const T* X, const T* y, int64_t n, int64_t d, const 
   return hipGetLastError();
 }
 
+// Partials and bad flags of k_predict_few: at most kFewBlocks workgroups.
+constexpr int64_t kFewBlocks = 1024;
+int64_t predict_few_slots(int64_t n, int64_t n_test) {
+  const int64_t rows = n_test > 32 ? 32 : 16;
+  return std::min<int64_t>(kFewBlocks, (n + rows - 1) / rows);
+}
+template <typename T, int KER>
+static void predict_few(const PredictFew<T>& a, unsigned grid, hipStream_t s) {
+  if (a.n_test > 64)
+    hipLaunchKernelGGL((k_predict_few<T, KER, 2, 8>), dim3(grid), dim3(NT), 0, s, a);
+  else if (a.n_test > 32)
+    hipLaunchKernelGGL((k_predict_few<T, KER, 2, 4>), dim3(grid), dim3(NT), 0, s, a);
+  else if (a.n_test > 16)
+    hipLaunchKernelGGL((k_predict_few<T, KER, 1, 2>), dim3(grid), dim3(NT), 0, s, a);
+  else
+    hipLaunchKernelGGL((k_predict_few<T, KER, 1, 1>), dim3(grid), dim3(NT), 0, s, a);
+}
+template <typename T>
+hipError_t launch_predict_few(PredictFew<T> a, int kernel, double b, T* scores, int32_t* labels,
+                              int* flags, hipStream_t s) {
+  if (a.n_test > kFewTests || kernel == KLIN) return hipErrorInvalidValue;
+  constexpr int V = 16 / (int)sizeof(T);
+  a.vec = a.d % V == 0 && reinterpret_cast<uintptr_t>(a.Xtr) % 16 == 0 &&
+          reinterpret_cast<uintptr_t>(a.Xte) % 16 == 0;
+  const int64_t slots = predict_few_slots(a.n, a.n_test);
+  if (kernel == KPOLY) predict_few<T, KPOLY>(a, (unsigned)slots, s);
+  else predict_few<T, KRBF>(a, (unsigned)slots, s);
+  hipLaunchKernelGGL(k_predict_few_end<T>, dim3((unsigned)a.n_test), dim3(NT), 0, s, a.part, a.bad,
+                     slots, b, scores, labels, flags);
+  return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_linear_predict(const T* Xtr, const T* alpha, int64_t n, int64_t d, const T* Xte,
                                  int64_t n_test, double b, double* part, double* w, double* f,
@@ -2074,6 +2314,8 @@ hipError_t static_scratch(double** ptr, int64_t* capacity) {
                                         const RankOne&, T*, int*, hipStream_t);                   \
   template int lin_vec<T>(const T*, int64_t);                                                     \
   template int64_t lin_gather_blocks<T>(const T*, int64_t, int64_t);                              \
+  template hipError_t launch_predict_few<T>(PredictFew<T>, int, double, T*, int32_t*, int*,       \
+                                            hipStream_t);                                         \
   template hipError_t launch_lin_train<T>(const T*, const T*, int64_t, int64_t, const LinTrain&,  \
                                           T*, hipStream_t);                                       \
   template hipError_t launch_linear_predict<T>(const T*, const T*, int64_t, int64_t, const T*,    \

@@ -240,6 +240,25 @@ template <typename T>
 hipError_t launch_linear_predict(const T* Xtr, const T* alpha, int64_t n, int64_t d, const T* Xte,
                                  int64_t n_test, double b, double* part, double* w, double* f,
                                  T* scores, int32_t* labels, int* flags, hipStream_t s);
+// Decision values of at most kFewTests points on a polynomial or RBF model
+// (k_predict_few): part holds n_test predict_few_slots(n, n_test) doubles, bad
+// as many ints as slots.
+constexpr int64_t kFewTests = 128;
+template <typename T>
+struct PredictFew {
+  const T *Xtr, *Xte, *alpha;
+  int64_t n, n_test, d;
+  int vec;   // set by the launcher
+  T gamma, coef0, rbf_scale;
+  int degree;
+  double* part;
+  int* bad;
+};
+int64_t predict_few_slots(int64_t n, int64_t n_test);
+template <typename T>
+hipError_t launch_predict_few(PredictFew<T> a, int kernel, double b, T* scores, int32_t* labels,
+                              int* flags, hipStream_t s);
+
 // A whole linear training in one workgroup (k_lin_train): what it needs beside
 // the points, and where it leaves x, rhs, q and the scalars (the status fields,
 // S_KMM, S_DELTA0, S_B, S_INFLAGS, S_TIMES). alpha is written only if the inputs
