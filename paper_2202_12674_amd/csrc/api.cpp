@@ -99,6 +99,8 @@ struct Geometry {
   int64_t lin_tail_split;  // the launch's trailing workgroups, split this many ways
   int64_t tail_q;   // other kernels: tiles of the last partial round that are split (or 0)
   int64_t tail_split;  // ... over this many workgroups each
+  int64_t few_split;   // other kernels, few tiles: workgroups per tile (1: whole tiles)
+  int64_t few_blocks;  // ... and the staged blocks of each (even; the last has what is left)
 };
 
 #ifndef LSSVM_FUSED_SMALL
@@ -111,7 +113,7 @@ struct Geometry {
 // points the same fusion cost more than it saved: the release and ticket of
 // each of ~1000 workgroups made the launch ~50 us longer than the product.)
 inline bool fused_iteration(const Geometry& g, int32_t kernel) {
-  const bool one_launch = kernel == LSSVM_LINEAR ? g.lin_tail_q == 0 : g.tail_q == 0;
+  const bool one_launch = kernel != LSSVM_LINEAR || g.lin_tail_q == 0;
   return LSSVM_FUSED_SMALL && g.NP <= kFusedMaxNP && one_launch;
 }
 
@@ -211,6 +213,25 @@ inline void tail_plan(int64_t nT, int64_t nkb, int64_t* q, int64_t* split) {
   *split = *q > 0 ? S : 1;
 }
 
+// Few tiles (at most one per CU) of many features leave most of the chip idle:
+// their staged blocks are shared over S workgroups each, as many as one round
+// takes, of at least 4 blocks. (Shares need not divide the blocks evenly.) The
+// splits are parked and a second launch sums and finishes the tiles, which costs
+// about 12 us, so it has to save that: a staged block of 16 features takes a
+// workgroup alone on its CU about 1.8 us in fp64 and 0.5 us in fp32. Per CG
+// iteration, whole and split: FEW_US.
+inline void few_plan(int64_t W, int64_t nkb, double block_us, int64_t* split, int64_t* blocks) {
+  *split = 1;
+  *blocks = nkb;
+  if (W < 1 || W > 256) return;
+  const int64_t want = std::min<int64_t>(std::min<int64_t>(kResidentTiles / W, 64), nkb / 4);
+  if (want < 2) return;
+  const int64_t per = round_up((nkb + want - 1) / want, 2), S = (nkb + per - 1) / per;
+  if (S < 2 || (double)(nkb - per) * block_us < 12.0) return;
+  *split = S;
+  *blocks = per;
+}
+
 template <typename T>
 Geometry geometry(int64_t n, int64_t d) {
   Geometry g{};
@@ -229,8 +250,11 @@ Geometry geometry(int64_t n, int64_t d) {
   // An even number of staged blocks (two LDS stages), as many as planned where
   // a plan shares them out: in fp32, whose staged blocks are half a planned
   // one, that can be 32 features of padding more.
-  const bool shared = g.tail_q > 0 || g.NP <= kFusedMaxNP;
+  const int64_t W = tri_count(g.nT);
+  const bool shared = (g.tail_q > 0 && W > 256) || g.NP <= kFusedMaxNP;
   g.d_pad = shared ? g.plan_nkb * g.bk : round_up(d, 2 * TileShape<T>::SB);
+  few_plan(W, g.d_pad / TileShape<T>::SB, sizeof(T) == 8 ? 1.8 : 0.5, &g.few_split,
+           &g.few_blocks);
   return g;
 }
 
@@ -280,7 +304,8 @@ TrainWs<T> carve_train(const Geometry& g, void* base) {
   // Row sums: two 64-bit words per row, however many tiles add to them; the
   // split tail's parked inner products (at most a quarter round of tiles).
   w.acc = c.take<int64_t>(2 * g.NP);
-  w.gpart = c.take<T>(g.tail_q * g.tail_split * g.tile * g.tile);
+  w.gpart = c.take<T>(std::max(g.few_split > 1 ? tri_count(g.nT) * g.few_split : 0,
+                               g.tail_q * g.tail_split) * g.tile * g.tile);
   const int64_t chunks = lin_max_chunks(g.n, g.d);
   w.pq = c.take<double>(2 * std::max(g.nT, chunks));
   w.rhs = c.take<double>(g.NP);
@@ -539,6 +564,7 @@ TileArgs<T> sym_args(const Geometry& g, const TrainWs<T>& w, const lssvm_params&
   a.degree = kp.degree;
   a.nTc = g.nT;
   a.ksplit = product_split(g, kernel);
+  a.split_blocks = a.nkb / a.ksplit;
   a.order = LSSVM_TILE_GROUP > 0 ? w.order : nullptr;
   a.acc = w.acc;
   a.fx = w.scal + S_PMAX;      // [S_PMAX], [S_NMAX], [S_FIXSC]
@@ -546,21 +572,12 @@ TileArgs<T> sym_args(const Geometry& g, const TrainWs<T>& w, const lssvm_params&
   return a;
 }
 
-#ifndef LSSVM_DIAG_TAIL
-#define LSSVM_DIAG_TAIL 1
-#endif
-
 // The tile visit order, written into the workspace on the device (once per
-// call). The linear kernel's finer-split last round takes diagonal tiles
-// where there are enough: each of its T splits then adds into one panel of
-// row sums, where the last tiles of the grouped order share a few panels
-// (up to a super-tile's worth of tiles times T atomic additions per word).
-// The same launch zeroes the flags, the scalars and the row-sum words.
+// call); the same launch zeroes the flags, the scalars and the row-sum words.
 template <typename T>
-int clear_and_order(const Geometry& g, const TrainWs<T>& w, int32_t kernel, hipStream_t s) {
+int clear_and_order(const Geometry& g, const TrainWs<T>& w, hipStream_t s) {
   const bool ordered = LSSVM_TILE_GROUP > 0 && g.nT > 0;
-  const int64_t nd = (LSSVM_DIAG_TAIL && kernel == LSSVM_LINEAR) ? std::min(g.lin_tail_q, g.nT) : 0;
-  LSSVM_HIP(launch_setup_clear(g.nT, LSSVM_TILE_GROUP, nd, ordered ? w.order : nullptr, w.flags,
+  LSSVM_HIP(launch_setup_clear(g.nT, LSSVM_TILE_GROUP, ordered ? w.order : nullptr, w.flags,
                                w.scal, w.acc, 2 * g.NP, w.ticket, s));
   return LSSVM_OK;
 }
@@ -606,7 +623,7 @@ int rescale_points(const Geometry& g, TrainWs<T>& w, const T* X, hipStream_t s) 
 template <typename T>
 int setup_points(const Geometry& g, TrainWs<T>& w, const T* X, int32_t kernel,
                  const lssvm_params& kp, hipStream_t s, bool check = true) {
-  LSSVM_TRY(clear_and_order<T>(g, w, kernel, s));
+  LSSVM_TRY(clear_and_order<T>(g, w, s));
   LSSVM_HIP(launch_layout<T>(X, g.n, g.d, w.Xt, g.ld, g.d_pad, 1.f, w.flags, s));
   LSSVM_HIP(launch_norms_q<T>(w.Xt, g.ld, g.d_pad, g.N, g.N, kernel, kp.gamma, kp.coef0,
                               kp.degree, w.norms, w.q64, w.scal, s));
@@ -660,38 +677,38 @@ struct LinearPasses {
   }
 };
 
-// The tile launches of one product: all tiles whole (the linear kernel's
-// split tiles included), or the full rounds whole and the tail split, parked
-// and fixed up.
-// The one launch of a linear product: its workgroup count, with a's fields
-// for the finer-split last round set. Feature splits add up, so the last
-// round only splits finer, as the launch's trailing workgroups: they start
-// as the whole tiles finish, with no second launch to wait for.
+// The first of a product's split launches: parks the inner products of `tiles`
+// tiles from `first` on, split as a says.
 template <typename T>
-int64_t linear_launch(const Geometry& g, TileArgs<T>& a) {
-  const int64_t F = tri_count(g.nT) - g.lin_tail_q;
-  if (g.lin_tail_q == 0) return F * a.ksplit;
-  a.tail_slot = F * a.ksplit;
-  a.tail_split = g.lin_tail_split;
-  a.tail_tile = F;
-  return F * a.ksplit + g.lin_tail_q * g.lin_tail_split;
+hipError_t launch_parked(TileArgs<T>& a, int32_t kernel, int64_t first, int64_t tiles,
+                         int64_t split, int64_t blocks, T* gpart, hipStream_t s) {
+  a.tile_offset = first;
+  a.ksplit = split;
+  a.split_blocks = blocks;
+  a.gpart = gpart;
+  return launch_tiles_sym<T>(a, kernel, kPartial, tiles * split, s);
 }
 
+// The tile launches of one product: all tiles whole (the linear kernel's split
+// tiles included), or all split, parked and fixed up (few tiles), or the full
+// rounds whole and the tail split.
 template <typename T>
 hipError_t launch_product(const Geometry& g, TileArgs<T> a, int32_t kernel, T* gpart,
                           hipStream_t s) {
   const int64_t W = tri_count(g.nT);
-  if (kernel == LSSVM_LINEAR) return launch_tiles_sym<T>(a, kernel, kWhole, linear_launch(g, a), s);
-  if (g.tail_q == 0) return launch_tiles_sym<T>(a, kernel, kWhole, W, s);
-  const int64_t F = W - g.tail_q;
-  hipError_t e = launch_tiles_sym<T>(a, kernel, kWhole, F, s);
+  if (kernel == LSSVM_LINEAR) return launch_tiles_sym<T>(a, kernel, kWhole, W * a.ksplit, s);
+  const bool few = g.few_split > 1;
+  const int64_t split = few ? W : W > 256 ? g.tail_q : 0;   // tiles split
+  if (split < W) {
+    const hipError_t e = launch_tiles_sym<T>(a, kernel, kWhole, W - split, s);
+    if (e != hipSuccess || split == 0) return e;
+  }
+  const hipError_t e =
+      few ? launch_parked<T>(a, kernel, 0, W, g.few_split, g.few_blocks, gpart, s)
+          : launch_parked<T>(a, kernel, W - split, split, g.tail_split, a.nkb / g.tail_split,
+                             gpart, s);
   if (e != hipSuccess) return e;
-  a.tile_offset = F;
-  a.ksplit = g.tail_split;
-  a.gpart = gpart;
-  e = launch_tiles_sym<T>(a, kernel, kPartial, g.tail_q * g.tail_split, s);
-  if (e != hipSuccess) return e;
-  return launch_tiles_sym<T>(a, kernel, kFixup, g.tail_q, s);
+  return launch_tiles_sym<T>(a, kernel, kFixup, split, s);
 }
 
 // One implicit product K p into the partial-sum buffer (plus the per-panel
@@ -904,7 +921,7 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
   const int64_t NP = passes ? g.N : g.NP, nb = cg_blocks(NP);
   const LinearPasses<T> lin(g, w, X, C, s);
   if (passes) {
-    LSSVM_HIP(launch_setup_clear(0, LSSVM_TILE_GROUP, 0, nullptr, w.flags, w.scal, nullptr, 0,
+    LSSVM_HIP(launch_setup_clear(0, LSSVM_TILE_GROUP, nullptr, w.flags, w.scal, nullptr, 0,
                                  nullptr, s));
     LSSVM_HIP(launch_lin_q<T>(X, g.n, g.d, w.q64, w.scal, w.flags, s));
   } else {
@@ -993,8 +1010,12 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
         a.stop = w.scal + S_STATUS + ST_DONE;
         FusedCg f{w.ticket, rank_one(g, w, kernel, C, w.dir), w.qv, w.x, w.r, w.dir, w.scal,
                   w.hist, g.NP, g.N, k, g.NP + 1, par};
-        const int64_t nwg = kernel == LSSVM_LINEAR ? linear_launch(g, a) : tri_count(g.nT);
-        LSSVM_HIP(launch_tiles_cg<T>(a, kernel, nwg, f, s));
+        const int64_t W = tri_count(g.nT);
+        const bool split = kernel != LSSVM_LINEAR && g.few_split > 1;
+        if (split)
+          LSSVM_HIP(launch_parked<T>(a, kernel, 0, W, g.few_split, g.few_blocks, w.gpart, s));
+        LSSVM_HIP(launch_tiles_cg<T>(a, kernel, split ? kFixup : kWhole,
+                                     kernel == LSSVM_LINEAR ? W * a.ksplit : W, f, s));
         LSSVM_HIP(tm.stop(s));
         continue;
       }
@@ -1145,7 +1166,7 @@ int matvec_impl(const T* X, int64_t n, int64_t d, int32_t kernel, const lssvm_pa
   LSSVM_HIP(g_ctx->ensure());
   if (linear_passes(g, kernel)) {   // out stays untouched if X is not finite: one wait, at the end
     const LinearPasses<T> lin(g, w, X, C, s);
-    LSSVM_HIP(launch_setup_clear(0, LSSVM_TILE_GROUP, 0, nullptr, w.flags, w.scal, nullptr, 0,
+    LSSVM_HIP(launch_setup_clear(0, LSSVM_TILE_GROUP, nullptr, w.flags, w.scal, nullptr, 0,
                                  nullptr, s));
     LSSVM_HIP(launch_lin_q<T>(X, g.n, g.d, w.q64, w.scal, w.flags, s));
     LSSVM_HIP(launch_pad_to_f64<T>(p, g.N, w.dir, g.N, nullptr, s));

@@ -1534,12 +1534,9 @@ __device__ inline int64_t grouped_position(int64_t nT, int64_t G, int64_t i, int
 }
 
 // Thread t takes tile (i, j) of the column-major triangle and writes it,
-// packed (i << 16) | j, at its position. The last nd diagonal tiles
-// (i = j >= nT - nd) move to the end of the order, the others close up:
-// a split last round made of diagonal tiles adds into nd disjoint panels,
-// one tile each, instead of into the few panels the order ends on.
-// The same launch zeroes the flags, the scalars and the row-sum words.
-__global__ __launch_bounds__(256) void k_setup_clear(int64_t nT, int64_t G, int64_t nd,
+// packed (i << 16) | j, at its position. The same launch zeroes the flags, the
+// scalars and the row-sum words.
+__global__ __launch_bounds__(256) void k_setup_clear(int64_t nT, int64_t G,
                                                      uint32_t* __restrict__ order,
                                                      int* __restrict__ flags,
                                                      double* __restrict__ scal,
@@ -1555,21 +1552,7 @@ __global__ __launch_bounds__(256) void k_setup_clear(int64_t nT, int64_t G, int6
   for (int64_t t = t0; t < W; t += stride) {
     int64_t i, j;
     tri_index(t, i, j);
-    int64_t p;
-    if (i == j && i >= nT - nd) {
-      p = W - nd + (i - (nT - nd));
-    } else {
-      // the moved tiles that came before it: diagonal positions grow with k
-      p = grouped_position(nT, G, i, j);
-      int64_t lo = nT - nd, hi = nT;   // first k in [lo, hi) placed after p
-      while (lo < hi) {
-        const int64_t mid = (lo + hi) / 2;
-        if (grouped_position(nT, G, mid, mid) < p) lo = mid + 1;
-        else hi = mid;
-      }
-      p -= lo - (nT - nd);
-    }
-    order[p] = (uint32_t)((i << 16) | j);
+    order[grouped_position(nT, G, i, j)] = (uint32_t)((i << 16) | j);
   }
 }
 
@@ -1650,11 +1633,12 @@ __global__ __launch_bounds__(256) void k_finish_sum(const double* bpart, int64_t
 // fences its partial sums (device-scope release) before it takes a ticket;
 // the one that draws the last ticket fences again (acquire) and reads them
 // all. Rows r = tid + 256 k sit in registers (NP <= 1024 -> k < 4). ONE:
-// linear tiles split into single feature blocks (see tile_body).
-template <typename T, int KER, bool ONE>
+// linear tiles split into single feature blocks (see tile_body). PART: whole
+// tiles, or the fixup of tiles parked by a launch before.
+template <typename T, int KER, int PART, bool ONE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_tiles_cg(
     TileArgs<T> a, FusedCg f) {
-  if (!tile_body<T, true, KER, kWhole, ONE>(a)) return;   // CG had already stopped
+  if (!tile_body<T, true, KER, PART, ONE>(a)) return;   // CG had already stopped
   __shared__ int last;
   __shared__ double sh[NT / 64];
   // Every wave releases its own writes (row sums, rank-one partials) at agent
@@ -1794,14 +1778,14 @@ inline unsigned blocks_for(int64_t n) { return (unsigned)((n + NT - 1) / NT); }
 
 // ------------------------------------------------------------- launchers ----
 
-hipError_t launch_setup_clear(int64_t nT, int64_t group, int64_t diag_last, uint32_t* order,
+hipError_t launch_setup_clear(int64_t nT, int64_t group, uint32_t* order,
                               int* flags, double* scal, int64_t* acc, int64_t nacc,
                               unsigned* ticket, hipStream_t s) {
   const int64_t W = order ? nT * (nT + 1) / 2 : 0;
   const int64_t n = std::max<int64_t>(std::max<int64_t>(W, nacc), S_COUNT);
   const int64_t blocks = std::min<int64_t>((n + NT - 1) / NT, kVecBlocks);
   hipLaunchKernelGGL(k_setup_clear, dim3((unsigned)std::max<int64_t>(1, blocks)), dim3(NT), 0, s,
-                     nT, group, diag_last, order, flags, scal, acc, nacc, ticket);
+                     nT, group, order, flags, scal, acc, nacc, ticket);
   return hipGetLastError();
 }
 
@@ -1860,17 +1844,18 @@ hipError_t launch_norms_q(const store_t<T>* Xt, int64_t ld, int64_t d_pad, int64
 constexpr int64_t kMaxTileGrid = int64_t(1) << 23;
 
 // Feature blocks per workgroup: even (the two-stage loop runs them in pairs)
-// or exactly one (the single-block variant).
+// or exactly one (the single-block variant); every split holds some.
 template <typename T>
-inline bool blocks_ok(const TileArgs<T>& a, int64_t split) {
-  if (split < 1 || a.nkb % split != 0) return false;
-  const int64_t per = a.nkb / split;
-  return per % 2 == 0 || per == 1;
+inline bool blocks_ok(const TileArgs<T>& a) {
+  if (a.ksplit == 1) return true;
+  const int64_t per = a.split_blocks;
+  return a.ksplit > 1 && (per == 1 || (per > 0 && per % 2 == 0)) && per * a.ksplit >= a.nkb &&
+         per * (a.ksplit - 1) < a.nkb;
 }
 
 template <typename T, bool SYM, int PART>
 hipError_t launch_tiles(TileArgs<T> a, int kernel, int64_t nwg, hipStream_t s) {
-  if (SYM && PART != kFixup && !blocks_ok(a, a.ksplit)) return hipErrorInvalidValue;
+  if (SYM && !blocks_ok(a)) return hipErrorInvalidValue;
   a.ntiles = nwg;
   for (int64_t base = 0; base < nwg; base += kMaxTileGrid) {
     a.tile_base = base;
@@ -1911,27 +1896,34 @@ hipError_t launch_tiles_gen(const TileArgs<T>& a, int kernel, int64_t nTr, hipSt
 }
 
 template <typename T>
-hipError_t launch_tiles_cg(const TileArgs<T>& a0, int kernel, int64_t nwg, const FusedCg& f,
-                           hipStream_t s) {
+hipError_t launch_tiles_cg(const TileArgs<T>& a0, int kernel, int part, int64_t nwg,
+                           const FusedCg& f, hipStream_t s) {
   if (nwg > kMaxTileGrid) return hipErrorInvalidValue;   // small problems only: one chunk
   TileArgs<T> a = a0;
   a.ntiles = nwg;
   a.tile_base = 0;
-  const bool one = kernel == KLIN && a.nkb == a.ksplit;   // a single feature block each
-  if ((kernel != KLIN && a.ksplit != 1) || !blocks_ok(a, a.ksplit)) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)nwg);
+  const bool fixup = part == kFixup;
+  if ((kernel != KLIN && !fixup && a.ksplit != 1) || (kernel == KLIN && fixup) || !blocks_ok(a))
+    return hipErrorInvalidValue;
   switch (kernel) {
     case KLIN:
-      if (one)
-        hipLaunchKernelGGL((k_tiles_cg<T, KLIN, true>), dim3((unsigned)nwg), dim3(256), 0, s, a, f);
+      if (a.nkb == a.ksplit)   // a single feature block each
+        hipLaunchKernelGGL((k_tiles_cg<T, KLIN, kWhole, true>), grid, dim3(256), 0, s, a, f);
       else
-        hipLaunchKernelGGL((k_tiles_cg<T, KLIN, false>), dim3((unsigned)nwg), dim3(256), 0, s, a,
-                           f);
+        hipLaunchKernelGGL((k_tiles_cg<T, KLIN, kWhole, false>), grid, dim3(256), 0, s, a, f);
       break;
     case KPOLY:
-      hipLaunchKernelGGL((k_tiles_cg<T, KPOLY, false>), dim3((unsigned)nwg), dim3(256), 0, s, a, f);
+      if (fixup)
+        hipLaunchKernelGGL((k_tiles_cg<T, KPOLY, kFixup, false>), grid, dim3(256), 0, s, a, f);
+      else
+        hipLaunchKernelGGL((k_tiles_cg<T, KPOLY, kWhole, false>), grid, dim3(256), 0, s, a, f);
       break;
     default:
-      hipLaunchKernelGGL((k_tiles_cg<T, KRBF, false>), dim3((unsigned)nwg), dim3(256), 0, s, a, f);
+      if (fixup)
+        hipLaunchKernelGGL((k_tiles_cg<T, KRBF, kFixup, false>), grid, dim3(256), 0, s, a, f);
+      else
+        hipLaunchKernelGGL((k_tiles_cg<T, KRBF, kWhole, false>), grid, dim3(256), 0, s, a, f);
       break;
   }
   return hipGetLastError();
@@ -2289,7 +2281,7 @@ hipError_t static_scratch(double** ptr, int64_t* capacity) {
                                         hipStream_t);                                             \
   template hipError_t launch_tiles_sym<T>(const TileArgs<T>&, int, int, int64_t, hipStream_t);    \
   template hipError_t launch_tiles_gen<T>(const TileArgs<T>&, int, int64_t, hipStream_t);         \
-  template hipError_t launch_tiles_cg<T>(const TileArgs<T>&, int, int64_t, const FusedCg&,        \
+  template hipError_t launch_tiles_cg<T>(const TileArgs<T>&, int, int, int64_t, const FusedCg&,   \
                                          hipStream_t);                                            \
   template hipError_t launch_rhs_init<T>(const T*, int64_t, int64_t, double*, double*, double*,   \
                                          double*, double*, double*, int*, double*, hipStream_t);  \

@@ -134,7 +134,7 @@ constexpr int64_t kFusedMaxNP = 1024;
 // scalars (S_COUNT doubles), the row-sum words (nacc int64) and the fused
 // iteration's ticket (if given), and writes the tile visit order (order may
 // be null: then nothing but the zeroing).
-hipError_t launch_setup_clear(int64_t nT, int64_t group, int64_t diag_last, uint32_t* order,
+hipError_t launch_setup_clear(int64_t nT, int64_t group, uint32_t* order,
                               int* flags, double* scal, int64_t* acc, int64_t nacc,
                               unsigned* ticket, hipStream_t s);
 
@@ -156,16 +156,15 @@ hipError_t launch_tiles_sym(const TileArgs<T>& a, int kernel, int part, int64_t 
                             hipStream_t s);
 template <typename T>
 hipError_t launch_tiles_gen(const TileArgs<T>& a, int kernel, int64_t nTr, hipStream_t s);
-// A whole CG iteration in one launch for small problems (NP <= kFusedMaxNP,
-// a single whole-tile launch per
-// product): the symmetric tiles of q = Q~ d, then the workgroup that
-// finishes last (an atomic ticket after a device-scope release fence) adds the
+// A whole CG iteration for small problems (NP <= kFusedMaxNP) in one launch of
+// whole tiles, or in the fixup launch of split ones: the symmetric tiles of q =
+// Q~ d, then the workgroup that finishes last (an atomic ticket after a device-scope release fence) adds the
 // rank-one terms and does the update and the new direction, with the same
 // status, stop test and breakdown handling as the separate kernels. Nothing
 // waits on another workgroup.
 template <typename T>
-hipError_t launch_tiles_cg(const TileArgs<T>& a, int kernel, int64_t nwg, const FusedCg& f,
-                           hipStream_t s);
+hipError_t launch_tiles_cg(const TileArgs<T>& a, int kernel, int part, int64_t nwg,
+                           const FusedCg& f, hipStream_t s);
 // rhs = ybar - y_m 1, x = xbest = 0, r = dir = rhs, the block partials of
 // r^T r; raises scal[S_PMAX] to max |dir| (the first product multiplies it).
 template <typename T>

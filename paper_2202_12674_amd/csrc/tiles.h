@@ -354,28 +354,18 @@ __device__ __forceinline__ bool tile_body(const TileArgs<T>& a) {
   }
   int64_t I, J;
   // Symmetric tiles may have their features split over KS workgroups. For
-  // the linear kernel each split sums K p over its share into slots of its
-  // own (the sums add up because the kernel value is the inner product
-  // itself); otherwise the splits meet in the kFixup launch. Workgroup slot v
-  // takes split v % KS of tile v / KS of this launch, which starts at
-  // a.tile_offset of the visit order; a linear launch's trailing slots run
-  // its last round split finer (a.tail_slot).
-  int64_t KS = (SYM && (KER == KLIN || PART != kWhole)) ? a.ksplit : 1;
-  int64_t ks = 0, trel = 0, first = a.tile_offset;
+  // the linear kernel each split adds K p over its share to the row sums
+  // (they add up because the kernel value is the inner product itself);
+  // otherwise the splits meet in the kFixup launch. Workgroup slot v takes
+  // split v % KS of tile v / KS of this launch, which starts at a.tile_offset
+  // of the visit order.
+  const int64_t KS = (SYM && (KER == KLIN || PART != kWhole)) ? a.ksplit : 1;
+  int64_t ks = 0, trel = 0;
   const int64_t t = a.tile_base + (int64_t)blockIdx.x;   // this workgroup's slot
   if constexpr (SYM) {
-    int64_t v = t, G = a.ntiles;
-    if (KER == KLIN && PART == kWhole && a.tail_split > 0) {
-      if (t >= a.tail_slot) {
-        KS = a.tail_split;
-        first = a.tail_tile;
-        v = t - a.tail_slot;
-        G = 0;   // no XCD runs: each tail tile adds into a panel of its own
-      } else {
-        G = a.tail_slot;
-      }
-    }
-    if (a.order && PART != kFixup && G > 0) {
+    int64_t v = t;
+    const int64_t G = a.ntiles;
+    if (a.order && PART != kFixup) {
       // workgroup w runs on XCD w % 8 (chunks start at multiples of 8, so this
       // holds for the slot t too): give each XCD a contiguous run of the order
       const int64_t x = t % kNumXcd, per = G / kNumXcd, extra = G % kNumXcd;
@@ -386,7 +376,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs<T>& a) {
       trel = v / KS;
       ks = v - trel * KS;
     }
-    const int64_t tile = first + trel;
+    const int64_t tile = a.tile_offset + trel;
     if (a.order) {
       const uint32_t packed = a.order[tile];
       I = packed >> 16;
@@ -421,10 +411,11 @@ __device__ __forceinline__ bool tile_body(const TileArgs<T>& a) {
   }
 
   // panel I is a.nkb consecutive staged blocks of SLAB elements; this workgroup
-  // contracts blocks [ks nkb, (ks + 1) nkb) of it
-  const int64_t nkb = a.nkb / KS;
-  const ST* __restrict__ Ap = a.A + (I * a.nkb + ks * nkb) * SLAB;
-  const ST* __restrict__ Bp = a.B + (J * a.nkb + ks * nkb) * SLAB;
+  // contracts nkb of them from its split's first on
+  const int64_t kb0 = KS > 1 ? ks * a.split_blocks : 0;
+  const int64_t nkb = KS > 1 && a.nkb - kb0 > a.split_blocks ? a.split_blocks : a.nkb - kb0;
+  const ST* __restrict__ Ap = a.A + (I * a.nkb + kb0) * SLAB;
+  const ST* __restrict__ Bp = a.B + (J * a.nkb + kb0) * SLAB;
   constexpr int64_t block_bytes = (int64_t)SLAB * sizeof(ST);
 
   // Direct loads of block kb into a stage, memory -> LDS with no registers in
