@@ -99,8 +99,9 @@ struct Geometry {
   int64_t lin_tail_split;  // the launch's trailing workgroups, split this many ways
   int64_t tail_q;   // other kernels: tiles of the last partial round that are split (or 0)
   int64_t tail_split;  // ... over this many workgroups each
-  int64_t few_split;   // other kernels, few tiles: workgroups per tile (1: whole tiles)
-  int64_t few_blocks;  // ... and the staged blocks of each (even; the last has what is left)
+  int64_t part_q;      // other kernels: the tiles, the last of the visit order, that are split
+  int64_t part_split;  // ... over this many workgroups each
+  int64_t part_blocks; // ... of so many staged blocks (even; the last has what is left)
 };
 
 #ifndef LSSVM_FUSED_SMALL
@@ -132,7 +133,8 @@ inline bool linear_passes(const Geometry& g, int32_t kernel) {
 inline int64_t tri_count(int64_t nT) { return nT * (nT + 1) / 2; }
 
 // Workgroups resident at once in a tile launch: two per CU on 256 CUs.
-constexpr int64_t kResidentTiles = 512;
+constexpr int64_t kCUs = 256;
+constexpr int64_t kResidentTiles = 2 * kCUs;
 #ifndef LSSVM_LINEAR_SPLIT_MAX
 #define LSSVM_LINEAR_SPLIT_MAX 16
 #endif
@@ -213,23 +215,53 @@ inline void tail_plan(int64_t nT, int64_t nkb, int64_t* q, int64_t* split) {
   *split = *q > 0 ? S : 1;
 }
 
-// Few tiles (at most one per CU) of many features leave most of the chip idle:
-// their staged blocks are shared over S workgroups each, as many as one round
-// takes, of at least 4 blocks. (Shares need not divide the blocks evenly.) The
-// splits are parked and a second launch sums and finishes the tiles, which costs
-// about 12 us, so it has to save that: a staged block of 16 features takes a
-// workgroup alone on its CU about 1.8 us in fp64 and 0.5 us in fp32. Per CG
-// iteration, whole and split: FEW_US.
-inline void few_plan(int64_t W, int64_t nkb, double block_us, int64_t* split, int64_t* blocks) {
+// Shares of Q tiles over one round of workgroups: as many each as the round
+// takes, at most `most`, of at least 4 staged blocks (which the shares need not
+// divide evenly). 1 if the tiles are better left whole: the splits are parked and
+// one more launch sums and finishes the tiles, which costs `cost_us`, so it has to
+// save that. A staged block of 16 features takes a workgroup alone on its CU
+// about 1.8 us in fp64 and 0.5 us in fp32.
+inline int64_t share_tiles(int64_t Q, int64_t nkb, int64_t most, double block_us, double cost_us,
+                           int64_t* blocks) {
+  *blocks = nkb;
+  const int64_t want = std::min(std::min(kResidentTiles / Q, most), nkb / 4);
+  if (want < 2) return 1;
+  const int64_t per = round_up((nkb + want - 1) / want, 2), S = (nkb + per - 1) / per;
+  if (S < 2 || (double)(nkb - per) * block_us < cost_us) return 1;
+  *blocks = per;
+  return S;
+}
+
+// Which tiles of the polynomial and RBF kernels' products are split.
+// - Few tiles (at most one per CU) leave most of the chip idle: all of them.
+//   Trainings, whole and split: 502 x 2877 fp64 RBF 4.10 and 1.15 ms, 907 x 1100
+//   2.50 and 1.08, 300 x 4000 fp32 cubic 2.09 and 0.61, 1500 x 2000 fp32 RBF 1.48
+//   and 1.00.
+// - Tiles left after the last full round of two per CU: tail_plan.
+// - Otherwise those left after the last full round of one per CU, where they are
+//   at most two thirds of one, in fp64: the CUs that take one more tile than the
+//   others would run alone. A product: 5003 x 777 cubic (52 of 820 tiles) 0.407 and
+//   0.375 ms, 3000 x 1000 RBF (44 of 300) 0.260 and 0.212, 4500 x 1500 (154 of 666)
+//   0.586 and 0.560. The same in fp32, whose tiles are shorter, changed nothing
+//   (3000 x 4000 0.260 and 0.262, 4358 x 1110 0.134 and 0.132).
+inline void part_plan(int64_t W, int64_t tail_q, int64_t tail_split, int64_t nkb, bool fp64,
+                      int64_t* q, int64_t* split, int64_t* blocks) {
+  const double block_us = fp64 ? 1.8 : 0.5;
+  *q = 0;
   *split = 1;
   *blocks = nkb;
-  if (W < 1 || W > 256) return;
-  const int64_t want = std::min<int64_t>(std::min<int64_t>(kResidentTiles / W, 64), nkb / 4);
-  if (want < 2) return;
-  const int64_t per = round_up((nkb + want - 1) / want, 2), S = (nkb + per - 1) / per;
-  if (S < 2 || (double)(nkb - per) * block_us < 12.0) return;
-  *split = S;
-  *blocks = per;
+  if (W < 1) return;
+  if (W <= kCUs) {
+    *split = share_tiles(W, nkb, 64, block_us, 12.0, blocks);
+    *q = *split > 1 ? W : 0;
+  } else if (tail_q > 0) {
+    *q = tail_q;
+    *split = tail_split;
+    *blocks = nkb / tail_split;
+  } else if (fp64 && W % kCUs > 0 && W % kCUs <= kResidentTiles / 3) {
+    *split = share_tiles(W % kCUs, nkb, 16, block_us, 24.0, blocks);
+    *q = *split > 1 ? W % kCUs : 0;
+  }
 }
 
 template <typename T>
@@ -251,10 +283,10 @@ Geometry geometry(int64_t n, int64_t d) {
   // a plan shares them out: in fp32, whose staged blocks are half a planned
   // one, that can be 32 features of padding more.
   const int64_t W = tri_count(g.nT);
-  const bool shared = (g.tail_q > 0 && W > 256) || g.NP <= kFusedMaxNP;
+  const bool shared = (g.tail_q > 0 && W > kCUs) || g.NP <= kFusedMaxNP;
   g.d_pad = shared ? g.plan_nkb * g.bk : round_up(d, 2 * TileShape<T>::SB);
-  few_plan(W, g.d_pad / TileShape<T>::SB, sizeof(T) == 8 ? 1.8 : 0.5, &g.few_split,
-           &g.few_blocks);
+  part_plan(W, g.tail_q, g.tail_split, g.d_pad / TileShape<T>::SB, sizeof(T) == 8,
+            &g.part_q, &g.part_split, &g.part_blocks);
   return g;
 }
 
@@ -304,8 +336,7 @@ TrainWs<T> carve_train(const Geometry& g, void* base) {
   // Row sums: two 64-bit words per row, however many tiles add to them; the
   // split tail's parked inner products (at most a quarter round of tiles).
   w.acc = c.take<int64_t>(2 * g.NP);
-  w.gpart = c.take<T>(std::max(g.few_split > 1 ? tri_count(g.nT) * g.few_split : 0,
-                               g.tail_q * g.tail_split) * g.tile * g.tile);
+  w.gpart = c.take<T>(g.part_q * g.part_split * g.tile * g.tile);
   const int64_t chunks = lin_max_chunks(g.n, g.d);
   w.pq = c.take<double>(2 * std::max(g.nT, chunks));
   w.rhs = c.take<double>(g.NP);
@@ -677,38 +708,32 @@ struct LinearPasses {
   }
 };
 
-// The first of a product's split launches: parks the inner products of `tiles`
-// tiles from `first` on, split as a says.
+// The first of the two launches of a product's split tiles: parks their inner
+// products, and leaves a as the second, the fixup, takes it.
 template <typename T>
-hipError_t launch_parked(TileArgs<T>& a, int32_t kernel, int64_t first, int64_t tiles,
-                         int64_t split, int64_t blocks, T* gpart, hipStream_t s) {
-  a.tile_offset = first;
-  a.ksplit = split;
-  a.split_blocks = blocks;
+hipError_t launch_parked(const Geometry& g, TileArgs<T>& a, int32_t kernel, T* gpart,
+                         hipStream_t s) {
+  a.tile_offset = tri_count(g.nT) - g.part_q;
+  a.ksplit = g.part_split;
+  a.split_blocks = g.part_blocks;
   a.gpart = gpart;
-  return launch_tiles_sym<T>(a, kernel, kPartial, tiles * split, s);
+  return launch_tiles_sym<T>(a, kernel, kPartial, g.part_q * g.part_split, s);
 }
 
 // The tile launches of one product: all tiles whole (the linear kernel's split
-// tiles included), or all split, parked and fixed up (few tiles), or the full
-// rounds whole and the tail split.
+// tiles included) but the last part_q, which are split, parked and fixed up.
 template <typename T>
 hipError_t launch_product(const Geometry& g, TileArgs<T> a, int32_t kernel, T* gpart,
                           hipStream_t s) {
   const int64_t W = tri_count(g.nT);
   if (kernel == LSSVM_LINEAR) return launch_tiles_sym<T>(a, kernel, kWhole, W * a.ksplit, s);
-  const bool few = g.few_split > 1;
-  const int64_t split = few ? W : W > 256 ? g.tail_q : 0;   // tiles split
-  if (split < W) {
-    const hipError_t e = launch_tiles_sym<T>(a, kernel, kWhole, W - split, s);
-    if (e != hipSuccess || split == 0) return e;
+  if (g.part_q < W) {
+    const hipError_t e = launch_tiles_sym<T>(a, kernel, kWhole, W - g.part_q, s);
+    if (e != hipSuccess || g.part_q == 0) return e;
   }
-  const hipError_t e =
-      few ? launch_parked<T>(a, kernel, 0, W, g.few_split, g.few_blocks, gpart, s)
-          : launch_parked<T>(a, kernel, W - split, split, g.tail_split, a.nkb / g.tail_split,
-                             gpart, s);
+  const hipError_t e = launch_parked<T>(g, a, kernel, gpart, s);
   if (e != hipSuccess) return e;
-  return launch_tiles_sym<T>(a, kernel, kFixup, split, s);
+  return launch_tiles_sym<T>(a, kernel, kFixup, g.part_q, s);
 }
 
 // One implicit product K p into the partial-sum buffer (plus the per-panel
@@ -1011,9 +1036,8 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
         FusedCg f{w.ticket, rank_one(g, w, kernel, C, w.dir), w.qv, w.x, w.r, w.dir, w.scal,
                   w.hist, g.NP, g.N, k, g.NP + 1, par};
         const int64_t W = tri_count(g.nT);
-        const bool split = kernel != LSSVM_LINEAR && g.few_split > 1;
-        if (split)
-          LSSVM_HIP(launch_parked<T>(a, kernel, 0, W, g.few_split, g.few_blocks, w.gpart, s));
+        const bool split = kernel != LSSVM_LINEAR && g.part_q > 0;   // all: few tiles
+        if (split) LSSVM_HIP(launch_parked<T>(g, a, kernel, w.gpart, s));
         LSSVM_HIP(launch_tiles_cg<T>(a, kernel, split ? kFixup : kWhole,
                                      kernel == LSSVM_LINEAR ? W * a.ksplit : W, f, s));
         LSSVM_HIP(tm.stop(s));
