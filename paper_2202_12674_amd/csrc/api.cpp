@@ -1074,8 +1074,8 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
         if (refresh || b + 1 == nq) {
           LSSVM_HIP(launch_cg_direction(w.bp1, nb, w.scal, par, k, w.r, dir, NP, w.hist, g.NP + 1,
                                         refresh ? k / kReplaceEvery : 0,
-                                        trusted || refresh || k == max_iter, w.bp2, w.x, w.xbest,
-                                        s));
+                                        trusted || refresh || k == max_iter, 0, w.bp2, w.x,
+                                        w.xbest, s));
           pending = false;
         }
         continue;
@@ -1093,8 +1093,8 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
                                    g.NP, s));
       }
       LSSVM_HIP(launch_cg_direction(w.bp1, g.nb, w.scal, par, k, w.r, w.dir, g.NP, w.hist,
-                                    g.NP + 1, refresh ? k / kReplaceEvery : 0, 1, w.bp2, w.x,
-                                    w.xbest, s));
+                                    g.NP + 1, refresh ? k / kReplaceEvery : 0, 1, 1, w.bp2,
+                                    w.x, w.xbest, s));
     }
     LSSVM_HIP(hipMemcpyAsync(st, w.scal + S_STATUS, ST_COUNT * sizeof(double),
                              hipMemcpyDeviceToHost, s));

@@ -488,12 +488,15 @@ __global__ __launch_bounds__(256) void k_cg_gather(RankOne c, int64_t NP, int64_
 
 // x += a d and r -= a q (or only x += a d when the residual is about to be
 // recomputed from x). On curvature breakdown (d^T q <= 0 or a step that is
-// not finite) every block leaves the vectors as they are.
+// not finite) every block leaves the vectors as they are. Bound by memory; four
+// elements of every vector in flight per thread (16-byte accesses instead of 8
+// measured slower at 2^26: 4.77 against 5.25 TB/s over the step).
 __global__ __launch_bounds__(256) void k_cg_update(int x_only, const double* __restrict__ bp_in,
                                                    int64_t nb, double* scal, int par,
                                                    const double* __restrict__ dir,
-                                                   const double* __restrict__ qv, double* x,
-                                                   double* r, double* bp_out, int64_t NP) {
+                                                   const double* __restrict__ qv,
+                                                   double* __restrict__ x, double* __restrict__ r,
+                                                   double* bp_out, int64_t NP) {
   __shared__ double sh[NT / 64];
   if (scal[S_STATUS + ST_DONE] != 0.0) return;
   const double gam = sum_partials(bp_in, nb, sh);
@@ -512,21 +515,22 @@ __global__ __launch_bounds__(256) void k_cg_update(int x_only, const double* __r
   }
   if (broke) return;
   double v = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < NP; i += (int64_t)gridDim.x * NT) {
-    const double xi = x[i] + alpha * dir[i];
-    x[i] = xi;
-    if (!x_only) {
+  if (!x_only) {
+#pragma unroll 4
+    for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < NP; i += (int64_t)gridDim.x * NT) {
+      x[i] = x[i] + alpha * dir[i];
       const double ri = r[i] - alpha * qv[i];
       r[i] = ri;
       v += ri * ri;
-    } else {
-      v = fmax(v, fabs(xi));
     }
-  }
-  if (!x_only) {
     const double t = block_sum(v, sh);
     if (threadIdx.x == 0) bp_out[blockIdx.x] = t;
   } else {   // the residual recomputation multiplies x next
+    for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < NP; i += (int64_t)gridDim.x * NT) {
+      const double xi = x[i] + alpha * dir[i];
+      x[i] = xi;
+      v = fmax(v, fabs(xi));
+    }
     const double mx = block_max(v, sh);
     if (threadIdx.x == 0) raise_pmax(scal, mx);
   }
@@ -581,7 +585,7 @@ __global__ __launch_bounds__(256) void k_true_residual(RankOne c, int64_t NP, in
 // beta = r^T r (new) / r^T r (old); d = r + beta d (beta = 0 if the old
 // r^T r is 0, an exact solution). Block 0 records the iteration in the
 // status (and the history) and raises done once r^T r <= eps^2 r0^T r0 (with
-// `test` clear only on r = 0).
+// `test` clear only on r = 0). raise: bound |d| for a product on tiles.
 //
 // At the refresh-th residual recomputation (refresh > 0) r is a true
 // residual. Unless it met eps, CG has progressed if r^T r or the energy
@@ -591,17 +595,30 @@ __global__ __launch_bounds__(256) void k_true_residual(RankOne c, int64_t NP, in
 // writes). A new smallest r^T r copies x to xbest; no progress at all stops
 // CG, stalled, and the status then reports the best r^T r, whose iterate is
 // in xbest.
+//
+// With `scalars` (lssvm_cg_step) block 0 also reports r^T r, d^T q, the step and
+// beta there; after a breakdown, which left the vectors as they were, r^T r stays
+// and beta is 0.
 __global__ __launch_bounds__(256) void k_cg_direction(const double* __restrict__ bp_in, int64_t nb,
                                                       double* scal, int par, int64_t iter,
-                                                      const double* __restrict__ r, double* dir,
-                                                      int64_t NP, double* hist, int64_t hist_cap,
-                                                      int64_t refresh, int test,
+                                                      const double* __restrict__ r,
+                                                      double* __restrict__ dir, int64_t NP, double* hist, int64_t hist_cap,
+                                                      int64_t refresh, int test, int raise,
                                                       const double* __restrict__ bp_phi,
                                                       const double* __restrict__ x,
-                                                      double* __restrict__ xbest) {
+                                                      double* __restrict__ xbest,
+                                                      double* __restrict__ scalars) {
   __shared__ double sh[NT / 64];
   double* st = scal + S_STATUS;
-  if (st[ST_DONE] != 0.0) return;
+  if (st[ST_DONE] != 0.0) {
+    if (scalars && blockIdx.x == 0 && threadIdx.x == 0) {
+      scalars[0] = scal[S_DHIST + par];
+      scalars[1] = scal[S_GAMMA];
+      scalars[2] = scal[S_ALPHA];
+      scalars[3] = 0.0;
+    }
+    return;
+  }
   const double dnew = sum_partials(bp_in, nb, sh);
   const double dold = scal[S_DHIST + par];
   const bool conv = dnew <= (test ? st[ST_STOP] : 0.0);
@@ -626,14 +643,17 @@ __global__ __launch_bounds__(256) void k_cg_direction(const double* __restrict__
   const double beta = dold != 0.0 ? dnew / dold : 0.0;
   if (!stall) {
     double dmax = 0.0;
+#pragma unroll 4
     for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < NP;
          i += (int64_t)gridDim.x * NT) {
       const double di = r[i] + beta * dir[i];
       dir[i] = di;
       dmax = fmax(dmax, fabs(di));
     }
-    const double mx = block_max(dmax, sh);   // the next product multiplies dir
-    if (threadIdx.x == 0) raise_pmax(scal, mx);
+    if (raise) {   // the next product multiplies dir
+      const double mx = block_max(dmax, sh);
+      if (threadIdx.x == 0) raise_pmax(scal, mx);
+    }
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     scal[S_DHIST + (par ^ 1)] = dnew;
@@ -642,6 +662,12 @@ __global__ __launch_bounds__(256) void k_cg_direction(const double* __restrict__
     st[ST_STEP] = scal[S_ALPHA];
     st[ST_ITER] = (double)iter;
     if (iter <= hist_cap) hist[iter - 1] = dnew;
+    if (scalars) {
+      scalars[0] = dnew;
+      scalars[1] = scal[S_GAMMA];
+      scalars[2] = scal[S_ALPHA];
+      scalars[3] = beta;   // 0 where r^T r was 0: r = 0
+    }
     if (conv) st[ST_DONE] = 1.0;
     if (stall) {
       st[ST_STALL] = 1.0;
@@ -682,38 +708,27 @@ __global__ __launch_bounds__(256) void k_warm_start(const double* __restrict__ b
 
 // ------------------------------------------------- a5 on caller vectors -----
 // One CG iteration on vectors the caller holds, with q = A d supplied: the
-// caller's scalars[0] (r^T r) enters the double-buffered slot, the status is
-// cleared with a stop threshold no r^T r reaches, and after the update and
-// direction kernels the new r^T r, d^T q, step and beta go back to scalars.
-__global__ void k_step_begin(const double* scalars, double* scal) {
-  if (threadIdx.x == 0) {
+// block partials of d^T q; block 0 also enters the caller's scalars[0] (r^T r) in
+// the double-buffered slot and clears the status, with a stop threshold that no
+// r^T r reaches, for the update and direction kernels, which follow.
+__global__ __launch_bounds__(256) void k_step_dot(const double* __restrict__ a,
+                                                  const double* __restrict__ b, int64_t len,
+                                                  double* __restrict__ bp_out,
+                                                  const double* __restrict__ scalars,
+                                                  double* __restrict__ scal) {
+  __shared__ double sh[NT / 64];
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
     scal[S_DHIST + 0] = scalars[0];
     scal[S_DHIST + 1] = scalars[0];
     for (int k = 0; k < ST_COUNT; ++k) scal[S_STATUS + k] = 0.0;
     scal[S_STATUS + ST_STOP] = -1.0;
   }
-}
-
-__global__ __launch_bounds__(256) void k_dot_partials(const double* __restrict__ a,
-                                                      const double* __restrict__ b, int64_t len,
-                                                      double* bp_out) {
-  __shared__ double sh[NT / 64];
   double v = 0.0;
+#pragma unroll 4
   for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < len; i += (int64_t)gridDim.x * NT)
     v += a[i] * b[i];
   const double t = block_sum(v, sh);
   if (threadIdx.x == 0) bp_out[blockIdx.x] = t;
-}
-
-__global__ void k_step_end(const double* scal, double* scalars) {
-  if (threadIdx.x == 0) {
-    const bool broke = scal[S_STATUS + ST_BREAK] != 0.0;
-    const double rr_old = scal[S_DHIST + 0], rr_new = scal[S_DHIST + 1];
-    scalars[0] = broke ? rr_old : rr_new;
-    scalars[1] = scal[S_GAMMA];
-    scalars[2] = scal[S_ALPHA];
-    scalars[3] = broke || rr_old == 0.0 ? 0.0 : rr_new / rr_old;   // rr_old = 0: r = 0, beta 0
-  }
 }
 
 // ------------------------------------------------------------- a6 bias ------
@@ -1976,11 +1991,11 @@ hipError_t launch_true_residual(const RankOne& c, int64_t NP, int64_t N, const d
 hipError_t launch_cg_direction(const double* bp_in, int64_t nb, double* scal, int par,
                                int64_t iter, const double* r, double* dir, int64_t NP,
                                double* hist, int64_t hist_cap, int64_t refresh, int test,
-                               const double* bp_phi, const double* x, double* xbest,
+                               int raise, const double* bp_phi, const double* x, double* xbest,
                                hipStream_t s) {
   hipLaunchKernelGGL(k_cg_direction, dim3((unsigned)cg_blocks(NP)), dim3(NT), 0, s, bp_in, nb,
-                     scal, par, iter, r, dir, NP, hist, hist_cap, refresh, test, bp_phi, x,
-                     xbest);
+                     scal, par, iter, r, dir, NP, hist, hist_cap, refresh, test, raise, bp_phi, x,
+                     xbest, (double*)nullptr);
   return hipGetLastError();
 }
 
@@ -1992,18 +2007,20 @@ hipError_t launch_warm_start(const double* bp_in, const double* bp_phi, int64_t 
   return hipGetLastError();
 }
 
+// Three launches (the scalars go in and out with the first and the last). No
+// bound on |d| is kept: 1024 blocks raising one word took longer than the vector
+// (with the caller's product, 8 steps: 10^6 doubles 341 -> 227 us, 4 x 10^6 730 ->
+// 622 us, 3 x 10^5 256 -> 154 us).
 hipError_t launch_cg_step(int64_t N, double* x, double* r, double* d, const double* q,
                           double* scalars, double* scal, double* bp0, double* bp1,
                           hipStream_t s) {
   const int64_t nb = vec_blocks(N);
-  hipLaunchKernelGGL(k_step_begin, dim3(1), dim3(64), 0, s, scalars, scal);
-  hipLaunchKernelGGL(k_dot_partials, dim3((unsigned)nb), dim3(NT), 0, s, d, q, N, bp0);
-  hipLaunchKernelGGL(k_cg_update, dim3((unsigned)nb), dim3(NT), 0, s, 0, bp0, nb, scal, 0, d, q,
-                     x, r, bp1, N);
-  hipLaunchKernelGGL(k_cg_direction, dim3((unsigned)nb), dim3(NT), 0, s, bp1, nb, scal, 0,
-                     (int64_t)1, r, d, N, (double*)nullptr, (int64_t)0, (int64_t)0, 1,
-                     (const double*)nullptr, (const double*)nullptr, (double*)nullptr);
-  hipLaunchKernelGGL(k_step_end, dim3(1), dim3(64), 0, s, scal, scalars);
+  const dim3 grid((unsigned)nb);
+  hipLaunchKernelGGL(k_step_dot, grid, dim3(NT), 0, s, d, q, N, bp0, scalars, scal);
+  hipLaunchKernelGGL(k_cg_update, grid, dim3(NT), 0, s, 0, bp0, nb, scal, 0, d, q, x, r, bp1, N);
+  hipLaunchKernelGGL(k_cg_direction, grid, dim3(NT), 0, s, bp1, nb, scal, 0, (int64_t)1, r, d, N,
+                     (double*)nullptr, (int64_t)0, (int64_t)0, 1, 0, (const double*)nullptr,
+                     (const double*)nullptr, (double*)nullptr, scalars);
   return hipGetLastError();
 }
 

@@ -204,7 +204,7 @@ hipError_t launch_cg_step(int64_t N, double* x, double* r, double* d, const doub
 hipError_t launch_cg_direction(const double* bp_in, int64_t nb, double* scal, int par,
                                int64_t iter, const double* r, double* dir, int64_t NP,
                                double* hist, int64_t hist_cap, int64_t refresh, int test,
-                               const double* bp_phi, const double* x, double* xbest,
+                               int raise, const double* bp_phi, const double* x, double* xbest,
                                hipStream_t s);
 template <typename T>
 hipError_t launch_bias(const double* x, const double* q64, int64_t N, const T* y, double* scal,
