@@ -415,7 +415,8 @@ struct HostCtx {
   hipError_t ensure() {
     if (p) return hipSuccess;
     void* v = nullptr;
-    hipError_t e = hipHostMalloc(&v, 64 * sizeof(double), hipHostMallocDefault);
+    hipError_t e = hipHostMalloc(&v, 64 * sizeof(double),
+                                 hipHostMallocPortable | hipHostMallocMapped);
     if (e != hipSuccess) return e;
     p = static_cast<double*>(v);
     flags = reinterpret_cast<int*>(p + 32);
@@ -447,6 +448,13 @@ struct CtxLease {
   CtxLease(const CtxLease&) = delete;
   CtxLease& operator=(const CtxLease&) = delete;
 };
+
+// The input flags into g_ctx->flags, once the stream has been waited for.
+hipError_t read_flags(const int* flags, hipStream_t s) {
+  static_assert(F_COUNT * sizeof(int) == 2 * sizeof(double), "the flags are two words");
+  return launch_read_back(reinterpret_cast<const double*>(flags), 2,
+                          reinterpret_cast<double*>(g_ctx->flags), s);
+}
 
 // HIP events around each implicit product, recorded on the launch stream.
 // Pairs carry the CG iteration they belong to, so products that ran after
@@ -647,23 +655,17 @@ int rescale_points(const Geometry& g, TrainWs<T>& w, const T* X, hipStream_t s) 
   return LSSVM_OK;
 }
 
-// a1 + a2: layout, norms, q and k_mm (left on the device). With check set,
-// reads back the input flags, reports a non-finite X and relays out tiny
-// values (the norms stand: the slices add up to every value); otherwise the
-// caller reads them back with its next result.
+// a1 + a2: layout, norms, q and k_mm, left on the device. The caller reads the
+// input flags back with its result: a non-finite X is an error, and tiny values
+// are laid out again (the norms stand: the slices add up to every value).
 template <typename T>
-int setup_points(const Geometry& g, TrainWs<T>& w, const T* X, int32_t kernel,
-                 const lssvm_params& kp, hipStream_t s, bool check = true) {
+int setup_points(const Geometry& g, const TrainWs<T>& w, const T* X, int32_t kernel,
+                 const lssvm_params& kp, hipStream_t s) {
   LSSVM_TRY(clear_and_order<T>(g, w, s));
   LSSVM_HIP(launch_layout<T>(X, g.n, g.d, w.Xt, g.ld, g.d_pad, 1.f, w.flags, s));
   LSSVM_HIP(launch_norms_q<T>(w.Xt, g.ld, g.d_pad, g.N, g.N, kernel, kp.gamma, kp.coef0,
                               kp.degree, w.norms, w.q64, w.scal, s));
-  if (!check) return LSSVM_OK;
-  LSSVM_HIP(hipMemcpyAsync(g_ctx->flags, w.flags, F_COUNT * sizeof(int), hipMemcpyDeviceToHost,
-                           s));
-  LSSVM_HIP(hipStreamSynchronize(s));
-  if (g_ctx->flags[F_NONFINITE]) return fail(LSSVM_ENONFINITE, "X holds a NaN or an infinity");
-  return g_ctx->flags[F_TINY] ? rescale_points<T>(g, w, X, s) : LSSVM_OK;
+  return LSSVM_OK;
 }
 
 // A finished product's row sums and the terms of Q~ p the tiles leave out.
@@ -860,7 +862,7 @@ int train_small_linear(const Geometry& g, const TrainWs<T>& w, const T* X, const
   a.hist_cap = g.NP + 1;
   a.flags = w.flags;
   LSSVM_HIP(launch_lin_train<T>(X, y, g.n, g.d, a, alpha_out, s));
-  LSSVM_HIP(hipMemcpyAsync(g_ctx->p, w.scal, S_COUNT * sizeof(double), hipMemcpyDeviceToHost, s));
+  LSSVM_HIP(launch_read_back(w.scal, S_COUNT, g_ctx->p, s));
   LSSVM_HIP(hipStreamSynchronize(s));
   const double* p = g_ctx->p;
   const double* st = p + S_STATUS;
@@ -919,8 +921,7 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
     LSSVM_HIP(hipMemsetAsync(w.flags, 0, F_COUNT * sizeof(int), s));
     LSSVM_HIP(launch_layout<T>(X, g.n, g.d, w.Xt, g.ld, g.d_pad, 1.f, w.flags, s));
     LSSVM_HIP(launch_single_point<T>(y, alpha_out, w.scal, w.flags, s));
-    LSSVM_HIP(hipMemcpyAsync(g_ctx->flags, w.flags, F_COUNT * sizeof(int),
-                             hipMemcpyDeviceToHost, s));
+    LSSVM_HIP(read_flags(w.flags, s));
     LSSVM_HIP(hipMemcpyAsync(g_ctx->p, w.scal + S_B, sizeof(double), hipMemcpyDeviceToHost, s));
     LSSVM_HIP(hipStreamSynchronize(s));
     if (g_ctx->flags[F_NONFINITE]) return fail(LSSVM_ENONFINITE, "X holds a NaN or an infinity");
@@ -950,14 +951,13 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
                                  nullptr, s));
     LSSVM_HIP(launch_lin_q<T>(X, g.n, g.d, w.q64, w.scal, w.flags, s));
   } else {
-    LSSVM_TRY(setup_points<T>(g, w, X, kernel, kp, s, /*check=*/false));
+    LSSVM_TRY(setup_points<T>(g, w, X, kernel, kp, s));
   }
   LSSVM_HIP(launch_rhs_init<T>(y, g.N, NP, w.rhs, w.x, w.xbest, w.r, w.dir, w.bp0, w.flags,
                                w.scal, s));
   LSSVM_HIP(launch_finish_delta0(w.bp0, nb, w.scal, eps * eps, w.flags, s));
   // one read-back: r0^T r0 and the input flags
-  LSSVM_HIP(hipMemcpyAsync(g_ctx->p, w.scal + S_DELTA0, (S_INFLAGS - S_DELTA0 + 1) * sizeof(double),
-                           hipMemcpyDeviceToHost, s));
+  LSSVM_HIP(launch_read_back(w.scal + S_DELTA0, S_INFLAGS - S_DELTA0 + 1, g_ctx->p, s));
   LSSVM_HIP(hipStreamSynchronize(s));
   const int inflags = (int)g_ctx->p[S_INFLAGS - S_DELTA0];
   if (inflags & 1) return fail(LSSVM_ENONFINITE, "X holds a NaN or an infinity");
@@ -997,8 +997,7 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
     else LSSVM_TRY(matvec_partials<T>(g, w, kp, kernel, w.x, s));
     LSSVM_HIP(launch_cg_residual(product_of(w.x), NP, g.N, w.rhs, w.r, w.bp1, w.bp2, s));
     LSSVM_HIP(launch_warm_start(w.bp1, w.bp2, nb, w.scal, w.r, w.dir, w.x, w.xbest, NP, s));
-    LSSVM_HIP(hipMemcpyAsync(st, w.scal + S_STATUS, ST_COUNT * sizeof(double),
-                             hipMemcpyDeviceToHost, s));
+    LSSVM_HIP(launch_read_back(w.scal + S_STATUS, ST_COUNT, st, s));
     LSSVM_HIP(hipStreamSynchronize(s));
     delta = st[ST_DELTA];
     done = st[ST_DONE] != 0.0;
@@ -1096,8 +1095,7 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
                                     g.NP + 1, refresh ? k / kReplaceEvery : 0, 1, 1, w.bp2,
                                     w.x, w.xbest, s));
     }
-    LSSVM_HIP(hipMemcpyAsync(st, w.scal + S_STATUS, ST_COUNT * sizeof(double),
-                             hipMemcpyDeviceToHost, s));
+    LSSVM_HIP(launch_read_back(w.scal + S_STATUS, ST_COUNT, st, s));
     LSSVM_HIP(hipStreamSynchronize(s));
     it = (int64_t)st[ST_ITER];
     done = st[ST_DONE] != 0.0;
@@ -1143,7 +1141,7 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
 
   // ---- a6: alpha_m and b
   LSSVM_HIP(launch_bias<T>(w.x, w.q64, g.N, y, w.scal, 1.0 / C, alpha_out, s));
-  LSSVM_HIP(hipMemcpyAsync(g_ctx->p, w.scal + S_B, sizeof(double), hipMemcpyDeviceToHost, s));
+  LSSVM_HIP(launch_read_back(w.scal + S_B, 1, g_ctx->p, s));
   LSSVM_HIP(hipStreamSynchronize(s));
   *b_out = g_ctx->p[0];
   end_report(g, e, info, t0);
@@ -1197,18 +1195,22 @@ int matvec_impl(const T* X, int64_t n, int64_t d, int32_t kernel, const lssvm_pa
     LSSVM_HIP(lin.weights(lin.vec(w.dir, false)));
     LSSVM_HIP(launch_lin_out<T>(X, g.N, g.d, w.lin_w, lin.rank_one(w.dir, nullptr), out, w.flags,
                                 s));
-    LSSVM_HIP(hipMemcpyAsync(g_ctx->flags, w.flags, F_COUNT * sizeof(int), hipMemcpyDeviceToHost,
-                             s));
+    LSSVM_HIP(read_flags(w.flags, s));
     LSSVM_HIP(hipStreamSynchronize(s));
     if (g_ctx->flags[F_NONFINITE]) return fail(LSSVM_ENONFINITE, "X holds a NaN or an infinity");
     return LSSVM_OK;
   }
   LSSVM_TRY(setup_points<T>(g, w, X, kernel, kp, s));
   LSSVM_HIP(launch_pad_to_f64<T>(p, g.N, w.dir, g.NP, w.scal, s));
-  LSSVM_TRY(matvec_partials<T>(g, w, kp, kernel, w.dir, s));
-  LSSVM_HIP(launch_mv_out<T>(rank_one(g, w, kernel, C, w.dir), g.NP, g.N, out, s));
-  LSSVM_HIP(hipStreamSynchronize(s));
-  return LSSVM_OK;
+  for (bool again = false;; again = true) {   // one wait, at the end
+    LSSVM_TRY(matvec_partials<T>(g, w, kp, kernel, w.dir, s));
+    LSSVM_HIP(launch_mv_out<T>(rank_one(g, w, kernel, C, w.dir), g.NP, g.N, out, s));
+    LSSVM_HIP(read_flags(w.flags, s));
+    LSSVM_HIP(hipStreamSynchronize(s));
+    if (g_ctx->flags[F_NONFINITE]) return fail(LSSVM_ENONFINITE, "X holds a NaN or an infinity");
+    if (!g_ctx->flags[F_TINY] || again) return LSSVM_OK;
+    LSSVM_TRY(rescale_points<T>(g, w, X, s));   // tiny values: once more, scaled up
+  }
 }
 
 template <typename T>
@@ -1235,8 +1237,7 @@ int predict_impl(const T* Xtr, const T* alpha, double b, int64_t n, int64_t d, i
     a.part = w.few_part;
     a.bad = w.few_bad;
     LSSVM_HIP(launch_predict_few<T>(a, kernel, b, scores, labels, w.flags, s));
-    LSSVM_HIP(hipMemcpyAsync(g_ctx->flags, w.flags, F_COUNT * sizeof(int), hipMemcpyDeviceToHost,
-                             s));
+    LSSVM_HIP(read_flags(w.flags, s));
     LSSVM_HIP(hipStreamSynchronize(s));
     if (g_ctx->flags[F_NONFINITE])
       return fail(LSSVM_ENONFINITE, "X_train or X_test holds a NaN or an infinity");
@@ -1246,8 +1247,7 @@ int predict_impl(const T* Xtr, const T* alpha, double b, int64_t n, int64_t d, i
   if (kernel == LSSVM_LINEAR) {  // Eq. (15): w = sum_i alpha_i x_i, f(x) = <w, x> + b
     LSSVM_HIP(launch_linear_predict<T>(Xtr, alpha, n, d, Xte, n_test, b, w.lin_part, w.lin_w,
                                        w.lin_f, scores, labels, w.flags, s));
-    LSSVM_HIP(hipMemcpyAsync(g_ctx->flags, w.flags, F_COUNT * sizeof(int), hipMemcpyDeviceToHost,
-                             s));
+    LSSVM_HIP(read_flags(w.flags, s));
     LSSVM_HIP(hipStreamSynchronize(s));
     if (g_ctx->flags[F_NONFINITE])
       return fail(LSSVM_ENONFINITE, "X_train or X_test holds a NaN or an infinity");
@@ -1283,8 +1283,7 @@ int predict_impl(const T* Xtr, const T* alpha, double b, int64_t n, int64_t d, i
     LSSVM_HIP(launch_tiles_gen<T>(a, kernel, w.nTr, s));
     LSSVM_HIP(launch_predict_finish<T>(w.part, w.nTc, w.ld_te, n_test, b, scores, labels, w.flags,
                                        s));
-    LSSVM_HIP(hipMemcpyAsync(g_ctx->flags, w.flags, F_COUNT * sizeof(int), hipMemcpyDeviceToHost,
-                             s));
+    LSSVM_HIP(read_flags(w.flags, s));
     LSSVM_HIP(hipStreamSynchronize(s));
     if (g_ctx->flags[F_NONFINITE])
       return fail(LSSVM_ENONFINITE, "X_train or X_test holds a NaN or an infinity");

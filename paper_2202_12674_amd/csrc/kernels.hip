@@ -328,30 +328,34 @@ template <> struct PointRow<float> {
 
 // ||x_i||^2 and, if a pivot m is given, the cached q_i = k(x_i, x_m) for
 // i < N (zero beyond) and k(x_m, x_m). fp64 sums. A workgroup takes PPB
-// points, 256 / PPB threads per point, each summing every (256 / PPB)-th
+// points, 1024 / PPB threads per point, each summing every (1024 / PPB)-th
 // chunk of the point's row; the point's partial sums are then added in a fixed
-// order. The points of a wave's load instruction are neighbours in the layout:
+// order. (256 threads left a few hundred points of many features to a few dozen
+// waves: 561 x 1207 fp32 18.7 us, 502 x 2877 fp64 13.9 us; NORMS_US so.) The points of a wave's load instruction are neighbours in the layout:
 // fp64 8 chunks (a whole 128-byte row) of 8 points, fp32 one chunk of 32
 // points (512 contiguous bytes per slice).
 template <typename T> constexpr int kNormPoints = sizeof(T) == 8 ? 16 : 32;
+constexpr int kNormThreads = 1024;
 template <typename T, int KER>
-__global__ __launch_bounds__(256) void k_norms_q(const store_t<T>* __restrict__ Xb, int64_t nkb,
-                                                 int64_t m, int64_t N, double gamma, double coef0,
-                                                 int degree, T* __restrict__ norms,
-                                                 double* __restrict__ q64,
-                                                 double* __restrict__ scal) {
-  constexpr int PPB = kNormPoints<T>, TPP = 256 / PPB;
+__global__ __launch_bounds__(kNormThreads) void k_norms_q(const store_t<T>* __restrict__ Xb,
+                                                          int64_t nkb, int64_t m, int64_t N,
+                                                          double gamma, double coef0, int degree,
+                                                          T* __restrict__ norms,
+                                                          double* __restrict__ q64,
+                                                          double* __restrict__ scal) {
+  constexpr int PPB = kNormPoints<T>, TPP = kNormThreads / PPB, WAVES = kNormThreads / 64;
   static_assert(TileShape<T>::T % PPB == 0, "a workgroup's points lie in one panel");
+  static_assert(sizeof(T) == 8 ? TPP == 64 : TPP == 2 * WAVES, "a wave per point, or half of 32");
   constexpr int VEC = PointRow<T>::VEC;
-  __shared__ double sh[NT / 64];
-  __shared__ double part[3][TPP][PPB];
+  __shared__ double sh[WAVES];
+  __shared__ double part[3][sizeof(T) == 8 ? 1 : WAVES][PPB];
   const int tid = (int)threadIdx.x;
   const int q = sizeof(T) == 8 ? tid % TPP : tid / PPB;    // this thread's share of the chunks
   const int pl = sizeof(T) == 8 ? tid / TPP : tid % PPB;   // its point
   const int64_t i = (int64_t)blockIdx.x * PPB + pl;        // below the padded point count
   const int64_t nchunks = nkb * PointRow<T>::CPS;
   const PointRow<T> ri(Xb, nkb, i);
-  double nrm = 0.0, dot = 0.0, dist = 0.0;
+  double s[3] = {0.0, 0.0, 0.0};   // norm, dot, squared distance
   if (m >= 0) {
     const PointRow<T> rm(Xb, nkb, m);
 #pragma unroll 4
@@ -361,10 +365,10 @@ __global__ __launch_bounds__(256) void k_norms_q(const store_t<T>* __restrict__ 
       rm.load(c, xm);
 #pragma unroll
       for (int e = 0; e < VEC; ++e) {
-        nrm += xi[e] * xi[e];
-        dot += xi[e] * xm[e];
+        s[0] += xi[e] * xi[e];
+        s[1] += xi[e] * xm[e];
         const double df = xi[e] - xm[e];
-        dist += df * df;
+        s[2] += df * df;
       }
     }
   } else {
@@ -373,25 +377,31 @@ __global__ __launch_bounds__(256) void k_norms_q(const store_t<T>* __restrict__ 
       double xi[VEC];
       ri.load(c, xi);
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) nrm += xi[e] * xi[e];
+      for (int e = 0; e < VEC; ++e) s[0] += xi[e] * xi[e];
     }
   }
-  part[0][q][pl] = nrm;
-  part[1][q][pl] = dot;
-  part[2][q][pl] = dist;
-  __syncthreads();
-  nrm = 0.0;
-  if (tid < PPB) {
-    dot = dist = 0.0;
-    for (int t = 0; t < TPP; ++t) {
-      nrm += part[0][t][tid];
-      dot += part[1][t][tid];
-      dist += part[2][t][tid];
+#pragma unroll
+  for (int t = 0; t < 3; ++t) {
+    if constexpr (sizeof(T) == 8) {
+      s[t] = wave_sum(s[t]);
+      if (tid % 64 == 0) part[t][0][pl] = s[t];
+    } else {
+      s[t] += __shfl_xor(s[t], 32);
+      if (tid % 64 < PPB) part[t][tid / 64][pl] = s[t];
     }
+  }
+  __syncthreads();
+  double nrm = 0.0;
+  if (tid < PPB) {
+    double v[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+      for (int w = 0; w < (sizeof(T) == 8 ? 1 : WAVES); ++w) v[t] += part[t][w][tid];
+    nrm = v[0];
     const int64_t r = (int64_t)blockIdx.x * PPB + tid;
     norms[r] = (T)nrm;
     if (m >= 0) {
-      const double kv = kernel_value64<KER>(dot, dist, gamma, coef0, degree);
+      const double kv = kernel_value64<KER>(v[1], v[2], gamma, coef0, degree);
       q64[r] = r < N ? kv : 0.0;
       if (r == m) scal[S_KMM] = kv;
     }
@@ -1583,6 +1593,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_mv_out(RankOne c, int64_t NP, int64_t N,
                                                 T* __restrict__ out) {
   __shared__ double sh[NT / 64];
+  if (c.flags[F_NONFINITE] != 0) return;   // out stays untouched on error
   const RankOneSums ro = rank_one_sums(c, sh);
   const double inv = 1.0 / c.scal[S_FIXSC];
   const bool bad = c.flags[F_PRODUCT] != 0;
@@ -1632,6 +1643,12 @@ __global__ __launch_bounds__(256) void k_pad_to_f64(const T* __restrict__ src, i
     const double mx = block_max(fabs(v), sh);
     if (threadIdx.x == 0) raise_pmax(scal, mx);
   }
+}
+
+// A few doubles to pinned host memory: a copy by the stream's copy path takes
+// several microseconds more than this launch.
+__global__ void k_read_back(const double* __restrict__ src, int count, double* __restrict__ dst) {
+  if ((int)threadIdx.x < count) dst[threadIdx.x] = src[threadIdx.x];
 }
 
 __global__ __launch_bounds__(256) void k_finish_sum(const double* bpart, int64_t nb, double* scal,
@@ -1839,15 +1856,15 @@ hipError_t launch_norms_q(const store_t<T>* Xt, int64_t ld, int64_t d_pad, int64
   const unsigned g = (unsigned)(ld / kNormPoints<T>);   // ld is a multiple of the tile edge
   switch (kernel) {
     case KLIN:
-      hipLaunchKernelGGL((k_norms_q<T, KLIN>), dim3(g), dim3(NT), 0, s, Xt, nkb, m, N, gamma,
+      hipLaunchKernelGGL((k_norms_q<T, KLIN>), dim3(g), dim3(kNormThreads), 0, s, Xt, nkb, m, N, gamma,
                          coef0, degree, norms, q64, scal);
       break;
     case KPOLY:
-      hipLaunchKernelGGL((k_norms_q<T, KPOLY>), dim3(g), dim3(NT), 0, s, Xt, nkb, m, N, gamma,
+      hipLaunchKernelGGL((k_norms_q<T, KPOLY>), dim3(g), dim3(kNormThreads), 0, s, Xt, nkb, m, N, gamma,
                          coef0, degree, norms, q64, scal);
       break;
     default:
-      hipLaunchKernelGGL((k_norms_q<T, KRBF>), dim3(g), dim3(NT), 0, s, Xt, nkb, m, N, gamma,
+      hipLaunchKernelGGL((k_norms_q<T, KRBF>), dim3(g), dim3(kNormThreads), 0, s, Xt, nkb, m, N, gamma,
                          coef0, degree, norms, q64, scal);
       break;
   }
@@ -2065,6 +2082,11 @@ hipError_t launch_pad_to_f64(const T* src, int64_t len, double* dst, int64_t len
                              double* scal, hipStream_t s) {
   hipLaunchKernelGGL(k_pad_to_f64<T>, dim3(blocks_for(len_pad)), dim3(NT), 0, s, src, len, dst,
                      len_pad, scal);
+  return hipGetLastError();
+}
+
+hipError_t launch_read_back(const double* src, int count, double* dst, hipStream_t s) {
+  hipLaunchKernelGGL(k_read_back, dim3(1), dim3(64), 0, s, src, count, dst);
   return hipGetLastError();
 }
 

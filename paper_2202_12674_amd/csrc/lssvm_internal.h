@@ -227,6 +227,9 @@ hipError_t launch_predict_finish(const double* part, int64_t nslots, int64_t ld,
 template <typename T>
 hipError_t launch_pad_to_f64(const T* src, int64_t len, double* dst, int64_t len_pad,
                              double* scal, hipStream_t s);
+// count <= 64 doubles from the device to pinned host memory, for a host that waits
+// for the stream next.
+hipError_t launch_read_back(const double* src, int count, double* dst, hipStream_t s);
 hipError_t launch_finish_sum(const double* bpart, int64_t nb, double* scal, int slot,
                              hipStream_t s);
 hipError_t launch_true_residual(const RankOne& c, int64_t NP, int64_t N, const double* rhs,
