@@ -9,8 +9,9 @@
  * which is solved by conjugate gradients (Sec. III-B). Q~ is never stored:
  * every product Q~ p recomputes its entries (Eq. (16))
  *     Q~_ij = k(x_i,x_j) + delta_ij/C - k(x_m,x_j) - k(x_i,x_m) + k(x_m,x_m) + 1/C
- * tile by tile on the matrix cores. alpha_m = -sum(alpha~) (last row of
- * Eq. (11)) and b follows Eq. (15).
+ * tile by tile on the matrix cores, except for the linear kernel, whose product
+ * is evaluated as X (X^T p), in two passes over the points. alpha_m =
+ * -sum(alpha~) (last row of Eq. (11)) and b follows Eq. (15).
  *
  * Conventions shared by every entry point:
  * - Array arguments are DEVICE pointers unless marked "host". The caller
@@ -159,6 +160,9 @@ size_t lssvm_predict_workspace_bytes(int64_t n, int64_t n_test, int64_t d, int32
  *     smallest recomputed residual);
  *   - on curvature breakdown, d^T Q~ d <= 0 (LSSVM_EBREAKDOWN, outputs
  *     untouched; Q~ is positive definite for coef0 >= 0).
+ * For eps < 1e-12 a linear training whose products are passes over the points
+ * takes convergence from recomputed residuals only (and from the last iteration
+ * allowed): its recurrence falls below what fp64 iterates attain.
  * n = 1 or all labels equal give alpha = 0, b = y_m without iterating.
  */
 int lssvm_train(const void* X, const void* y, int64_t n, int64_t d, int32_t dtype,
@@ -207,8 +211,8 @@ size_t lssvm_cg_step_workspace_bytes(int64_t N);
  * with q = A d already computed,
  *     gamma = d^T q,  a = rr / gamma,  x += a d,  r -= a q,
  *     rr' = r^T r,    beta = rr' / rr, d = r + beta d.
- * This is the vector work of one iteration of lssvm_train, in the same
- * kernels (three passes over the vectors: 8 reads and 3 writes of N doubles).
+ * This is the vector work of one iteration of lssvm_train (three launches
+ * and passes over the vectors: 8 reads and 3 writes of N doubles).
  *
  * x, r, d    device, N doubles each, updated in place; q device, N doubles,
  *            read. The four must not overlap.
@@ -277,25 +281,28 @@ const char* lssvm_last_error(void);
  * 0 for an unknown dtype. Informational: sizes need no padding by the caller. */
 int32_t lssvm_tile_size(int32_t dtype);
 
-/* How the implicit products of lssvm_train and lssvm_matvec lay out their
- * upper-triangle tiles over workgroups for n >= 2 points of d features.
+/* How tiles of the upper triangle are laid out over workgroups for n >= 2
+ * points of d features, in rounds of two workgroups per CU.
  * On success writes plan[0..2] (host memory, caller-owned):
  *   plan[0]  workgroups per tile in the full rounds: 1, except for the
  *            linear kernel on problems with few tiles, whose features are
  *            split over 2..16 workgroups per tile (the partial sums add up
  *            because the linear kernel value is the inner product itself);
  *   plan[1]  tiles of a last partial round that run split finer (0 if none):
- *            the linear kernel runs them as the trailing workgroups of
- *            the same launch, split the same additive way; the other
- *            kernels park their partial inner products and sum them in a
- *            fix-up launch;
+ *            they park their partial inner products, which a fix-up launch
+ *            sums (or, in the linear kernel's plan, add up);
  *   plan[2]  workgroups per such tile (plan[0] when plan[1] is 0).
  * Every split leaves an even number of feature blocks per workgroup, except
  * on small problems (n <= 1025 without a split last round, whose CG
  * iterations are single launches): there the linear kernel's tiles split as
  * far as one round of workgroups allows, down to one feature block each.
- * Every product of a problem (CG iterations, residual recomputations,
- * lssvm_matvec) uses the same plan.
+ * The plan is that of these rules alone. Products follow it with these
+ * exceptions: the linear kernel uses tiles only up to 1025 points of at most
+ * 128 features (its other products are passes over the points, which no plan
+ * describes); and the other kernels share out the tiles of problems of up to 256
+ * tiles, and in fp64 those after the last full round of one per CU, in shares
+ * that need not be equal. Every product of a problem (CG iterations, residual
+ * recomputations, lssvm_matvec) is laid out the same way.
  * Returns LSSVM_EINVAL (plan untouched) for n, d, dtype or kernel out of
  * range or a null plan. Informational. */
 int lssvm_tile_plan(int64_t n, int64_t d, int32_t dtype, int32_t kernel, int64_t* plan);

@@ -220,10 +220,14 @@ inline void tail_plan(int64_t nT, int64_t nkb, int64_t* q, int64_t* split) {
 // divide evenly). 1 if the tiles are better left whole: the splits are parked and
 // one more launch sums and finishes the tiles, which costs `cost_us`, so it has to
 // save that. A staged block of 16 features takes a workgroup alone on its CU
-// about 1.8 us in fp64 and 0.5 us in fp32.
+// about 1.8 us in fp64 and 0.5 us in fp32, and a tile's splits are summed one
+// after the other, about 0.6 of a block each, so no more than sqrt(nkb / 0.6) pay:
+// the training at 502 x 2877 fp64 took 1.16 ms with 45 shares and takes 0.78 with
+// 17, 561 x 1207 fp32 0.50 and 0.41.
 inline int64_t share_tiles(int64_t Q, int64_t nkb, int64_t most, double block_us, double cost_us,
                            int64_t* blocks) {
   *blocks = nkb;
+  most = std::min(most, (int64_t)std::sqrt((double)nkb / 0.6));
   const int64_t want = std::min(std::min(kResidentTiles / Q, most), nkb / 4);
   if (want < 2) return 1;
   const int64_t per = round_up((nkb + want - 1) / want, 2), S = (nkb + per - 1) / per;
@@ -234,9 +238,9 @@ inline int64_t share_tiles(int64_t Q, int64_t nkb, int64_t most, double block_us
 
 // Which tiles of the polynomial and RBF kernels' products are split.
 // - Few tiles (at most one per CU) leave most of the chip idle: all of them.
-//   Trainings, whole and split: 502 x 2877 fp64 RBF 4.10 and 1.15 ms, 907 x 1100
-//   2.50 and 1.08, 300 x 4000 fp32 cubic 2.09 and 0.61, 1500 x 2000 fp32 RBF 1.48
-//   and 1.00.
+//   Trainings, whole and split: 502 x 2877 fp64 RBF 4.09 and 0.78 ms, 907 x 1100
+//   2.50 and 1.10, 561 x 1207 fp32 cubic 1.00 and 0.41, 1500 x 2000 fp32 RBF 1.47
+//   and 0.97.
 // - Tiles left after the last full round of two per CU: tail_plan.
 // - Otherwise those left after the last full round of one per CU, where they are
 //   at most two thirds of one, in fp64: the CUs that take one more tile than the

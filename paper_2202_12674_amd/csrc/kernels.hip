@@ -9,7 +9,10 @@
 //                     rank-one and diagonal terms that make it Q~ p (Eqs. (13), (16))
 // a5  k_cg_*          CG vector updates with fixed-order fp64 reductions (Sec. III-B)
 // a6  k_bias          alpha_m and b (Eqs. (11), (15))
-// a7  k_tiles<gen>    decision values sum_j alpha_j k(x_j, x) + b (Eq. (10))
+// a7  k_tiles<gen>    decision values sum_j alpha_j k(x_j, x) + b (Eq. (10));
+//     k_predict_few   the same for up to 128 points, from the caller's rows
+// Linear kernel: k_lin_w, k_lin_rows (products and decision values through w =
+// X^T p), k_lin_train (a whole small training in one workgroup).
 //
 // Every reduction sums in a fixed order (no floating-point atomics), so the
 // results are bitwise reproducible run to run.
@@ -331,7 +334,7 @@ template <> struct PointRow<float> {
 // points, 1024 / PPB threads per point, each summing every (1024 / PPB)-th
 // chunk of the point's row; the point's partial sums are then added in a fixed
 // order. (256 threads left a few hundred points of many features to a few dozen
-// waves: 561 x 1207 fp32 18.7 us, 502 x 2877 fp64 13.9 us; NORMS_US so.) The points of a wave's load instruction are neighbours in the layout:
+// waves: 561 x 1207 fp32 18.7 us, 502 x 2877 fp64 13.9 us; 8.7 and 9.6 us so.) The points of a wave's load instruction are neighbours in the layout:
 // fp64 8 chunks (a whole 128-byte row) of 8 points, fp32 one chunk of 32
 // points (512 contiguous bytes per slice).
 template <typename T> constexpr int kNormPoints = sizeof(T) == 8 ? 16 : 32;
