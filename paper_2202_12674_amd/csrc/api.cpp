@@ -603,6 +603,8 @@ TileArgs<T> sym_args(const Geometry& g, const TrainWs<T>& w, const lssvm_params&
   a.gscale = w.gscale;
   a.gamma = (T)kp.gamma;
   a.coef0 = (T)kp.coef0;
+  a.gamma64 = kp.gamma;
+  a.coef64 = kp.coef0;
   a.rbf_scale = rbf_scale<T>(kp.gamma);
   a.degree = kp.degree;
   a.nTc = g.nT;
@@ -1276,6 +1278,8 @@ int predict_impl(const T* Xtr, const T* alpha, double b, int64_t n, int64_t d, i
   a.gscale = T(1);
   a.gamma = (T)kp.gamma;
   a.coef0 = (T)kp.coef0;
+  a.gamma64 = kp.gamma;
+  a.coef64 = kp.coef0;
   a.rbf_scale = rbf_scale<T>(kp.gamma);
   a.degree = kp.degree;
   a.nTc = w.nTc;

@@ -1888,6 +1888,9 @@ inline bool blocks_ok(const TileArgs<T>& a) {
          per * (a.ksplit - 1) < a.nkb;
 }
 
+// Splits of a single staged block exist in fp64 only: fp32's are half a planned one.
+template <typename T> constexpr bool kOneBlock = TileShape<T>::SB == TileShape<T>::BK;
+
 template <typename T, bool SYM, int PART>
 hipError_t launch_tiles(TileArgs<T> a, int kernel, int64_t nwg, hipStream_t s) {
   if (SYM && !blocks_ok(a)) return hipErrorInvalidValue;
@@ -1896,12 +1899,19 @@ hipError_t launch_tiles(TileArgs<T> a, int kernel, int64_t nwg, hipStream_t s) {
     a.tile_base = base;
     const dim3 grid((unsigned)std::min(kMaxTileGrid, nwg - base));
     switch (kernel) {
-      case KLIN:
-        if (SYM && PART == kWhole && a.nkb == a.ksplit)   // a single feature block each
-          hipLaunchKernelGGL((k_tiles_one<T>), grid, dim3(256), 0, s, a);
-        else
+      case KLIN:   // whole symmetric tiles only (its splits add up, its scores need none)
+        if constexpr (SYM && PART == kWhole) {
+          if constexpr (kOneBlock<T>) {
+            if (a.nkb == a.ksplit) {
+              hipLaunchKernelGGL((k_tiles_one<T>), grid, dim3(256), 0, s, a);
+              break;
+            }
+          }
           hipLaunchKernelGGL((k_tiles<T, SYM, KLIN, PART>), grid, dim3(256), 0, s, a);
-        break;
+          break;
+        } else {
+          return hipErrorInvalidValue;
+        }
       case KPOLY:
         hipLaunchKernelGGL((k_tiles<T, SYM, KPOLY, PART>), grid, dim3(256), 0, s, a);
         break;
@@ -1943,10 +1953,13 @@ hipError_t launch_tiles_cg(const TileArgs<T>& a0, int kernel, int part, int64_t 
     return hipErrorInvalidValue;
   switch (kernel) {
     case KLIN:
-      if (a.nkb == a.ksplit)   // a single feature block each
-        hipLaunchKernelGGL((k_tiles_cg<T, KLIN, kWhole, true>), grid, dim3(256), 0, s, a, f);
-      else
-        hipLaunchKernelGGL((k_tiles_cg<T, KLIN, kWhole, false>), grid, dim3(256), 0, s, a, f);
+      if constexpr (kOneBlock<T>) {
+        if (a.nkb == a.ksplit) {
+          hipLaunchKernelGGL((k_tiles_cg<T, KLIN, kWhole, true>), grid, dim3(256), 0, s, a, f);
+          break;
+        }
+      }
+      hipLaunchKernelGGL((k_tiles_cg<T, KLIN, kWhole, false>), grid, dim3(256), 0, s, a, f);
       break;
     case KPOLY:
       if (fixup)

@@ -55,6 +55,7 @@ struct TileArgs {
   T gscale;   // fp32: what the stored points' inner products are multiplied by, a power
               // of two: 1 unless they were stored scaled up (k_layout_split)
   T gamma, coef0;
+  double gamma64, coef64;   // fp32 polynomial: its kernel values are formed in fp64
   T rbf_scale;   // RBF exponent scale: gamma (fp64, exp) or gamma log2(e) (fp32, exp2)
   int degree;
   int64_t nTc;   // column tiles (general mode); tiles per side (symmetric mode)

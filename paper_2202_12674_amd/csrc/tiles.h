@@ -11,6 +11,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <type_traits>
 
 namespace lssvm {
 namespace {
@@ -695,6 +696,15 @@ __device__ __forceinline__ bool tile_body(const TileArgs<T>& a) {
   // above the diagonal for both triangles, as off-diagonal tiles do, and half
   // of each diagonal value (exact) for either.
   constexpr bool HALF = SYM && SPLIT;
+  // The fp32 polynomial's base and power are formed in fp64 (an fma and a few
+  // products, as many as in fp32): rounded to fp32 they, and no longer the inner
+  // products, were most of its error. The training at 32768 x 4096, 8 inputs: alpha
+  // 1.09e-5 from the converged one (1.68e-5 so rounded, 1.84e-5 on the fp32
+  // instruction), b 1.9e-5 in the mean and 4.8e-5 at worst (3.0e-5 and 1.4e-4;
+  // 3.3e-5 and 1.3e-4), 25 iterations each time (25 to 27). The product costs the
+  // same at 4096 features and 4.5% more at 512 (2.65 and 2.77 ms, 32768 points).
+  constexpr bool POLY64 = SPLIT && KER == KPOLY;
+  using KT = typename std::conditional<POLY64, double, T>::type;
   double fxs = 1.0;   // fixed-point scale of the row sums (symmetric mode)
   if constexpr (SYM) {
     fxs = fixed_scale<KER>(a, fx_pmax, fx_nmax);
@@ -724,7 +734,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs<T>& a) {
   for (int i = 0; i < RB; ++i) {
 #pragma unroll
   for (int v0 = 0; v0 < MF::NACC; v0 += VH) {
-    T kv[VH][CB];
+    KT kv[VH][CB];
     double pAi[VH];
 #pragma unroll
     for (int vv = 0; vv < VH; ++vv) {
@@ -733,8 +743,10 @@ __device__ __forceinline__ bool tile_body(const TileArgs<T>& a) {
       pAi[vv] = SYM ? vp[0][li] : 0.0;
 #pragma unroll
       for (int j = 0; j < CB; ++j)
-        kv[vv][j] = kernel_value<KER, T>(acc[i][j][v0 + vv], nAi, nBj[j], a.gamma, a.coef0,
-                                         a.rbf_scale);
+        if constexpr (POLY64) kv[vv][j] = a.gamma64 * (double)acc[i][j][v0 + vv] + a.coef64;
+        else
+          kv[vv][j] = kernel_value<KER, T>(acc[i][j][v0 + vv], nAi, nBj[j], a.gamma, a.coef0,
+                                           a.rbf_scale);
     }
     if constexpr (KER == KPOLY) poly_power(kv, a.degree);
     if (HALF && diag) {   // uniform
@@ -744,7 +756,7 @@ __device__ __forceinline__ bool tile_body(const TileArgs<T>& a) {
 #pragma unroll
         for (int j = 0; j < CB; ++j) {
           const int lj = wn * C::WN + j * MF::M + cl;
-          kv[vv][j] *= li < lj ? T(1) : (li == lj ? T(0.5) : T(0));
+          kv[vv][j] *= li < lj ? KT(1) : (li == lj ? KT(0.5) : KT(0));
         }
       }
     }
