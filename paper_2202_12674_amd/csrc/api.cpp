@@ -110,12 +110,12 @@ struct Geometry {
 // Small problems run each CG iteration (except the residual recomputations)
 // as one launch: the product's tiles and, in the last workgroup, the vector
 // work (launch_tiles_cg). Their iterations are launch-bound: four dependent
-// launches of a few microseconds each against a product of ~10 us. (At 4096
-// points the same fusion cost more than it saved: the release and ticket of
-// each of ~1000 workgroups made the launch ~50 us longer than the product.)
+// launches of a few microseconds each against a product of ~10 us. Up to
+// kFusedMaxNP, where both are measured.
 inline bool fused_iteration(const Geometry& g, int32_t kernel) {
   const bool one_launch = kernel != LSSVM_LINEAR || g.lin_tail_q == 0;
-  return LSSVM_FUSED_SMALL && g.NP <= kFusedMaxNP && one_launch;
+  const int64_t most = kernel == LSSVM_LINEAR ? kFusedMaxLinear : kFusedMaxNP;
+  return LSSVM_FUSED_SMALL && g.NP <= most && one_launch;
 }
 
 // Linear products run in two passes over the points, w = X^T p and X w (k_lin_w,
@@ -287,7 +287,7 @@ Geometry geometry(int64_t n, int64_t d) {
   // a plan shares them out: in fp32, whose staged blocks are half a planned
   // one, that can be 32 features of padding more.
   const int64_t W = tri_count(g.nT);
-  const bool shared = (g.tail_q > 0 && W > kCUs) || g.NP <= kFusedMaxNP;
+  const bool shared = (g.tail_q > 0 && W > kCUs) || g.NP <= kFusedMaxLinear;
   g.d_pad = shared ? g.plan_nkb * g.bk : round_up(d, 2 * TileShape<T>::SB);
   part_plan(W, g.tail_q, g.tail_split, g.d_pad / TileShape<T>::SB, sizeof(T) == 8,
             &g.part_q, &g.part_split, &g.part_blocks);

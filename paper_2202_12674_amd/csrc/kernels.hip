@@ -1667,10 +1667,11 @@ __global__ __launch_bounds__(256) void k_finish_sum(const double* bpart, int64_t
 // k_cg_update and k_cg_direction do, for all rows at once. Each workgroup
 // fences its partial sums (device-scope release) before it takes a ticket;
 // the one that draws the last ticket fences again (acquire) and reads them
-// all. Rows r = tid + 256 k sit in registers (NP <= 1024 -> k < 4). ONE:
+// all. Rows r = tid + 256 k, k < R, sit in registers: R = 4 for NP <= 1024, else 8
+// (8 for all cost the small ones 3 to 6%). ONE:
 // linear tiles split into single feature blocks (see tile_body). PART: whole
 // tiles, or the fixup of tiles parked by a launch before.
-template <typename T, int KER, int PART, bool ONE>
+template <typename T, int KER, int PART, bool ONE, int R>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_tiles_cg(
     TileArgs<T> a, FusedCg f) {
   if (!tile_body<T, true, KER, PART, ONE>(a)) return;   // CG had already stopped
@@ -1689,7 +1690,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   __syncthreads();
   if (!last) return;
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  constexpr int R = (int)(kFusedMaxNP / NT);
   // Every global load of the vector step is issued here, at once: placed
   // where it is used, each would wait for the barrier of the reduction before
   // it and then for its own round trip, one after the other.
@@ -1940,38 +1940,46 @@ hipError_t launch_tiles_gen(const TileArgs<T>& a, int kernel, int64_t nTr, hipSt
   return launch_tiles<T, false, kWhole>(a, kernel, nTr * a.nTc, s);
 }
 
+template <typename T, int KER, int PART, bool ONE = false>
+static void tiles_cg(const TileArgs<T>& a, const FusedCg& f, hipStream_t s) {
+  const dim3 grid((unsigned)a.ntiles);
+  if constexpr (KER != KLIN) {   // linear ones are small: kFusedMaxLinear
+    if (f.NP > 4 * NT) {
+      hipLaunchKernelGGL((k_tiles_cg<T, KER, PART, ONE, 8>), grid, dim3(256), 0, s, a, f);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_tiles_cg<T, KER, PART, ONE, 4>), grid, dim3(256), 0, s, a, f);
+}
+
 template <typename T>
 hipError_t launch_tiles_cg(const TileArgs<T>& a0, int kernel, int part, int64_t nwg,
                            const FusedCg& f, hipStream_t s) {
-  if (nwg > kMaxTileGrid) return hipErrorInvalidValue;   // small problems only: one chunk
+  static_assert(kFusedMaxNP <= 8 * NT && kFusedMaxLinear <= 4 * NT, "rows in registers");
   TileArgs<T> a = a0;
   a.ntiles = nwg;
   a.tile_base = 0;
-  const dim3 grid((unsigned)nwg);
   const bool fixup = part == kFixup;
-  if ((kernel != KLIN && !fixup && a.ksplit != 1) || (kernel == KLIN && fixup) || !blocks_ok(a))
+  if (nwg > kMaxTileGrid || f.NP > (kernel == KLIN ? kFusedMaxLinear : kFusedMaxNP) ||
+      (kernel != KLIN && !fixup && a.ksplit != 1) || (kernel == KLIN && fixup) || !blocks_ok(a))
     return hipErrorInvalidValue;
   switch (kernel) {
     case KLIN:
       if constexpr (kOneBlock<T>) {
-        if (a.nkb == a.ksplit) {
-          hipLaunchKernelGGL((k_tiles_cg<T, KLIN, kWhole, true>), grid, dim3(256), 0, s, a, f);
+        if (a.nkb == a.ksplit) {   // a single feature block each
+          tiles_cg<T, KLIN, kWhole, true>(a, f, s);
           break;
         }
       }
-      hipLaunchKernelGGL((k_tiles_cg<T, KLIN, kWhole, false>), grid, dim3(256), 0, s, a, f);
+      tiles_cg<T, KLIN, kWhole>(a, f, s);
       break;
     case KPOLY:
-      if (fixup)
-        hipLaunchKernelGGL((k_tiles_cg<T, KPOLY, kFixup, false>), grid, dim3(256), 0, s, a, f);
-      else
-        hipLaunchKernelGGL((k_tiles_cg<T, KPOLY, kWhole, false>), grid, dim3(256), 0, s, a, f);
+      if (fixup) tiles_cg<T, KPOLY, kFixup>(a, f, s);
+      else tiles_cg<T, KPOLY, kWhole>(a, f, s);
       break;
     default:
-      if (fixup)
-        hipLaunchKernelGGL((k_tiles_cg<T, KRBF, kFixup, false>), grid, dim3(256), 0, s, a, f);
-      else
-        hipLaunchKernelGGL((k_tiles_cg<T, KRBF, kWhole, false>), grid, dim3(256), 0, s, a, f);
+      if (fixup) tiles_cg<T, KRBF, kFixup>(a, f, s);
+      else tiles_cg<T, KRBF, kWhole>(a, f, s);
       break;
   }
   return hipGetLastError();

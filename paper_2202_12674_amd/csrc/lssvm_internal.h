@@ -125,8 +125,14 @@ struct FusedCg {
   int par;            // r^T r of the current iterate lives in S_DHIST + par
 };
 // Largest padded length the fused iteration handles: one workgroup reads every
-// row sum and keeps each thread's rows (NP / 256) in registers.
-constexpr int64_t kFusedMaxNP = 1024;
+// row sum and keeps each thread's rows (NP / 256) in registers. Trainings, fused
+// and with a launch per vector step: 1900 x 100 fp32 RBF 1.04 and 1.43 ms, 1038 x 66
+// fp64 0.94 and 1.09, 2040 x 50 1.21 and 1.28. (At 4096 points the release and
+// ticket of each of the workgroups made the launch ~50 us longer than the
+// product, more than the launches cost.)
+constexpr int64_t kFusedMaxNP = 2048;
+// ... of the linear kernel, whose larger problems are passes over the points.
+constexpr int64_t kFusedMaxLinear = 1024;
 
 // The symmetric tiles' visit order (GROUP x GROUP super-tiles), packed
 // (I << 16) | J, nT (nT + 1) / 2 entries.
@@ -158,8 +164,8 @@ template <typename T>
 hipError_t launch_tiles_gen(const TileArgs<T>& a, int kernel, int64_t nTr, hipStream_t s);
 // A whole CG iteration for small problems (NP <= kFusedMaxNP) in one launch of
 // whole tiles, or in the fixup launch of split ones: the symmetric tiles of q =
-// Q~ d, then the workgroup that finishes last (an atomic ticket after a device-scope release fence) adds the
-// rank-one terms and does the update and the new direction, with the same
+// Q~ d, then the workgroup that finishes last (an atomic ticket after a
+// device-scope release fence) adds the rank-one terms and does the update and the new direction, with the same
 // status, stop test and breakdown handling as the separate kernels. Nothing
 // waits on another workgroup.
 template <typename T>
