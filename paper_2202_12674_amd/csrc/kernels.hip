@@ -1011,16 +1011,21 @@ enum LinP : int { P_VEC = 0, P_DIR = 1, P_ALPHA = 2 };
 
 // Sums of the linear passes carry their rounding errors along (an unevaluated
 // pair hi + lo: the exact error of a product by fma, of an addition by Knuth's
-// two-sum), so K p is rounded once, at the end. Memory-bound either way.
+// two-sum), so K p is rounded once, at the end. Contraction stays off in them:
+// an a * b merged into the additions that use p has its error counted twice
+// (2e-18 of sum |a b| over 1024 terms instead of some 1e-32, more where the sum
+// cancels). Ten instructions per value either way, and memory-bound.
 struct Pair {
   double hi, lo;
 };
 __device__ inline void pair_add(Pair& s, double v) {
+#pragma clang fp contract(off)
   const double t = s.hi + v, z = t - s.hi;
   s.lo += (s.hi - (t - z)) + (v - z);
   s.hi = t;
 }
 __device__ inline void pair_fma(Pair& s, double a, double b) {   // s += a b
+#pragma clang fp contract(off)
   const double p = a * b;
   s.lo += __builtin_fma(a, b, -p);
   pair_add(s, p);

@@ -81,3 +81,56 @@ def test_nonfinite_points_leave_the_outputs_untouched(torch_dev):
     with pytest.raises(P.LssvmError) as e:
         P.train(X, torch.cat([y, y[:1]]))
     assert e.value.code == -2
+
+
+def _exact(a):
+    from fractions import Fraction
+    return [Fraction(float(v)) for v in a]
+
+
+# four-wave rows with 16-byte and element-wise loads, a wave per four rows
+@pytest.mark.parametrize("d", [2000, 1101, 300])
+def test_scores_that_cancel_keep_the_pairs_bits(torch_dev, d):
+    """Decision values whose terms cancel to their last bits, against exact
+    rational sums. hi + lo holds every product's and every addition's error but
+    for the roundings of lo itself: below (d + n) 2^-53 times what lo can hold,
+    (d + n) 2^-53 sum |terms|. A sum that counts one error twice, or none, is
+    off by 1e-18 of the terms or more."""
+    torch, dev = torch_dev
+    import paper_2202_12674_amd as P
+    rng = np.random.default_rng(d)
+    n = 3
+    X, alpha = rng.standard_normal((n, d)), rng.standard_normal(n)
+    w = [sum(a * x for a, x in zip(_exact(alpha), _exact(X[:, k]))) for k in range(d)]
+    Y = rng.standard_normal((9, d))
+    ref, mag = [], []
+    for t in range(9):
+        head = sum(y * v for y, v in zip(_exact(Y[t, :-1]), w))
+        Y[t, -1] = float(-head / w[-1])
+        terms = [y * v for y, v in zip(_exact(Y[t]), w)]
+        ref.append(sum(terms))
+        mag.append(float(sum(abs(v) for v in terms)))
+    s, _ = P.predict(*(torch.from_numpy(v).to(dev) for v in (X, alpha)), 0.0,
+                     torch.from_numpy(Y).to(dev))
+    for t, got in enumerate(_exact(s.cpu().numpy())):
+        bar = ((d + n) * 2.0 ** -53) ** 2 * mag[t] + 2.0 ** -52 * abs(float(ref[t]))
+        assert abs(float(got - ref[t])) <= bar, (t, float(got - ref[t]) / mag[t])
+
+
+def test_weights_that_cancel_keep_the_pairs_bits(torch_dev):
+    """The same over the points: w_0 = sum alpha_i x_i0 cancels, over many chunks
+    of rows; the score of e_0 is w_0."""
+    torch, dev = torch_dev
+    import paper_2202_12674_amd as P
+    rng = np.random.default_rng(4)
+    n, d = 4001, 5
+    X, alpha = rng.standard_normal((n, d)), rng.standard_normal(n)
+    x0, a = _exact(X[:, 0]), _exact(alpha)
+    alpha[-1] = float(-sum(u * v for u, v in zip(x0[:-1], a[:-1])) / x0[-1])
+    terms = [u * v for u, v in zip(x0, _exact(alpha))]
+    Y = np.eye(1, d)
+    s, _ = P.predict(*(torch.from_numpy(v).to(dev) for v in (X, alpha)), 0.0,
+                     torch.from_numpy(Y).to(dev))
+    bar = ((d + n) * 2.0 ** -53) ** 2 * float(sum(map(abs, terms))) + \
+        2.0 ** -52 * abs(float(sum(terms)))
+    assert abs(float(_exact(s.cpu().numpy())[0] - sum(terms))) <= bar
