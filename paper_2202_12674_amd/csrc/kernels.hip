@@ -1316,7 +1316,9 @@ __global__ __launch_bounds__(256) void k_lin_rows(const T* __restrict__ X, int64
 #pragma unroll
         for (int v = 1; v < CS; ++v) pair_join(own, red[v][orow]);
       }
-      const double f = own.hi + own.lo;
+      double f = own.hi + own.lo;
+      // a score beyond the range is the plain sum's infinity (lo is NaN there)
+      if (M == R_SCORE && !__builtin_isfinite(own.hi)) f = own.hi;
       if (i < nrows) {
         if constexpr (M == R_Q) {
           if (i == m) c.scal[S_KMM] = f;

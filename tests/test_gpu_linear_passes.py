@@ -134,3 +134,20 @@ def test_weights_that_cancel_keep_the_pairs_bits(torch_dev):
     bar = ((d + n) * 2.0 ** -53) ** 2 * float(sum(map(abs, terms))) + \
         2.0 ** -52 * abs(float(sum(terms)))
     assert abs(float(_exact(s.cpu().numpy())[0] - sum(terms))) <= bar
+
+
+@pytest.mark.parametrize("d", [5, 2000])
+def test_scores_that_overflow_are_infinite(torch_dev, d):
+    """An infinite coefficient, or values whose products overflow, give infinite
+    scores of the plain sums' sign, not NaN."""
+    torch, dev = torch_dev
+    import paper_2202_12674_amd as P
+    X = torch.rand(40, d, dtype=torch.float64, device=dev) + 0.5
+    Y = torch.rand(6, d, dtype=torch.float64, device=dev) + 0.5
+    Y[3:] *= -1.0
+    for a, scale in ((float("inf"), 1.0), (1e200, 1e200)):
+        alpha = torch.full((40,), 1.0, dtype=torch.float64, device=dev)
+        alpha[17] = a
+        s, lab = P.predict(X * scale, alpha, 0.5, Y)
+        assert s.tolist() == [float("inf")] * 3 + [-float("inf")] * 3
+        assert lab.tolist() == [1] * 3 + [-1] * 3
