@@ -370,8 +370,8 @@ struct PredictWs {
   T *ntr, *nte, *alpha;
   double* part;
   int* flags;
-  double* few_part;  // few test points: partial scores, and whether a workgroup met
-  int* few_bad;      // a value that is not finite
+  double* few_part;  // few test points (over the layouts): partial scores, and whether
+  int* few_bad;      // a workgroup met a value that is not finite
   double* lin_part;  // linear kernel: partial sums of w over point chunks
   double* lin_w;     // linear kernel: w = sum_i alpha_i x_i
   double* lin_f;     // linear kernel: <w, x> per test point
@@ -396,12 +396,17 @@ PredictWs<T> carve_predict(const Geometry& g, int64_t n_test, void* base) {
   w.lin_part = c.take<double>(2 * lin_max_chunks(g.n, g.d) * g.d);
   w.lin_w = c.take<double>(2 * g.d);
   w.lin_f = c.take<double>(n_test);
-  if (n_test <= kFewTests) {
-    const int64_t slots = predict_few_slots(g.n, n_test);
-    w.few_part = c.take<double>(slots * n_test);
-    w.few_bad = c.take<int>(slots);
-  }
   w.bytes = c.off;
+  if (n_test <= kFewTests) {
+    // in place of the layouts, which few points do not use: at most 34 bytes per
+    // model point, where a panel of the model takes 192 or more, so the size does
+    // not depend on the path and never falls as n_test grows
+    Carver f(base);
+    const int64_t slots = predict_few_slots(g.n, n_test);
+    w.few_part = f.take<double>(slots * n_test);
+    w.few_bad = f.take<int>(slots);
+    w.bytes = std::max(w.bytes, f.off);
+  }
   return w;
 }
 

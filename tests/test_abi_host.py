@@ -67,6 +67,16 @@ def test_workspace_sizes_at_the_supported_limits():
         assert L.lssvm_predict_workspace_bytes(2, 1, wide + 1, dt) == 0
 
 
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("n,d", [(1, 1), (15, 3), (300, 30), (2000, 65), (32768, 32),
+                                 (32768, 100), (32768, 512), (70000, 1000)])
+def test_predict_workspace_never_falls_as_test_points_grow(n, d, dtype):
+    """A workspace sized for the largest batch serves every smaller one."""
+    L = P.lib()
+    sizes = [L.lssvm_predict_workspace_bytes(n, t, d, dtype) for t in range(1, 2001)]
+    assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+
+
 def test_workspace_grows_with_the_points_not_their_square():
     """A product's row sums take two 64-bit words per row (fixed-point
     accumulators), not a partial slot per tile column: at 2^20 points of 16
