@@ -1386,7 +1386,9 @@ __global__ __launch_bounds__(kLinTrainThreads) void k_lin_train(const T* __restr
                                                     const T* __restrict__ y, int n, int d,
                                                     LinTrain a, T* __restrict__ alpha_out) {
   __shared__ __attribute__((aligned(16))) char lds[kLinTrainLds];
-  __shared__ double red[8][16];   // one reduction's wave sums each
+  // one reduction's wave sums each; a slot is written again only behind a barrier
+  // that follows its reads (the last sums have slots of their own: CG may take none)
+  __shared__ double red[9][16];
   const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6, N = n - 1;
   const int ld = (int)lin_train_ld(d), G = lin_train_lanes(d), H = lin_train_lanes(n);
   T* xs = reinterpret_cast<T*>(lds);
@@ -1522,9 +1524,9 @@ __global__ __launch_bounds__(kLinTrainThreads) void k_lin_train(const T* __restr
 
   // ---- alpha_m, b (k_bias), the report
   put(6, owner ? x : 0.0);
-  put(0, owner ? qi * x : 0.0);
+  put(8, owner ? qi * x : 0.0);
   __syncthreads();
-  const double sx = get(6), sqx = get(0);
+  const double sx = get(6), sqx = get(8);
   if (inflags == 0 && !broke) {
     if (owner) alpha_out[row] = (T)x;
     if (tid == 0) alpha_out[N] = (T)(-sx);

@@ -69,3 +69,17 @@ def test_bad_inputs_are_reported(torch_dev, what):
     with pytest.raises(P.LssvmError) as e:
         P.train(X, y)
     assert e.value.code == (-2 if what == "point" else -3)
+
+
+def test_nothing_to_solve_beside_overflowing_values(torch_dev):
+    """Equal labels end before the first iteration whatever q holds: alpha = 0 in
+    every run, also where q_i overflows (b is then NaN, as 0 times it is)."""
+    torch, dev = torch_dev
+    import paper_2202_12674_amd as P
+    X = torch.rand(256, 64, dtype=torch.float64, device=dev) + 0.5
+    y = torch.ones(256, dtype=torch.float64, device=dev)
+    for scale in (1.0, 1e200):
+        for _ in range(20):
+            r = P.train(X * scale, y, C=1.0, eps=1e-10)
+            assert r.converged and r.iterations == 0 and bool((r.alpha == 0).all())
+            assert r.b == 1.0 if scale == 1.0 else np.isnan(r.b)
