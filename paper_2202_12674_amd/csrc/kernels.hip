@@ -135,6 +135,16 @@ __device__ inline double block_max(double v, double* sh) {
   return m;
 }
 
+// The stop flag, as one thread of the block reads it: in a launch that may raise
+// the flag itself, waves that each read it could disagree, and those that stay
+// would sum over a partial that the others never wrote.
+__device__ inline bool block_stopped(const double* scal) {
+  __shared__ int stopped;
+  if (threadIdx.x == 0) stopped = scal[S_STATUS + ST_DONE] != 0.0;
+  __syncthreads();
+  return stopped != 0;
+}
+
 // Raise scal[S_PMAX], the bound on |p_j| that fixes the next product's
 // fixed-point scale, to m >= 0: the bits of non-negative doubles order like
 // their values, so an integer atomic max keeps the largest whatever the order.
@@ -511,7 +521,7 @@ __global__ __launch_bounds__(256) void k_cg_update(int x_only, const double* __r
                                                    double* __restrict__ x, double* __restrict__ r,
                                                    double* bp_out, int64_t NP) {
   __shared__ double sh[NT / 64];
-  if (scal[S_STATUS + ST_DONE] != 0.0) return;
+  if (block_stopped(scal)) return;
   const double gam = sum_partials(bp_in, nb, sh);
   const double delta = scal[S_DHIST + par];
   const double alpha = delta / gam;
@@ -623,7 +633,7 @@ __global__ __launch_bounds__(256) void k_cg_direction(const double* __restrict__
                                                       double* __restrict__ scalars) {
   __shared__ double sh[NT / 64];
   double* st = scal + S_STATUS;
-  if (st[ST_DONE] != 0.0) {
+  if (block_stopped(scal)) {
     if (scalars && blockIdx.x == 0 && threadIdx.x == 0) {
       scalars[0] = scal[S_DHIST + par];
       scalars[1] = scal[S_GAMMA];
@@ -1112,7 +1122,9 @@ __global__ __launch_bounds__(256) void k_lin_w(const T* __restrict__ X, int64_t 
   auto tile_rows = [&](int64_t r0) { return (int)(i1 - r0 < kLinTile ? i1 - r0 : kLinTile); };
   load_rows(i0, tile_rows(i0), wave);
   double beta = 0.0;
-  if constexpr (P != P_ALPHA) {
+  if constexpr (P == P_DIR) {   // this launch may raise the flag
+    if (v.stop && block_stopped(v.scal)) return;
+  } else if constexpr (P == P_VEC) {
     if (v.stop && v.scal[S_STATUS + ST_DONE] != 0.0) return;
   }
   if constexpr (P == P_DIR) {

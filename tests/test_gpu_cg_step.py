@@ -90,6 +90,22 @@ def test_cg_step_breakdown_keeps_vectors(torch_dev):
     assert got[0] == 7.0 and got[1] == -float(n) and got[3] == 0.0
 
 
+@pytest.mark.parametrize("n", [300000, 1000003])
+def test_cg_step_breakdown_keeps_long_vectors(torch_dev, n):
+    """The same over more blocks than run at once, where the launch that finds
+    the breakdown raises the stop flag while its later blocks test it."""
+    torch, dev = torch_dev
+    import paper_2202_12674_amd as P
+    x, r, d = (torch.full((n,), v, dtype=torch.float64, device=dev) for v in (1.0, 2.0, 3.0))
+    q = -d
+    ws = P.alloc_workspace(P.lib().lssvm_cg_step_workspace_bytes(n), dev)
+    for _ in range(50):
+        sc = torch.tensor([7.0, 0, 0, 0], dtype=torch.float64, device=dev)
+        P.cg_step(x, r, d, q, sc, workspace=ws)
+        assert bool((x == 1.0).all() & (r == 2.0).all() & (d == 3.0).all())
+        assert sc.tolist() == [7.0, -9.0 * n, 7.0 / (-9.0 * n), 0.0]
+
+
 @pytest.mark.parametrize("dtype,published", [("float32", 157.3), ("float64", 78.6)])
 def test_mfma_peak_probe_is_plausible(torch_dev, dtype, published):
     """The measured matrix-core loop rate lies near the published peak (one
