@@ -224,14 +224,29 @@ inline void tail_plan(int64_t nT, int64_t nkb, int64_t* q, int64_t* split) {
 // after the other, about 0.6 of a block each, so no more than sqrt(nkb / 0.6) pay:
 // the training at 502 x 2877 fp64 took 1.16 ms with 45 shares and takes 0.78 with
 // 17, 561 x 1207 fp32 0.50 and 0.41.
-inline int64_t share_tiles(int64_t Q, int64_t nkb, int64_t most, double block_us, double cost_us,
+//
+// Beyond 256 shares some CUs take two, which share its matrix cores. In fp64 those
+// are busy with one workgroup already and the launch waits for the CUs with two,
+// 3.3 us per block; in fp32 a block takes up to 0.9 us as more CUs have two.
+// Trainings whole and so shared: fp64 2800 x 260 (253 tiles, 506 shares) 1.54 and
+// 2.05 ms, 2040 x 200 (136, 408) 1.30 and 1.57, 2800 x 1200 3.20 and 3.35, but 2040
+// x 420 1.66 and 1.59, 2800 x 2000 4.93 and 4.77; fp32 2800 x 800 0.65 and 0.71, 2800
+// x 1200 0.75 and 0.78, but 2200 x 1200 (171, 342) 0.75 and 0.70, 2040 x 800 0.54 and
+// 0.50, 2800 x 2000 1.06 and 1.04.
+inline int64_t share_tiles(int64_t Q, int64_t nkb, int64_t most, bool fp64, double cost_us,
                            int64_t* blocks) {
   *blocks = nkb;
   most = std::min(most, (int64_t)std::sqrt((double)nkb / 0.6));
   const int64_t want = std::min(std::min(kResidentTiles / Q, most), nkb / 4);
   if (want < 2) return 1;
   const int64_t per = round_up((nkb + want - 1) / want, 2), S = (nkb + per - 1) / per;
-  if (S < 2 || (double)(nkb - per) * block_us < cost_us) return 1;
+  const double block_us = fp64 ? 1.8 : 0.5, whole = (double)nkb * block_us;
+  if (S < 2 || whole - (double)per * block_us < cost_us) return 1;
+  if (Q * S > kCUs) {
+    const double two = (double)(Q * S - kCUs) / kCUs;   // of the CUs
+    const double each = fp64 ? 3.32 : block_us + 0.38 * two;
+    if (whole - (double)per * each < (fp64 ? cost_us + 2.0 : 7.0)) return 1;
+  }
   *blocks = per;
   return S;
 }
@@ -250,20 +265,19 @@ inline int64_t share_tiles(int64_t Q, int64_t nkb, int64_t most, double block_us
 //   (3000 x 4000 0.260 and 0.262, 4358 x 1110 0.134 and 0.132).
 inline void part_plan(int64_t W, int64_t tail_q, int64_t tail_split, int64_t nkb, bool fp64,
                       int64_t* q, int64_t* split, int64_t* blocks) {
-  const double block_us = fp64 ? 1.8 : 0.5;
   *q = 0;
   *split = 1;
   *blocks = nkb;
   if (W < 1) return;
   if (W <= kCUs) {
-    *split = share_tiles(W, nkb, 64, block_us, 12.0, blocks);
+    *split = share_tiles(W, nkb, 64, fp64, 12.0, blocks);
     *q = *split > 1 ? W : 0;
   } else if (tail_q > 0) {
     *q = tail_q;
     *split = tail_split;
     *blocks = nkb / tail_split;
   } else if (fp64 && W % kCUs > 0 && W % kCUs <= kResidentTiles / 3) {
-    *split = share_tiles(W % kCUs, nkb, 16, block_us, 24.0, blocks);
+    *split = share_tiles(W % kCUs, nkb, 16, fp64, 24.0, blocks);
     *q = *split > 1 ? W % kCUs : 0;
   }
 }

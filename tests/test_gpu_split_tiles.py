@@ -23,10 +23,10 @@ def _reduced(kernel, X, C, gamma):
 
 # (one tile, uneven shares; three; fused trainings, the last of 4 rows a thread and
 # the first and last of 8; the first not fused; 351 and 300 tiles: 95 and 44 of
-# them split in fp64)
+# them split in fp64; 136 tiles in 408 shares in fp64, 253 left whole)
 @pytest.mark.parametrize("n,d", [(2, 5000), (129, 1100), (257, 333), (502, 2877), (907, 1100),
                                  (1025, 700), (1026, 40), (1400, 1000), (2049, 70),
-                                 (2050, 300), (3300, 800), (3000, 513)])
+                                 (2050, 300), (3300, 800), (3000, 513), (2040, 420), (2800, 260)])
 @pytest.mark.parametrize("kernel,dtype", [("poly", "f64"), ("rbf", "f32"), ("rbf", "f64"),
                                           ("poly", "f32")])
 def test_product_and_training(torch_dev, kernel, dtype, n, d):
