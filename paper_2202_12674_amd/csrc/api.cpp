@@ -1255,8 +1255,8 @@ int predict_impl(const T* Xtr, const T* alpha, double b, int64_t n, int64_t d, i
     a.n = n;
     a.n_test = n_test;
     a.d = d;
-    a.gamma = (T)kp.gamma;
-    a.coef0 = (T)kp.coef0;
+    a.gamma = kp.gamma;
+    a.coef0 = kp.coef0;
     a.rbf_scale = rbf_scale<T>(kp.gamma);
     a.degree = kp.degree;
     a.part = w.few_part;

@@ -955,12 +955,15 @@ __global__ __launch_bounds__(256) void k_predict_few(PredictFew<T> a) {
       double nr = 0.0;
       if constexpr (KER == KRBF)
         nr = ((nrm[0][0][r] + nrm[0][1][r]) + nrm[0][2][r]) + nrm[0][3][r];
-      T kv = kernel_value<KER, T>(g[r * LDG + c], (T)nt, (T)nr, a.gamma, a.coef0, a.rbf_scale);
+      double kv;   // the polynomial's base and power in fp64, as on tiles
       if constexpr (KER == KPOLY) {
-        const T base = kv;
+        const double base = a.gamma * (double)g[r * LDG + c] + a.coef0;
+        kv = base;
         for (int e = 1; e < a.degree; ++e) kv *= base;
+      } else {
+        kv = (double)kernel_value<KER, T>(g[r * LDG + c], (T)nt, (T)nr, T(0), T(0), a.rbf_scale);
       }
-      total += (double)kv * (double)a.alpha[i];
+      total += kv * (double)a.alpha[i];
     }
     __syncthreads();   // g and nrm are free
   }

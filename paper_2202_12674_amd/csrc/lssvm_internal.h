@@ -257,7 +257,8 @@ struct PredictFew {
   const T *Xtr, *Xte, *alpha;
   int64_t n, n_test, d;
   int vec;   // set by the launcher
-  T gamma, coef0, rbf_scale;
+  double gamma, coef0;
+  T rbf_scale;
   int degree;
   double* part;
   int* bad;

@@ -66,3 +66,20 @@ def test_nonfinite_values_leave_the_outputs_untouched(torch_dev, where):
     code = P.lib().lssvm_predict(p[0], p[1], 0.0, 500, 9, 0, 1, ctypes.byref(kp), p[2], 5, p[3],
                                  ws.numel(), p[4], None, None)
     assert code == B.ENONFINITE and bool((s == 7.0).all())
+
+
+@pytest.mark.parametrize("nt", [5, 128, 129])
+def test_fp32_polynomial_values_are_formed_in_fp64(torch_dev, nt):
+    """Inner products that fp32 holds exactly: what is left is the rounding of
+    the score, 2^-24, whichever path the number of points takes (the base and
+    the power in fp32 would add their own)."""
+    torch, dev = torch_dev
+    import paper_2202_12674_amd as P
+    rng = np.random.default_rng(nt)
+    X, Y = (rng.integers(0, 4, (k, 20)).astype(np.float32) for k in (40, nt))
+    a = rng.integers(1, 5, 40).astype(np.float32)
+    kw = dict(gamma=0.1, coef0=0.3, degree=7)
+    f = _decision("poly", *(v.astype(np.float64) for v in (X, a, Y)), **kw)
+    s, _ = P.predict(*(torch.from_numpy(v).to(dev) for v in (X, a)), 0.0,
+                     torch.from_numpy(Y).to(dev), kernel="poly", **kw)
+    assert (np.abs(s.double().cpu().numpy() - f) <= 2.0 ** -24 * (1 + 1e-6) * f).all()
