@@ -85,6 +85,14 @@ struct MaxOp {
 };
 __device__ inline double wave_sum(double v) { return wave_reduce(v, AddOp{}); }
 
+__device__ inline double sum_lanes(double s, int lanes) {   // over 1, 2, 4, 8 or 16 lanes
+  if (lanes >= 2) s += dpp_move<kDppQuadXor1>(s);
+  if (lanes >= 4) s += dpp_move<kDppQuadXor2>(s);
+  if (lanes >= 8) s += dpp_move<kDppRowHalfMirror>(s);
+  if (lanes >= 16) s += dpp_move<kDppRowRor8>(s);
+  return s;
+}
+
 // Block-wide sum of one double per thread; every thread gets the result.
 // Fixed reduction order, so every block that sums the same values agrees.
 __device__ inline double block_sum(double v, double* sh) {
@@ -344,21 +352,27 @@ template <> struct PointRow<float> {
 // points, 1024 / PPB threads per point, each summing every (1024 / PPB)-th
 // chunk of the point's row; the point's partial sums are then added in a fixed
 // order. (256 threads left a few hundred points of many features to a few dozen
-// waves: 561 x 1207 fp32 18.7 us, 502 x 2877 fp64 13.9 us; 8.7 and 9.6 us so.) The points of a wave's load instruction are neighbours in the layout:
-// fp64 8 chunks (a whole 128-byte row) of 8 points, fp32 one chunk of 32
-// points (512 contiguous bytes per slice).
-template <typename T> constexpr int kNormPoints = sizeof(T) == 8 ? 16 : 32;
+// waves: 561 x 1207 fp32 18.7 us, 502 x 2877 fp64 13.9 us; 8.7 and 9.6 us so.) The
+// points of a wave's load instruction are neighbours in the layout: fp64 8 chunks
+// (a whole 128-byte row) of 8 points, fp32 one chunk of 32 points (512 contiguous
+// bytes per slice). fp64 rows of up to 128 features, which 64 threads read at most
+// once (SHORT), take 16 threads: with 64, most of them idle, the norms of 400000 x 30
+// took 84 us (20 now), norms and q of 60000 x 64 48 us (15), of 4000 x 100 6.2 us
+// (4.5); up to 1000 points there is no difference.
+template <typename T, bool SHORT = false>
+constexpr int kNormPoints = sizeof(T) == 4 ? 32 : SHORT ? 64 : 16;
 constexpr int kNormThreads = 1024;
-template <typename T, int KER>
+template <typename T, int KER, bool SHORT>
 __global__ __launch_bounds__(kNormThreads) void k_norms_q(const store_t<T>* __restrict__ Xb,
                                                           int64_t nkb, int64_t m, int64_t N,
                                                           double gamma, double coef0, int degree,
                                                           T* __restrict__ norms,
                                                           double* __restrict__ q64,
                                                           double* __restrict__ scal) {
-  constexpr int PPB = kNormPoints<T>, TPP = kNormThreads / PPB, WAVES = kNormThreads / 64;
+  constexpr int PPB = kNormPoints<T, SHORT>, TPP = kNormThreads / PPB, WAVES = kNormThreads / 64;
   static_assert(TileShape<T>::T % PPB == 0, "a workgroup's points lie in one panel");
-  static_assert(sizeof(T) == 8 ? TPP == 64 : TPP == 2 * WAVES, "a wave per point, or half of 32");
+  static_assert(sizeof(T) == 8 ? TPP == (SHORT ? 16 : 64) : TPP == 2 * WAVES,
+                "a wave per point or per four, or half of 32");
   constexpr int VEC = PointRow<T>::VEC;
   __shared__ double sh[WAVES];
   __shared__ double part[3][sizeof(T) == 8 ? 1 : WAVES][PPB];
@@ -396,8 +410,8 @@ __global__ __launch_bounds__(kNormThreads) void k_norms_q(const store_t<T>* __re
 #pragma unroll
   for (int t = 0; t < 3; ++t) {
     if constexpr (sizeof(T) == 8) {
-      s[t] = wave_sum(s[t]);
-      if (tid % 64 == 0) part[t][0][pl] = s[t];
+      s[t] = SHORT ? sum_lanes(s[t], 16) : wave_sum(s[t]);
+      if (q == 0) part[t][0][pl] = s[t];
     } else {
       s[t] += __shfl_xor(s[t], 32);
       if (tid % 64 < PPB) part[t][tid / 64][pl] = s[t];
@@ -1388,14 +1402,6 @@ __host__ __device__ inline int64_t lin_train_ld(int64_t d) {
 }
 constexpr int64_t kLinTrainLds = 152 * 1024;
 
-__device__ inline double sum_lanes(double s, int lanes) {   // over 1, 2, 4, 8 or 16 lanes
-  if (lanes >= 2) s += dpp_move<kDppQuadXor1>(s);
-  if (lanes >= 4) s += dpp_move<kDppQuadXor2>(s);
-  if (lanes >= 8) s += dpp_move<kDppRowHalfMirror>(s);
-  if (lanes >= 16) s += dpp_move<kDppRowRor8>(s);
-  return s;
-}
-
 template <typename T>
 __global__ __launch_bounds__(kLinTrainThreads) void k_lin_train(const T* __restrict__ X,
                                                     const T* __restrict__ y, int n, int d,
@@ -1875,27 +1881,41 @@ hipError_t launch_abs_max(const float* X, int64_t count, int* out, hipStream_t s
   return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_norms_q(const store_t<T>* Xt, int64_t ld, int64_t d_pad, int64_t m, int64_t N,
+template <typename T, bool SHORT>
+static hipError_t norms_q(const store_t<T>* Xt, int64_t ld, int64_t d_pad, int64_t m, int64_t N,
                           int kernel, double gamma, double coef0, int degree, T* norms,
                           double* q64, double* scal, hipStream_t s) {
   const int64_t nkb = d_pad / TileShape<T>::SB;
-  const unsigned g = (unsigned)(ld / kNormPoints<T>);   // ld is a multiple of the tile edge
+  // ld is a multiple of the tile edge
+  const dim3 grid((unsigned)(ld / kNormPoints<T, SHORT>)), block(kNormThreads);
   switch (kernel) {
     case KLIN:
-      hipLaunchKernelGGL((k_norms_q<T, KLIN>), dim3(g), dim3(kNormThreads), 0, s, Xt, nkb, m, N, gamma,
+      hipLaunchKernelGGL((k_norms_q<T, KLIN, SHORT>), grid, block, 0, s, Xt, nkb, m, N, gamma,
                          coef0, degree, norms, q64, scal);
       break;
     case KPOLY:
-      hipLaunchKernelGGL((k_norms_q<T, KPOLY>), dim3(g), dim3(kNormThreads), 0, s, Xt, nkb, m, N, gamma,
+      hipLaunchKernelGGL((k_norms_q<T, KPOLY, SHORT>), grid, block, 0, s, Xt, nkb, m, N, gamma,
                          coef0, degree, norms, q64, scal);
       break;
     default:
-      hipLaunchKernelGGL((k_norms_q<T, KRBF>), dim3(g), dim3(kNormThreads), 0, s, Xt, nkb, m, N, gamma,
+      hipLaunchKernelGGL((k_norms_q<T, KRBF, SHORT>), grid, block, 0, s, Xt, nkb, m, N, gamma,
                          coef0, degree, norms, q64, scal);
       break;
   }
   return hipGetLastError();
+}
+template <typename T>
+hipError_t launch_norms_q(const store_t<T>* Xt, int64_t ld, int64_t d_pad, int64_t m, int64_t N,
+                          int kernel, double gamma, double coef0, int degree, T* norms,
+                          double* q64, double* scal, hipStream_t s) {
+  // 64 threads per fp64 point take at most one chunk of these rows each
+  constexpr int64_t kShortRow = 64 / PointRow<T>::CPS;
+  if constexpr (sizeof(T) == 8) {
+    if (d_pad / TileShape<T>::SB <= kShortRow)
+      return norms_q<T, true>(Xt, ld, d_pad, m, N, kernel, gamma, coef0, degree, norms, q64, scal,
+                              s);
+  }
+  return norms_q<T, false>(Xt, ld, d_pad, m, N, kernel, gamma, coef0, degree, norms, q64, scal, s);
 }
 
 // Workgroups per tile launch: 2^23 x 256 threads stays below the 2^32 work
