@@ -1238,6 +1238,26 @@ int matvec_impl(const T* X, int64_t n, int64_t d, int32_t kernel, const lssvm_pa
   }
 }
 
+// Whether a prediction takes k_predict_few, which reads the model once but gives
+// every point its own epilogue in the registers of one (fp64) or two workgroups
+// per CU: up to 64 points nearly always. From 65 on its instance holds 128 points
+// and a round of workgroups covers 8192 (fp64) or 16384 model points, about 40 us
+// each; the tiles pay for the layout instead, which many features make dear. Call
+// times on the tiles and so, 128 points: cubic fp64 8192 x 30 46 and 41 us, 12000 x
+// 30 48 and 54, 50000 x 30 62 and 114, 16384 x 1000 216 and 153; cubic fp32 16384 x
+// 30 47 and 41, 50000 x 30 57 and 68; RBF fp64 24500 x 30 67 and 62, 50000 x 30 84
+// and 102; RBF fp32 50000 x 30 79 and 68. 64 points of fp64 RBF: 100000 x 30 105
+// and 102, 200000 x 30 150 and 171.
+inline bool few_points(int32_t kernel, bool fp64, int64_t n, int64_t d, int64_t n_test) {
+  const int64_t round = fp64 ? 8192 : 16384;
+  if (kernel == LSSVM_LINEAR || n_test > kFewTests) return false;
+  if (n_test > 64) {
+    if (kernel == LSSVM_POLY) return n <= round * (d < 512 ? 1 : d < 1000 ? 2 : 3);
+    return d >= 1000 || n <= 3 * round;
+  }
+  return !(n_test > 32 && kernel == LSSVM_RBF && fp64 && d < 128) || n <= 12 * round;
+}
+
 template <typename T>
 int predict_impl(const T* Xtr, const T* alpha, double b, int64_t n, int64_t d, int32_t kernel,
                  const lssvm_params& kp, const T* Xte, int64_t n_test, void* workspace,
@@ -1247,7 +1267,7 @@ int predict_impl(const T* Xtr, const T* alpha, double b, int64_t n, int64_t d, i
   LSSVM_TRY(check_workspace(workspace, ws_bytes, w.bytes));
   w = carve_predict<T>(g, n_test, workspace);
   LSSVM_HIP(g_ctx->ensure());
-  if (kernel != LSSVM_LINEAR && n_test <= kFewTests) {
+  if (few_points(kernel, sizeof(T) == 8, n, d, n_test)) {
     PredictFew<T> a{};
     a.Xtr = Xtr;
     a.Xte = Xte;

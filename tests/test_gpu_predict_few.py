@@ -21,7 +21,9 @@ def _decision(kernel, X, a, Y, gamma, coef0, degree):
 
 @pytest.mark.parametrize("n,nt,d", [(1, 1, 1), (15, 16, 3), (16, 17, 16), (33, 32, 17),
                                     (2049, 33, 100), (31, 64, 257), (40000, 65, 20),
-                                    (1000, 128, 65), (300, 129, 65), (20000, 2, 1)])
+                                    (1000, 128, 65), (300, 129, 65), (20000, 2, 1),
+                                    (8192, 100, 20), (8193, 100, 20), (16385, 65, 33),
+                                    (8193, 70, 512)])
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
 @pytest.mark.parametrize("kernel", ["poly", "rbf"])
 def test_scores_and_labels(torch_dev, kernel, dtype, n, nt, d):
