@@ -355,12 +355,13 @@ template <> struct PointRow<float> {
 // waves: 561 x 1207 fp32 18.7 us, 502 x 2877 fp64 13.9 us; 8.7 and 9.6 us so.) The
 // points of a wave's load instruction are neighbours in the layout: fp64 8 chunks
 // (a whole 128-byte row) of 8 points, fp32 one chunk of 32 points (512 contiguous
-// bytes per slice). fp64 rows of up to 128 features, which 64 threads read at most
-// once (SHORT), take 16 threads: with 64, most of them idle, the norms of 400000 x 30
-// took 84 us (20 now), norms and q of 60000 x 64 48 us (15), of 4000 x 100 6.2 us
-// (4.5); up to 1000 points there is no difference.
+// bytes per slice). Rows of up to 128 features (SHORT), which that many threads read at
+// most once, take 16 (fp64) or 8 threads a point: with 64 and 32, most of them idle,
+// the norms of 400000 x 30 fp64 took 84 us (20 now), norms and q of 60000 x 64 fp64 48
+// us (15), of 4000 x 100 6.2 us (4.5), the norms of 50000 x 64 fp32 10.9 us (5.0);
+// up to 1000 points there is no difference.
 template <typename T, bool SHORT = false>
-constexpr int kNormPoints = sizeof(T) == 4 ? 32 : SHORT ? 64 : 16;
+constexpr int kNormPoints = sizeof(T) == 4 ? (SHORT ? 128 : 32) : SHORT ? 64 : 16;
 constexpr int kNormThreads = 1024;
 template <typename T, int KER, bool SHORT>
 __global__ __launch_bounds__(kNormThreads) void k_norms_q(const store_t<T>* __restrict__ Xb,
@@ -371,11 +372,14 @@ __global__ __launch_bounds__(kNormThreads) void k_norms_q(const store_t<T>* __re
                                                           double* __restrict__ scal) {
   constexpr int PPB = kNormPoints<T, SHORT>, TPP = kNormThreads / PPB, WAVES = kNormThreads / 64;
   static_assert(TileShape<T>::T % PPB == 0, "a workgroup's points lie in one panel");
-  static_assert(sizeof(T) == 8 ? TPP == (SHORT ? 16 : 64) : TPP == 2 * WAVES,
-                "a wave per point or per four, or half of 32");
+  // fp64: a wave per point, or per four; fp32: a wave per two chunks of 32 points, or
+  // per chunk of 64. The point's partial sums that its waves (fp32) leave:
+  constexpr int PARTS = sizeof(T) == 8 ? 1 : SHORT ? TPP : WAVES;
+  static_assert(sizeof(T) == 8 ? TPP == (SHORT ? 16 : 64) : TPP == (SHORT ? 8 : 2 * WAVES),
+                "launch shape");
   constexpr int VEC = PointRow<T>::VEC;
   __shared__ double sh[WAVES];
-  __shared__ double part[3][sizeof(T) == 8 ? 1 : WAVES][PPB];
+  __shared__ double part[3][PARTS][PPB];
   const int tid = (int)threadIdx.x;
   const int q = sizeof(T) == 8 ? tid % TPP : tid / PPB;    // this thread's share of the chunks
   const int pl = sizeof(T) == 8 ? tid / TPP : tid % PPB;   // its point
@@ -409,9 +413,12 @@ __global__ __launch_bounds__(kNormThreads) void k_norms_q(const store_t<T>* __re
   }
 #pragma unroll
   for (int t = 0; t < 3; ++t) {
+    if (t > 0 && m < 0) break;   // uniform: the norm alone
     if constexpr (sizeof(T) == 8) {
       s[t] = SHORT ? sum_lanes(s[t], 16) : wave_sum(s[t]);
       if (q == 0) part[t][0][pl] = s[t];
+    } else if constexpr (SHORT) {
+      part[t][q][pl] = s[t];
     } else {
       s[t] += __shfl_xor(s[t], 32);
       if (tid % 64 < PPB) part[t][tid / 64][pl] = s[t];
@@ -422,8 +429,11 @@ __global__ __launch_bounds__(kNormThreads) void k_norms_q(const store_t<T>* __re
   if (tid < PPB) {
     double v[3] = {0.0, 0.0, 0.0};
 #pragma unroll
-    for (int t = 0; t < 3; ++t)
-      for (int w = 0; w < (sizeof(T) == 8 ? 1 : WAVES); ++w) v[t] += part[t][w][tid];
+    for (int t = 0; t < 3; ++t) {
+      if (t > 0 && m < 0) break;
+#pragma unroll
+      for (int w = 0; w < PARTS; ++w) v[t] += part[t][w][tid];
+    }
     nrm = v[0];
     const int64_t r = (int64_t)blockIdx.x * PPB + tid;
     norms[r] = (T)nrm;
@@ -1908,13 +1918,10 @@ template <typename T>
 hipError_t launch_norms_q(const store_t<T>* Xt, int64_t ld, int64_t d_pad, int64_t m, int64_t N,
                           int kernel, double gamma, double coef0, int degree, T* norms,
                           double* q64, double* scal, hipStream_t s) {
-  // 64 threads per fp64 point take at most one chunk of these rows each
-  constexpr int64_t kShortRow = 64 / PointRow<T>::CPS;
-  if constexpr (sizeof(T) == 8) {
-    if (d_pad / TileShape<T>::SB <= kShortRow)
-      return norms_q<T, true>(Xt, ld, d_pad, m, N, kernel, gamma, coef0, degree, norms, q64, scal,
-                              s);
-  }
+  // up to 128 features: at most one chunk per thread of 64 (fp64), half a one of 32
+  constexpr int64_t kShortRow = 8;
+  if (d_pad / TileShape<T>::SB <= kShortRow)
+    return norms_q<T, true>(Xt, ld, d_pad, m, N, kernel, gamma, coef0, degree, norms, q64, scal, s);
   return norms_q<T, false>(Xt, ld, d_pad, m, N, kernel, gamma, coef0, degree, norms, q64, scal, s);
 }
 

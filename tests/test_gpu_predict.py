@@ -112,19 +112,21 @@ def test_predict_layout_beyond_one_dispatch(torch_dev):
     torch.cuda.empty_cache()
 
 
-@pytest.mark.parametrize("n,d", [(65537, 1), (70000, 33), (65600, 128), (65600, 129)])
-def test_norms_of_many_points_of_few_features(torch_dev, n, d):
-    """fp64 RBF scores on models of 2^16 points and more, up to 128 features with
-    16 threads per squared norm, with 64 above: sampled test points against fp64.
-    A value is off by d + 40 roundings of distances up to 4 d gamma = 4."""
+@pytest.mark.parametrize("n,d", [(65537, 1), (70000, 33), (65600, 128), (65600, 129), (300, 97)])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_norms_of_points_of_few_features(torch_dev, n, d, dtype):
+    """RBF scores whose squared norms take fewer threads a point up to 128 features
+    than above: sampled test points against fp64. A value is off by d + 40 roundings
+    of distances up to 4 d gamma = 4."""
     torch, dev = torch_dev
     import paper_2202_12674_amd as P
     rng = np.random.default_rng(n + d)
-    X, Y = rng.uniform(-1.0, 1.0, (n, d)), rng.uniform(-1.0, 1.0, (130, d))
-    a = rng.standard_normal(n)
+    npd, u = (np.float64, 2.0 ** -53) if dtype == "f64" else (np.float32, 2.0 ** -24)
+    X, Y, a = (v.astype(npd) for v in (rng.uniform(-1.0, 1.0, (n, d)),
+                                       rng.uniform(-1.0, 1.0, (130, d)), rng.standard_normal(n)))
     s, _ = P.predict(*(torch.from_numpy(v).to(dev) for v in (X, a)), 0.5,
                      torch.from_numpy(Y).to(dev), kernel="rbf", gamma=1.0 / d)
-    got = s.cpu().numpy()
+    got, X, Y, a = (v.astype(np.float64) for v in (s.cpu().numpy(), X, Y, a))
     for t in (0, 64, 129):
         f = np.exp(-((X - Y[t]) ** 2).sum(1) / d) @ a + 0.5
-        assert abs(got[t] - f) <= (d + 40) * 4 * 2.0 ** -53 * np.abs(a).sum()
+        assert abs(got[t] - f) <= (d + 40) * 4 * u * np.abs(a).sum()
