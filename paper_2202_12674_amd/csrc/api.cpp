@@ -384,6 +384,7 @@ struct PredictWs {
   T *ntr, *nte, *alpha;
   double* part;
   int* flags;
+  double* wait;      // nonzero while the scores wait for another layout
   double* few_part;  // few test points (over the layouts): partial scores, and whether
   int* few_bad;      // a workgroup met a value that is not finite
   double* lin_part;  // linear kernel: partial sums of w over point chunks
@@ -407,6 +408,7 @@ PredictWs<T> carve_predict(const Geometry& g, int64_t n_test, void* base) {
   w.nte = c.take<T>(w.ld_te);
   w.part = c.take<double>(w.nTc * w.ld_te);
   w.flags = c.take<int>(F_COUNT);
+  w.wait = c.take<double>(1);
   w.lin_part = c.take<double>(2 * lin_max_chunks(g.n, g.d) * g.d);
   w.lin_w = c.take<double>(2 * g.d);
   w.lin_f = c.take<double>(n_test);
@@ -651,7 +653,7 @@ int clear_and_order(const Geometry& g, const TrainWs<T>& w, hipStream_t s) {
 // subnormal: s = 46 lifts the smallest float's 24 bits, less where the largest
 // value leaves no room for the products (its 2^104 times 2^21 features; values
 // 2^155 below the largest then keep fewer bits). *gscale is multiplied by 2^-s.
-// Rare, so it may wait for the device.
+// Rare, so it may wait for the device. The flag is down afterwards.
 int relayout_tiny(const float* X, int64_t n, int64_t d, uint16_t* Xt, int64_t ld, int64_t d_pad,
                   int* flags, float* gscale, hipStream_t s) {
   int* word = flags + F_TINY;
@@ -662,7 +664,8 @@ int relayout_tiny(const float* X, int64_t n, int64_t d, uint16_t* Xt, int64_t ld
   float top;
   std::memcpy(&top, g_ctx->flags, sizeof top);
   const int up = std::min(46, std::max(0, 52 - (top > 0.f ? std::ilogb(top) : 0)));
-  LSSVM_HIP(launch_layout<float>(X, n, d, Xt, ld, d_pad, std::ldexp(1.f, up), flags, s));
+  LSSVM_HIP(hipMemsetAsync(word, 0, sizeof(int), s));
+  LSSVM_HIP(launch_layout<float>(X, n, d, Xt, ld, d_pad, std::ldexp(1.f, up), 0, flags, s));
   *gscale = std::ldexp(*gscale, -up);
   return LSSVM_OK;
 }
@@ -687,7 +690,7 @@ template <typename T>
 int setup_points(const Geometry& g, const TrainWs<T>& w, const T* X, int32_t kernel,
                  const lssvm_params& kp, hipStream_t s) {
   LSSVM_TRY(clear_and_order<T>(g, w, s));
-  LSSVM_HIP(launch_layout<T>(X, g.n, g.d, w.Xt, g.ld, g.d_pad, 1.f, w.flags, s));
+  LSSVM_HIP(launch_layout<T>(X, g.n, g.d, w.Xt, g.ld, g.d_pad, 1.f, 1, w.flags, s));
   LSSVM_HIP(launch_norms_q<T>(w.Xt, g.ld, g.d_pad, g.N, g.N, kernel, kp.gamma, kp.coef0,
                               kp.degree, w.norms, w.q64, w.scal, s));
   return LSSVM_OK;
@@ -944,7 +947,7 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
 
   if (n == 1) {  // alpha = [0], b = y_0
     LSSVM_HIP(hipMemsetAsync(w.flags, 0, F_COUNT * sizeof(int), s));
-    LSSVM_HIP(launch_layout<T>(X, g.n, g.d, w.Xt, g.ld, g.d_pad, 1.f, w.flags, s));
+    LSSVM_HIP(launch_layout<T>(X, g.n, g.d, w.Xt, g.ld, g.d_pad, 1.f, 1, w.flags, s));
     LSSVM_HIP(launch_single_point<T>(y, alpha_out, w.scal, w.flags, s));
     LSSVM_HIP(read_flags(w.flags, s));
     LSSVM_HIP(hipMemcpyAsync(g_ctx->p, w.scal + S_B, sizeof(double), hipMemcpyDeviceToHost, s));
@@ -1017,7 +1020,7 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
   if (info && info->warm_start && !done) {
     // x0 = the caller's alpha~, r0 = rhs - Q~ x0, dir = r0; the stop threshold
     // set from rhs^T rhs above is kept
-    LSSVM_HIP(launch_pad_to_f64<T>(alpha_out, g.N, w.x, NP, w.scal, s));
+    LSSVM_HIP(launch_pad_to_f64<T>(alpha_out, g.N, w.x, NP, w.scal, nullptr, s));
     if (passes) LSSVM_TRY(lin.product(w.x, false));
     else LSSVM_TRY(matvec_partials<T>(g, w, kp, kernel, w.x, s));
     LSSVM_HIP(launch_cg_residual(product_of(w.x), NP, g.N, w.rhs, w.r, w.bp1, w.bp2, s));
@@ -1216,7 +1219,7 @@ int matvec_impl(const T* X, int64_t n, int64_t d, int32_t kernel, const lssvm_pa
     LSSVM_HIP(launch_setup_clear(0, LSSVM_TILE_GROUP, nullptr, w.flags, w.scal, nullptr, 0,
                                  nullptr, s));
     LSSVM_HIP(launch_lin_q<T>(X, g.n, g.d, w.q64, w.scal, w.flags, s));
-    LSSVM_HIP(launch_pad_to_f64<T>(p, g.N, w.dir, g.N, nullptr, s));
+    LSSVM_HIP(launch_pad_to_f64<T>(p, g.N, w.dir, g.N, nullptr, nullptr, s));
     LSSVM_HIP(lin.weights(lin.vec(w.dir, false)));
     LSSVM_HIP(launch_lin_out<T>(X, g.N, g.d, w.lin_w, lin.rank_one(w.dir, nullptr), out, w.flags,
                                 s));
@@ -1226,15 +1229,17 @@ int matvec_impl(const T* X, int64_t n, int64_t d, int32_t kernel, const lssvm_pa
     return LSSVM_OK;
   }
   LSSVM_TRY(setup_points<T>(g, w, X, kernel, kp, s));
-  LSSVM_HIP(launch_pad_to_f64<T>(p, g.N, w.dir, g.NP, w.scal, s));
+  LSSVM_HIP(launch_pad_to_f64<T>(p, g.N, w.dir, g.NP, w.scal, w.flags, s));
   for (bool again = false;; again = true) {   // one wait, at the end
-    LSSVM_TRY(matvec_partials<T>(g, w, kp, kernel, w.dir, s));
+    TileArgs<T> a = sym_args<T>(g, w, kp, kernel, w.dir);
+    if (!again) a.stop = w.scal + S_STATUS + ST_DONE;
+    LSSVM_HIP(launch_product<T>(g, a, kernel, w.gpart, s));
     LSSVM_HIP(launch_mv_out<T>(rank_one(g, w, kernel, C, w.dir), g.NP, g.N, out, s));
     LSSVM_HIP(read_flags(w.flags, s));
     LSSVM_HIP(hipStreamSynchronize(s));
     if (g_ctx->flags[F_NONFINITE]) return fail(LSSVM_ENONFINITE, "X holds a NaN or an infinity");
-    if (!g_ctx->flags[F_TINY] || again) return LSSVM_OK;
-    LSSVM_TRY(rescale_points<T>(g, w, X, s));   // tiny values: once more, scaled up
+    if (!g_ctx->flags[F_TINY]) return LSSVM_OK;
+    LSSVM_TRY(rescale_points<T>(g, w, X, s));   // tiny values: the product has waited for this
   }
 }
 
@@ -1298,15 +1303,15 @@ int predict_impl(const T* Xtr, const T* alpha, double b, int64_t n, int64_t d, i
       return fail(LSSVM_ENONFINITE, "X_train or X_test holds a NaN or an infinity");
     return LSSVM_OK;
   }
-  LSSVM_HIP(launch_layout<T>(Xtr, n, d, w.Xtr, g.ld, g.d_pad, 1.f, w.flags, s));
-  LSSVM_HIP(launch_layout<T>(Xte, n_test, d, w.Xte, w.ld_te, g.d_pad, 1.f, w.flags, s));
+  LSSVM_HIP(launch_layout<T>(Xtr, n, d, w.Xtr, g.ld, g.d_pad, 1.f, 1, w.flags, s));
+  LSSVM_HIP(launch_layout<T>(Xte, n_test, d, w.Xte, w.ld_te, g.d_pad, 1.f, 1, w.flags, s));
   if (kernel == LSSVM_RBF) {  // squared norms are only read by the radial kernel
     LSSVM_HIP(launch_norms_q<T>(w.Xtr, g.ld, g.d_pad, -1, 0, kernel, kp.gamma, kp.coef0,
                                 kp.degree, w.ntr, nullptr, nullptr, s));
     LSSVM_HIP(launch_norms_q<T>(w.Xte, w.ld_te, g.d_pad, -1, 0, kernel, kp.gamma, kp.coef0,
                                 kp.degree, w.nte, nullptr, nullptr, s));
   }
-  LSSVM_HIP(launch_pad_vec<T>(alpha, n, w.alpha, g.ld, s));
+  LSSVM_HIP(launch_pad_vec<T>(alpha, n, w.alpha, g.ld, w.flags, w.wait, s));
   TileArgs<T> a{};
   a.A = w.Xte;
   a.B = w.Xtr;
@@ -1325,7 +1330,7 @@ int predict_impl(const T* Xtr, const T* alpha, double b, int64_t n, int64_t d, i
   a.ksplit = 1;
   a.part = w.part;
   a.part_ld = w.ld_te;
-  bool relaid = false;
+  a.stop = w.wait;
   for (;;) {
     LSSVM_HIP(launch_tiles_gen<T>(a, kernel, w.nTr, s));
     LSSVM_HIP(launch_predict_finish<T>(w.part, w.nTc, w.ld_te, n_test, b, scores, labels, w.flags,
@@ -1334,11 +1339,11 @@ int predict_impl(const T* Xtr, const T* alpha, double b, int64_t n, int64_t d, i
     LSSVM_HIP(hipStreamSynchronize(s));
     if (g_ctx->flags[F_NONFINITE])
       return fail(LSSVM_ENONFINITE, "X_train or X_test holds a NaN or an infinity");
-    if (!g_ctx->flags[F_TINY] || relaid) return LSSVM_OK;
-    // tiny values on either side: once more on points stored scaled up
+    if (!g_ctx->flags[F_TINY]) return LSSVM_OK;
+    // tiny values on either side: the scores have waited for points stored scaled up
     LSSVM_TRY(relayout_tiny(Xtr, n, d, w.Xtr, g.ld, g.d_pad, w.flags, &a.gscale, s));
     LSSVM_TRY(relayout_tiny(Xte, n_test, d, w.Xte, w.ld_te, g.d_pad, w.flags, &a.gscale, s));
-    relaid = true;
+    a.stop = nullptr;
   }
 }
 

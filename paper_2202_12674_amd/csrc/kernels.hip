@@ -254,7 +254,8 @@ __global__ __launch_bounds__(256) void k_layout(const double* __restrict__ X, in
 __global__ __launch_bounds__(256) void k_layout_split(const float* __restrict__ X, int64_t n,
                                                       int64_t d, uint16_t* __restrict__ Xb,
                                                       int64_t nblk, int64_t nkb32, int vec_ok,
-                                                      float scale, int* __restrict__ flags) {
+                                                      float scale, int check,
+                                                      int* __restrict__ flags) {
   using TS = TileShape<float>;
   constexpr int TP = TS::T, CPR = TS::BK / 8, PER = TP * CPR / 256, SLAB = kSlabElems<float>;
   static_assert(TS::SB == 16 && TS::BK == 32 && TP * CPR % 256 == 0, "two slabs per block");
@@ -290,7 +291,7 @@ __global__ __launch_bounds__(256) void k_layout_split(const float* __restrict__ 
         *reinterpret_cast<u32x4*>(slab + 8 * split_chunk(t, p, q & 1)) = w[t];
     }
     if (bad) flags[F_NONFINITE] = 1;
-    if (tiny) flags[F_TINY] = 1;
+    if (tiny && check) flags[F_TINY] = 1;
   }
 }
 
@@ -1627,8 +1628,11 @@ __global__ __launch_bounds__(256) void k_setup_clear(int64_t nT, int64_t G,
 // ---------------------------------------------------------- misc vectors ----
 template <typename T>
 __global__ __launch_bounds__(256) void k_pad_vec(const T* __restrict__ src, int64_t len,
-                                                 T* __restrict__ dst, int64_t len_pad) {
+                                                 T* __restrict__ dst, int64_t len_pad,
+                                                 const int* __restrict__ flags,
+                                                 double* __restrict__ wait) {
   const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
+  if (i == 0) *wait = (double)flags[F_TINY];
   if (i < len_pad) dst[i] = i < len ? src[i] : T(0);
 }
 
@@ -1636,7 +1640,8 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_mv_out(RankOne c, int64_t NP, int64_t N,
                                                 T* __restrict__ out) {
   __shared__ double sh[NT / 64];
-  if (c.flags[F_NONFINITE] != 0) return;   // out stays untouched on error
+  // out stays untouched on error, and until the points' layout stands
+  if (c.flags[F_NONFINITE] != 0 || c.flags[F_TINY] != 0) return;
   const RankOneSums ro = rank_one_sums(c, sh);
   const double inv = 1.0 / c.scal[S_FIXSC];
   const bool bad = c.flags[F_PRODUCT] != 0;
@@ -1652,7 +1657,8 @@ __global__ __launch_bounds__(256) void k_predict_finish(const double* __restrict
                                                         double b, T* __restrict__ scores,
                                                         int32_t* __restrict__ labels,
                                                         const int* __restrict__ flags) {
-  if (flags[F_NONFINITE] != 0) return;   // outputs untouched on error
+  // outputs untouched on error, and until the points' layout stands
+  if (flags[F_NONFINITE] != 0 || flags[F_TINY] != 0) return;
   // 64 test points per workgroup: wave w sums slots w, w + 4, ... (eight
   // loads in flight per lane), then the four wave sums are added in order.
   __shared__ double sh[NT / 64][64];
@@ -1677,9 +1683,10 @@ __global__ __launch_bounds__(256) void k_predict_finish(const double* __restrict
 template <typename T>
 __global__ __launch_bounds__(256) void k_pad_to_f64(const T* __restrict__ src, int64_t len,
                                                     double* __restrict__ dst, int64_t len_pad,
-                                                    double* scal) {
+                                                    double* scal, const int* __restrict__ flags) {
   __shared__ double sh[NT / 64];
   const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
+  if (i == 0 && flags) scal[S_STATUS + ST_DONE] = (double)flags[F_TINY];
   const double v = i < len ? (double)src[i] : 0.0;
   if (i < len_pad) dst[i] = v;
   if (scal) {   // a product multiplies dst next
@@ -1868,7 +1875,7 @@ hipError_t launch_setup_clear(int64_t nT, int64_t group, uint32_t* order,
 // what one dispatch should hold).
 template <>
 hipError_t launch_layout<double>(const double* X, int64_t n, int64_t d, double* Xt, int64_t ld,
-                                 int64_t d_pad, float, int* flags, hipStream_t s) {
+                                 int64_t d_pad, float, int, int* flags, hipStream_t s) {
   const int64_t nkb = d_pad / TileShape<double>::BK, nblk = (ld / TileShape<double>::T) * nkb;
   const int vec_ok = d % 2 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
   const int64_t blocks = std::min<int64_t>(nblk, int64_t(1) << 20);
@@ -1878,12 +1885,13 @@ hipError_t launch_layout<double>(const double* X, int64_t n, int64_t d, double* 
 }
 template <>
 hipError_t launch_layout<float>(const float* X, int64_t n, int64_t d, uint16_t* Xt, int64_t ld,
-                                int64_t d_pad, float scale, int* flags, hipStream_t s) {
+                                int64_t d_pad, float scale, int check, int* flags,
+                                hipStream_t s) {
   const int64_t nkb = d_pad / TileShape<float>::BK, nblk = (ld / TileShape<float>::T) * nkb;
   const int vec_ok = d % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
   const int64_t blocks = std::min<int64_t>(nblk, int64_t(1) << 20);
   hipLaunchKernelGGL(k_layout_split, dim3((unsigned)blocks), dim3(256), 0, s, X, n, d, Xt, nblk,
-                     nkb, vec_ok, scale, flags);
+                     nkb, vec_ok, scale, check, flags);
   return hipGetLastError();
 }
 hipError_t launch_abs_max(const float* X, int64_t count, int* out, hipStream_t s) {
@@ -2131,9 +2139,10 @@ hipError_t launch_single_point(const T* y, T* alpha_out, double* scal, int* flag
 }
 
 template <typename T>
-hipError_t launch_pad_vec(const T* src, int64_t len, T* dst, int64_t len_pad, hipStream_t s) {
+hipError_t launch_pad_vec(const T* src, int64_t len, T* dst, int64_t len_pad, const int* flags,
+                          double* wait, hipStream_t s) {
   hipLaunchKernelGGL(k_pad_vec<T>, dim3(blocks_for(len_pad)), dim3(NT), 0, s, src, len, dst,
-                     len_pad);
+                     len_pad, flags, wait);
   return hipGetLastError();
 }
 
@@ -2154,9 +2163,9 @@ hipError_t launch_predict_finish(const double* part, int64_t nslots, int64_t ld,
 
 template <typename T>
 hipError_t launch_pad_to_f64(const T* src, int64_t len, double* dst, int64_t len_pad,
-                             double* scal, hipStream_t s) {
+                             double* scal, const int* flags, hipStream_t s) {
   hipLaunchKernelGGL(k_pad_to_f64<T>, dim3(blocks_for(len_pad)), dim3(NT), 0, s, src, len, dst,
-                     len_pad, scal);
+                     len_pad, scal, flags);
   return hipGetLastError();
 }
 
@@ -2402,12 +2411,13 @@ hipError_t static_scratch(double** ptr, int64_t* capacity) {
   template hipError_t launch_bias<T>(const double*, const double*, int64_t, const T*, double*,    \
                                      double, T*, hipStream_t);                                    \
   template hipError_t launch_single_point<T>(const T*, T*, double*, int*, hipStream_t);           \
-  template hipError_t launch_pad_vec<T>(const T*, int64_t, T*, int64_t, hipStream_t);             \
+  template hipError_t launch_pad_vec<T>(const T*, int64_t, T*, int64_t, const int*, double*,      \
+                                        hipStream_t);                                             \
   template hipError_t launch_mv_out<T>(const RankOne&, int64_t, int64_t, T*, hipStream_t);       \
   template hipError_t launch_predict_finish<T>(const double*, int64_t, int64_t, int64_t, double,  \
                                                T*, int32_t*, const int*, hipStream_t);            \
   template hipError_t launch_pad_to_f64<T>(const T*, int64_t, double*, int64_t, double*,          \
-                                           hipStream_t);                                          \
+                                           const int*, hipStream_t);                                          \
   template hipError_t launch_lin_w<T>(const T*, int64_t, int64_t, const LinVec&, const double*,   \
                                       double*, double*, double*, hipStream_t);                    \
   template hipError_t launch_lin_q<T>(const T*, int64_t, int64_t, double*, double*, int*,         \

@@ -70,7 +70,8 @@ inline int64_t cg_blocks(int64_t NP) { return vec_blocks(NP); }
 // Flags raised by kernels (int32 each).
 // F_PRODUCT: a symmetric product had a row sum that is not finite (its
 // entries then come out as NaN, so CG reports a breakdown).
-// F_TINY: an fp32 point holds a nonzero value below kSplitMin.
+// F_TINY: an fp32 point holds a nonzero value below kSplitMin, and the points are not
+// yet laid out to suit (products and scores wait for that: TileArgs::stop).
 enum Flag : int { F_NONFINITE = 0, F_BADLABEL = 1, F_PRODUCT = 2, F_TINY = 3, F_COUNT = 4 };
 
 
@@ -144,10 +145,11 @@ hipError_t launch_setup_clear(int64_t nT, int64_t group, uint32_t* order,
                               int* flags, double* scal, int64_t* acc, int64_t nacc,
                               unsigned* ticket, hipStream_t s);
 
-// scale: what fp32 values are multiplied by as they are stored (a power of two).
+// scale: what fp32 values are multiplied by as they are stored (a power of two);
+// check: raise F_TINY.
 template <typename T>
 hipError_t launch_layout(const T* X, int64_t n, int64_t d, store_t<T>* Xt, int64_t ld, int64_t d_pad,
-                         float scale, int* flags, hipStream_t s);
+                         float scale, int check, int* flags, hipStream_t s);
 // Raises *out (an int32 set to 0 before) to the bits of the largest |X[k]| of
 // `count` values.
 hipError_t launch_abs_max(const float* X, int64_t count, int* out, hipStream_t s);
@@ -219,8 +221,10 @@ hipError_t launch_bias(const double* x, const double* q64, int64_t N, const T* y
 // label passed the checks (flags set by the layout kernel before it).
 template <typename T>
 hipError_t launch_single_point(const T* y, T* alpha_out, double* scal, int* flags, hipStream_t s);
+// dst = src zero-padded; *wait = 1 if F_TINY is up, else 0.
 template <typename T>
-hipError_t launch_pad_vec(const T* src, int64_t len, T* dst, int64_t len_pad, hipStream_t s);
+hipError_t launch_pad_vec(const T* src, int64_t len, T* dst, int64_t len_pad, const int* flags,
+                          double* wait, hipStream_t s);
 template <typename T>
 hipError_t launch_mv_out(const RankOne& c, int64_t NP, int64_t N, T* out, hipStream_t s);
 // scores = b + the sum of nslots partial slots; nothing is written if the
@@ -229,10 +233,11 @@ template <typename T>
 hipError_t launch_predict_finish(const double* part, int64_t nslots, int64_t ld, int64_t n_test,
                                  double b, T* scores, int32_t* labels, const int* flags,
                                  hipStream_t s);
-// dst = src zero-padded, in fp64; with scal, also raises scal[S_PMAX] to max |dst|.
+// dst = src zero-padded, in fp64; with scal, also raises scal[S_PMAX] to max |dst|;
+// with flags, sets the stop flag (ST_DONE) to 1 if F_TINY is up.
 template <typename T>
 hipError_t launch_pad_to_f64(const T* src, int64_t len, double* dst, int64_t len_pad,
-                             double* scal, hipStream_t s);
+                             double* scal, const int* flags, hipStream_t s);
 // count <= 64 doubles from the device to pinned host memory, for a host that waits
 // for the stream next.
 hipError_t launch_read_back(const double* src, int count, double* dst, hipStream_t s);

@@ -77,8 +77,8 @@ struct TileArgs {
   // fixed-point scale); fx[2] receives the scale 2^s the launch used
   double* fx;
   int* fx_bad;          // symmetric mode: raised when a row sum is not finite
-  const double* stop;   // symmetric mode: nonzero once CG has stopped (the launch then
-                        // returns at once), or null
+  const double* stop;   // nonzero: the launch returns at once, as CG has stopped or as the
+                        // points have to be laid out anew first (F_TINY). Or null.
   int64_t part_ld;
   // A product's tiles may outnumber one launch (the dispatch grid counts work
   // items in 32 bits), so the launcher splits them into chunks: workgroup b of

@@ -277,7 +277,7 @@ constexpr int kBufferWord3 = 0x00020000;
 // global -> LDS loads) have completed: s_waitcnt vmcnt(0), other counters free.
 __device__ inline void vm_wait_all() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
-// The stop flag of launches that have none (a product outside CG).
+// The stop flag of launches that have none.
 __device__ const double kNeverStop = 0.0;
 
 // ---------------------------------------------------------- a4 tiles --------
@@ -348,11 +348,8 @@ __device__ __forceinline__ bool tile_body(const TileArgs<T>& a) {
   // CG already stopped? A whole or partial tile reads the flag with its
   // first loads in flight: waiting for it first would add a round trip to
   // every product of a small problem.
-  double stop_v = 0.0;
-  if constexpr (SYM) {
-    stop_v = *(a.stop ? a.stop : &kNeverStop);
-    if (PART == kFixup && stop_v != 0.0) return false;
-  }
+  const double stop_v = *(a.stop ? a.stop : &kNeverStop);
+  if (PART == kFixup && stop_v != 0.0) return false;
   int64_t I, J;
   // Symmetric tiles may have their features split over KS workgroups. For
   // the linear kernel each split adds K p over its share to the row sums

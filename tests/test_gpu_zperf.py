@@ -43,3 +43,39 @@ def test_product_rate_floor(torch_dev, kernel, dtype, n, d):
     frac = N * (N + 1) * d / (ms * 1e-3) / 1e12 / PEAK_TFLOPS[dtype]
     print(f"{cfg.name}: {ms:.3f} ms per product, {100 * frac:.1f}% of peak", flush=True)
     assert frac >= FLOOR, f"{cfg.name}: {100 * frac:.1f}% of the matrix-core peak"
+
+
+@pytest.mark.gpu
+def test_one_tiny_value_costs_a_layout_not_a_product(torch_dev):
+    """A value whose slices would be subnormal has an fp32 model laid out anew,
+    scaled up: the product and the scores wait for that instead of running twice."""
+    torch, dev = torch_dev
+    import paper_2202_12674_amd as P
+    n, d = 32768, 1024
+    g = torch.Generator(device=dev)
+    g.manual_seed(1)
+    X = torch.rand(n, d, generator=g, device=dev) * 2 - 1
+    v = torch.randn(n, generator=g, device=dev)
+    Y = X[:2048] * 0.5
+    ws = P.alloc_workspace(max(P.workspace_bytes(n, d, X.dtype),
+                               P.predict_workspace_bytes(n, 2048, d, X.dtype)), dev)
+
+    def ms(f):
+        f()
+        times = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            f()
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        return sorted(times)[2]
+
+    kw = dict(kernel="rbf", gamma=1.0 / d, workspace=ws)
+    calls = [lambda: P.matvec(X, v[:-1], **kw), lambda: P.predict(X, v, 0.0, Y, **kw)]
+    plain = [ms(f) for f in calls]
+    X[77, 3] = 1e-37
+    tiny = [ms(f) for f in calls]
+    print(f"product and scores: {plain} ms, with a tiny value {tiny} ms", flush=True)
+    assert tiny[0] <= 1.35 * plain[0] and tiny[1] <= 1.6 * plain[1]
