@@ -339,7 +339,8 @@ struct TrainWs {
   uint32_t* order;
   double* hist;
   unsigned* ticket;   // workgroups done in a fused iteration's launch
-  T gscale = T(1);    // what the stored points' inner products are multiplied by
+  // what the stored points' inner products are multiplied by
+  T gscale = T(1) / (T)(int64_t(1) << (2 * kStoredUp<T>));
   size_t bytes;
 };
 
@@ -648,52 +649,62 @@ int clear_and_order(const Geometry& g, const TrainWs<T>& w, hipStream_t s) {
   return LSSVM_OK;
 }
 
-// fp32 points with values below kSplitMin (F_TINY, raised by the layout kernel)
-// are laid out again, scaled up by 2^s so that no slice of any value is
-// subnormal: s = 46 lifts the smallest float's 24 bits, less where the largest
-// value leaves no room for the products (its 2^104 times 2^21 features; values
-// 2^155 below the largest then keep fewer bits). *gscale is multiplied by 2^-s.
-// Rare, so it may wait for the device. The flag is down afterwards.
-int relayout_tiny(const float* X, int64_t n, int64_t d, uint16_t* Xt, int64_t ld, int64_t d_pad,
-                  int* flags, float* gscale, hipStream_t s) {
-  int* word = flags + F_TINY;
+// fp32 points with values that the usual scale does not serve (F_RANGE, raised by the
+// layout kernel) are laid out again, multiplied by 2^up so that their largest value is
+// about 2^52, whose products (2^104, times 2^21 features) still fit. up stays below
+// 64, for 2^-2up to be a float, and at 0 for larger values, whose products may not fit
+// as they are. (Beside values above 2^40, products more than 2^206 below the square of
+// the largest lose bits that fp32 would hold.) Rare, so it may wait for the device. The
+// flag is down afterwards.
+int relayout(const float* X, int64_t n, int64_t d, uint16_t* Xt, int64_t ld, int64_t d_pad,
+             int* flags, int* up, hipStream_t s) {
+  int* word = flags + F_RANGE;
   LSSVM_HIP(hipMemsetAsync(word, 0, sizeof(int), s));
   LSSVM_HIP(launch_abs_max(X, n * d, word, s));
   LSSVM_HIP(hipMemcpyAsync(g_ctx->flags, word, sizeof(int), hipMemcpyDeviceToHost, s));
   LSSVM_HIP(hipStreamSynchronize(s));
   float top;
   std::memcpy(&top, g_ctx->flags, sizeof top);
-  const int up = std::min(46, std::max(0, 52 - (top > 0.f ? std::ilogb(top) : 0)));
+  *up = std::min(63, std::max(0, 52 - (top > 0.f ? std::ilogb(top) : 0)));
   LSSVM_HIP(hipMemsetAsync(word, 0, sizeof(int), s));
-  LSSVM_HIP(launch_layout<float>(X, n, d, Xt, ld, d_pad, std::ldexp(1.f, up), 0, flags, s));
-  *gscale = std::ldexp(*gscale, -up);
+  LSSVM_HIP(launch_layout<float>(X, n, d, Xt, ld, d_pad, *up, 0, flags, s));
   return LSSVM_OK;
 }
-int relayout_tiny(const double*, int64_t, int64_t, double*, int64_t, int64_t, int*, double*,
-                  hipStream_t) {
+int relayout(const double*, int64_t, int64_t, double*, int64_t, int64_t, int*, int*,
+             hipStream_t) {
   return LSSVM_OK;   // fp64 points are stored as they are
 }
 
-// The training points: rows and columns of every product.
+// Norms, q and k_mm of the training points as they lie in the layout.
 template <typename T>
-int rescale_points(const Geometry& g, TrainWs<T>& w, const T* X, hipStream_t s) {
-  T one_side = T(1);
-  LSSVM_TRY(relayout_tiny(X, g.n, g.d, w.Xt, g.ld, g.d_pad, w.flags, &one_side, s));
-  w.gscale = one_side * one_side;
+int setup_norms(const Geometry& g, const TrainWs<T>& w, int up, int32_t kernel,
+                const lssvm_params& kp, hipStream_t s) {
+  LSSVM_HIP(launch_norms_q<T>(w.Xt, g.ld, g.d_pad, g.N, g.N, up, kernel, kp.gamma, kp.coef0,
+                              kp.degree, w.norms, w.q64, w.scal, s));
   return LSSVM_OK;
 }
 
+// The training points, rows and columns of every product, laid out by their range;
+// what the first layout's norms and q overflowed in is formed again.
+template <typename T>
+int rescale_points(const Geometry& g, TrainWs<T>& w, const T* X, int32_t kernel,
+                   const lssvm_params& kp, hipStream_t s) {
+  int up = 0;
+  LSSVM_TRY(relayout(X, g.n, g.d, w.Xt, g.ld, g.d_pad, w.flags, &up, s));
+  w.gscale = (T)std::ldexp(1.0, -2 * up);
+  LSSVM_HIP(hipMemsetAsync(w.scal + S_NMAX, 0, sizeof(double), s));
+  return setup_norms<T>(g, w, up, kernel, kp, s);
+}
+
 // a1 + a2: layout, norms, q and k_mm, left on the device. The caller reads the
-// input flags back with its result: a non-finite X is an error, and tiny values
-// are laid out again (the norms stand: the slices add up to every value).
+// input flags back with its result: a non-finite X is an error, and points out of the
+// usual range are laid out again.
 template <typename T>
 int setup_points(const Geometry& g, const TrainWs<T>& w, const T* X, int32_t kernel,
                  const lssvm_params& kp, hipStream_t s) {
   LSSVM_TRY(clear_and_order<T>(g, w, s));
-  LSSVM_HIP(launch_layout<T>(X, g.n, g.d, w.Xt, g.ld, g.d_pad, 1.f, 1, w.flags, s));
-  LSSVM_HIP(launch_norms_q<T>(w.Xt, g.ld, g.d_pad, g.N, g.N, kernel, kp.gamma, kp.coef0,
-                              kp.degree, w.norms, w.q64, w.scal, s));
-  return LSSVM_OK;
+  LSSVM_HIP(launch_layout<T>(X, g.n, g.d, w.Xt, g.ld, g.d_pad, kStoredUp<T>, 1, w.flags, s));
+  return setup_norms<T>(g, w, kStoredUp<T>, kernel, kp, s);
 }
 
 // A finished product's row sums and the terms of Q~ p the tiles leave out.
@@ -947,7 +958,7 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
 
   if (n == 1) {  // alpha = [0], b = y_0
     LSSVM_HIP(hipMemsetAsync(w.flags, 0, F_COUNT * sizeof(int), s));
-    LSSVM_HIP(launch_layout<T>(X, g.n, g.d, w.Xt, g.ld, g.d_pad, 1.f, 1, w.flags, s));
+    LSSVM_HIP(launch_layout<T>(X, g.n, g.d, w.Xt, g.ld, g.d_pad, kStoredUp<T>, 1, w.flags, s));
     LSSVM_HIP(launch_single_point<T>(y, alpha_out, w.scal, w.flags, s));
     LSSVM_HIP(read_flags(w.flags, s));
     LSSVM_HIP(hipMemcpyAsync(g_ctx->p, w.scal + S_B, sizeof(double), hipMemcpyDeviceToHost, s));
@@ -991,7 +1002,7 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
   if (inflags & 1) return fail(LSSVM_ENONFINITE, "X holds a NaN or an infinity");
   if (inflags & 2) return fail(LSSVM_EBADLABEL, "labels must be +1 or -1");
   const double delta0 = g_ctx->p[0];
-  if (inflags & 4) LSSVM_TRY(rescale_points<T>(g, w, X, s));
+  if (inflags & 4) LSSVM_TRY(rescale_points<T>(g, w, X, kernel, kp, s));
   const double t_setup = ms_since(t0);
   MatvecTimer tm;
   LSSVM_HIP(tm.init(info && info->time_matvec, info ? info->matvec_times : nullptr,
@@ -1238,8 +1249,8 @@ int matvec_impl(const T* X, int64_t n, int64_t d, int32_t kernel, const lssvm_pa
     LSSVM_HIP(read_flags(w.flags, s));
     LSSVM_HIP(hipStreamSynchronize(s));
     if (g_ctx->flags[F_NONFINITE]) return fail(LSSVM_ENONFINITE, "X holds a NaN or an infinity");
-    if (!g_ctx->flags[F_TINY]) return LSSVM_OK;
-    LSSVM_TRY(rescale_points<T>(g, w, X, s));   // tiny values: the product has waited for this
+    if (!g_ctx->flags[F_RANGE]) return LSSVM_OK;
+    LSSVM_TRY(rescale_points<T>(g, w, X, kernel, kp, s));   // the product has waited for this
   }
 }
 
@@ -1303,14 +1314,18 @@ int predict_impl(const T* Xtr, const T* alpha, double b, int64_t n, int64_t d, i
       return fail(LSSVM_ENONFINITE, "X_train or X_test holds a NaN or an infinity");
     return LSSVM_OK;
   }
-  LSSVM_HIP(launch_layout<T>(Xtr, n, d, w.Xtr, g.ld, g.d_pad, 1.f, 1, w.flags, s));
-  LSSVM_HIP(launch_layout<T>(Xte, n_test, d, w.Xte, w.ld_te, g.d_pad, 1.f, 1, w.flags, s));
-  if (kernel == LSSVM_RBF) {  // squared norms are only read by the radial kernel
-    LSSVM_HIP(launch_norms_q<T>(w.Xtr, g.ld, g.d_pad, -1, 0, kernel, kp.gamma, kp.coef0,
-                                kp.degree, w.ntr, nullptr, nullptr, s));
-    LSSVM_HIP(launch_norms_q<T>(w.Xte, w.ld_te, g.d_pad, -1, 0, kernel, kp.gamma, kp.coef0,
-                                kp.degree, w.nte, nullptr, nullptr, s));
-  }
+  LSSVM_HIP(launch_layout<T>(Xtr, n, d, w.Xtr, g.ld, g.d_pad, kStoredUp<T>, 1, w.flags, s));
+  LSSVM_HIP(launch_layout<T>(Xte, n_test, d, w.Xte, w.ld_te, g.d_pad, kStoredUp<T>, 1, w.flags, s));
+  auto norms = [&](int up_tr, int up_te) {   // only the radial kernel reads them
+    if (kernel != LSSVM_RBF) return hipSuccess;
+    const hipError_t e = launch_norms_q<T>(w.Xtr, g.ld, g.d_pad, -1, 0, up_tr, kernel, kp.gamma,
+                                           kp.coef0, kp.degree, w.ntr, nullptr, nullptr, s);
+    if (e != hipSuccess) return e;
+    return launch_norms_q<T>(w.Xte, w.ld_te, g.d_pad, -1, 0, up_te, kernel, kp.gamma, kp.coef0,
+                             kp.degree, w.nte, nullptr, nullptr, s);
+  };
+  int up_tr = kStoredUp<T>, up_te = kStoredUp<T>;
+  LSSVM_HIP(norms(up_tr, up_te));
   LSSVM_HIP(launch_pad_vec<T>(alpha, n, w.alpha, g.ld, w.flags, w.wait, s));
   TileArgs<T> a{};
   a.A = w.Xte;
@@ -1319,7 +1334,7 @@ int predict_impl(const T* Xtr, const T* alpha, double b, int64_t n, int64_t d, i
   a.nA = w.nte;
   a.nB = w.ntr;
   a.wB = w.alpha;
-  a.gscale = T(1);
+  a.gscale = (T)std::ldexp(1.0, -up_tr - up_te);
   a.gamma = (T)kp.gamma;
   a.coef0 = (T)kp.coef0;
   a.gamma64 = kp.gamma;
@@ -1339,10 +1354,12 @@ int predict_impl(const T* Xtr, const T* alpha, double b, int64_t n, int64_t d, i
     LSSVM_HIP(hipStreamSynchronize(s));
     if (g_ctx->flags[F_NONFINITE])
       return fail(LSSVM_ENONFINITE, "X_train or X_test holds a NaN or an infinity");
-    if (!g_ctx->flags[F_TINY]) return LSSVM_OK;
-    // tiny values on either side: the scores have waited for points stored scaled up
-    LSSVM_TRY(relayout_tiny(Xtr, n, d, w.Xtr, g.ld, g.d_pad, w.flags, &a.gscale, s));
-    LSSVM_TRY(relayout_tiny(Xte, n_test, d, w.Xte, w.ld_te, g.d_pad, w.flags, &a.gscale, s));
+    if (!g_ctx->flags[F_RANGE]) return LSSVM_OK;
+    // out of the usual range on either side: the scores have waited for this
+    LSSVM_TRY(relayout(Xtr, n, d, w.Xtr, g.ld, g.d_pad, w.flags, &up_tr, s));
+    LSSVM_TRY(relayout(Xte, n_test, d, w.Xte, w.ld_te, g.d_pad, w.flags, &up_te, s));
+    LSSVM_HIP(norms(up_tr, up_te));
+    a.gscale = (T)std::ldexp(1.0, -up_tr - up_te);
     a.stop = nullptr;
   }
 }

@@ -263,7 +263,10 @@ __global__ __launch_bounds__(256) void k_layout_split(const float* __restrict__ 
   for (int64_t b = blockIdx.x; b < nblk; b += gridDim.x) {
     const int64_t pb = b / nkb32, kb = b - pb * nkb32;
     float v[PER][8];
-    bool bad = false, tiny = false;
+    bool bad = false, out = false;   // out of the range the stored scale serves
+    auto outside = [](float x) {
+      return (fabsf(x) < kSplitMin && x != 0.f) || fabsf(x) >= kSplitMax;
+    };
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
       const int c = u * 256 + (int)threadIdx.x;
@@ -278,8 +281,7 @@ __global__ __launch_bounds__(256) void k_layout_split(const float* __restrict__ 
 #pragma unroll
       for (int e = 0; e < 8; e += 2) {
         uint16_t s0[3], s1[3];
-        tiny |= fabsf(v[u][e]) < kSplitMin && v[u][e] != 0.f;
-        tiny |= fabsf(v[u][e + 1]) < kSplitMin && v[u][e + 1] != 0.f;
+        out |= outside(v[u][e]) || outside(v[u][e + 1]);
         bf16_split(v[u][e] * scale, s0);
         bf16_split(v[u][e + 1] * scale, s1);
 #pragma unroll
@@ -291,7 +293,7 @@ __global__ __launch_bounds__(256) void k_layout_split(const float* __restrict__ 
         *reinterpret_cast<u32x4*>(slab + 8 * split_chunk(t, p, q & 1)) = w[t];
     }
     if (bad) flags[F_NONFINITE] = 1;
-    if (tiny && check) flags[F_TINY] = 1;
+    if (out && check) flags[F_RANGE] = 1;
   }
 }
 
@@ -308,7 +310,7 @@ __global__ __launch_bounds__(256) void k_abs_max(const float* __restrict__ X, in
 // ----------------------------------------------------------- a2 norms, q ----
 // VEC consecutive features of a point, from chunk c (VEC features each) of
 // its row in the layout: 8 for fp32 (the three slices of a chunk summed, which
-// gives the value back exactly), 2 for fp64.
+// gives the value as stored back exactly), 2 for fp64.
 template <typename T> struct PointRow;
 template <> struct PointRow<double> {
   static constexpr int VEC = 2, CPS = TileShape<double>::SB / VEC;   // chunks per slab row
@@ -367,6 +369,7 @@ constexpr int kNormThreads = 1024;
 template <typename T, int KER, bool SHORT>
 __global__ __launch_bounds__(kNormThreads) void k_norms_q(const store_t<T>* __restrict__ Xb,
                                                           int64_t nkb, int64_t m, int64_t N,
+                                                          double unscale2,
                                                           double gamma, double coef0, int degree,
                                                           T* __restrict__ norms,
                                                           double* __restrict__ q64,
@@ -434,6 +437,7 @@ __global__ __launch_bounds__(kNormThreads) void k_norms_q(const store_t<T>* __re
       if (t > 0 && m < 0) break;
 #pragma unroll
       for (int w = 0; w < PARTS; ++w) v[t] += part[t][w][tid];
+      if constexpr (sizeof(T) == 4) v[t] *= unscale2;   // a power of two
     }
     nrm = v[0];
     const int64_t r = (int64_t)blockIdx.x * PPB + tid;
@@ -492,7 +496,7 @@ __global__ __launch_bounds__(256) void k_finish_delta0(const double* bpart, int6
   const double s = sum_partials(bpart, nb, sh);
   if (threadIdx.x == 0) {
     scal[S_INFLAGS] = (flags[F_NONFINITE] ? 1.0 : 0.0) + (flags[F_BADLABEL] ? 2.0 : 0.0) +
-                      (flags[F_TINY] ? 4.0 : 0.0);
+                      (flags[F_RANGE] ? 4.0 : 0.0);
     scal[S_DELTA0] = s;
     scal[S_DHIST + 0] = s;
     double* st = scal + S_STATUS;
@@ -1632,7 +1636,7 @@ __global__ __launch_bounds__(256) void k_pad_vec(const T* __restrict__ src, int6
                                                  const int* __restrict__ flags,
                                                  double* __restrict__ wait) {
   const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
-  if (i == 0) *wait = (double)flags[F_TINY];
+  if (i == 0) *wait = (double)flags[F_RANGE];
   if (i < len_pad) dst[i] = i < len ? src[i] : T(0);
 }
 
@@ -1641,7 +1645,7 @@ __global__ __launch_bounds__(256) void k_mv_out(RankOne c, int64_t NP, int64_t N
                                                 T* __restrict__ out) {
   __shared__ double sh[NT / 64];
   // out stays untouched on error, and until the points' layout stands
-  if (c.flags[F_NONFINITE] != 0 || c.flags[F_TINY] != 0) return;
+  if (c.flags[F_NONFINITE] != 0 || c.flags[F_RANGE] != 0) return;
   const RankOneSums ro = rank_one_sums(c, sh);
   const double inv = 1.0 / c.scal[S_FIXSC];
   const bool bad = c.flags[F_PRODUCT] != 0;
@@ -1658,7 +1662,7 @@ __global__ __launch_bounds__(256) void k_predict_finish(const double* __restrict
                                                         int32_t* __restrict__ labels,
                                                         const int* __restrict__ flags) {
   // outputs untouched on error, and until the points' layout stands
-  if (flags[F_NONFINITE] != 0 || flags[F_TINY] != 0) return;
+  if (flags[F_NONFINITE] != 0 || flags[F_RANGE] != 0) return;
   // 64 test points per workgroup: wave w sums slots w, w + 4, ... (eight
   // loads in flight per lane), then the four wave sums are added in order.
   __shared__ double sh[NT / 64][64];
@@ -1686,7 +1690,7 @@ __global__ __launch_bounds__(256) void k_pad_to_f64(const T* __restrict__ src, i
                                                     double* scal, const int* __restrict__ flags) {
   __shared__ double sh[NT / 64];
   const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
-  if (i == 0 && flags) scal[S_STATUS + ST_DONE] = (double)flags[F_TINY];
+  if (i == 0 && flags) scal[S_STATUS + ST_DONE] = (double)flags[F_RANGE];
   const double v = i < len ? (double)src[i] : 0.0;
   if (i < len_pad) dst[i] = v;
   if (scal) {   // a product multiplies dst next
@@ -1875,7 +1879,7 @@ hipError_t launch_setup_clear(int64_t nT, int64_t group, uint32_t* order,
 // what one dispatch should hold).
 template <>
 hipError_t launch_layout<double>(const double* X, int64_t n, int64_t d, double* Xt, int64_t ld,
-                                 int64_t d_pad, float, int, int* flags, hipStream_t s) {
+                                 int64_t d_pad, int, int, int* flags, hipStream_t s) {
   const int64_t nkb = d_pad / TileShape<double>::BK, nblk = (ld / TileShape<double>::T) * nkb;
   const int vec_ok = d % 2 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
   const int64_t blocks = std::min<int64_t>(nblk, int64_t(1) << 20);
@@ -1885,13 +1889,13 @@ hipError_t launch_layout<double>(const double* X, int64_t n, int64_t d, double* 
 }
 template <>
 hipError_t launch_layout<float>(const float* X, int64_t n, int64_t d, uint16_t* Xt, int64_t ld,
-                                int64_t d_pad, float scale, int check, int* flags,
+                                int64_t d_pad, int up, int check, int* flags,
                                 hipStream_t s) {
   const int64_t nkb = d_pad / TileShape<float>::BK, nblk = (ld / TileShape<float>::T) * nkb;
   const int vec_ok = d % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
   const int64_t blocks = std::min<int64_t>(nblk, int64_t(1) << 20);
   hipLaunchKernelGGL(k_layout_split, dim3((unsigned)blocks), dim3(256), 0, s, X, n, d, Xt, nblk,
-                     nkb, vec_ok, scale, check, flags);
+                     nkb, vec_ok, std::ldexp(1.f, up), check, flags);
   return hipGetLastError();
 }
 hipError_t launch_abs_max(const float* X, int64_t count, int* out, hipStream_t s) {
@@ -1901,36 +1905,39 @@ hipError_t launch_abs_max(const float* X, int64_t count, int* out, hipStream_t s
 
 template <typename T, bool SHORT>
 static hipError_t norms_q(const store_t<T>* Xt, int64_t ld, int64_t d_pad, int64_t m, int64_t N,
-                          int kernel, double gamma, double coef0, int degree, T* norms,
+                          double unscale2, int kernel, double gamma, double coef0, int degree, T* norms,
                           double* q64, double* scal, hipStream_t s) {
   const int64_t nkb = d_pad / TileShape<T>::SB;
   // ld is a multiple of the tile edge
   const dim3 grid((unsigned)(ld / kNormPoints<T, SHORT>)), block(kNormThreads);
   switch (kernel) {
     case KLIN:
-      hipLaunchKernelGGL((k_norms_q<T, KLIN, SHORT>), grid, block, 0, s, Xt, nkb, m, N, gamma,
-                         coef0, degree, norms, q64, scal);
+      hipLaunchKernelGGL((k_norms_q<T, KLIN, SHORT>), grid, block, 0, s, Xt, nkb, m, N,
+                         unscale2, gamma, coef0, degree, norms, q64, scal);
       break;
     case KPOLY:
-      hipLaunchKernelGGL((k_norms_q<T, KPOLY, SHORT>), grid, block, 0, s, Xt, nkb, m, N, gamma,
-                         coef0, degree, norms, q64, scal);
+      hipLaunchKernelGGL((k_norms_q<T, KPOLY, SHORT>), grid, block, 0, s, Xt, nkb, m, N,
+                         unscale2, gamma, coef0, degree, norms, q64, scal);
       break;
     default:
-      hipLaunchKernelGGL((k_norms_q<T, KRBF, SHORT>), grid, block, 0, s, Xt, nkb, m, N, gamma,
-                         coef0, degree, norms, q64, scal);
+      hipLaunchKernelGGL((k_norms_q<T, KRBF, SHORT>), grid, block, 0, s, Xt, nkb, m, N,
+                         unscale2, gamma, coef0, degree, norms, q64, scal);
       break;
   }
   return hipGetLastError();
 }
 template <typename T>
 hipError_t launch_norms_q(const store_t<T>* Xt, int64_t ld, int64_t d_pad, int64_t m, int64_t N,
-                          int kernel, double gamma, double coef0, int degree, T* norms,
+                          int up, int kernel, double gamma, double coef0, int degree, T* norms,
                           double* q64, double* scal, hipStream_t s) {
   // up to 128 features: at most one chunk per thread of 64 (fp64), half a one of 32
   constexpr int64_t kShortRow = 8;
+  const double unscale2 = std::ldexp(1.0, -2 * up);
   if (d_pad / TileShape<T>::SB <= kShortRow)
-    return norms_q<T, true>(Xt, ld, d_pad, m, N, kernel, gamma, coef0, degree, norms, q64, scal, s);
-  return norms_q<T, false>(Xt, ld, d_pad, m, N, kernel, gamma, coef0, degree, norms, q64, scal, s);
+    return norms_q<T, true>(Xt, ld, d_pad, m, N, unscale2, kernel, gamma, coef0, degree, norms, q64,
+                            scal, s);
+  return norms_q<T, false>(Xt, ld, d_pad, m, N, unscale2, kernel, gamma, coef0, degree, norms, q64,
+                           scal, s);
 }
 
 // Workgroups per tile launch: 2^23 x 256 threads stays below the 2^32 work
@@ -2400,7 +2407,7 @@ hipError_t static_scratch(double** ptr, int64_t* capacity) {
 
 #define LSSVM_INSTANTIATE(T)                                                                      \
   template hipError_t launch_norms_q<T>(const store_t<T>*, int64_t, int64_t, int64_t, int64_t,    \
-                                        int, double, double, int, T*, double*, double*,           \
+                                        int, int, double, double, int, T*, double*, double*,           \
                                         hipStream_t);                                             \
   template hipError_t launch_tiles_sym<T>(const TileArgs<T>&, int, int, int64_t, hipStream_t);    \
   template hipError_t launch_tiles_gen<T>(const TileArgs<T>&, int, int64_t, hipStream_t);         \

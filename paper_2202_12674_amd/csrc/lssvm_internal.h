@@ -46,7 +46,7 @@ enum Scalar : int {
   S_NMAX = 21,
   S_FIXSC = 22,
   S_INFLAGS = 23,   // the input flags as read after the right-hand side: 1 non-finite
-                    // X, 2 a label other than +-1, 4 F_TINY (one read-back with S_DELTA0)
+                    // X, 2 a label other than +-1, 4 F_RANGE (one read-back with S_DELTA0)
   S_TIMES = 24,     // k_lin_train: wall clock ticks of its setup, and of the rest
   S_COUNT = 26
 };
@@ -70,9 +70,10 @@ inline int64_t cg_blocks(int64_t NP) { return vec_blocks(NP); }
 // Flags raised by kernels (int32 each).
 // F_PRODUCT: a symmetric product had a row sum that is not finite (its
 // entries then come out as NaN, so CG reports a breakdown).
-// F_TINY: an fp32 point holds a nonzero value below kSplitMin, and the points are not
-// yet laid out to suit (products and scores wait for that: TileArgs::stop).
-enum Flag : int { F_NONFINITE = 0, F_BADLABEL = 1, F_PRODUCT = 2, F_TINY = 3, F_COUNT = 4 };
+// F_RANGE: an fp32 point holds a value that the usual stored scale does not serve
+// (kSplitMin, kSplitMax), and the points are not yet laid out to suit (products and
+// scores wait for that: TileArgs::stop).
+enum Flag : int { F_NONFINITE = 0, F_BADLABEL = 1, F_PRODUCT = 2, F_RANGE = 3, F_COUNT = 4 };
 
 
 // One symmetric product as its readers see it: (K p)_i in the fixed-point
@@ -145,17 +146,17 @@ hipError_t launch_setup_clear(int64_t nT, int64_t group, uint32_t* order,
                               int* flags, double* scal, int64_t* acc, int64_t nacc,
                               unsigned* ticket, hipStream_t s);
 
-// scale: what fp32 values are multiplied by as they are stored (a power of two);
-// check: raise F_TINY.
+// fp32 values are stored multiplied by 2^up; check: raise F_RANGE.
+template <typename T> constexpr int kStoredUp = sizeof(T) == 4 ? 16 : 0;
 template <typename T>
 hipError_t launch_layout(const T* X, int64_t n, int64_t d, store_t<T>* Xt, int64_t ld, int64_t d_pad,
-                         float scale, int check, int* flags, hipStream_t s);
+                         int up, int check, int* flags, hipStream_t s);
 // Raises *out (an int32 set to 0 before) to the bits of the largest |X[k]| of
 // `count` values.
 hipError_t launch_abs_max(const float* X, int64_t count, int* out, hipStream_t s);
 template <typename T>
 hipError_t launch_norms_q(const store_t<T>* Xt, int64_t ld, int64_t d_pad, int64_t m, int64_t N,
-                          int kernel, double gamma, double coef0, int degree, T* norms,
+                          int up, int kernel, double gamma, double coef0, int degree, T* norms,
                           double* q64, double* scal, hipStream_t s);
 template <typename T>
 // Symmetric tile launch of nwg workgroups doing `part` (a TilePart; a fixup
@@ -221,7 +222,7 @@ hipError_t launch_bias(const double* x, const double* q64, int64_t N, const T* y
 // label passed the checks (flags set by the layout kernel before it).
 template <typename T>
 hipError_t launch_single_point(const T* y, T* alpha_out, double* scal, int* flags, hipStream_t s);
-// dst = src zero-padded; *wait = 1 if F_TINY is up, else 0.
+// dst = src zero-padded; *wait = 1 if F_RANGE is up, else 0.
 template <typename T>
 hipError_t launch_pad_vec(const T* src, int64_t len, T* dst, int64_t len_pad, const int* flags,
                           double* wait, hipStream_t s);
@@ -234,7 +235,7 @@ hipError_t launch_predict_finish(const double* part, int64_t nslots, int64_t ld,
                                  double b, T* scores, int32_t* labels, const int* flags,
                                  hipStream_t s);
 // dst = src zero-padded, in fp64; with scal, also raises scal[S_PMAX] to max |dst|;
-// with flags, sets the stop flag (ST_DONE) to 1 if F_TINY is up.
+// with flags, sets the stop flag (ST_DONE) to 1 if F_RANGE is up.
 template <typename T>
 hipError_t launch_pad_to_f64(const T* src, int64_t len, double* dst, int64_t len_pad,
                              double* scal, const int* flags, hipStream_t s);

@@ -53,7 +53,7 @@ struct TileArgs {
   double* pq;         // symmetric mode: per panel I, sum p_j at [I], sum q_j p_j at [nTc + I]
   const T* wB;        // general mode: per-column weights (alpha)
   T gscale;   // fp32: what the stored points' inner products are multiplied by, a power
-              // of two: 1 unless they were stored scaled up (k_layout_split)
+              // of two (they are stored scaled up: k_layout_split)
   T gamma, coef0;
   double gamma64, coef64;   // fp32 polynomial: its kernel values are formed in fp64
   T rbf_scale;   // RBF exponent scale: gamma (fp64, exp) or gamma log2(e) (fp32, exp2)
@@ -78,7 +78,7 @@ struct TileArgs {
   double* fx;
   int* fx_bad;          // symmetric mode: raised when a row sum is not finite
   const double* stop;   // nonzero: the launch returns at once, as CG has stopped or as the
-                        // points have to be laid out anew first (F_TINY). Or null.
+                        // points have to be laid out anew first (F_RANGE). Or null.
   int64_t part_ld;
   // A product's tiles may outnumber one launch (the dispatch grid counts work
   // items in 32 bits), so the launcher splits them into chunks: workgroup b of

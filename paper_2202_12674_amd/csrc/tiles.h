@@ -75,17 +75,18 @@ template <> __device__ inline float rbf_exp<float>(float x) { return __builtin_a
 template <> __device__ inline double rbf_exp<double>(double x) { return exp(x); }
 
 // Kernel value from the inner product g = <x_i, x_j> (and squared norms for
-// RBF, with rbf_scale = gamma, times log2(e) in fp32). For the polynomial
+// RBF, with rbf_scale = gamma, times log2(e) in fp32; two is 2 by what g has to be
+// multiplied by). For the polynomial
 // kernel this returns the base gamma g + coef0; poly_power raises a whole
 // batch of bases to the degree with one uniform loop.
 template <int KER, typename T>
-__device__ inline T kernel_value(T g, T ni, T nj, T gamma, T coef0, T rbf_scale) {
+__device__ inline T kernel_value(T g, T ni, T nj, T gamma, T coef0, T rbf_scale, T two = T(2)) {
   if constexpr (KER == KLIN) {
     return g;
   } else if constexpr (KER == KPOLY) {
     return gamma * g + coef0;
   } else {
-    T dist = ni + nj - T(2) * g;
+    T dist = ni + nj - two * g;
     dist = dist > T(0) ? dist : T(0);
     return rbf_exp<T>(-rbf_scale * dist);
   }
@@ -222,10 +223,17 @@ __device__ inline void fixed_add(int64_t* acc, int* bad, int64_t row, double v, 
 // partial products h h, h m, m h, m m, h l and l h, each exact in fp32, summed
 // by the matrix cores in fp32; the three left out (m l, l m, l l) are below
 // 2^-23 |x y|, and 2^-26 |x y| in the root mean square over random values.
-// The bf16 instructions take subnormal operands as zero, so points holding
-// values below kSplitMin, whose lowest slice may be subnormal, are stored
-// scaled up by a power of two.
-constexpr float kSplitMin = 0x1p-103f;   // 24 bits down from here: 2^-126
+// The bf16 instructions take subnormal operands as zero, and a product of lower
+// slices loses bits below 2^-149 that x y, up to 2^24 larger, still has (points
+// around 2^-58: 39 units of 2^-24 x y, 15 on the fp32 instruction). So points are
+// stored scaled up by 2^kStoredUp, and the inner products scaled back with the
+// kernel's own factor, which costs nothing. That serves values from kSplitMin, whose
+// stored products are 2^-112 and more, to kSplitMax, where 2^21 products of 2^104
+// still fit; points outside are laid out anew by their largest value. (By 2^12 values
+// around 1 toggle enough exponent bits between their slices to draw more power, which
+// bounds the large products: 32768 x 4096 cubic 21.2-21.8 ms; 2^0, 2^16, 2^24 and
+// 2^32 21.0-21.5.)
+constexpr float kSplitMin = 0x1p-72f, kSplitMax = 0x1p36f;
 __device__ inline uint32_t bf16_round(float x) {   // bf16 bits of finite x
   const uint32_t u = __builtin_bit_cast(uint32_t, x);
   const uint32_t r = (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
@@ -621,12 +629,6 @@ __device__ __forceinline__ bool tile_body(const TileArgs<T>& a) {
     for (int i = 0; i < RB; ++i)
 #pragma unroll
       for (int j = 0; j < CB; ++j) acc[i][j] += low[i][j];
-    if (PART == kWhole && a.gscale != T(1)) {   // uniform
-#pragma unroll
-      for (int i = 0; i < RB; ++i)
-#pragma unroll
-        for (int j = 0; j < CB; ++j) acc[i][j] *= a.gscale;
-    }
   }
 
   // Split tiles: park this split's inner products, or sum all splits of the
@@ -670,12 +672,6 @@ __device__ __forceinline__ bool tile_body(const TileArgs<T>& a) {
               for (int e = 0; e < PER; ++e) acc[i][j][w * PER + e] += x[e];
             }
       }
-      if (SPLIT && a.gscale != T(1)) {   // uniform
-#pragma unroll
-        for (int i = 0; i < RB; ++i)
-#pragma unroll
-          for (int j = 0; j < CB; ++j) acc[i][j] *= a.gscale;
-      }
     }
   }
 
@@ -707,6 +703,9 @@ __device__ __forceinline__ bool tile_body(const TileArgs<T>& a) {
     fxs = fixed_scale<KER>(a, fx_pmax, fx_nmax);
     if (blockIdx.x == 0 && tid == 0) a.fx[2] = fxs;   // every workgroup finds the same
   }
+  // fp32: the inner products of the points as stored, scaled back on the way
+  const T two = SPLIT ? T(2) * a.gscale : T(2);
+  const double gamma_g = POLY64 ? a.gamma64 * (double)a.gscale : 0.0;
   T nBj[CB];
   double pBj[CB];
 #pragma unroll
@@ -740,10 +739,11 @@ __device__ __forceinline__ bool tile_body(const TileArgs<T>& a) {
       pAi[vv] = SYM ? vp[0][li] : 0.0;
 #pragma unroll
       for (int j = 0; j < CB; ++j)
-        if constexpr (POLY64) kv[vv][j] = a.gamma64 * (double)acc[i][j][v0 + vv] + a.coef64;
+        if constexpr (POLY64) kv[vv][j] = gamma_g * (double)acc[i][j][v0 + vv] + a.coef64;
+        else if constexpr (SPLIT && KER == KLIN) kv[vv][j] = acc[i][j][v0 + vv] * a.gscale;
         else
           kv[vv][j] = kernel_value<KER, T>(acc[i][j][v0 + vv], nAi, nBj[j], a.gamma, a.coef0,
-                                           a.rbf_scale);
+                                           a.rbf_scale, two);
     }
     if constexpr (KER == KPOLY) poly_power(kv, a.degree);
     if (HALF && diag) {   // uniform

@@ -90,3 +90,60 @@ def test_products_and_training_on_tiny_points(torch_dev, kernel, kw):
     rhs = (y[:N] - y[N]).astype(np.float64)
     x = r.alpha.double().cpu().numpy()[:N]
     assert r.converged and np.linalg.norm(rhs - Q @ x) <= 1e-3 * np.linalg.norm(rhs)
+
+
+# the smallest inner products that fp32 holds in full, and some below
+@pytest.mark.parametrize("exponent", [52, 56, 58, 60, 62, 70])
+@pytest.mark.parametrize("n,nt,d", [(130, 200, 1), (130, 129, 3), (256, 200, 40)])
+def test_small_values_keep_fp32_accuracy(torch_dev, exponent, n, nt, d):
+    """Points around 2^-exponent: the products of lower slices lie far below the
+    smallest normal float long before x y does. gamma brings the values back."""
+    torch, dev = torch_dev
+    import paper_2202_12674_amd as P
+    rng = np.random.default_rng(d + exponent)
+    A, B = ((rng.uniform(-1.0, 1.0, (k, d)) * 2.0 ** -exponent).astype(np.float32)
+            for k in (n, nt))
+    gamma = 2.0 ** (2 * exponent)
+    ref = gamma * (A.astype(np.float64) @ B.astype(np.float64).T)
+    mag = gamma * (np.abs(A.astype(np.float64)) @ np.abs(B.astype(np.float64)).T)
+    tol = (4 + -(-d // 16)) * 2.0 ** -23 * mag   # as above
+    Ad, Bd = torch.from_numpy(A).to(dev), torch.from_numpy(B).to(dev)
+    for j in range(0, n, 13):
+        e = torch.zeros(n, dtype=torch.float32, device=dev)
+        e[j] = 1.0
+        s, _ = P.predict(Ad, e, 0.0, Bd, kernel="poly", gamma=gamma, coef0=0.0, degree=1)
+        err = np.abs(s.cpu().numpy().astype(np.float64) - ref[j])
+        assert (err <= tol[j]).all(), (j, float((err / tol[j]).max()))
+
+
+@pytest.mark.parametrize("low,high", [(-75, 10), (-40, 35), (-40, 45), (-120, 0), (-60, 60)])
+def test_values_of_any_range_by_the_products(torch_dev, low, high):
+    """Values spread over 2^low .. 2^high (the stored scale is chosen by the range):
+    RBF products and degree-1 products against fp64, a training to eps. gamma makes
+    the largest values' distances about 1."""
+    torch, dev = torch_dev
+    import paper_2202_12674_amd as P
+    rng = np.random.default_rng(high - low)
+    n, d = 300, 21
+    X = rng.uniform(-1.0, 1.0, (n, d)) * 2.0 ** high
+    X[:, 1::2] *= 2.0 ** rng.uniform(low - high, 0.0, (n, len(range(1, d, 2))))
+    X = X.astype(np.float32)
+    X64, N = X.astype(np.float64), n - 1
+    G = X64 @ X64.T
+    gamma = 2.0 ** (-2 * high) / d
+    nrm = np.diag(G)
+    K = {"rbf": np.exp(-gamma * np.maximum(nrm[:, None] + nrm[None, :] - 2 * G, 0.0)),
+         "poly": gamma * G + 0.5}
+    Xd = torch.from_numpy(X).to(dev)
+    p = rng.standard_normal(N).astype(np.float32)
+    y = np.where(rng.random(n) < 0.5, 1.0, -1.0).astype(np.float32)
+    for kernel, k in K.items():
+        kw = dict(kernel=kernel, gamma=gamma, coef0=0.5, degree=1, C=1.0)
+        Q = k[:N, :N] - k[:N, N:] - k[N:, :N] + k[N, N] + 1.0 + np.eye(N)
+        out = P.matvec(Xd, torch.from_numpy(p).to(dev), **kw).double().cpu().numpy()
+        ref = Q @ p.astype(np.float64)
+        assert np.abs(out - ref).max() <= 1e-5 * np.abs(ref).max(), kernel
+        r = P.train(Xd, torch.from_numpy(y).to(dev), eps=1e-5, **kw)
+        rhs = (y[:N] - y[N]).astype(np.float64)
+        x = r.alpha.double().cpu().numpy()[:N]
+        assert r.converged and np.linalg.norm(rhs - Q @ x) <= 1e-4 * np.linalg.norm(rhs), kernel
