@@ -161,8 +161,11 @@ size_t lssvm_predict_workspace_bytes(int64_t n, int64_t n_test, int64_t d, int32
  *   - on curvature breakdown, d^T Q~ d <= 0 (LSSVM_EBREAKDOWN, outputs
  *     untouched; Q~ is positive definite for coef0 >= 0).
  * For eps < 1e-12 a linear training whose products are passes over the points
- * takes convergence from recomputed residuals only (and from the last iteration
- * allowed): its recurrence falls below what fp64 iterates attain.
+ * (too large for one workgroup, and more than 1025 points or 128 features) takes
+ * convergence from recomputed residuals only (and from the last iteration
+ * allowed): its recurrence falls below what fp64 iterates attain. Where it meets
+ * eps the residual is recomputed there (one more product, counted in n_matvec),
+ * and CG goes on from that if it does not meet eps.
  * n = 1 or all labels equal give alpha = 0, b = y_m without iterating.
  */
 int lssvm_train(const void* X, const void* y, int64_t n, int64_t d, int32_t dtype,

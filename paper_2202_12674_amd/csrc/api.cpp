@@ -72,8 +72,10 @@ constexpr int64_t kReplaceEvery = 50;  // residual recomputed every 50th iterati
 // The products of linear trainings are so nearly exact that the CG recurrence
 // goes on falling below the residual that fp64 iterates can have (4096 x 1024,
 // eps 1e-13: 7.7e-14 at iteration 161 against a true 1.3e-12). So for an eps
-// below this, a linear training of passes (or whole, in one workgroup)
-// converges on recomputed residuals only (every 50th iteration, and the last one allowed).
+// below this, a linear training of passes recomputes the residual as soon as the
+// recurrence meets eps, and converges on that (or at the last iteration allowed). Left
+// to the next 50th iteration a recurrence of few features falls as far as the
+// underflow, where d^T Q~ d = 0 ends CG as a breakdown.
 constexpr double kTrustedEps = 1e-12;
 
 inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
@@ -892,7 +894,6 @@ int train_small_linear(const Geometry& g, const TrainWs<T>& w, const T* X, const
   a.eps2 = eps * eps;
   a.max_iter = max_iter > 0 ? max_iter : g.N;
   a.replace_every = kReplaceEvery;
-  a.trusted = eps >= kTrustedEps;
   a.x = w.x;
   a.rhs = w.rhs;
   a.q64 = w.q64;
@@ -1024,7 +1025,8 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
   int status = LSSVM_OK;
   int64_t batch = 1;   // fused (small) problems start at 8, below
   double* st = g_ctx->p;
-  int64_t warm_products = 0;
+  int64_t extra_products = 0;
+  constexpr int64_t kMaxBatch = 32;
   auto product_of = [&](const double* p) {   // a finished product, for its readers
     return passes ? lin.rank_one(p, w.qv) : rank_one(g, w, kernel, C, p);
   };
@@ -1040,7 +1042,7 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
     LSSVM_HIP(hipStreamSynchronize(s));
     delta = st[ST_DELTA];
     done = st[ST_DONE] != 0.0;
-    warm_products = 1;
+    extra_products = 1;
     if (!std::isfinite(delta))
       return fail(LSSVM_ENONFINITE, "the warm-start alpha gives a non-finite residual");
   }
@@ -1060,7 +1062,8 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
   // batch is formed on its own, so that the status is complete when read.
   double *dir = w.dir, *dir_other = w.dir2;
   bool pending = false;
-  const bool trusted = eps >= kTrustedEps;
+  const bool trusted = !passes || eps >= kTrustedEps;
+  double* dir_of[kMaxBatch];   // linear passes: the direction of each iteration of a batch
   while (!done && queued < max_iter) {
     const int64_t nq = std::min<int64_t>(std::min(batch, need), max_iter - queued);
     for (int64_t b = 0; b < nq; ++b) {
@@ -1091,11 +1094,11 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
           v.nb = nb;
           v.par = par ^ 1;
           v.iter = k - 1;
-          v.test = trusted;
           v.hist = w.hist;
           v.hist_cap = g.NP + 1;
           std::swap(dir, dir_other);
         }
+        dir_of[b] = dir;
         LSSVM_HIP(lin.weights(v));
         LSSVM_HIP(launch_lin_gather<T>(X, g.N, g.d, w.lin_w, lin.rank_one(dir, nullptr), w.qv,
                                        w.bp0, s));
@@ -1111,9 +1114,8 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
         }
         if (refresh || b + 1 == nq) {
           LSSVM_HIP(launch_cg_direction(w.bp1, nb, w.scal, par, k, w.r, dir, NP, w.hist, g.NP + 1,
-                                        refresh ? k / kReplaceEvery : 0,
-                                        trusted || refresh || k == max_iter, 0, w.bp2, w.x,
-                                        w.xbest, s));
+                                        refresh ? k / kReplaceEvery : 0, 0, w.bp2, w.x, w.xbest,
+                                        s));
           pending = false;
         }
         continue;
@@ -1131,9 +1133,10 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
                                    g.NP, s));
       }
       LSSVM_HIP(launch_cg_direction(w.bp1, g.nb, w.scal, par, k, w.r, w.dir, g.NP, w.hist,
-                                    g.NP + 1, refresh ? k / kReplaceEvery : 0, 1, 1, w.bp2,
+                                    g.NP + 1, refresh ? k / kReplaceEvery : 0, 1, w.bp2,
                                     w.x, w.xbest, s));
     }
+    const int64_t first = queued - nq + 1;
     LSSVM_HIP(launch_read_back(w.scal + S_STATUS, ST_COUNT, st, s));
     LSSVM_HIP(hipStreamSynchronize(s));
     it = (int64_t)st[ST_ITER];
@@ -1147,12 +1150,30 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
                     (long long)it, st[ST_CURV]);
       break;
     }
+    if (!trusted && done && !stalled && it % kReplaceEvery != 0 && it < max_iter) {
+      // the recurrence met eps: the residual itself, and on from there if it does not
+      dir = dir_of[it - first];
+      dir_other = dir == w.dir ? w.dir2 : w.dir;
+      queued = it;
+      extra_products += 1;
+      LSSVM_HIP(hipMemsetAsync(w.scal + S_STATUS + ST_DONE, 0, sizeof(double), s));
+      LSSVM_HIP(tm.start(s, it));
+      LSSVM_TRY(lin.product(w.x, false));
+      LSSVM_HIP(tm.stop(s));
+      LSSVM_HIP(launch_cg_residual(product_of(w.x), NP, g.N, w.rhs, w.r, w.bp1, w.bp2, s));
+      LSSVM_HIP(launch_cg_direction(w.bp1, nb, w.scal, (int)((it - 1) & 1), it, w.r, dir, NP,
+                                    w.hist, g.NP + 1, 0, 0, w.bp2, w.x, w.xbest, s));
+      LSSVM_HIP(launch_read_back(w.scal + S_STATUS, ST_COUNT, st, s));
+      LSSVM_HIP(hipStreamSynchronize(s));
+      LSSVM_HIP(tm.harvest(it));
+      done = st[ST_DONE] != 0.0;
+    }
     delta = st[ST_DELTA];
     if (log_enabled())
       std::fprintf(stderr, "[lssvm] CG iteration %lld: relative residual %.3e (%.1f ms)\n",
                    (long long)it, delta0 > 0.0 ? std::sqrt(delta / delta0) : 0.0,
                    ms_since(t1));
-    batch = std::min<int64_t>(2 * batch, 32);
+    batch = std::min<int64_t>(2 * batch, kMaxBatch);
     need = max_iter;
     if (it > it_prev && delta > 0.0 && delta < delta_prev && st[ST_STOP] < delta) {
       const double per_it = std::log(delta / delta_prev) / (double)(it - it_prev);   // < 0
@@ -1164,7 +1185,7 @@ int train_impl(const T* X, const T* y, int64_t n, int64_t d, int32_t kernel,
   }
   CgEnd e;
   e.it = it;
-  e.extra_products = warm_products;
+  e.extra_products = extra_products;
   e.converged = done && !broke && !stalled;
   e.broke = broke;
   e.stalled = stalled;

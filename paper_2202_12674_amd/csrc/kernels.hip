@@ -636,8 +636,8 @@ __global__ __launch_bounds__(256) void k_true_residual(RankOne c, int64_t NP, in
 
 // beta = r^T r (new) / r^T r (old); d = r + beta d (beta = 0 if the old
 // r^T r is 0, an exact solution). Block 0 records the iteration in the
-// status (and the history) and raises done once r^T r <= eps^2 r0^T r0 (with
-// `test` clear only on r = 0). raise: bound |d| for a product on tiles.
+// status (and the history) and raises done once r^T r <= eps^2 r0^T r0, and d then
+// stays. raise: bound |d| for a product on tiles.
 //
 // At the refresh-th residual recomputation (refresh > 0) r is a true
 // residual. Unless it met eps, CG has progressed if r^T r or the energy
@@ -655,7 +655,7 @@ __global__ __launch_bounds__(256) void k_cg_direction(const double* __restrict__
                                                       double* scal, int par, int64_t iter,
                                                       const double* __restrict__ r,
                                                       double* __restrict__ dir, int64_t NP, double* hist, int64_t hist_cap,
-                                                      int64_t refresh, int test, int raise,
+                                                      int64_t refresh, int raise,
                                                       const double* __restrict__ bp_phi,
                                                       const double* __restrict__ x,
                                                       double* __restrict__ xbest,
@@ -673,7 +673,7 @@ __global__ __launch_bounds__(256) void k_cg_direction(const double* __restrict__
   }
   const double dnew = sum_partials(bp_in, nb, sh);
   const double dold = scal[S_DHIST + par];
-  const bool conv = dnew <= (test ? st[ST_STOP] : 0.0);
+  const bool conv = dnew <= st[ST_STOP];
   bool stall = false;
   double dbest = dnew;
   if (refresh > 0 && !conv) {   // uniform over the grid: every block sums the same partials
@@ -693,7 +693,7 @@ __global__ __launch_bounds__(256) void k_cg_direction(const double* __restrict__
         xbest[i] = x[i];
   }
   const double beta = dold != 0.0 ? dnew / dold : 0.0;
-  if (!stall) {
+  if (!stall && !conv) {
     double dmax = 0.0;
 #pragma unroll 4
     for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < NP;
@@ -1163,7 +1163,7 @@ __global__ __launch_bounds__(256) void k_lin_w(const T* __restrict__ X, int64_t 
     double* st = v.scal + S_STATUS;
     const double dnew = sum_partials(v.bp, v.nb, sh);
     const double dold = v.scal[S_DHIST + v.par];
-    const bool conv = dnew <= (v.test ? st[ST_STOP] : 0.0);   // uniform over the grid
+    const bool conv = dnew <= st[ST_STOP];   // uniform over the grid
     if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) {
       v.scal[S_DHIST + (v.par ^ 1)] = dnew;
       st[ST_DELTA] = dnew;
@@ -1535,7 +1535,7 @@ __global__ __launch_bounds__(kLinTrainThreads) void k_lin_train(const T* __restr
     }
     const double dnew = get(4);
     ++it;
-    conv = dnew <= (a.trusted || refresh || it == a.max_iter ? stop : 0.0);
+    conv = dnew <= stop;
     double dbest = dnew;
     if (refresh && !conv) {
       const bool lower = dnew < best, lower_phi = phi < phi_best;
@@ -2097,11 +2097,11 @@ hipError_t launch_true_residual(const RankOne& c, int64_t NP, int64_t N, const d
 
 hipError_t launch_cg_direction(const double* bp_in, int64_t nb, double* scal, int par,
                                int64_t iter, const double* r, double* dir, int64_t NP,
-                               double* hist, int64_t hist_cap, int64_t refresh, int test,
-                               int raise, const double* bp_phi, const double* x, double* xbest,
+                               double* hist, int64_t hist_cap, int64_t refresh, int raise,
+                               const double* bp_phi, const double* x, double* xbest,
                                hipStream_t s) {
   hipLaunchKernelGGL(k_cg_direction, dim3((unsigned)cg_blocks(NP)), dim3(NT), 0, s, bp_in, nb,
-                     scal, par, iter, r, dir, NP, hist, hist_cap, refresh, test, raise, bp_phi, x,
+                     scal, par, iter, r, dir, NP, hist, hist_cap, refresh, raise, bp_phi, x,
                      xbest, (double*)nullptr);
   return hipGetLastError();
 }
@@ -2126,7 +2126,7 @@ hipError_t launch_cg_step(int64_t N, double* x, double* r, double* d, const doub
   hipLaunchKernelGGL(k_step_dot, grid, dim3(NT), 0, s, d, q, N, bp0, scalars, scal);
   hipLaunchKernelGGL(k_cg_update, grid, dim3(NT), 0, s, 0, bp0, nb, scal, 0, d, q, x, r, bp1, N);
   hipLaunchKernelGGL(k_cg_direction, grid, dim3(NT), 0, s, bp1, nb, scal, 0, (int64_t)1, r, d, N,
-                     (double*)nullptr, (int64_t)0, (int64_t)0, 1, 0, (const double*)nullptr,
+                     (double*)nullptr, (int64_t)0, (int64_t)0, 0, (const double*)nullptr,
                      (const double*)nullptr, (double*)nullptr, scalars);
   return hipGetLastError();
 }

@@ -106,7 +106,6 @@ struct LinVec {
   int64_t nb;
   double* scal;
   int par, stop;      // stop: return at once when CG has stopped
-  int test;           // test r^T r against the stop threshold
   int64_t iter;
   double* hist;
   int64_t hist_cap;
@@ -212,8 +211,8 @@ hipError_t launch_cg_step(int64_t N, double* x, double* r, double* d, const doub
 // minimum).
 hipError_t launch_cg_direction(const double* bp_in, int64_t nb, double* scal, int par,
                                int64_t iter, const double* r, double* dir, int64_t NP,
-                               double* hist, int64_t hist_cap, int64_t refresh, int test,
-                               int raise, const double* bp_phi, const double* x, double* xbest,
+                               double* hist, int64_t hist_cap, int64_t refresh, int raise,
+                               const double* bp_phi, const double* x, double* xbest,
                                hipStream_t s);
 template <typename T>
 hipError_t launch_bias(const double* x, const double* q64, int64_t N, const T* y, double* scal,
@@ -281,7 +280,6 @@ hipError_t launch_predict_few(PredictFew<T> a, int kernel, double b, T* scores, 
 struct LinTrain {
   double invC, eps2;
   int64_t max_iter, replace_every;
-  int trusted;   // converge on the recurrence too, not only at recomputations
   double *x, *rhs, *q64, *scal, *hist;
   int64_t hist_cap;
   int* flags;

@@ -326,3 +326,46 @@ def test_cg_step_at_an_exact_solution(torch_dev):
     np.testing.assert_array_equal(d.cpu().numpy(), do)
     assert got[0] == rro == 0.0 and got[2] == ao == 0.0 and got[3] == bo == 0.0
     assert got[1] == pytest.approx(go, rel=1e-12)
+
+
+@pytest.mark.parametrize("n,d", [(45, 1), (93, 1), (69, 2), (120, 4),              # one workgroup
+                                 (1500, 1), (1500, 2), (3001, 3), (2000, 8)])   # passes
+def test_linear_eps_near_the_floor_stops_where_it_is_met(torch_dev, n, d):
+    """A linear problem of d features has d + 2 distinct eigenvalues, so CG ends
+    within a few iterations of that at any eps. Let run on to the next residual
+    recomputation its recurrence underflows, and d^T Q~ d = 0 is a breakdown."""
+    torch, dev = torch_dev
+    import paper_2202_12674_amd as P
+    for seed in range(4):
+        rng = np.random.default_rng(1000 * seed + n)
+        X = rng.uniform(-1.0, 1.0, (n, d))
+        y = np.where(rng.random(n) < 0.5, 1.0, -1.0)
+        y[0], y[-1] = 1.0, -1.0
+        C = 10.0 / n
+        r = P.train(to_dev(torch, dev, X), to_dev(torch, dev, y), C=C, eps=2e-13,
+                    true_residual=True, history=100)
+        assert r.converged and r.iterations <= 2 * (d + 2) + 4, (seed, r.iterations)
+        assert r.true_rel_residual <= 1e-12
+        assert len(r.history) == r.iterations
+        if n > 1025:   # a recomputed residual
+            assert r.true_rel_residual <= 2e-13 * (1 + 1e-6)
+            assert r.n_matvec == r.iterations + 1
+
+
+def test_linear_eps_below_the_floor_goes_on_from_the_residual(torch_dev):
+    """Where the recurrence meets an eps that the residual does not, CG goes on from
+    the residual, and ends at the floor: at a later one that meets eps, or stalled."""
+    torch, dev = torch_dev
+    import paper_2202_12674_amd as P
+    for d, C in ((1, 1.0), (3, 1.0), (8, 1e-2)):
+        rng = np.random.default_rng(d)
+        X = rng.uniform(-1.0, 1.0, (2500, d))
+        y = np.where(rng.random(2500) < 0.5, 1.0, -1.0)
+        r = P.train(to_dev(torch, dev, X), to_dev(torch, dev, y), C=C, eps=1e-16,
+                    true_residual=True, time_matvec=True)
+        log(f"  d {d} C {C}: {r.iterations} it, {r.n_matvec} products, converged {r.converged}, "
+            f"stalled {r.stalled}, true {r.true_rel_residual:.1e}")
+        assert r.converged or (r.stalled and r.iterations % 50 == 0)
+        assert r.n_matvec > r.iterations + r.iterations // 50
+        assert r.true_rel_residual <= 1e-11
+        assert r.true_rel_residual == pytest.approx(r.rel_residual, rel=1e-6)
