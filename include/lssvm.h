@@ -284,28 +284,24 @@ const char* lssvm_last_error(void);
  * 0 for an unknown dtype. Informational: sizes need no padding by the caller. */
 int32_t lssvm_tile_size(int32_t dtype);
 
-/* How tiles of the upper triangle are laid out over workgroups for n >= 2
- * points of d features, in rounds of two workgroups per CU.
+/* How the implicit products of lssvm_train and lssvm_matvec lay out their
+ * upper-triangle tiles over workgroups for n >= 2 points of d features.
  * On success writes plan[0..2] (host memory, caller-owned):
- *   plan[0]  workgroups per tile in the full rounds: 1, except for the
- *            linear kernel on problems with few tiles, whose features are
- *            split over 2..16 workgroups per tile (the partial sums add up
- *            because the linear kernel value is the inner product itself);
- *   plan[1]  tiles of a last partial round that run split finer (0 if none):
- *            they park their partial inner products, which a fix-up launch
- *            sums (or, in the linear kernel's plan, add up);
- *   plan[2]  workgroups per such tile (plan[0] when plan[1] is 0).
- * Every split leaves an even number of feature blocks per workgroup, except
- * on small problems (n <= 1025 without a split last round, whose CG
- * iterations are single launches): there the linear kernel's tiles split as
- * far as one round of workgroups allows, down to one feature block each.
- * The plan is that of these rules alone. Products follow it with these
- * exceptions: the linear kernel uses tiles only up to 1025 points of at most
- * 128 features (its other products are passes over the points, which no plan
- * describes); and the other kernels share out the tiles of problems of up to 256
- * tiles, and in fp64 those after the last full round of one per CU, in shares
- * that need not be equal. Every product of a problem (CG iterations, residual
- * recomputations, lssvm_matvec) is laid out the same way.
+ *   plan[0]  workgroups per whole tile: 1 for the polynomial and RBF kernels. For
+ *            the linear kernel up to 1025 points of at most 128 features 1..16: a
+ *            tile's features are split as far as one round of two workgroups per
+ *            CU allows, down to one feature block each (the partial sums add up
+ *            because the linear kernel value is the inner product itself); beyond
+ *            that 0: its products are two passes over the points and use no tiles;
+ *   plan[1]  tiles, the last ones visited, that are split instead (0 if none, as
+ *            for the linear kernel): all tiles of a problem of few, or those after
+ *            the last full round of two workgroups per CU, or, in fp64, of one.
+ *            They park their partial inner products, which a fix-up launch sums;
+ *   plan[2]  workgroups per such tile (plan[0] when plan[1] is 0), each with an
+ *            even number of feature blocks; the last may have fewer than the others.
+ * Every product of a problem (CG iterations, residual recomputations,
+ * lssvm_matvec) is laid out the same way. (A linear training that fits one
+ * workgroup's LDS runs whole in it, without these products.)
  * Returns LSSVM_EINVAL (plan untouched) for n, d, dtype or kernel out of
  * range or a null plan. Informational. */
 int lssvm_tile_plan(int64_t n, int64_t d, int32_t dtype, int32_t kernel, int64_t* plan);

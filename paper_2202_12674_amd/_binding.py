@@ -399,9 +399,10 @@ def cg_step_noalloc(x, r, d, q, scalars):
 
 
 def tile_plan(n: int, d: int, dtype: str, kernel: str) -> tuple:
-    """lssvm_tile_plan: (workgroups per tile, tiles of the finer-split last
-    round, workgroups per such tile) of the implicit product for n points of
-    d features; dtype "f64" or "f32", kernel "linear", "poly" or "rbf"."""
+    """lssvm_tile_plan: (workgroups per whole tile, or 0 where the product uses no
+    tiles, tiles that are split instead, workgroups per such tile) of the implicit
+    product for n points of d features; dtype "f64" or "f32", kernel "linear",
+    "poly" or "rbf"."""
     plan = (ctypes.c_int64 * 3)()
     _check(lib().lssvm_tile_plan(int(n), int(d), {"f64": 0, "f32": 1}[dtype],
                                  {"linear": 0, "poly": 1, "rbf": 2}[kernel], plan))

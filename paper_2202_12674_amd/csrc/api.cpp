@@ -96,12 +96,10 @@ struct Geometry {
   int64_t nT;       // tiles per edge of the reduced system
   int64_t NP;       // nT * tile: padded length of every CG vector
   int64_t nb;       // blocks of the CG vector kernels over NP (block partials per reduction)
-  int64_t ksplit;   // linear kernel: workgroups per tile, each over a share of the features
-  int64_t lin_tail_q;      // linear kernel: tiles of the last partial round (or 0), run by
-  int64_t lin_tail_split;  // the launch's trailing workgroups, split this many ways
-  int64_t tail_q;   // other kernels: tiles of the last partial round that are split (or 0)
+  // polynomial and RBF kernels:
+  int64_t tail_q;      // tiles of the last partial round that tail_plan splits (or 0)
   int64_t tail_split;  // ... over this many workgroups each
-  int64_t part_q;      // other kernels: the tiles, the last of the visit order, that are split
+  int64_t part_q;      // the tiles, the last of the visit order, that are split
   int64_t part_split;  // ... over this many workgroups each
   int64_t part_blocks; // ... of so many staged blocks (even; the last has what is left)
 };
@@ -115,9 +113,8 @@ struct Geometry {
 // launches of a few microseconds each against a product of ~10 us. Up to
 // kFusedMaxNP, where both are measured.
 inline bool fused_iteration(const Geometry& g, int32_t kernel) {
-  const bool one_launch = kernel != LSSVM_LINEAR || g.lin_tail_q == 0;
   const int64_t most = kernel == LSSVM_LINEAR ? kFusedMaxLinear : kFusedMaxNP;
-  return LSSVM_FUSED_SMALL && g.NP <= most && one_launch;
+  return LSSVM_FUSED_SMALL && g.NP <= most;
 }
 
 // Linear products run in two passes over the points, w = X^T p and X w (k_lin_w,
@@ -140,69 +137,6 @@ constexpr int64_t kResidentTiles = 2 * kCUs;
 #ifndef LSSVM_LINEAR_SPLIT_MAX
 #define LSSVM_LINEAR_SPLIT_MAX 16
 #endif
-
-#ifndef LSSVM_LINEAR_TAIL
-#define LSSVM_LINEAR_TAIL 1
-#endif
-#ifndef LSSVM_LINEAR_TAIL_MAX
-#define LSSVM_LINEAR_TAIL_MAX 64
-#endif
-
-// Finer split of the linear kernel's tiles in a last partial round that
-// already runs S ways: the largest T (up to 64) with Q T within one round of
-// resident workgroups and an even number of feature blocks per share.
-inline int64_t linear_tail_split(int64_t Q, int64_t S, int64_t nkb) {
-  int64_t T = S;
-  while (LSSVM_LINEAR_TAIL && T < LSSVM_LINEAR_TAIL_MAX && Q * T * 2 <= kResidentTiles && nkb % (4 * T) == 0)
-    T *= 2;
-  return T;
-}
-
-// Feature split of the linear kernel's tiles. A product of W tiles split S
-// ways runs in rounds of R resident workgroups, each as long as 1/S of a
-// tile plus a fixed cost of about two feature blocks (the first block's load
-// latency and the epilogue). The full rounds take floor(W S / R) of those;
-// the Q tiles left for a last partial round run as the launch's trailing
-// workgroups, split T >= S ways (the feature shares add into the row sums
-// like any split's, so no fixup is needed), which takes 1/T of a tile plus
-// the fixed cost. S (and T) halve the block count, which must stay even. A
-// problem of one round or less keeps its tiles in one launch.
-inline void linear_plan(int64_t nT, int64_t nkb, int64_t* split, int64_t* q, int64_t* tail_split) {
-  const int64_t W = tri_count(nT);
-  const double f = 2.0 / (double)nkb;
-  auto plan = [&](int64_t S, int64_t* Q, int64_t* T) {
-    *Q = 0;
-    *T = S;
-    if (W * S <= kResidentTiles) return 1.0 / (double)S + f;
-    const int64_t full = W * S / kResidentTiles;
-    const int64_t left = W - full * (kResidentTiles / S);
-    double c = (double)full * (1.0 / (double)S + f);
-    if (left > 0) {
-      const int64_t t = linear_tail_split(left, S, nkb);
-      c += 1.0 / (double)t + f;
-      if (t > S) {
-        *Q = left;
-        *T = t;
-      }
-    }
-    return c;
-  };
-  int64_t best = 1, bq, bt;
-  double best_cost = plan(1, &bq, &bt);
-  for (int64_t S = 2; S <= LSSVM_LINEAR_SPLIT_MAX && nkb % (2 * S) == 0; S *= 2) {
-    int64_t Q, T;
-    const double c = plan(S, &Q, &T);
-    if (c < 0.95 * best_cost) {   // a clear gain only: each split adds workgroups and atomics
-      best = S;
-      best_cost = c;
-      bq = Q;
-      bt = T;
-    }
-  }
-  *split = best;
-  *q = bq;
-  *tail_split = bt;
-}
 
 // The tiles beyond the last full round of resident workgroups run one per
 // CU and take about as long as a whole round. When they are at most a
@@ -297,7 +231,6 @@ Geometry geometry(int64_t n, int64_t d) {
   g.NP = g.nT * g.tile;
   g.nb = cg_blocks(g.NP);
   g.plan_nkb = round_up(d, 2 * g.bk) / g.bk;
-  linear_plan(g.nT, g.plan_nkb, &g.ksplit, &g.lin_tail_q, &g.lin_tail_split);
   tail_plan(g.nT, g.plan_nkb, &g.tail_q, &g.tail_split);
   // An even number of staged blocks (two LDS stages), as many as planned where
   // a plan shares them out: in fp32, whose staged blocks are half a planned
@@ -591,18 +524,18 @@ template <> double rbf_scale<double>(double gamma) { return gamma; }
 
 // Workgroups per tile of every product of n points (a training's CG
 // iterations, its residual recomputations, a warm start's and the true
-// residual's products, lssvm_matvec). On a small problem, whose iterations
-// are fused launches, the few tiles take one CU each and their matrix work
-// is most of the launch, so the linear kernel's split goes as far as one
-// round of workgroups allows, down to a single feature block per workgroup.
+// residual's products, lssvm_matvec) on whole tiles. The linear kernel has tiles
+// only on small problems, whose iterations are fused launches: the few tiles take
+// one CU each and their matrix work is most of the launch, so their features are
+// split as far as one round of workgroups allows, down to a single feature block
+// per workgroup.
 // All products of a problem take the same split: each split rounds the
 // operator its own way (fp32 partial inner products), and a recomputed
 // residual from a differently rounded operator than the iterations' stalls
 // fp32 CG above its eps.
 inline int64_t product_split(const Geometry& g, int32_t kernel) {
   if (kernel != LSSVM_LINEAR) return 1;
-  int64_t S = g.ksplit;
-  if (!fused_iteration(g, kernel)) return S;
+  int64_t S = 1;
   const int64_t nkb = g.plan_nkb, W = tri_count(g.nT);
   // double while every workgroup keeps an even block count (the two-stage
   // loop) or gets exactly one (the single-block variant)
@@ -1494,10 +1427,9 @@ int lssvm_tile_plan(int64_t n, int64_t d, int32_t dtype, int32_t kernel, int64_t
   if (!plan) return fail(LSSVM_EINVAL, "tile_plan: null plan");
   const Geometry g = dtype == LSSVM_F64 ? geometry<double>(n, d) : geometry<float>(n, d);
   const bool lin = kernel == LSSVM_LINEAR;
-  plan[0] = product_split(g, kernel);
-  plan[1] = lin ? g.lin_tail_q : g.tail_q;
-  plan[2] = lin ? g.lin_tail_split : g.tail_split;
-  if (plan[1] == 0) plan[2] = plan[0];
+  plan[0] = linear_passes(g, kernel) ? 0 : product_split(g, kernel);
+  plan[1] = lin ? 0 : g.part_q;
+  plan[2] = plan[1] == 0 ? plan[0] : g.part_split;
   return LSSVM_OK;
 }
 

@@ -20,7 +20,8 @@ TOL_MV = BAR_MV
 TOL_ALPHA = BAR_SOL
 
 __all__ = ["GOLDEN", "TOL_MV", "TOL_ALPHA", "BAR_MV", "BAR_SOL", "rel_err", "log", "spec_of",
-           "kw_of", "small_cfg", "data_of", "to_dev", "golden", "golden_tight", "SPLIT_SHAPES",
+           "kw_of", "small_cfg", "data_of", "to_dev", "golden", "golden_tight", "PASS_SHAPES",
+           "SPLIT_SHAPES",
            "TAIL_SHAPES", "random_cases", "random_large_cases", "random_param_cases", "random_param_train_cases",
            "fp32_sensitivity", "OracleRef", "oracle_ref", "check_train", "labels_match"]
 
@@ -70,23 +71,30 @@ def golden(name):
     return np.load(path, allow_pickle=False)
 
 
-# Linear products of few tiles split each tile's features over several
-# workgroups; these shapes give every split the library uses.
-# (dtype, n, d, plan) of the linear kernel's feature splits; plan is the
-# library's (workgroups per tile, tiles of the finer-split last round,
-# workgroups per such tile): splits without a tail, a tail over the split
-# full rounds, and a tail after unsplit ones (the 4096 x 1024 fp64 workload).
-SPLIT_SHAPES = [("f64", 600, 256, (16, 0, 16)), ("f64", 2000, 512, (4, 8, 16)),
-                ("f64", 1000, 2048, (16, 4, 64)), ("f64", 3000, 256, (2, 44, 8)),
-                ("f64", 4096, 1024, (1, 16, 32)), ("f32", 1000, 256, (8, 0, 8)),
-                ("f32", 600, 1024, (16, 0, 16)), ("f32", 2000, 1024, (4, 8, 16)),
-                ("f32", 3000, 512, (2, 44, 8)), ("f32", 4096, 256, (1, 16, 4))]
+# (dtype, n, d, plan) of the linear kernel; plan is the library's (workgroups per
+# whole tile, tiles that are split instead, workgroups per such tile). No tiles:
+# two passes over the points, of rows in 16-byte and in single loads, of many and
+# of few column blocks.
+PASS_SHAPES = [("f64", 600, 256, (0, 0, 0)), ("f64", 2000, 512, (0, 0, 0)),
+               ("f64", 1000, 2048, (0, 0, 0)), ("f64", 3000, 256, (0, 0, 0)),
+               ("f64", 4096, 1024, (0, 0, 0)), ("f32", 1000, 256, (0, 0, 0)),
+               ("f32", 600, 1024, (0, 0, 0)), ("f32", 2000, 1024, (0, 0, 0)),
+               ("f32", 3000, 512, (0, 0, 0)), ("f32", 4096, 256, (0, 0, 0)),
+               ("f64", 12288, 1024, (0, 0, 0)), ("f64", 1026, 129, (0, 0, 0))]
 
-# (dtype, kernel, n, d, plan): the tiles after the last full round of 512
-# workgroups split 4..16 ways, parked and fixed up (linear: added up).
-TAIL_SHAPES = [("f64", "rbf", 600, 256, (1, 15, 8)), ("f32", "poly", 600, 256, (1, 15, 4)),
+# Up to 1025 points of at most 128 features each tile's features are split over
+# several workgroups: every split, down to single blocks (8, 4, 2) and none, and the
+# most tiles (36).
+SPLIT_SHAPES = [("f64", 600, 128, (8, 0, 8)), ("f64", 1000, 64, (4, 0, 4)),
+                ("f64", 1025, 128, (8, 0, 8)), ("f64", 900, 32, (2, 0, 2)),
+                ("f64", 500, 96, (1, 0, 1)), ("f32", 1000, 128, (4, 0, 4)),
+                ("f32", 1025, 64, (2, 0, 2))]
+
+# (dtype, kernel, n, d, plan): split tiles, parked and fixed up: all of few, those
+# after the last full round of 512 workgroups, those after the last of 256.
+TAIL_SHAPES = [("f64", "rbf", 600, 256, (1, 15, 4)), ("f32", "poly", 600, 1200, (1, 15, 10)),
                ("f64", "poly", 4096, 256, (1, 16, 8)), ("f32", "rbf", 4096, 512, (1, 16, 8)),
-               ("f64", "linear", 12288, 1024, (1, 48, 8))]
+               ("f64", "poly", 3000, 1000, (1, 44, 8))]
 
 
 def random_cases(count=24, seed=2026):

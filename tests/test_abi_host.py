@@ -95,14 +95,14 @@ def test_workspace_grows_with_the_points_not_their_square():
 
 def test_tile_plan():
     """The launch plan of the implicit product: pinned for the five benchmark
-    workloads, the paper-sized linear problem and the smallest workload, and
-    for every shape split widths that leave an even number of feature blocks
-    per workgroup (on the small problems whose CG iterations are single
-    launches, n <= 1025 without a split last round, the linear kernel's tiles
-    split as far as one round of workgroups allows, down to one block each),
-    a tail exactly the tiles after the last full round, and at most one round
-    of workgroups in a tail launch; EINVAL (plan untouched) outside the
-    range."""
+    workloads, the paper-sized linear problem and the smallest workload, and for
+    every shape: the linear kernel's tiles (up to 1025 points of 128 features)
+    split as far as the blocks and one round of workgroups allow, with an even
+    count of feature blocks or one each, and no tiles beyond; the other kernels'
+    split tiles all of a few, those after the last full round of two workgroups
+    per CU or, in fp64, of one, with at least four blocks each (two after the
+    full rounds) and at most one round of workgroups; EINVAL (plan untouched)
+    outside the range."""
     L = P.lib()
     plan = (ctypes.c_int64 * 3)(-5, -5, -5)
     for args in [(1, 64, 0, 0), (256, 0, 0, 0), (256, 64, 9, 0), (256, 64, 0, 3),
@@ -110,8 +110,8 @@ def test_tile_plan():
         assert L.lssvm_tile_plan(*args, plan) == B.EINVAL, args
         assert list(plan) == [-5, -5, -5]
     assert L.lssvm_tile_plan(256, 64, 0, 0, None) == B.EINVAL
-    pins = {("f64", "linear", 4096, 1024): (1, 16, 32),
-            ("f64", "linear", 16384, 4096): (1, 64, 8),
+    pins = {("f64", "linear", 4096, 1024): (0, 0, 0),
+            ("f64", "linear", 16384, 4096): (0, 0, 0),
             ("f64", "rbf", 16384, 2048): (1, 64, 8),
             ("f32", "poly", 32768, 4096): (1, 128, 4),
             ("f32", "rbf", 65536, 1024): (1, 0, 1),
@@ -122,35 +122,35 @@ def test_tile_plan():
     for dtype in ("f64", "f32"):
         bk = 16 if dtype == "f64" else 32
         for kernel in ("linear", "poly", "rbf"):
-            for n in (2, 129, 600, 1000, 2000, 3000, 4096, 6000, 8192, 12000, 40000):
-                for d in (1, 7, 64, 100, 256, 1024, 4096):
+            for n in (2, 129, 600, 1000, 1025, 1026, 2000, 3000, 4096, 6000, 8192, 12000, 40000):
+                for d in (1, 7, 64, 100, 128, 129, 256, 1024, 4096):
                     S, Q, T = P.tile_plan(n, d, dtype, kernel)
-                    nkb = -(-d // (2 * bk)) * 2
+                    nkb = -(-d // (2 * bk)) * 2    # blocks the linear split counts
+                    staged = -(-d // 16)           # blocks of 16 features, before padding
                     nT = -(-(n - 1) // 128)
                     W = nT * (nT + 1) // 2
                     where = (dtype, kernel, n, d, S, Q, T)
-                    small = kernel == "linear" and n <= 1025 and Q == 0
-                    assert S in (1, 2, 4, 8, 16), where
-                    if small and S == nkb:
-                        assert S > 1 and W * S <= 512, where   # one feature block each
-                    else:
-                        assert nkb % (2 * S) == 0, where       # an even count each
-                    if small and S < nkb:
-                        # as split as the blocks and one round of workgroups allow
-                        assert (S == 16 or W * 2 * S > 512
-                                or (nkb % (4 * S) != 0 and nkb != 2 * S)), where
-                    assert T in (1, 2, 4, 8, 16, 32, 64) and (nkb % (2 * T) == 0 or T == S == nkb), where
-                    if kernel != "linear":
-                        assert S == 1, where
-                    if Q == 0:
-                        assert T == S, where
-                        continue
-                    assert T > S and Q * T <= 512, where
                     if kernel == "linear":
-                        full = W * S // 512
-                        assert full >= 1 and Q == W - full * (512 // S), where
+                        assert Q == 0 and T == S, where
+                        if n > 1025 or d > 128:
+                            assert S == 0, where
+                            continue
+                        assert S in (1, 2, 4, 8, 16) and W * S <= 512, where
+                        assert S == nkb or nkb % (2 * S) == 0, where
+                        assert (S in (16, nkb) or W * 2 * S > 512
+                                or (nkb % (4 * S) != 0 and nkb != 2 * S)), where
+                        continue
+                    assert S == 1, where
+                    if Q == 0:
+                        assert T == 1, where
+                        continue
+                    assert T > 1 and Q * T <= 512, where
+                    if W <= 256:
+                        assert Q == W and 4 * T <= staged + 3, where
+                    elif Q == W % 512:
+                        assert 4 <= T <= 16 and 2 * T <= staged + 3, where
                     else:
-                        assert Q == W % 512 and 4 <= T <= 16, where
+                        assert dtype == "f64" and Q == W % 256 and 4 * T <= staged + 3, where
 
 
 def _train(n=10, d=3, dtype=0, kernel=0, params=None, C=1.0, eps=1e-3, max_iter=0,

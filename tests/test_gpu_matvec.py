@@ -10,7 +10,7 @@ import pytest
 
 import oracle as O
 import synthdata as S
-from gpu_common import (GOLDEN, TOL_ALPHA, TOL_MV, SPLIT_SHAPES, TAIL_SHAPES, check_train,  # noqa: F401
+from gpu_common import (GOLDEN, TOL_ALPHA, TOL_MV, PASS_SHAPES, SPLIT_SHAPES, TAIL_SHAPES, check_train,  # noqa: F401
                         data_of, golden, golden_tight, kw_of, labels_match, log, oracle_ref,
                         random_cases, random_large_cases, random_param_cases, rel_err, small_cfg,
                         spec_of,
@@ -59,7 +59,7 @@ def _check_plan_product(torch, dev, P, cfg, plan):
     del Qt
 
 
-@pytest.mark.parametrize("dtype,n,d,plan", SPLIT_SHAPES)
+@pytest.mark.parametrize("dtype,n,d,plan", PASS_SHAPES + SPLIT_SHAPES)
 def test_matvec_linear_feature_split(torch_dev, dtype, n, d, plan):
     torch, dev = torch_dev
     import paper_2202_12674_amd as P
@@ -246,10 +246,8 @@ def test_matvec_large_n_sampled_rows(torch_dev, dtype, kernel, n, d):
     """The implicit product at n up to 2^20 points (33.6M tiles adding into
     2^21 fixed-point words): sampled rows, including the last row and
     the ragged last tile, against the oracle's rows computed one by one; over
-    all rows, p^T Q~ p > 0 (Q~ is SPD) and every entry finite. At 530000 x 256
-    fp64 the linear product's 8.6M tiles take two launch chunks and its last
-    round (11 tiles split 8 ways) runs as the trailing workgroups of the
-    second."""
+    all rows, p^T Q~ p > 0 (Q~ is SPD) and every entry finite. The linear
+    products are passes over the points, of few and of many features."""
     torch, dev = torch_dev
     import paper_2202_12674_amd as P
     log(f"[large n] {kernel} {dtype} n={n} d={d}")

@@ -14,7 +14,7 @@ import pytest
 
 import oracle as O
 import synthdata as S
-from gpu_common import (GOLDEN, TOL_ALPHA, TOL_MV, SPLIT_SHAPES, TAIL_SHAPES, check_train,  # noqa: F401
+from gpu_common import (GOLDEN, TOL_ALPHA, TOL_MV, PASS_SHAPES, SPLIT_SHAPES, TAIL_SHAPES, check_train,  # noqa: F401
                         fp32_sensitivity,
                         data_of, golden, golden_tight, kw_of, labels_match, log, oracle_ref,
                         random_cases, random_large_cases, random_param_train_cases, rel_err,
@@ -24,10 +24,10 @@ from gpu_common import (GOLDEN, TOL_ALPHA, TOL_MV, SPLIT_SHAPES, TAIL_SHAPES, ch
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("dtype,n,d,plan", [SPLIT_SHAPES[2], SPLIT_SHAPES[7]])
+@pytest.mark.parametrize("dtype,n,d,plan", [PASS_SHAPES[2], PASS_SHAPES[7], SPLIT_SHAPES[2],
+                                             SPLIT_SHAPES[5]])
 def test_train_linear_feature_split(torch_dev, dtype, n, d, plan):
-    """Trainings whose products split the features, with a finer-split last
-    round. The fp32 system's alpha~ tolerance follows its sensitivity to the
+    """Trainings in passes over the points, and on tiles whose features are split. The fp32 system's alpha~ tolerance follows its sensitivity to the
     rounding of the kernel values (as in test_train_random_shapes)."""
     torch, dev = torch_dev
     cfg = small_cfg("linear", dtype, n, d, C=1.0)
@@ -40,7 +40,7 @@ def test_train_linear_feature_split(torch_dev, dtype, n, d, plan):
     check_train(torch, dev, cfg, ref, X, y, Xte, f_te, alpha_tol=tol)
 
 
-@pytest.mark.parametrize("dtype,kernel,n,d,plan", [TAIL_SHAPES[2], TAIL_SHAPES[3]])
+@pytest.mark.parametrize("dtype,kernel,n,d,plan", [TAIL_SHAPES[0], TAIL_SHAPES[2], TAIL_SHAPES[3]])
 def test_train_tail_split(torch_dev, dtype, kernel, n, d, plan):
     torch, dev = torch_dev
     cfg = small_cfg(kernel, dtype, n, d, C=1.0)
