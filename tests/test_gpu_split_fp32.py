@@ -28,11 +28,30 @@ def _values(rng, kind, shape):
     return x.astype(np.float32)
 
 
-# points at tile edges, features at the edges of 16- and 32-feature blocks
-@pytest.mark.parametrize("n,nt,d", [(3, 1, 1), (127, 128, 15), (129, 5, 17), (256, 129, 33),
-                                    (130, 200, 64), (150, 100, 1025)])
-@pytest.mark.parametrize("kind", ["plain", "positive", "spread", "huge", "tiny", "subnormal"])
+KINDS = ["plain", "positive", "spread", "huge", "tiny", "subnormal"]
+
+
+# points at tile edges, features at the edges of 16- and 32-feature blocks; more than
+# 128 test points, which tiles take
+@pytest.mark.parametrize("n,nt,d", [(3, 129, 1), (127, 130, 15), (129, 129, 17), (256, 129, 33),
+                                    (130, 200, 64), (150, 129, 1025)])
+@pytest.mark.parametrize("kind", KINDS)
 def test_inner_products_keep_fp32_accuracy(torch_dev, kind, n, nt, d):
+    # three dropped products (2^-23), one ulp (2^-23) per sum of 16 features and
+    # slice pair order, and the roundings of the joined sum and of the score
+    _check_inner_products(torch_dev, kind, n, nt, d, (4 + -(-d // 16)) * 2.0 ** -23)
+
+
+# the fp32 instruction of few test points, straight from the rows
+@pytest.mark.parametrize("n,nt,d", [(3, 1, 1), (127, 128, 15), (129, 5, 17), (150, 100, 1025)])
+@pytest.mark.parametrize("kind", KINDS)
+def test_inner_products_of_few_points_keep_fp32_accuracy(torch_dev, kind, n, nt, d):
+    # half an ulp for each product and each addition of a wave's quarter of the
+    # features, for the three additions of the waves' sums and for the score
+    _check_inner_products(torch_dev, kind, n, nt, d, (8 + -(-d // 2)) * 2.0 ** -24)
+
+
+def _check_inner_products(torch_dev, kind, n, nt, d, rel):
     torch, dev = torch_dev
     import paper_2202_12674_amd as P
     rng = np.random.default_rng(1000 * d + n)
@@ -43,9 +62,7 @@ def test_inner_products_keep_fp32_accuracy(torch_dev, kind, n, nt, d):
          * np.float32(other)).astype(np.float32)
     ref = A.astype(np.float64) @ B.astype(np.float64).T
     mag = np.abs(A.astype(np.float64)) @ np.abs(B.astype(np.float64)).T
-    # three dropped products (2^-23), one ulp (2^-23) per sum of 16 features and
-    # slice pair order, and the roundings of the joined sum and of the score
-    tol = (4 + -(-d // 16)) * 2.0 ** -23 * mag
+    tol = rel * mag
     Ad, Bd = torch.from_numpy(A).to(dev), torch.from_numpy(B).to(dev)
     for j in sorted({0, n // 2, n - 1}):
         e = torch.zeros(n, dtype=torch.float32, device=dev)
