@@ -825,8 +825,8 @@ int train_small_linear(const Geometry& g, const TrainWs<T>& w, const T* X, const
   LinTrain a{};
   a.invC = 1.0 / C;
   a.eps2 = eps * eps;
-  a.max_iter = max_iter > 0 ? max_iter : g.N;
-  a.replace_every = kReplaceEvery;
+  a.max_iter = (int)std::min<int64_t>(max_iter > 0 ? max_iter : g.N, INT32_MAX);
+  a.replace_every = (int)kReplaceEvery;
   a.x = w.x;
   a.rhs = w.rhs;
   a.q64 = w.q64;

@@ -1506,7 +1506,7 @@ __global__ __launch_bounds__(kLinTrainThreads) void k_lin_train(const T* __restr
   const double stop = a.eps2 * delta0;
   double x = 0.0, xbest = 0.0, r = rhs, dir = rhs, delta = delta0, best = delta0, phi_best = 0.0;
   double gam = 0.0, step = 0.0;
-  int64_t it = 0;
+  int it = 0;
   bool broke = false, stalled = false, conv = delta0 == 0.0 || inflags != 0;
   while (!conv && it < a.max_iter) {
     const bool refresh = (it + 1) % a.replace_every == 0;

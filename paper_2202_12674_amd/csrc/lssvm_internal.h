@@ -279,7 +279,8 @@ hipError_t launch_predict_few(PredictFew<T> a, int kernel, double b, T* scores, 
 // passed and CG did not break down.
 struct LinTrain {
   double invC, eps2;
-  int64_t max_iter, replace_every;
+  int max_iter, replace_every;   // 64-bit ones cost the loop scalar registers, which spill
+                                 // (256 x 64 fp64: 299 us, 277 so)
   double *x, *rhs, *q64, *scal, *hist;
   int64_t hist_cap;
   int* flags;
