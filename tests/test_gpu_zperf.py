@@ -1,7 +1,8 @@
 """Throughput floor of the implicit product: a change that keeps every result
-right but loses a large share of the matrix-core rate fails here. The floor
-is 70% of the published peak (the product runs at 86-89% on these shapes),
-far enough below to hold on any healthy board. Collected last, so a slow
+right but loses a large share of the matrix-core rate fails here. The floors
+are 70% of the published fp64 peak (the product runs at 93-94% of it) and, for
+fp32 on the bf16 matrix cores, 160 TFLOP/s (it runs at 208-225), far enough
+below to hold on any healthy board. Collected last, so a slow
 board cannot hide a parity failure behind it."""
 from __future__ import annotations
 
@@ -9,8 +10,7 @@ import pytest
 
 import synthdata as S
 
-PEAK_TFLOPS = {"f64": 78.6, "f32": 157.3}
-FLOOR = 0.70
+FLOOR_TFLOPS = {"f64": 0.70 * 78.6, "f32": 160.0}
 
 
 @pytest.fixture(scope="module")
@@ -40,9 +40,9 @@ def test_product_rate_floor(torch_dev, kernel, dtype, n, d):
     assert r.converged and len(r.matvec_times) >= 3
     ms = sorted(r.matvec_times)[len(r.matvec_times) // 2]
     N = n - 1
-    frac = N * (N + 1) * d / (ms * 1e-3) / 1e12 / PEAK_TFLOPS[dtype]
-    print(f"{cfg.name}: {ms:.3f} ms per product, {100 * frac:.1f}% of peak", flush=True)
-    assert frac >= FLOOR, f"{cfg.name}: {100 * frac:.1f}% of the matrix-core peak"
+    rate = N * (N + 1) * d / (ms * 1e-3) / 1e12
+    print(f"{cfg.name}: {ms:.3f} ms per product, {rate:.1f} TFLOP/s", flush=True)
+    assert rate >= FLOOR_TFLOPS[dtype], f"{cfg.name}: {rate:.1f} TFLOP/s"
 
 
 @pytest.mark.gpu
