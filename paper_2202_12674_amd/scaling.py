@@ -5,9 +5,11 @@ The paper measures how its GPU training time grows with the data: in points
 (Sec. IV-D). This harness runs the same two sweeps on one MI355X, with
 synthetic data of the workloads' recipe, and prints one JSON line per size:
 the implicit product's time (HIP events around each product inside the
-training), its rate in the symmetric count N(N+1)d against the matrix-core
-peak, the CG iterations and the time to eps (data resident in HBM). Each
-size is trained twice and the second run is reported.
+training), its rate, the CG iterations and the time to eps (data resident in
+HBM). The rate is the symmetric count N(N+1)d against the matrix-core peak, or,
+for the linear kernel, whose products are two passes over the points, the bytes
+of two reads of them against the HBM peak (points that fit the cache exceed it).
+Each size is trained twice and the second run is reported.
 
     python -m paper_2202_12674_amd.scaling [--dtype f64 --kernel linear --eps 1e-3]
     python -m paper_2202_12674_amd.scaling --only 16384 4096
@@ -19,7 +21,9 @@ import json
 import os
 import sys
 
-PEAK_TFLOPS = {"f64": 78.6, "f32": 157.3}   # MI355X dense matrix-core peaks
+# MI355X dense matrix-core peaks; fp32 tiles take six bf16 products per fp32 one
+PEAK_TFLOPS = {"f64": 78.6, "f32": 2516.6 / 6}
+HBM_GBS = 8000.0
 
 
 def sizes(points_exp=(8, 15), features_exp=(6, 14), d_fixed=4096, n_fixed=32768):
@@ -46,11 +50,16 @@ def measure(cfg, device, reps: int = 2):
         r = B.train(Xd, yd, C=cfg.C, eps=cfg.eps, workspace=ws, time_matvec=True, **kw)
     N = cfg.n - 1
     mv_ms = r.t_matvec_ms / max(1, r.n_matvec_timed)
-    tflops = N * (N + 1) * cfg.d / (mv_ms * 1e-3) / 1e12 if mv_ms > 0 else 0.0
+    s = mv_ms * 1e-3
+    if cfg.kernel == "linear":
+        gbs = 2 * N * cfg.d * Xd.element_size() / s / 1e9 if s > 0 else 0.0
+        rate = {"product_gbs": round(gbs, 1), "frac_of_peak": round(gbs / HBM_GBS, 4)}
+    else:
+        tflops = N * (N + 1) * cfg.d / s / 1e12 if s > 0 else 0.0
+        rate = {"product_tflops": round(tflops, 2),
+                "frac_of_peak": round(tflops / PEAK_TFLOPS[cfg.dtype], 4)}
     return {"n": cfg.n, "d": cfg.d, "iterations": r.iterations, "converged": r.converged,
-            "time_to_eps_ms": round(r.t_total_ms, 3), "product_ms": round(mv_ms, 4),
-            "product_tflops": round(tflops, 2),
-            "frac_of_peak": round(tflops / PEAK_TFLOPS[cfg.dtype], 4)}
+            "time_to_eps_ms": round(r.t_total_ms, 3), "product_ms": round(mv_ms, 4), **rate}
 
 
 def main(argv=None):
