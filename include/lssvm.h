@@ -119,11 +119,14 @@ typedef struct lssvm_info {
 } lssvm_info;
 
 /* Device workspace needed by lssvm_train and lssvm_matvec for n points of
- * d features. Returns 0 if n or d is outside the supported range (below) or
+ * d features, padded to whole tiles: 8 bytes per fp64 feature value, 6 per fp32 one
+ * (three bf16 slices: 0.79 GiB at 32768 x 4096, whose points are 0.5 GiB), the CG
+ * vectors, and up to 64 MiB for the parked inner products of split tiles. Returns 0 if n or d is outside the supported range (below) or
  * dtype is unknown. */
 size_t lssvm_workspace_bytes(int64_t n, int64_t d, int32_t dtype);
 
-/* Device workspace needed by lssvm_predict. Returns 0 if a size is outside
+/* Device workspace needed by lssvm_predict: model and test points as above, and
+ * partial scores; it never falls as n_test grows. Returns 0 if a size is outside
  * the supported range or dtype is unknown. */
 size_t lssvm_predict_workspace_bytes(int64_t n, int64_t n_test, int64_t d, int32_t dtype);
 
