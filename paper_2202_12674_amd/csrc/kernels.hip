@@ -540,14 +540,16 @@ __global__ __launch_bounds__(256) void k_cg_gather(RankOne c, int64_t NP, int64_
 
 // x += a d and r -= a q (or only x += a d when the residual is about to be
 // recomputed from x). On curvature breakdown (d^T q <= 0 or a step that is
-// not finite) every block leaves the vectors as they are. Bound by memory; four
-// elements of every vector in flight per thread (16-byte accesses instead of 8
-// measured slower at 2^26: 4.77 against 5.25 TB/s over the step).
+// not finite) every block leaves the vectors as they are. Bound by memory, which
+// one element of every vector in flight per thread covers: four (unrolled, the
+// vectors restrict) measured slower over the step, 1.12 against 1.05 ms at 2^26
+// doubles, 250 against 241 us at 16 x 10^6 and 68.3 against 66.7 at 4 x 10^6, as did
+// 16-byte accesses at 2^26 (4.77 against 5.25 TB/s).
 __global__ __launch_bounds__(256) void k_cg_update(int x_only, const double* __restrict__ bp_in,
                                                    int64_t nb, double* scal, int par,
                                                    const double* __restrict__ dir,
                                                    const double* __restrict__ qv,
-                                                   double* __restrict__ x, double* __restrict__ r,
+                                                   double* x, double* r,
                                                    double* bp_out, int64_t NP) {
   __shared__ double sh[NT / 64];
   if (block_stopped(scal)) return;
@@ -568,7 +570,6 @@ __global__ __launch_bounds__(256) void k_cg_update(int x_only, const double* __r
   if (broke) return;
   double v = 0.0;
   if (!x_only) {
-#pragma unroll 4
     for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < NP; i += (int64_t)gridDim.x * NT) {
       x[i] = x[i] + alpha * dir[i];
       const double ri = r[i] - alpha * qv[i];
@@ -654,7 +655,8 @@ __global__ __launch_bounds__(256) void k_true_residual(RankOne c, int64_t NP, in
 __global__ __launch_bounds__(256) void k_cg_direction(const double* __restrict__ bp_in, int64_t nb,
                                                       double* scal, int par, int64_t iter,
                                                       const double* __restrict__ r,
-                                                      double* __restrict__ dir, int64_t NP, double* hist, int64_t hist_cap,
+                                                      double* dir, int64_t NP, double* hist,
+                                                      int64_t hist_cap,
                                                       int64_t refresh, int raise,
                                                       const double* __restrict__ bp_phi,
                                                       const double* __restrict__ x,
@@ -695,7 +697,6 @@ __global__ __launch_bounds__(256) void k_cg_direction(const double* __restrict__
   const double beta = dold != 0.0 ? dnew / dold : 0.0;
   if (!stall && !conv) {
     double dmax = 0.0;
-#pragma unroll 4
     for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < NP;
          i += (int64_t)gridDim.x * NT) {
       const double di = r[i] + beta * dir[i];
@@ -776,7 +777,6 @@ __global__ __launch_bounds__(256) void k_step_dot(const double* __restrict__ a,
     scal[S_STATUS + ST_STOP] = -1.0;
   }
   double v = 0.0;
-#pragma unroll 4
   for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < len; i += (int64_t)gridDim.x * NT)
     v += a[i] * b[i];
   const double t = block_sum(v, sh);
