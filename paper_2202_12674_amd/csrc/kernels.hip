@@ -538,18 +538,28 @@ __global__ __launch_bounds__(256) void k_cg_gather(RankOne c, int64_t NP, int64_
   }
 }
 
+// Vectors of the CG step: with CACHED, four elements of each in flight per thread
+// (unrolled; restrict lets the loads move ahead of the stores), otherwise one. While
+// the step's four vectors fit the Infinity Cache (256 MiB: 2^23 doubles) latency
+// counts, beyond that the order in which HBM is read and written: a step with four
+// and with one takes 42.7 and 45.0 us at 2 x 10^6 doubles, 125.5 and 128.1 at 2^23,
+// 182.9 and 182.1 at 12 x 10^6, 250 and 241 at 16 x 10^6, 1.12 and 1.05 ms at 2^26.
+// (16-byte accesses measured slower at 2^26: 4.77 against 5.25 TB/s.)
+constexpr int64_t kCachedStep = int64_t(1) << 23;
+template <bool CACHED> struct StepVec { using type = double* __restrict__; };
+template <> struct StepVec<false> { using type = double*; };
+template <bool CACHED> using step_vec = typename StepVec<CACHED>::type;
+template <bool CACHED> constexpr int kStepUnroll = CACHED ? 4 : 1;
+
 // x += a d and r -= a q (or only x += a d when the residual is about to be
 // recomputed from x). On curvature breakdown (d^T q <= 0 or a step that is
-// not finite) every block leaves the vectors as they are. Bound by memory, which
-// one element of every vector in flight per thread covers: four (unrolled, the
-// vectors restrict) measured slower over the step, 1.12 against 1.05 ms at 2^26
-// doubles, 250 against 241 us at 16 x 10^6 and 68.3 against 66.7 at 4 x 10^6, as did
-// 16-byte accesses at 2^26 (4.77 against 5.25 TB/s).
+// not finite) every block leaves the vectors as they are. Bound by memory.
+template <bool CACHED>
 __global__ __launch_bounds__(256) void k_cg_update(int x_only, const double* __restrict__ bp_in,
                                                    int64_t nb, double* scal, int par,
                                                    const double* __restrict__ dir,
                                                    const double* __restrict__ qv,
-                                                   double* x, double* r,
+                                                   step_vec<CACHED> x, step_vec<CACHED> r,
                                                    double* bp_out, int64_t NP) {
   __shared__ double sh[NT / 64];
   if (block_stopped(scal)) return;
@@ -570,6 +580,7 @@ __global__ __launch_bounds__(256) void k_cg_update(int x_only, const double* __r
   if (broke) return;
   double v = 0.0;
   if (!x_only) {
+#pragma unroll kStepUnroll<CACHED>
     for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < NP; i += (int64_t)gridDim.x * NT) {
       x[i] = x[i] + alpha * dir[i];
       const double ri = r[i] - alpha * qv[i];
@@ -655,8 +666,8 @@ __global__ __launch_bounds__(256) void k_true_residual(RankOne c, int64_t NP, in
 __global__ __launch_bounds__(256) void k_cg_direction(const double* __restrict__ bp_in, int64_t nb,
                                                       double* scal, int par, int64_t iter,
                                                       const double* __restrict__ r,
-                                                      double* dir, int64_t NP, double* hist,
-                                                      int64_t hist_cap,
+                                                      double* __restrict__ dir, int64_t NP,
+                                                      double* hist, int64_t hist_cap,
                                                       int64_t refresh, int raise,
                                                       const double* __restrict__ bp_phi,
                                                       const double* __restrict__ x,
@@ -697,6 +708,7 @@ __global__ __launch_bounds__(256) void k_cg_direction(const double* __restrict__
   const double beta = dold != 0.0 ? dnew / dold : 0.0;
   if (!stall && !conv) {
     double dmax = 0.0;
+#pragma unroll 4
     for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < NP;
          i += (int64_t)gridDim.x * NT) {
       const double di = r[i] + beta * dir[i];
@@ -764,6 +776,7 @@ __global__ __launch_bounds__(256) void k_warm_start(const double* __restrict__ b
 // block partials of d^T q; block 0 also enters the caller's scalars[0] (r^T r) in
 // the double-buffered slot and clears the status, with a stop threshold that no
 // r^T r reaches, for the update and direction kernels, which follow.
+template <bool CACHED>
 __global__ __launch_bounds__(256) void k_step_dot(const double* __restrict__ a,
                                                   const double* __restrict__ b, int64_t len,
                                                   double* __restrict__ bp_out,
@@ -777,6 +790,7 @@ __global__ __launch_bounds__(256) void k_step_dot(const double* __restrict__ a,
     scal[S_STATUS + ST_STOP] = -1.0;
   }
   double v = 0.0;
+#pragma unroll kStepUnroll<CACHED>
   for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < len; i += (int64_t)gridDim.x * NT)
     v += a[i] * b[i];
   const double t = block_sum(v, sh);
@@ -2076,7 +2090,7 @@ hipError_t launch_cg_gather(const RankOne& c, int64_t NP, int64_t N, double* qv,
 hipError_t launch_cg_update(int x_only, const double* bp_in, int64_t nb, double* scal, int par,
                             const double* dir, const double* qv, double* x, double* r,
                             double* bp_out, int64_t NP, hipStream_t s) {
-  hipLaunchKernelGGL(k_cg_update, dim3((unsigned)cg_blocks(NP)), dim3(NT), 0, s, x_only, bp_in,
+  hipLaunchKernelGGL(k_cg_update<true>, dim3((unsigned)cg_blocks(NP)), dim3(NT), 0, s, x_only, bp_in,
                      nb, scal, par, dir, qv, x, r, bp_out, NP);
   return hipGetLastError();
 }
@@ -2123,8 +2137,15 @@ hipError_t launch_cg_step(int64_t N, double* x, double* r, double* d, const doub
                           hipStream_t s) {
   const int64_t nb = vec_blocks(N);
   const dim3 grid((unsigned)nb);
-  hipLaunchKernelGGL(k_step_dot, grid, dim3(NT), 0, s, d, q, N, bp0, scalars, scal);
-  hipLaunchKernelGGL(k_cg_update, grid, dim3(NT), 0, s, 0, bp0, nb, scal, 0, d, q, x, r, bp1, N);
+  if (N <= kCachedStep) {
+    hipLaunchKernelGGL(k_step_dot<true>, grid, dim3(NT), 0, s, d, q, N, bp0, scalars, scal);
+    hipLaunchKernelGGL(k_cg_update<true>, grid, dim3(NT), 0, s, 0, bp0, nb, scal, 0, d, q, x, r,
+                       bp1, N);
+  } else {
+    hipLaunchKernelGGL(k_step_dot<false>, grid, dim3(NT), 0, s, d, q, N, bp0, scalars, scal);
+    hipLaunchKernelGGL(k_cg_update<false>, grid, dim3(NT), 0, s, 0, bp0, nb, scal, 0, d, q, x, r,
+                       bp1, N);
+  }
   hipLaunchKernelGGL(k_cg_direction, grid, dim3(NT), 0, s, bp1, nb, scal, 0, (int64_t)1, r, d, N,
                      (double*)nullptr, (int64_t)0, (int64_t)0, 0, (const double*)nullptr,
                      (const double*)nullptr, (double*)nullptr, scalars);

@@ -16,10 +16,12 @@ from gpu_common import (GOLDEN, TOL_ALPHA, TOL_MV, SPLIT_SHAPES, TAIL_SHAPES, ch
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("N", [1, 255, 256, 1000, 65537, 600_001, 1 << 22])
+@pytest.mark.parametrize("N", [1, 255, 256, 1000, 65537, 600_001, 1 << 22, 1 << 23,
+                               (1 << 23) + 1, 10_000_019])
 def test_cg_step_matches_oracle(torch_dev, N):
     """One step on random vectors, including lengths past the block cap
-    of the vector kernels (grid-stride regime)."""
+    of the vector kernels (grid-stride regime) and past 2^23, from which on
+    they take one element per thread at a time."""
     torch, dev = torch_dev
     import paper_2202_12674_amd as P
     log(f"[cg_step] N={N}")
